@@ -5,6 +5,7 @@
 // correctly rounded division (compile with -fhip-fp32-correctly-rounded-divide-sqrt,
 // no fast-math) and rint = ties-to-even.
 #include "qail_internal.h"
+#include <algorithm>
 
 namespace qail {
 
@@ -164,25 +165,68 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint32_t* __restrict_
 
 // ---- activations ---------------------------------------------------------
 
-__global__ void act_scale_init_kernel(float* s_a) { *reinterpret_cast<uint32_t*>(s_a) = 0u; }
+// One step for a whole tensor: max / kTop over max(a) (unsigned codes) or max|a| (signed ones), 1 where
+// that is 0.  Bound by the one read of a.  Non-negative floats are ordered like their bit patterns, so
+// blocks meet in *s_a through an integer atomic maximum, whatever their order.  Atomics on one address
+// go one after the other (11 ns each): a block adds its maximum once, and only if it is larger than what
+// it finds there (an old value is a smaller one, so nothing is lost).  One atomic per wave of 4096 small
+// blocks took 188 us for 3.2 M values; one per block of 1024 threads, a block per CU, takes 6.7 us.
+constexpr int kScaleBlock = 1024;
 
-// max(max(a), 0) through an integer atomic: non-negative floats are ordered
-// like their bit patterns, and a tensor with no positive element leaves 0.
-__global__ __launch_bounds__(256) void act_scale_reduce_kernel(const float* __restrict__ a, size_t n,
-                                                               float* s_a) {
-    float m = 0.f;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        m = fmaxf(m, a[i]);
+template <bool kAbs>
+__device__ __forceinline__ float block_top(const float* __restrict__ a, size_t n, size_t first, size_t stride) {
+    __shared__ float red[kScaleBlock / kWave];
+    auto up = [](float m, float v) { return fmaxf(m, kAbs ? fabsf(v) : v); };
+    const size_t n4 = n / 4;
+    const float4* a4 = reinterpret_cast<const float4*>(a);
+    float m[4] = {0.f, 0.f, 0.f, 0.f};
+    size_t i = first;
+    for (; i + 3 * stride < n4; i += 4 * stride) {   // four loads in flight per thread
+        float4 v[4];
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-    if (threadIdx.x % kWave == 0 && m > 0.f)
-        atomicMax(reinterpret_cast<uint32_t*>(s_a), __builtin_bit_cast(uint32_t, m));
+        for (int u = 0; u < 4; ++u) v[u] = a4[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m[u] = up(up(up(up(m[u], v[u].x), v[u].y), v[u].z), v[u].w);
+    }
+    for (; i < n4; i += stride) {
+        const float4 v = a4[i];
+        m[0] = up(up(up(up(m[0], v.x), v.y), v.z), v.w);
+    }
+    for (size_t e = n4 * 4 + first; e < n; e += stride) m[1] = up(m[1], a[e]);
+    float t = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) t = fmaxf(t, __shfl_xor(t, off, kWave));
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = t;
+    __syncthreads();
+    t = red[0];
+#pragma unroll
+    for (int w = 1; w < kScaleBlock / kWave; ++w) t = fmaxf(t, red[w]);
+    return t;
 }
 
-__global__ void act_scale_final_kernel(float* s_a) {
-    const float m = *s_a;
-    *s_a = (m > 0.f) ? m / 15.0f : 1.0f;
+template <bool kAbs>
+__device__ __forceinline__ float step_of(float top) { return top > 0.f ? top / (kAbs ? 127.0f : 15.0f) : 1.0f; }
+
+__global__ void act_scale_init_kernel(float* s_a) { *reinterpret_cast<uint32_t*>(s_a) = 0u; }
+
+template <bool kAbs>
+__global__ __launch_bounds__(kScaleBlock) void act_scale_reduce_kernel(const float* __restrict__ a, size_t n, float* s_a) {
+    const float m = block_top<kAbs>(a, n, (size_t)blockIdx.x * kScaleBlock + threadIdx.x, (size_t)gridDim.x * kScaleBlock);
+    if (threadIdx.x == 0 && m > 0.f) {
+        uint32_t* const top = reinterpret_cast<uint32_t*>(s_a);
+        const uint32_t bits = __builtin_bit_cast(uint32_t, m);
+        if (bits > __hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(top, bits);
+    }
+}
+
+template <bool kAbs>
+__global__ void act_scale_final_kernel(float* s_a) { *s_a = step_of<kAbs>(*s_a); }
+
+// A tensor that one block reads in the time of a launch or two: everything in one launch.
+template <bool kAbs>
+__global__ __launch_bounds__(kScaleBlock) void act_scale_small_kernel(const float* __restrict__ a, size_t n, float* s_a) {
+    const float m = block_top<kAbs>(a, n, threadIdx.x, kScaleBlock);
+    if (threadIdx.x == 0) *s_a = step_of<kAbs>(m);
 }
 
 __global__ __launch_bounds__(256) void act_quant_kernel(const float* __restrict__ a, size_t words,
@@ -253,15 +297,24 @@ hipError_t launch_unpack(const qail_wdesc& d, const uint32_t* qw, uint8_t* codes
     return hipGetLastError();
 }
 
-hipError_t launch_act_scale(const float* a, size_t n, float* s_a, hipStream_t st) {
+template <bool kAbs>
+static hipError_t act_scale(const float* a, size_t n, float* s_a, hipStream_t st) {
+    constexpr size_t kOneBlock = 65536;   // values: 256 KB, about what one compute unit reads in 2 us
+    if (n <= kOneBlock) {
+        hipLaunchKernelGGL(act_scale_small_kernel<kAbs>, dim3(1), dim3(kScaleBlock), 0, st, a, n, s_a);
+        return hipGetLastError();
+    }
+    // at most one block per compute unit: 16 waves with four loads each keep it busy, and the
+    // atomics at the end of a block stay few
+    const size_t blocks = std::min<size_t>((n / 4 + 2 * kScaleBlock - 1) / (2 * kScaleBlock), (size_t)device_cu_count());
     hipLaunchKernelGGL(act_scale_init_kernel, dim3(1), dim3(1), 0, st, s_a);
-    size_t blocks = (n + 256 * 8 - 1) / (256 * 8);
-    if (blocks > 2048) blocks = 2048;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(act_scale_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, n, s_a);
-    hipLaunchKernelGGL(act_scale_final_kernel, dim3(1), dim3(1), 0, st, s_a);
+    hipLaunchKernelGGL(act_scale_reduce_kernel<kAbs>, dim3((unsigned)blocks), dim3(kScaleBlock), 0, st, a, n, s_a);
+    hipLaunchKernelGGL(act_scale_final_kernel<kAbs>, dim3(1), dim3(1), 0, st, s_a);
     return hipGetLastError();
 }
+
+hipError_t launch_act_scale(const float* a, size_t n, float* s_a, hipStream_t st) { return act_scale<false>(a, n, s_a, st); }
+hipError_t launch_act_scale_s8(const float* a, size_t n, float* s_a, hipStream_t st) { return act_scale<true>(a, n, s_a, st); }
 
 hipError_t launch_act_quant(const float* a, size_t n, const float* s_a, uint32_t* out, hipStream_t st) {
     const size_t words = n / 8;

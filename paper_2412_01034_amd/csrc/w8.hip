@@ -63,22 +63,6 @@ __global__ __launch_bounds__(256) void quantize_s8_kernel(const float* __restric
     for (int i = lane; i < g / 4; i += kWave) dst[i] = pack4_s8(src[i], s);
 }
 
-__global__ void abs_scale_init_kernel(float* s_a) { *reinterpret_cast<uint32_t*>(s_a) = 0u; }
-
-// max |a| through an integer atomic on the bit pattern (order-preserving for non-negative floats)
-__global__ __launch_bounds__(256) void abs_scale_reduce_kernel(const float* __restrict__ a, size_t n, float* s_a) {
-    float m = 0.f;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) m = fmaxf(m, fabsf(a[i]));
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
-    if (threadIdx.x % kWave == 0) atomicMax(reinterpret_cast<uint32_t*>(s_a), __builtin_bit_cast(uint32_t, m));
-}
-
-__global__ void abs_scale_final_kernel(float* s_a) {
-    const float m = *s_a;
-    *s_a = (m == 0.f) ? 1.0f : m / 127.0f;
-}
-
 __global__ __launch_bounds__(256) void act_quant_s8_kernel(const float* __restrict__ a, size_t words,
                                                            const float* __restrict__ s_a, uint32_t* __restrict__ out) {
     const float s = *s_a;
@@ -182,17 +166,6 @@ hipError_t launch_quantize_s8(const qail_wdesc& d, const float* w, uint32_t* qw,
         hipLaunchKernelGGL(quantize_s8_kernel<true>, dim3(blocks), dim3(256), 0, st, w, qw, scales, range_errors, ngroups, g);
     else
         hipLaunchKernelGGL(quantize_s8_kernel<false>, dim3(blocks), dim3(256), 0, st, w, qw, scales, range_errors, ngroups, g);
-    return hipGetLastError();
-}
-
-hipError_t launch_act_scale_s8(const float* a, size_t n, float* s_a, hipStream_t st) {
-    hipLaunchKernelGGL(abs_scale_init_kernel, dim3(1), dim3(1), 0, st, s_a);
-    if (n > 0) {
-        size_t blocks = (n + 255) / 256;
-        if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(abs_scale_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, n, s_a);
-    }
-    hipLaunchKernelGGL(abs_scale_final_kernel, dim3(1), dim3(1), 0, st, s_a);
     return hipGetLastError();
 }
 

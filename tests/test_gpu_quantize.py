@@ -142,3 +142,20 @@ def test_activation_scale_and_codes_bit_exact(B):
     o2 = torch.zeros(1, dtype=torch.int32, device="cuda")
     B.qail_quantize_act_u4(dev(v), one, o2)
     assert host(o2, np.uint32)[0] == O.pack_nibbles(O.quantize_act_u4(v, 1.0))[0]
+
+
+@pytest.mark.parametrize("n", [1, 3, 4096, 65536, 65537, 65543, 1_200_003])
+@pytest.mark.parametrize("where", ["first", "last", "none"])
+def test_activation_scale_sizes_and_places(B, n, where):
+    """One block up to 65536 values, many above; the largest value in the first or the last (ragged) place, or
+    nothing above zero.  *s_a holds something larger before each call."""
+    import torch
+    a = -np.random.default_rng(n).random(n).astype(np.float32)
+    if where == "none":
+        a[:] = 0.0
+    else:
+        a[0 if where == "first" else -1] = 3.75
+    s_a = torch.full((1,), 1e6, dtype=torch.float32, device="cuda")
+    for scale, ref in ((B.qail_act_scale_u4, O.act_scale_u4(a)), (B.qail_act_scale_s8, O.act_scale_s8(a))):
+        scale(dev(a), s_a)
+        assert host(s_a, np.uint32)[0] == np.float32(ref).view(np.uint32)
