@@ -184,6 +184,33 @@ __device__ __forceinline__ uint32_t fused_word(const int (&acc)[8], const ConvOu
     return fused_pack(acc, sc, bi, r, o);
 }
 
+// Two words of codes as MFMA operand bytes: activations as they are, weights times 16.
+__device__ __forceinline__ i32x4_t widen_a(uint32_t x, uint32_t y) {
+    return i32x4_t{(int)(x & 0x0F0F0F0Fu), (int)((x >> 4) & 0x0F0F0F0Fu), (int)(y & 0x0F0F0F0Fu),
+                   (int)((y >> 4) & 0x0F0F0F0Fu)};
+}
+__device__ __forceinline__ i32x4_t widen_b(uint32_t x, uint32_t y) {
+    return i32x4_t{(int)((x << 4) & 0xF0F0F0F0u), (int)(x & 0xF0F0F0F0u), (int)((y << 4) & 0xF0F0F0F0u),
+                   (int)(y & 0xF0F0F0F0u)};
+}
+
+// Plain outputs of 4 consecutive channels n0.. of a pixel, o = their position; 16-byte stores when Cout allows
+// (sc, bi: the channels' scales and biases, fetched by the caller in that case).
+__device__ __forceinline__ void store_plain(const i32x4_t v, const ConvOut& out, size_t o, int n0, int cout, const float4 sc,
+                                            const float4 bi) {
+    if ((cout % 4) == 0) {
+        if (out.acc) *reinterpret_cast<i32x4_t*>(out.acc + o) = v;
+        if (out.y)
+            *reinterpret_cast<float4*>(out.y + o) = make_float4(fmaf((float)v[0], sc.x, bi.x), fmaf((float)v[1], sc.y, bi.y),
+                                                                fmaf((float)v[2], sc.z, bi.z), fmaf((float)v[3], sc.w, bi.w));
+    } else {
+        for (int e = 0; e < 4 && n0 + e < cout; ++e) {
+            if (out.acc) out.acc[o + e] = v[e];
+            if (out.y) out.y[o + e] = fmaf((float)v[e], out.scale[n0 + e], out.bias[n0 + e]);
+        }
+    }
+}
+
 // Global -> LDS copy by the load unit through a buffer descriptor: lane l's 16 bytes at byte
 // offset `off` of the buffer land at LDS address lds + 16 l; a lane whose offset lies outside the
 // buffer writes 16 zero bytes (checked on the GPU with a probe), which is exactly what image
@@ -358,14 +385,6 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
                 for (int r = 0; r < 16; ++r) acc[i][j][c][r] = 0;
 
     i32x4_t af[2][kUM][2], bf[2][kUN][2];
-    auto widen_a = [](uint32_t x, uint32_t y) {
-        return i32x4_t{(int)(x & 0x0F0F0F0Fu), (int)((x >> 4) & 0x0F0F0F0Fu), (int)(y & 0x0F0F0F0Fu),
-                       (int)((y >> 4) & 0x0F0F0F0Fu)};
-    };
-    auto widen_b = [](uint32_t x, uint32_t y) {
-        return i32x4_t{(int)((x << 4) & 0xF0F0F0F0u), (int)(x & 0xF0F0F0F0u), (int)((y << 4) & 0xF0F0F0F0u),
-                       (int)(y & 0xF0F0F0F0u)};
-    };
     auto fetch = [&](int slot, int sub, int reg) {
         const unsigned char* As = smem + slot * kStageBytes + wm * (BM / 2) * 64;
         const unsigned char* Bs = smem + slot * kStageBytes + BM * 64 + wn * (BN / 2) * 64;
@@ -563,21 +582,7 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
                 for (int g = 0; g < KS; ++g)
                     v += *reinterpret_cast<const i32x4_t*>(
                         &reinterpret_cast<const int32_t*>(smem_all + g * kGroupBytes)[row * kSPitch + qd * 4]);
-                const size_t o = (size_t)m * gm.Cout + n0;
-                if (vec) {
-                    if (out.acc) *reinterpret_cast<i32x4_t*>(out.acc + o) = v;
-                    if (out.y) {
-                        const float4 sc = scq, bi = biq;
-                        *reinterpret_cast<float4*>(out.y + o) =
-                            make_float4(fmaf((float)v[0], sc.x, bi.x), fmaf((float)v[1], sc.y, bi.y),
-                                        fmaf((float)v[2], sc.z, bi.z), fmaf((float)v[3], sc.w, bi.w));
-                    }
-                } else {
-                    for (int e = 0; e < 4 && n0 + e < gm.Cout; ++e) {
-                        if (out.acc) out.acc[o + e] = v[e];
-                        if (out.y) out.y[o + e] = fmaf((float)v[e], out.scale[n0 + e], out.bias[n0 + e]);
-                    }
-                }
+                store_plain(v, out, (size_t)m * gm.Cout + n0, n0, gm.Cout, scq, biq);
             }
         }
     }
@@ -598,6 +603,175 @@ __global__ __launch_bounds__(256 * KS, (KS > 1 ? 1 : (BM * BN >= 128 * 128 ? 2 :
     const ConvGeom gm = it.gm;
     if ((int)blockIdx.x * BN >= gm.Cout || (int)blockIdx.y * BM >= gm.M) return;   // the grid fits the largest item
     w4a4_conv_tile<BM, BN, KS, kBits>(gm, it.a, it.w, it.out, blockIdx.y * BM, blockIdx.x * BN);
+}
+
+// The same convolution for few output pixels (one or a few frames), where a tile grid leaves most of the
+// chip idle and a launch is a chain of latencies: set-up, table, ring fill, a barrier per K step, epilogue.
+// Here nothing is staged: the KS waves of a block share a (16 UM) x (16 UN) output tile and split K, a wave
+// loads its MFMA operands from global memory straight into registers, D steps at a time before it
+// multiplies any, and the waves' sums meet in LDS by integer adds (exact in any order).  One
+// round trip to memory for the operands, none for the shortcut, scales and biases, which are requested
+// together with them.
+//
+// v_mfma_i32_16x16x64_i8: lane l supplies row / column l % 16 and the 16 codes of quarter l / 16; it
+// receives D[4 (l / 16) + r][l % 16].  A 16-byte load per lane is 16 rows x 64 B, i.e. a step of 128 codes
+// (64 with bytes), and feeds two MFMAs (one).
+template <int UM, int UN, int KS, int D, int kBits>
+__device__ __forceinline__ void conv_direct_tile(const ConvGeom& gm, const uint32_t* __restrict__ a,
+                                                 const uint32_t* __restrict__ w, const ConvOut& out, const int bm,
+                                                 const int bn) {
+    constexpr int TM = 16 * UM, TN = 16 * UN, kPitch = TN + 4, kThreads = 64 * KS;
+    __shared__ __attribute__((aligned(16))) int32_t sums[TM * kPitch];
+    const int t = threadIdx.x, lane = t % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    const int r16 = lane & 15, chunk = lane >> 4;
+    const int cw = gm.Cin / (32 / kBits);
+    const int kwords = gm.KH * gm.KW * cw;
+    const int steps = (kwords + kStepWords - 1) / kStepWords;
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(a, (uint32_t)((size_t)gm.B * gm.H * gm.W * cw * 4));
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(w, (uint32_t)((size_t)gm.Cout * kwords * 4));
+
+    int abase[UM], ih0[UM], iw0[UM];   // the lane's pixel of each row block: byte offset of its first tap, image position
+#pragma unroll
+    for (int i = 0; i < UM; ++i) {
+        const int m = min(bm + 16 * i + r16, gm.M - 1);   // a row past the end works on the last one and is not stored
+        const int b = div_by(m, gm.OH * gm.OW, gm.mg_ohow, gm.fastdiv);
+        const int rem = m - b * (gm.OH * gm.OW);
+        const int oh = div_by(rem, gm.OW, gm.mg_ow, gm.fastdiv), ow = rem - oh * gm.OW;
+        ih0[i] = oh * gm.stride - gm.pad;
+        iw0[i] = ow * gm.stride - gm.pad;
+        abase[i] = ((b * gm.H + ih0[i]) * gm.W + iw0[i]) * cw * 4;
+    }
+    u32x4_t av[D][UM], bv[D][UN];
+    auto load = [&](int s, int d) {
+        const int kw0 = s * kStepWords + chunk * 4;   // first word of the lane's chunk: inside one tap
+        const bool kin = kw0 < kwords;
+        const int tap = div_by(kw0, cw, gm.mg_cw, gm.fastdiv), cword = kw0 - tap * cw;
+        const int kh = div_by(tap, gm.KW, gm.mg_kw, gm.fastdiv), kwi = tap - kh * gm.KW;
+        const int at = ((kh * gm.W + kwi) * cw + cword) * 4;
+#pragma unroll
+        for (int i = 0; i < UM; ++i) {
+            const bool in = kin && (uint32_t)(ih0[i] + kh) < (uint32_t)gm.H && (uint32_t)(iw0[i] + kwi) < (uint32_t)gm.W;
+            av[d][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, in ? (uint32_t)(abase[i] + at) : kOut, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < UN; ++j) {
+            const int n = bn + 16 * j + r16;
+            bv[d][j] = __builtin_amdgcn_raw_buffer_load_b128(
+                rw, kin && n < gm.Cout ? (uint32_t)(n * kwords + kw0) * 4u : kOut, 0, 0);
+        }
+    };
+    i32x4_t acc[UM][UN];
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+#pragma unroll
+        for (int j = 0; j < UN; ++j) acc[i][j] = i32x4_t{0, 0, 0, 0};
+    auto multiply = [&](int d) {
+        if constexpr (kBits == 4) {
+            i32x4_t af[UM][2], bf[UN][2];
+#pragma unroll
+            for (int i = 0; i < UM; ++i) {
+                af[i][0] = widen_a(av[d][i].x, av[d][i].y);
+                af[i][1] = widen_a(av[d][i].z, av[d][i].w);
+            }
+#pragma unroll
+            for (int j = 0; j < UN; ++j) {
+                bf[j][0] = widen_b(bv[d][j].x, bv[d][j].y);
+                bf[j][1] = widen_b(bv[d][j].z, bv[d][j].w);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < UM; ++i)
+#pragma unroll
+                    for (int j = 0; j < UN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[i][h], bf[j][h], acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < UM; ++i)
+#pragma unroll
+                for (int j = 0; j < UN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4_t, av[d][i]),
+                                                                      __builtin_bit_cast(i32x4_t, bv[d][j]), acc[i][j], 0, 0, 0);
+        }
+    };
+
+    // the first steps' operands, then what the epilogue needs of scales, biases and shortcut
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(wave + d * KS, d);
+    constexpr int kWordsPerRow = TN / 8, kQuadsPerRow = TN / 4;
+    static_assert(TM * kWordsPerRow <= kThreads && TM * kQuadsPerRow <= kThreads, "one piece of the output per thread");
+    const int mf = bm + t / kWordsPerRow, nf = bn + (t % kWordsPerRow) * 8;    // fused: 8 channels of a pixel
+    const bool finishf = t < TM * kWordsPerRow && mf < gm.M && nf < gm.Cout;
+    const int mq = bm + t / kQuadsPerRow, nq = bn + (t % kQuadsPerRow) * 4;    // plain: 4 channels of a pixel
+    const bool finishq = t < TM * kQuadsPerRow && mq < gm.M && nq < gm.Cout;
+    float4 scq = make_float4(0.f, 0.f, 0.f, 0.f), biq = scq;
+    float sc[8], bi[8], res[8];
+    uint32_t resw = 0;
+    if (out.out_u4 && finishf) {
+        load8(out.scale + nf, sc);
+        load8(out.bias + nf, bi);
+        if (out.res_u4) resw = out.res_u4[(size_t)mf * (gm.Cout / 8) + nf / 8];
+        else if (out.res_f32) load8(out.res_f32 + (size_t)mf * gm.Cout + nf, res);
+    } else if (out.y && finishq && (gm.Cout % 4) == 0) {
+        scq = *reinterpret_cast<const float4*>(out.scale + nq);
+        biq = *reinterpret_cast<const float4*>(out.bias + nq);
+    }
+    for (int i = t; i < TM * kPitch; i += kThreads) sums[i] = 0;
+    __syncthreads();
+    for (int s0 = wave;;) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) multiply(d);
+        s0 += D * KS;
+        if (s0 >= steps) break;
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(s0 + d * KS, d);
+    }
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+#pragma unroll
+        for (int j = 0; j < UN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                __hip_atomic_fetch_add(&sums[(16 * i + 4 * chunk + r) * kPitch + 16 * j + r16], acc[i][j][r],
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    constexpr int kShift = kBits == 4 ? 4 : 0;   // 4-bit: the sum is 16 * result
+    if (out.out_u4) {
+        if (!finishf) return;
+        const int32_t* sg = &sums[(t / kWordsPerRow) * kPitch + (t % kWordsPerRow) * 8];
+        const i32x4_t v0 = *reinterpret_cast<const i32x4_t*>(sg), v1 = *reinterpret_cast<const i32x4_t*>(sg + 4);
+        const int q[8] = {v0[0] >> kShift, v0[1] >> kShift, v0[2] >> kShift, v0[3] >> kShift,
+                          v1[0] >> kShift, v1[1] >> kShift, v1[2] >> kShift, v1[3] >> kShift};
+        if (out.res_u4) {
+            shortcut_from_codes(resw, out.res_scale, res);
+        } else if (!out.res_f32) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) res[e] = 0.f;
+        }
+        out.out_u4[(size_t)mf * (gm.Cout / 8) + nf / 8] = fused_pack(q, sc, bi, res, out);
+    } else {
+        if (!finishq) return;
+        i32x4_t v = *reinterpret_cast<const i32x4_t*>(&sums[(t / kQuadsPerRow) * kPitch + (t % kQuadsPerRow) * 4]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] >>= kShift;
+        store_plain(v, out, (size_t)mq * gm.Cout + nq, nq, gm.Cout, scq, biq);
+    }
+}
+
+template <int UM, int UN, int KS, int D, int kBits>
+__global__ __launch_bounds__(64 * KS) void conv_direct_kernel(const ConvGeom gm, const uint32_t* __restrict__ a,
+                                                              const uint32_t* __restrict__ w, const ConvOut out) {
+    conv_direct_tile<UM, UN, KS, D, kBits>(gm, a, w, out, blockIdx.y * 16 * UM, blockIdx.x * 16 * UN);
+}
+
+// Several per launch: item i is the grid's plane z = i.
+template <int UM, int UN, int KS, int D, int kBits>
+__global__ __launch_bounds__(64 * KS) void conv_direct_batch_kernel(const ConvBatch args) {
+    const ConvItem& it = args.it[blockIdx.z];
+    const ConvGeom gm = it.gm;
+    if ((int)blockIdx.x * 16 * UN >= gm.Cout || (int)blockIdx.y * 16 * UM >= gm.M) return;   // the grid fits the largest item
+    conv_direct_tile<UM, UN, KS, D, kBits>(gm, it.a, it.w, it.out, blockIdx.y * 16 * UM, blockIdx.x * 16 * UN);
 }
 
 // Any Cin that fills whole words: one thread per output.  Slow; for shapes whose Cin is not a
@@ -703,6 +877,26 @@ void launch_tiled(const ConvJob* jobs, int n, hipStream_t st) {
                            jobs[0].a, jobs[0].w, jobs[0].out);
 }
 
+// ... of the direct kernel.
+template <int kBits, int UM, int UN, int KS, int D>
+void launch_direct(const ConvJob* jobs, int n, hipStream_t st) {
+    ConvBatch cb;
+    int ny = 0, nx = 0;
+    for (int i = 0; i < kConvBatch; ++i) {
+        const ConvJob& j = jobs[i < n ? i : 0];
+        cb.it[i] = ConvItem{j.gm, j.a, j.w, j.out};
+        if (i < n) {
+            ny = std::max(ny, (j.gm.M + 16 * UM - 1) / (16 * UM));
+            nx = std::max(nx, (j.gm.Cout + 16 * UN - 1) / (16 * UN));
+        }
+    }
+    if (kBits == 4 && n > 1)
+        hipLaunchKernelGGL((conv_direct_batch_kernel<UM, UN, KS, D, 4>), dim3(nx, ny, n), dim3(64 * KS), 0, st, cb);
+    else
+        hipLaunchKernelGGL((conv_direct_kernel<UM, UN, KS, D, kBits>), dim3(nx, ny, 1), dim3(64 * KS), 0, st, jobs[0].gm,
+                           jobs[0].a, jobs[0].w, jobs[0].out);
+}
+
 template <int kBits>
 ConvJob make_job(const qail_conv_desc& d, const uint32_t* a, const uint32_t* w, const ConvOut& out) {
     constexpr int kPerWord = 32 / kBits;
@@ -752,9 +946,23 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     auto blocks = [&](int bm, int bn) {
         return (long long)((gm.M + bm - 1) / bm) * ((gm.Cout + bn - 1) / bn);
     };
-    long long all64 = 0;
-    for (int i = 0; i < n; ++i)
+    long long all64 = 0, all16 = 0;
+    for (int i = 0; i < n; ++i) {
         all64 += (long long)((jobs[i].gm.M + 63) / 64) * ((jobs[i].gm.Cout + 63) / 64);
+        all16 += (long long)((jobs[i].gm.M + 15) / 16) * ((jobs[i].gm.Cout + 15) / 16);
+    }
+    // Few 16 x 16 tiles: the direct kernel, whose tile and K split grow with them.  It reads every operand
+    // once per 16 or 32 rows (columns) it meets, so its time grows with tiles x K steps while the tiled
+    // kernel's stays near its fixed cost.  us per launch, direct / tiled, 4-bit ResNet layers of 64 / 128 /
+    // 256 / 512 channels (5 / 9 / 18 / 36 steps): one image 3.5 / 5.0, 3.3 / 4.9, 3.8 / 6.6, 4.6 / 8.3; four
+    // images 4.7 / 5.3, 4.6 / 5.0, 4.9 / 6.6, 5.4 / 8.4; eight images 7.0 / 5.7 (28 k tile steps, above the
+    // line), 5.4 / 5.1 (above), 6.7 / 6.8 (above), 6.5 / 8.5.  8-bit, 72 steps, four images 8.0 / 8.3, eight
+    // 9.9 / 8.5 (above the line).
+    const long long cus = device_cu_count(), work = all16 * ksteps;
+    if (all16 <= cus && work <= 120 * cus) return launch_direct<kBits, 1, 1, 8, 2>(jobs, n, st);
+    if (all16 <= 2 * cus && work <= 120 * cus) return launch_direct<kBits, 1, 2, 8, 2>(jobs, n, st);
+    if (all16 <= 4 * cus && work <= (kBits == 4 ? 120 : 96) * cus) return launch_direct<kBits, 2, 2, 8, 1>(jobs, n, st);
+    if (work <= 64 * cus) return launch_direct<kBits, 2, 2, 4, 1>(jobs, n, st);
     const bool wide = gm.Cout > 64;
     // (the 128 x 128 tile already from one and a half blocks per CU: at batch 256 it takes the
     // 512 -> 512 layers from 45.7 to 37.6 us against the 128 x 64 tile)

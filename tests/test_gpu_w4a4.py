@@ -421,3 +421,37 @@ def test_fused_u4_full_batch_sampled_images(B, batch):
         ref = O.fused_requant_u4(acc, scale, bias, s_out, res_codes=res, res_scale=rs if identity else None)
         assert np.array_equal(got[rows], O.pack_nibbles(ref)), s.name
         del out, a_dev
+
+
+# The edges of the dispatch between the direct kernel (few tiles x K steps) and the tiled one: T = 16 x 16 tiles.
+DISPATCH = [
+    synth.ConvShape("d0", 1, 7, 7, 512, 512, 3, 3, 1, 1),       # direct, T = 128, 36 K steps: several trips per wave
+    synth.ConvShape("d1", 1, 3, 3, 64, 8, 1, 1, 1, 0),          # direct, one tile, half a K step: most waves idle
+    synth.ConvShape("d2", 2, 15, 13, 96, 232, 3, 3, 1, 1),      # direct, T = 375, Cin no multiple of 64, ragged
+    synth.ConvShape("d3", 3, 23, 21, 64, 136, 3, 3, 1, 1),      # direct, T = 819, ragged M and N, five steps
+    synth.ConvShape("d4", 3, 33, 31, 64, 88, 5, 5, 2, 2),       # direct, 25 taps at stride 2
+    synth.ConvShape("d5", 3, 33, 31, 64, 88, 3, 3, 1, 1),       # direct, T = 1152
+    synth.ConvShape("d6", 3, 61, 59, 96, 72, 3, 3, 1, 1),       # tiled, 64 x 64
+    synth.ConvShape("d7", 3, 33, 31, 160, 136, 3, 3, 1, 1),     # tiled, two K groups
+    synth.ConvShape("d8", 8, 14, 14, 288, 248, 3, 3, 1, 1),     # tiled, four K groups
+]
+
+
+@pytest.mark.parametrize("s", DISPATCH, ids=[s.name for s in DISPATCH])
+def test_dispatch_edges_bit_exact(B, s):
+    """Both outputs of the plain call over the full code range, and the fused output with either shortcut."""
+    import torch
+    a = synth.random_codes((s.B, s.H, s.W, s.Cin), 0, 15, 71).astype(np.uint8)
+    aw, ww = O.pack_nibbles(a), O.pack_nibbles(synth.random_codes((s.Cout, s.K), -8, 7, 72))
+    acc_ref = O.w4a4_conv_acc(aw, ww, *geom(s))
+    rng = np.random.default_rng(s.M)
+    scale, bias = (rng.random(s.Cout) * 1e-3 + 1e-4).astype(np.float32), synth.conv_bias(s, 73)
+    acc, y = gpu_conv(B, s, aw, ww, scale, bias)
+    assert np.array_equal(acc, acc_ref)
+    check_requant(y, acc_ref, scale, bias)
+    s_out = np.float32(max(float(O.requant(acc_ref, scale, bias).max()), 1e-3) / 20.0)
+    rc = rng.integers(0, 16, size=(s.M, s.Cout)).astype(np.uint8)
+    rf = (rng.standard_normal((s.M, s.Cout)) * float(s_out) * 3).astype(np.float32)
+    for kw in (dict(), dict(res_codes=rc, res_scale=np.float32(s_out * 0.8)), dict(res_f32=rf)):
+        got = gpu_conv_u4(B, s, aw, ww, scale, bias, s_out, **kw)
+        assert np.array_equal(got, O.pack_nibbles(O.fused_requant_u4(acc_ref, scale, bias, s_out, **kw)))

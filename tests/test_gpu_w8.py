@@ -80,6 +80,16 @@ SHAPES = [
     synth.ConvShape("e5", 1, 6, 6, 512, 32, 3, 3, 1, 1),       # K = 4608: four wave groups
     synth.ConvShape("e6", 4, 28, 28, 128, 256, 3, 3, 2, 1),    # 128 x 128 tiles
     synth.ConvShape("e7", 2, 20, 20, 64, 64, 3, 3, 1, 1),      # 128 x 64 / 64 x 64 tiles, several blocks
+    # the direct kernel (few 16 x 16 tiles x K steps) by tile: two column blocks, two row blocks, long K, one step
+    synth.ConvShape("e8", 2, 15, 13, 80, 231, 3, 3, 1, 1),
+    synth.ConvShape("e9", 3, 23, 21, 64, 135, 3, 3, 1, 1),
+    synth.ConvShape("e10", 3, 33, 31, 64, 89, 3, 3, 1, 1),
+    synth.ConvShape("e11", 1, 7, 7, 512, 512, 3, 3, 1, 1),
+    synth.ConvShape("e12", 1, 3, 3, 16, 8, 1, 1, 1, 0),
+    # and above its line: the tiled kernel on ragged tiles, without and with K groups
+    synth.ConvShape("e13", 3, 61, 59, 48, 72, 3, 3, 1, 1),
+    synth.ConvShape("e14", 3, 33, 31, 112, 136, 3, 3, 1, 1),
+    synth.ConvShape("e15", 8, 14, 14, 144, 248, 3, 3, 1, 1),
 ]
 
 
