@@ -295,7 +295,7 @@ int qail_w4a16_linear_batch(const qail_w4a16_item* items, int32_t count, int32_t
         }
         while (j < count && takes_gemm(items[j].d, M)) ++j;
         if (j > i) {
-            if (launch_w4a16_gemm_f16_batch(items + i, j - i, M, workspace, st) != hipSuccess) return QAIL_ERR_HIP;
+            if (launch_w4a16_gemm_f16_batch(items + i, j - i, M, true, workspace, st) != hipSuccess) return QAIL_ERR_HIP;
             i = j;
             continue;
         }
@@ -550,7 +550,7 @@ int check_w8_item(const qail_w8a16_item& it, int M) {
 }
 
 // Workspace of a batch: runs of consecutive items that go to the GEMM share launches, eight at a time.
-size_t w8_batch_need(const qail_w8a16_item* items, int count, int M) {
+size_t w8_batch_need(const qail_w8a16_item* items, int count, int M, bool wide_tiles) {
     size_t need = 0;
     int i = 0;
     while (i < count) {
@@ -561,7 +561,7 @@ size_t w8_batch_need(const qail_w8a16_item* items, int count, int M) {
             ++j;
         }
         if (j > i) {
-            need = std::max(need, gemm_f16_batch_workspace(run, j - i, M));
+            need = std::max(need, gemm_f16_batch_workspace(run, j - i, M, wide_tiles));
             i = j;
         } else {
             ++i;
@@ -590,7 +590,7 @@ int qail_w8a16_batch_workspace(const qail_w8a16_item* items, int32_t count, int3
         if (e != QAIL_OK) return e;
         if (items[i].d.scheme != QAIL_W8_SYM_GROUP) return QAIL_ERR_UNSUPPORTED;
     }
-    *bytes = w8_batch_need(items, count, M);
+    *bytes = w8_batch_need(items, count, M, true);
     return QAIL_OK;
 }
 
@@ -603,7 +603,9 @@ int qail_w8a16_linear_batch(const qail_w8a16_item* items, int32_t count, int32_t
         const int e = check_w8_item(items[i], M);
         if (e != QAIL_OK) return e;
     }
-    const size_t need = w8_batch_need(items, count, M);
+    // a workspace that has no room for the slots of wide tiles is accepted and narrow ones are used
+    const size_t need = w8_batch_need(items, count, M, false);
+    const bool wide_tiles = workspace_bytes >= w8_batch_need(items, count, M, true);
     if (need > 0) {
         if (!workspace || workspace_bytes < need) return QAIL_ERR_WORKSPACE;
         if (reinterpret_cast<uintptr_t>(workspace) & 255u) return QAIL_ERR_ALIGN;
@@ -633,7 +635,7 @@ int qail_w8a16_linear_batch(const qail_w8a16_item* items, int32_t count, int32_t
             ++j;
         }
         if (j > i) {
-            if (launch_w4a16_gemm_f16_batch(run, j - i, M, workspace, st) != hipSuccess) return QAIL_ERR_HIP;
+            if (launch_w4a16_gemm_f16_batch(run, j - i, M, wide_tiles, workspace, st) != hipSuccess) return QAIL_ERR_HIP;
             i = j;
             continue;
         }

@@ -79,11 +79,11 @@ int device_cu_count();
 // fp16-MFMA GEMM for M > 16; needs gemm_f16_workspace() bytes of 256-byte aligned device memory.
 bool gemm_f16_supports(const qail_wdesc& d, int M);
 size_t gemm_f16_workspace(const qail_wdesc& d, int M);
-hipError_t launch_w4a16_gemm_f16(const qail_w4a16_item& it, int M, void* ws, hipStream_t st);
-// Several such linears (all supported, same M) in shared launches, each on a share of the blocks;
-// needs gemm_f16_batch_workspace() bytes.
-size_t gemm_f16_batch_workspace(const qail_w4a16_item* items, int count, int M);
-hipError_t launch_w4a16_gemm_f16_batch(const qail_w4a16_item* items, int count, int M, void* ws, hipStream_t st);
+// Several such linears (all supported, same M and code width) in shared launches, each on a share of the
+// blocks; needs gemm_f16_batch_workspace() bytes.  wide_tiles = false: 128-column tiles only, whose slots
+// take half the workspace.
+size_t gemm_f16_batch_workspace(const qail_w4a16_item* items, int count, int M, bool wide_tiles = true);
+hipError_t launch_w4a16_gemm_f16_batch(const qail_w4a16_item* items, int count, int M, bool wide_tiles, void* ws, hipStream_t st);
 hipError_t launch_w4a16_generic(const qail_w4a16_item& it, int M, hipStream_t st);
 
 // 8-bit variants.

@@ -28,9 +28,11 @@
 // conversion: (q ^ 0x80) is q + 128 as an unsigned byte u, and 0x6400 | u is the fp16 number
 // 1024 + u, so one XOR per word, one byte permute per pair of codes, a packed add of -1152 (exact)
 // and a packed multiply by the scale give (q * s): 14 vector operations per 8 codes.  The codes
-// come out in their natural order, so x is stored in natural order for this variant.  A lane's
-// 64 k of a step are four 16-byte pieces instead of two; with that the ring only fits LDS with
-// 128-column tiles.
+// come out in their natural order, so x is stored in natural order for this variant.  A step is
+// 64 k deep instead of 128, so that a lane's share of it is two 16-byte pieces as well and the ring
+// (four slots of half the depth) fits LDS beside the wide tiles.  With 128-k steps only 128-column
+// tiles fitted, on which every MFMA costs one 1 KB fragment read, the LDS's full bandwidth: one
+// decoder layer at M = 288 took 210 us with them, 200 us now.
 //
 // MFMA operand layout (32x32x16, wave64): lane l supplies row (A) / column (B) l%32 and
 // the 8 consecutive k starting at 8*(l/32); it receives D[8*(r/4) + 4*(l/32) + r%4][l%32]
@@ -49,7 +51,7 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kBK = 128;                // k per step
+constexpr int kPadK = 128;              // rows of the fp16 copy of x are padded to this
 constexpr int kMaxGemmBlocks = 512;     // upper bound of the grid (the workspace has two slots per block)
 constexpr int kRowPad = 128;            // workspace rows are padded to this
 
@@ -219,6 +221,23 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t ld
                  :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 
+// How a step is laid out in LDS, by code width.  The x tile has rows of kBK fp16, unpadded; the 16-byte
+// chunk s of row r is kept at position s ^ swizzle(r), which makes the 16 lanes of a fragment read (16
+// consecutive rows, same s) hit 16 different positions of a 256-byte line and 8 consecutive ones 8
+// different ones of a 128-byte line: conflict-free.
+template <int kBits>
+struct Step {
+    static constexpr int kBK = kBits == 4 ? 128 : 64;              // k per step
+    static constexpr int kSub = kBK / 16;                          // sub-steps: one MFMA per 32 x 32 block each
+    static constexpr int kStages = kBits == 4 ? 3 : 4;             // slots of the ring
+    static constexpr int kRowBytes = 2 * kBK;
+    static constexpr int kChunks = kRowBytes / 16;
+    static constexpr int kCodeLoads = kBK / 2 * kBits / 128;       // 16-byte pieces of a lane's codes of a step
+    static constexpr int kLane = kCodeLoads * 1024 + (kBits == 4 ? 512 : 256);   // bytes per wave and column block: codes, scale words, zero words
+    __device__ static __forceinline__ int swizzle(int r) { return kBits == 4 ? r & 15 : (r & 7) ^ ((r >> 3) & 1); }
+    static constexpr size_t lds(int rows, int col_blocks) { return (size_t)kStages * (rows * kRowBytes + col_blocks * kLane); }
+};
+
 struct GemmArgs {
     const uint32_t* qw;
     const uint16_t* sc;
@@ -249,23 +268,19 @@ __host__ __device__ inline int owner_of(long long u, long long units, int P) { r
 
 // Block tile (32 * MB) x (128 * WN): 4 waves side by side along n, each (32 * MB) x (32 * WN).
 //
-// The x tile of a step (32 * MB rows x 128 k, 256 B per row) is written into LDS by the
-// load unit itself (global_load_lds_dwordx4: lane l's 16 bytes land at base + 16 l, so a
-// wave fills four rows per instruction) and costs no registers.  Rows are not padded;
-// instead the 16-byte chunk s of row r is kept at position s ^ (r % 16), which the
-// loading lane arranges by choosing its global address, and which makes the 16 lanes of a
-// fragment read (16 consecutive rows, same s) hit 16 different positions: conflict-free.
+// The x tile of a step is written into LDS by the load unit itself (global_load_lds_dwordx4: lane l's 16
+// bytes land at base + 16 l, so a wave fills four or eight rows per instruction) and costs no registers.
 //
-// Latency.  A step is only about a microsecond of matrix work, less than a trip to L2 or
-// HBM under load, so the loads of step s + 2 are issued during step s: a ring of three x
-// tiles (and three sets of packed weights) in LDS.  Every load is unconditional (steps past the end of K
-// reload the last tile, which nothing reads), so the number of loads in flight at each
-// wait is a compile-time constant and the wait is an exact vmcnt, not a drain.
+// Latency.  A step is only about a microsecond of matrix work, less than a trip to L2 or HBM under load,
+// so the loads of step s + kStages - 1 are issued during step s: a ring of kStages x tiles (and sets of
+// packed weights) in LDS.  Every load is unconditional (steps past the end of K reload the last tile,
+// which nothing reads), so the number of loads in flight at each wait is a compile-time constant and the
+// wait is an exact vmcnt, not a drain.
 //
 // The K loop is one continuous pipeline of sub-steps (16 k of every lane pair = one MFMA per
 // 32 x 32 output block): the LDS reads and the expansion for sub-step u + 1 are issued
 // among the MFMAs of sub-step u.  The tile of step s + 1 must be complete one sub-step
-// before step s ends, so the wait + barrier sits between sub-steps 6 and 7.
+// before step s ends, so the wait + barrier sits in front of the step's last sub-step.
 //
 // The grid has at most one block per CU.  Tiles are dealt whole to the blocks as long as they
 // fill complete rounds; what is left (fewer tiles than blocks) can be dealt in K steps instead:
@@ -275,41 +290,37 @@ __host__ __device__ inline int owner_of(long long u, long long units, int P) { r
 // finished on the spot; otherwise its fp32 sums go to a slot of the workspace (two slots per
 // block: one for its first shared segment, one for any later one) and a second kernel adds the
 // slots of each such tile in K order, which keeps the result independent of timing.
-constexpr int kStages = 3;
-
 // s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt untouched.
 __host__ __device__ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 
-//
-// LW > 0: LW more waves per block that only load.  The first LW - LW / 2 of them share the x tile loads
-// of a step, the other LW / 2 the weight loads (for all four column groups, with the addresses the
-// owning lanes would use); each waits for the step that is due and meets the four MFMA waves at the
-// step's barrier.  The MFMA waves then issue no memory instruction in the K loop: with one wave per
-// SIMD every load instruction otherwise sits in the same instruction stream as the MFMAs it delays.
+// Besides the four multiplying waves a block has three that only load: two share the x tile loads of a
+// step, the third issues the weight loads (for all four column groups, with the addresses the owning
+// lanes would use); each waits for the step that is due and meets the MFMA waves at the step's barrier.
+// The MFMA waves then issue no memory instruction in the K loop: with one wave per SIMD every load
+// instruction otherwise sits in the same instruction stream as the MFMAs it delays.
 // A second wave on a SIMD halves the registers a wave may have (256), which the 128 x 256 tile just
 // fits.  Measured on a decoder layer's four linears with nibble weights: three loading waves (two for
 // x, one for the weights) are 4-9 % faster than none at every M from 33 to 2048; two are as good on
 // 96-row tiles and much slower on 128-row ones (32 x loads per step from one wave), four are slower
 // than three (a loading wave on every SIMD).
-template <int MB, int WN, int kBits, int LW>
-__global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const GemmBatch args) {
-    static_assert(LW == 0 || LW == 2 || LW == 3 || LW == 4, "no loader waves, or LW - LW / 2 for x and LW / 2 for the weights");
-    constexpr int kThreads = 256 + 64 * LW;
+constexpr int kXWaves = 2, kGemmThreads = 256 + 64 * (kXWaves + 1);
+template <int MB, int WN, int kBits>
+__global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const GemmBatch args) {
+    typedef Step<kBits> S;
+    constexpr int kBK = S::kBK, kStages = S::kStages, kRowBytes = S::kRowBytes, kCodeLoads = S::kCodeLoads, kBLane = S::kLane;
+    constexpr int kThreads = kGemmThreads;
     constexpr int kBM = 32 * MB;
     constexpr int kBN = 128 * WN;
-    constexpr int kALoads = kBM / 16;             // wave-wide 1 KB loads per wave per step
-    constexpr int kCodeLoads = kBits == 4 ? 2 : 4;               // 16-byte pieces of a lane's 64 codes of a step
-    constexpr int kBParts = kCodeLoads + (kBits == 4 ? 2 : 1);   // ... plus the scale word and (4-bit) the zero word
-    constexpr int kStepLoads = kALoads + kBParts * WN;           // all loads a lane issues per step
-    constexpr int kBufBytes = kBM * 256;          // one x tile
+    constexpr int kBufBytes = kBM * kRowBytes;    // one x tile
+    constexpr int kBStage = 4 * WN * kBLane;      // one set of packed weights
     constexpr int kCPitch = kBN * 2 + 16;         // bytes per row of the output staging tile
-    extern __shared__ __attribute__((aligned(16))) unsigned char As[];  // [kStages][kBM][256 B]
+    extern __shared__ __attribute__((aligned(16))) unsigned char As[];  // [kStages][kBM][kRowBytes]
 
     const int t = threadIdx.x;
     const int lane = t % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const int c = lane & 31, kb = lane >> 5;
-    const bool loader = LW > 0 && wave >= 4;   // wave-uniform
+    const bool loader = wave >= 4;   // wave-uniform
     int item = 0;
 #pragma unroll
     for (int i = 1; i < kGemmBatch; ++i)
@@ -399,85 +410,28 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
     }
     const int bm = tm * kBM, bn = tn * kBN;
 
-    // Byte offsets of this lane's weight rows (WN 32-column blocks).  All tensors here are
-    // below 4 GB (checked by the host), so addresses are a uniform base plus a 32-bit offset.
-    uint32_t qoff[WN], soff[WN], zoff[WN];
+    // This lane's weight rows (WN 32-column blocks): where their scales begin, and their power of two.
+    // All tensors here are below 4 GB (checked by the host), so addresses are a uniform base plus a
+    // 32-bit offset.
+    uint32_t soff[WN];
     float winv[WN];
-    const int cwave = LW > 0 ? (wave & 3) : wave;   // (a loader's own values of these are not used)
+    const int cwave = wave & 3;   // (a loading wave's own values of these are not used)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
         const int n = min(bn + (cwave * WN + j) * 32 + c, ga.N - 1);
-        qoff[j] = (uint32_t)n * (uint32_t)kw * 4u;
         soff[j] = (uint32_t)n * (uint32_t)G * 2u;
-        zoff[j] = (uint32_t)n * (uint32_t)zwords * 4u;
         winv[j] = __builtin_bit_cast(float, 0x7F000000u - __builtin_bit_cast(uint32_t, ga.wmul[n]));
     }
-    const char* qbase = reinterpret_cast<const char*>(ga.qw);
-    const char* sbase = reinterpret_cast<const char*>(ga.sc);
-    const char* zbase = reinterpret_cast<const char*>(ga.zr);
-    const char* xbase = reinterpret_cast<const char*>(ga.xh);
-
-    // x tile loader: load i of this thread fills LDS slot (row 16 i + t / 16, position t % 16)
-    // with chunk (t % 16) ^ (row % 16) of that row.
-    uint32_t xoff0;
-    {
-        const int row0 = t >> 4, pos = t & 15;
-        xoff0 = ((uint32_t)(bm + row0) * (uint32_t)ga.Kpad + (uint32_t)((pos ^ (row0 & 15)) * 8)) * 2u;
-    }
-    const uint32_t xstride = 16u * (uint32_t)ga.Kpad * 2u;  // 16 rows further per load
     const uint32_t as_lds = __builtin_amdgcn_readfirstlane(lds_addr(As));
-    // One step's loads are issued a few at a time between the sub-steps of an earlier step
-    // (all at once they would queue up behind each other in the load unit while the matrix
-    // pipe idles).  plan() fixes the offsets of a step, issue(i, slot) sends its i-th load.
-    uint32_t pk0b = 0;                    // x: byte offset of the step inside a row
-    uint32_t pq[WN], ps[WN], pz[WN];      // weights: byte offsets of codes, scale word, zero word
-    // fragment read offsets of this lane for the 8 sub-steps (row c of a 32-row block)
-    // (sub-step jj < 8 only touches the low three bits of the chunk index, so it folds in by an XOR)
-    const int aoff0 = c * 256 + (((8 * kb) ^ (c & 15)) << 4);
-
-    // Weight loader: the lane's 64 k of a step (two 16-byte pieces per column block) plus the
-    // 4-byte words holding its group's scale and zero-point, again through the load unit into
-    // LDS: each lane only ever reads back its own slots, so LDS is a per-lane FIFO here and
-    // no registers (and no compiler-inserted load waits) are tied up while the loads fly.
-    // The group of a lane's 64 k is tracked without divisions (the group size is a multiple
-    // of 64, so they never straddle two groups).
-    unsigned char* const Bs = As + kStages * kBufBytes;  // [kStages][4 waves][WN][2560 B]
-    constexpr int kBLane = kCodeLoads * 1024 + 512;       // codes, then 256 (scale) + 256 (zero)
-    constexpr int kBStage = 4 * WN * kBLane;
-    int lk = ka * kBK + 64 * kb, lgrp = lk / ga.g, lkin = lk - lgrp * ga.g;  // position of the next planned step
-    int pstep = ka;
-    auto plan = [&]() {
-        pk0b = (uint32_t)(min(pstep, ga.steps - 1) * kBK) * 2u;  // past the end of K: the last tile again, unused
-        ++pstep;
-        const bool v = lk < ga.K;
-        const uint32_t kc = v ? (uint32_t)lk : 0u;  // past the end: any valid address, the scale becomes 0
-        const uint32_t grp = v ? (uint32_t)lgrp : 0u;
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            pq[j] = qoff[j] + kc * kBits / 8;
-            ps[j] = (soff[j] + grp * 2u) & ~3u;
-            pz[j] = zoff[j] + (grp / 8u) * 4u;
-        }
-        lk += kBK;
-        lkin += kBK;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {  // the step is at most two groups long
-            const int over = lkin >= ga.g;
-            lkin -= over * ga.g;
-            lgrp += over;
-        }
-    };
-    auto issue = [&](int i, int slot) {
-        if (i < kALoads) {
-            dma16(xbase, xoff0 + i * xstride + pk0b, as_lds + slot * kBufBytes + (i * 256 + cwave * 64) * 16);
-        } else {
-            const int j = (i - kALoads) / kBParts, part = (i - kALoads) % kBParts;
-            const uint32_t dst = as_lds + kStages * kBufBytes + slot * kBStage + (cwave * WN + j) * kBLane;
-            if (part < kCodeLoads) dma16(qbase, pq[j] + 16 * part, dst + 1024 * part);
-            if (part == kCodeLoads) dma4(sbase, ps[j], dst + kCodeLoads * 1024);
-            if (part == kCodeLoads + 1) dma4(zbase, pz[j], dst + kCodeLoads * 1024 + 256);
-        }
-    };
+    // fragment read offset of this lane (row c of a 32-row block): its half of the step's k is the
+    // chunks kSub * kb + jj, and sub-step jj < kSub folds in by an XOR of the low bits
+    const int aoff0 = c * kRowBytes + (((S::kSub * kb) ^ S::swizzle(c)) << 4);
+    // The packed weights of a step: the lane's kBK / 2 k (two 16-byte pieces per column block) plus the
+    // 4-byte words holding its group's scale and zero-point.  Each lane only ever reads back its own
+    // slots, so LDS is a per-lane FIFO here and no registers (and no compiler-inserted load waits) are
+    // tied up while the loads fly.  The group of a lane's k is tracked without divisions (the group
+    // size is a multiple of 64, so they never straddle two groups).
+    unsigned char* const Bs = As + kStages * kBufBytes;  // [kStages][4 waves][WN][kBLane]
 
     // operands of the step being multiplied; ck / cgrp follow the consumed steps like lk / lgrp.
     // A step's codes, scale word and zero word are read back from the per-lane FIFO (take_read) and
@@ -486,7 +440,7 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
     uint32_t wq[WN][4 * kCodeLoads];
     uint32_t tsw[WN], tzw[WN];
     f16x2_t nz[WN], nz6[WN], s2[WN];
-    int ck = ka * kBK + 64 * kb, cgrp = ck / ga.g, ckin = ck - cgrp * ga.g;
+    int ck = ka * kBK + kBK / 2 * kb, cgrp = ck / ga.g, ckin = ck - cgrp * ga.g;
     auto take_read = [&](int stage) {
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
@@ -541,7 +495,7 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
     auto fetch = [&](int stage, int jj, int slot) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
-            af[slot][i] = *reinterpret_cast<const f16x8_t*>(As + stage * kBufBytes + i * (32 * 256) + (aoff0 ^ (jj << 4)));
+            af[slot][i] = *reinterpret_cast<const f16x8_t*>(As + stage * kBufBytes + i * (32 * kRowBytes) + (aoff0 ^ (jj << 4)));
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             if constexpr (kBits == 4)
@@ -567,57 +521,57 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
     };
 
     if (loader) {
-        // ---- the loading waves: one barrier after the first step has landed, then one per step, as
-        // the MFMA waves have them.  The first LW / 2 of them share the x tile: load q fills rows
-        // 4 q + lane / 16 (chunk lane % 16 of the row at its swizzled position) and wave i takes the
-        // loads q = i mod LW / 2.  The others share the 4 WN column blocks the same way: codes, scale
-        // words and zero words, each lane with the offsets of the lane that will read them.
-        constexpr int kXW = LW > 0 ? (LW + 1) / 2 : 1;   // waves sharing the x tile (LW = 0: this branch is never taken)
-        constexpr int kWW = LW > 1 ? LW / 2 : 1;         // waves sharing the weights
-        constexpr int kXLoads = kBM / 4 / kXW;           // per x wave and step
-        constexpr int kWBlocks = 4 * WN / kWW;           // column blocks per weight wave
-        constexpr int kWLoads = kWBlocks * kBParts;      // per weight wave and step
-        static_assert(kBM / 4 % kXW == 0 && 4 % kXW == 0 && 4 * WN % kWW == 0, "loads divide evenly");
-        static_assert(2 * kXLoads <= 64 && 2 * kWLoads <= 64, "two steps in flight fit the load counter (a 64th load only waits for the oldest)");
-        const bool xwave = wave < 4 + kXW;
-        const int share = xwave ? wave - 4 : wave - 4 - kXW;   // which of the waves of its kind
-        const int lr = lane >> 4, lp = lane & 15;
+        // ---- the loading waves: one barrier after the first step has landed, then one per step, as the
+        // MFMA waves have them.  The x waves take the x loads in turn; load q fills rows kRows q ..
+        // (chunk lane % kChunks of a row at its swizzled position).  The last wave takes the 4 WN column
+        // blocks: codes, scale words and zero words, each lane with the offsets of the lane that will
+        // read them.
+        constexpr int kRows = 64 / S::kChunks;           // rows per 1 KB load
+        constexpr int kXLoads = kBM / kRows / kXWaves;   // per x wave and step
+        constexpr int kWBlocks = 4 * WN;
+        constexpr int kWLoads = kWBlocks * (kCodeLoads + (kBits == 4 ? 2 : 1));
+        constexpr int kPeriod = 16 / (kRows * kXWaves);  // loads of a wave after which the swizzle repeats
+        static_assert(kBM % (kRows * kXWaves) == 0 && 16 % (kRows * kXWaves) == 0, "loads divide evenly");
+        static_assert((kStages - 2) * kXLoads < 64 && (kStages - 2) * kWLoads < 64, "the waits' counts fit the load counter");
+        const bool xwave = wave < 4 + kXWaves;
+        const int share = xwave ? wave - 4 : 0;
+        const int lr = lane / S::kChunks, lp = lane % S::kChunks;
         const uint32_t pitchb = (uint32_t)ga.Kpad * 2u;
-        const uint32_t xrow0 = (uint32_t)(bm + 4 * share + lr) * pitchb;
-        uint32_t xsw[4 / kXW];                           // swizzled chunk of load qq (period 4 rows x 4 loads)
+        const uint32_t xrow0 = (uint32_t)(bm + kRows * share + lr) * pitchb;
+        uint32_t xsw[kPeriod];
 #pragma unroll
-        for (int qm = 0; qm < 4 / kXW; ++qm) xsw[qm] = (uint32_t)((lp ^ ((4 * (kXW * qm + share) + lr) & 15)) * 16);
+        for (int qm = 0; qm < kPeriod; ++qm) xsw[qm] = (uint32_t)((lp ^ S::swizzle(kRows * (kXWaves * qm + share) + lr)) * 16);
         uint32_t qo[kWBlocks], so[kWBlocks], zo[kWBlocks];
 #pragma unroll
         for (int mm = 0; mm < kWBlocks; ++mm) {
-            const int n = min(bn + (kWW * mm + share) * 32 + c, ga.N - 1);
+            const int n = min(bn + mm * 32 + c, ga.N - 1);
             qo[mm] = (uint32_t)n * (uint32_t)kw * 4u;
             so[mm] = (uint32_t)n * (uint32_t)G * 2u;
             zo[mm] = (uint32_t)n * (uint32_t)zwords * 4u;
         }
-        int lk = ka * kBK + 64 * kb, lgrp = lk / ga.g, lkin = lk - lgrp * ga.g;
+        int lk = ka * kBK + kBK / 2 * kb, lgrp = lk / ga.g, lkin = lk - lgrp * ga.g;
         int pstep = ka;
         auto load_step = [&](int slot) {
             const uint32_t slot_x = as_lds + (uint32_t)slot * kBufBytes + (uint32_t)share * 1024u;
-            const uint32_t slot_w = as_lds + kStages * kBufBytes + (uint32_t)slot * kBStage + (uint32_t)share * kBLane;
+            const uint32_t slot_w = as_lds + kStages * kBufBytes + (uint32_t)slot * kBStage;
             if (xwave) {
                 const uint32_t k0b = (uint32_t)(min(pstep, ga.steps - 1) * kBK) * 2u;
 #pragma unroll
                 for (int qq = 0; qq < kXLoads; ++qq)
-                    dma16(xbase, xrow0 + (uint32_t)(qq * kXW) * 4u * pitchb + xsw[qq % (4 / kXW)] + k0b,
-                          slot_x + qq * kXW * 1024);
+                    dma16(ga.xh, xrow0 + (uint32_t)(qq * kXWaves * kRows) * pitchb + xsw[qq % kPeriod] + k0b,
+                          slot_x + qq * kXWaves * 1024);
             } else {
                 const bool v = lk < ga.K;
                 const uint32_t kc = v ? (uint32_t)lk : 0u;
                 const uint32_t grp = v ? (uint32_t)lgrp : 0u;
 #pragma unroll
                 for (int mm = 0; mm < kWBlocks; ++mm) {
-                    const uint32_t dst = slot_w + mm * kWW * kBLane;
+                    const uint32_t dst = slot_w + mm * kBLane;
 #pragma unroll
                     for (int part = 0; part < kCodeLoads; ++part)
-                        dma16(qbase, qo[mm] + kc * kBits / 8 + 16 * part, dst + 1024 * part);
-                    dma4(sbase, (so[mm] + grp * 2u) & ~3u, dst + kCodeLoads * 1024);
-                    if (kBits == 4) dma4(zbase, zo[mm] + (grp / 8u) * 4u, dst + kCodeLoads * 1024 + 256);
+                        dma16(ga.qw, qo[mm] + kc * kBits / 8 + 16 * part, dst + 1024 * part);
+                    dma4(ga.sc, (so[mm] + grp * 2u) & ~3u, dst + kCodeLoads * 1024);
+                    if (kBits == 4) dma4(ga.zr, zo[mm] + (grp / 8u) * 4u, dst + kCodeLoads * 1024 + 256);
                 }
             }
             ++pstep;
@@ -630,33 +584,23 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
                 lgrp += over;
             }
         };
-        load_step(0);
-        load_step(1);
-        // in flight: steps 0 and 1; step 0 has to be complete
-        if (xwave) __builtin_amdgcn_s_waitcnt(waitcnt_vm(kXLoads));
-        else __builtin_amdgcn_s_waitcnt(waitcnt_vm(kWLoads));
+#pragma unroll
+        for (int p = 0; p < kStages - 1; ++p) load_step(p);
+        // in flight: steps 0 .. kStages - 2; step 0 has to be complete
+        if (xwave) __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kXLoads));
+        else __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kWLoads));
         __syncthreads();
-        int fill = 2;
+        int fill = kStages - 1;
         for (int s = 0; s < steps; ++s) {
             // slot `fill` held step s - 1 and is free since the previous barrier
             load_step(fill);
-            fill = fill == 2 ? 0 : fill + 1;
-            if (xwave) __builtin_amdgcn_s_waitcnt(waitcnt_vm(kXLoads));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_vm(kWLoads));
+            fill = fill == kStages - 1 ? 0 : fill + 1;
+            // in flight: steps s + 1 .. s + kStages - 1; step s + 1 has to be complete
+            if (xwave) __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kXLoads));
+            else __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kWLoads));
             __syncthreads();
         }
     } else {
-    // steps 0 and 1 are loaded up front; from then on step s + 2 is loaded during step s
-    if constexpr (LW == 0) {
-#pragma unroll
-        for (int p = 0; p < kStages - 1; ++p) {
-            plan();
-#pragma unroll
-            for (int i = 0; i < kStepLoads; ++i) issue(i, p);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kStepLoads));
-    }
     __syncthreads();
     take_read(0);
     take_convert();
@@ -666,30 +610,21 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
 #pragma unroll
         for (int u = 0; u < kStages; ++u) {
             if (s0 + u >= steps) break;
-            const int cur = u, nxt = (u + 1) % kStages, fill = (u + 2) % kStages;
-            // slot `fill` held step s - 1 and is free since the previous barrier
-            if constexpr (LW == 0) plan();
+            const int cur = u, nxt = (u + 1) % kStages;
 #pragma unroll
-            for (int jj = 0; jj < 7; ++jj) {
+            for (int jj = 0; jj < S::kSub - 1; ++jj) {
                 __builtin_amdgcn_sched_barrier(0);
                 fetch(cur, jj + 1, (jj + 1) & 1);
                 multiply(jj & 1);
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (LW == 0) {
-#pragma unroll
-                    for (int i = 0; i < kStepLoads; ++i)
-                        if (i * 7 / kStepLoads == jj) issue(i, fill);
-                }
             }
             __builtin_amdgcn_sched_barrier(0);
-            // In flight: step s+1 (issued during step s-1) and step s+2 (just issued).  Step
-            // s+1 has to be complete; the wait also covers this wave's LDS reads (lgkmcnt 0),
-            // so after the barrier slot `cur` is dead for everyone once sub-step 7 is done
+            // The loading waves have seen step s + 1 land.  The wait covers this wave's LDS reads (lgkmcnt
+            // 0), so after the barrier slot `cur` is dead for everyone once the last sub-step is done
             // (its operands are already in registers).
-            __builtin_amdgcn_s_waitcnt(waitcnt_vm(LW == 0 ? kStepLoads : 0));
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
-            // Sub-step 7 of this step (operands already in registers) with the next step's set-up under
+            // The last sub-step of this step (operands already in registers) with the next step's set-up under
             // it: all LDS reads first (FIFO and A fragments), a few MFMAs while they are in flight, then
             // the conversions and the first expansion shared out among the remaining MFMAs.
             take_read(nxt);
@@ -702,7 +637,7 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[1][i], bf[1][j], acc[i][j], 0, 0, 0);
             constexpr int kLead = MB * WN < 4 ? 1 : 3;                     // MFMAs issued before any conversion
             constexpr int kSetupValu = (kBits == 4 ? 13 + 16 : 14 + 12) * WN + 8;
-            __builtin_amdgcn_sched_group_barrier(0x100, WN * (kCodeLoads + 2) + MB, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, WN * (kCodeLoads + (kBits == 4 ? 2 : 1)) + MB, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
             if constexpr (MB * WN > kLead) {
 #pragma unroll
@@ -722,7 +657,7 @@ __global__ __launch_bounds__(256 + 64 * LW) void w4a16_gemm_f16_kernel(const Gem
         // part of a tile's K: the raw sums go to this block's slot, tile-shaped [kBM][kBN],
         // through LDS so that they leave as 16-byte pieces of full lines
         constexpr int kPPitch = kBN + 4;  // floats per staged row
-        static_assert(kBM * kPPitch * 4 <= kStages * (kBufBytes + 4 * WN * kBLane), "the fp32 tile fits in the ring");
+        static_assert(kBM * kPPitch * 4 <= kStages * (kBufBytes + kBStage), "the fp32 tile fits in the ring");
         float* const stage = reinterpret_cast<float*>(As) + (4 * kb) * kPPitch + cwave * WN * 32 + c;
         if (!loader) {
 #pragma unroll
@@ -866,12 +801,12 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
 int gemm_max_blocks() { return device_cu_count() < kMaxGemmBlocks ? device_cu_count() : kMaxGemmBlocks; }
 
 // Fills in the work decomposition of one linear on `cus` blocks; returns the blocks it uses.
-template <int MB, int WN>
+template <int MB, int WN, int kBits>
 int plan_tiles(GemmArgs& ga, bool split_tail, int cus) {
     constexpr int kBM = 32 * MB, kBN = 128 * WN;
     ga.Tm = (ga.M + kBM - 1) / kBM;
     ga.tiles = ga.Tm * ((ga.N + kBN - 1) / kBN);
-    ga.steps = ga.Kpad / kBK;
+    ga.steps = (ga.K + Step<kBits>::kBK - 1) / Step<kBits>::kBK;
     ga.whole = split_tail ? ga.tiles / cus * cus : ga.tiles;
     const int tail = ga.tiles - ga.whole;
     const long long units = (long long)tail * ga.steps;
@@ -882,17 +817,16 @@ int plan_tiles(GemmArgs& ga, bool split_tail, int cus) {
 }
 
 // One launch for `n` linears that use the same tile, each on its own blocks (ga[i].block_begin, P set).
-// Loading waves per block (see the kernel), by code width.
-constexpr int kLoaderWaves4 = 3, kLoaderWaves8 = 0;
-template <int MB, int WN, int kBits, int LW = (kBits == 4 ? kLoaderWaves4 : kLoaderWaves8)>
+template <int MB, int WN, int kBits>
 hipError_t launch_tile(const GemmArgs* gas, int n, hipStream_t st) {
     constexpr int kBM = 32 * MB, kBN = 128 * WN;
-    const size_t lds = (size_t)kStages * (kBM * 256 + 4 * WN * ((kBits == 4 ? 2 : 4) * 1024 + 512));
+    constexpr size_t lds = Step<kBits>::lds(kBM, 4 * WN);
+    static_assert(lds <= 160 * 1024, "the ring fits LDS");
     // more than 64 KB of LDS needs an opt-in; the call is idempotent, so two host threads that
     // both find the flag clear may both make it
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&w4a16_gemm_f16_kernel<MB, WN, kBits, LW>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&w4a16_gemm_f16_kernel<MB, WN, kBits>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
@@ -912,7 +846,7 @@ hipError_t launch_tile(const GemmArgs* gas, int n, hipStream_t st) {
         }
     }
     gb.count = n;
-    hipLaunchKernelGGL((w4a16_gemm_f16_kernel<MB, WN, kBits, LW>), dim3(grid), dim3(256 + 64 * LW), lds, st, gb);
+    hipLaunchKernelGGL((w4a16_gemm_f16_kernel<MB, WN, kBits>), dim3(grid), dim3(kGemmThreads), lds, st, gb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (max_tail > 0) {
@@ -926,14 +860,6 @@ hipError_t launch_tile(const GemmArgs* gas, int n, hipStream_t st) {
 // `cus` blocks to itself.
 template <int MB>
 void choose_tile(const GemmArgs& ga, int cus, bool alone, bool narrow_only, int* wn_out, bool* split_out) {
-    if (narrow_only) {
-        // 8-bit codes: the ring fits LDS only with 128-column tiles.  A round or more of them: the
-        // incomplete last round in K steps when it is short; less than a round: everything in K steps.
-        const int t1 = ((ga.M + 32 * MB - 1) / (32 * MB)) * ((ga.N + 127) / 128);
-        *wn_out = 1;
-        *split_out = t1 < cus ? true : (t1 % cus) * 5 <= cus * 2;
-        return;
-    }
     // Measured on the four linears of a 7B decoder layer at M = 288 and 1024 (256 CUs), one launch each:
     //   * a round or more of wide tiles: wide tiles, and the incomplete last round is dealt in
     //     K steps only when it is short (a fuller one is cheaper left as it is: blocks that
@@ -947,9 +873,9 @@ void choose_tile(const GemmArgs& ga, int cus, bool alone, bool narrow_only, int*
     const int t2 = ((ga.M + 32 * MB - 1) / (32 * MB)) * ((ga.N + 255) / 256);
     int wn = 2;
     bool split = false;
-    if (ga.N <= 128) {
+    if (ga.N <= 128 || narrow_only) {
         wn = 1;
-        split = ga.Kpad / kBK >= 64;
+        split = ga.Kpad / kPadK >= 64;
     } else if (t2 >= cus) {
         split = (t2 % cus) * 5 <= cus * 2;
     } else if (!alone) {
@@ -960,7 +886,7 @@ void choose_tile(const GemmArgs& ga, int cus, bool alone, bool narrow_only, int*
         // in K steps when K is long, or when whole narrow tiles would leave half of the CUs idle
         // (measured on single linears at M = 48 .. 288: the out projection 27 -> 19 us at M = 64,
         // 37 -> 25 us at M = 128; with more tiles than that the shared tiles cost more than they give)
-        split = ga.Kpad / kBK >= 64 || (t2 * 4 <= cus && ga.Kpad / kBK >= 16);
+        split = ga.Kpad / kPadK >= 64 || (t2 * 4 <= cus && ga.Kpad / kPadK >= 16);
     }
     *wn_out = wn;
     *split_out = split;
@@ -981,28 +907,28 @@ bool gemm_f16_supports(const qail_wdesc& d, int M) {
     if (((unsigned long long)d.N * (unsigned long long)(d.K / d.group_size)) % 2 != 0) return false;
     // 32-bit byte offsets inside the kernel
     const unsigned long long lim = 0xFFFFFFFFull;
-    const unsigned long long Mpad = (unsigned long long)round_up(M, kRowPad), Kpad = (unsigned long long)round_up(d.K, kBK);
+    const unsigned long long Mpad = (unsigned long long)round_up(M, kRowPad), Kpad = (unsigned long long)round_up(d.K, kPadK);
     const unsigned long long code_bytes = (unsigned long long)d.N * d.K / (d.scheme == QAIL_W8_SYM_GROUP ? 1 : 2);
     return code_bytes <= lim && Mpad * Kpad * 2 <= lim && (unsigned long long)M * d.N * 2 <= lim;
 }
 
 // Workspace of one linear without the slots: x as fp16, the row scales, the weight rows' powers of two.
 static size_t gemm_head_bytes(const qail_wdesc& d, int M) {
-    const size_t Mpad = (size_t)round_up(M, kRowPad), Kpad = (size_t)round_up(d.K, kBK);
+    const size_t Mpad = (size_t)round_up(M, kRowPad), Kpad = (size_t)round_up(d.K, kPadK);
     const size_t b = Mpad * Kpad * 2 + Mpad * 4 + (size_t)round_up(d.N, 64) * 4;
     return (b + 255) / 256 * 256;
 }
 
 // Two tile-shaped fp32 slots per block of the grid for tiles whose K range is shared between blocks.
-static size_t gemm_slot_bytes(int M, bool wide) {   // wide: 256-column tiles (4-bit codes with N > 128)
+static size_t gemm_slot_bytes(int M, bool wide) {   // wide: 256-column tiles (N > 128)
     return 2 * (size_t)gemm_max_blocks() * (size_t)tile_rows(M) * (wide ? 256 : 128) * 4;
 }
 
 size_t gemm_f16_workspace(const qail_wdesc& d, int M) {
-    return gemm_head_bytes(d, M) + gemm_slot_bytes(M, d.N > 128 && d.scheme != QAIL_W8_SYM_GROUP);
+    return gemm_head_bytes(d, M) + gemm_slot_bytes(M, d.N > 128);
 }
 
-size_t gemm_f16_batch_workspace(const qail_w4a16_item* items, int count, int M) {
+size_t gemm_f16_batch_workspace(const qail_w4a16_item* items, int count, int M, bool wide_tiles) {
     // linears that share a launch (kGemmBatch at a time) need their heads side by side; the
     // slots are shared out with the blocks
     size_t need = 0;
@@ -1011,7 +937,7 @@ size_t gemm_f16_batch_workspace(const qail_w4a16_item* items, int count, int M) 
         bool wide = false;
         for (int i = i0; i < count && i < i0 + kGemmBatch; ++i) {
             b += gemm_head_bytes(items[i].d, M);
-            wide = wide || (items[i].d.N > 128 && items[i].d.scheme != QAIL_W8_SYM_GROUP);
+            wide = wide || (items[i].d.N > 128 && wide_tiles);
         }
         b += gemm_slot_bytes(M, wide);
         if (b > need) need = b;
@@ -1020,7 +946,7 @@ size_t gemm_f16_batch_workspace(const qail_w4a16_item* items, int count, int M) 
 }
 
 template <int MB>
-static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, void* ws, hipStream_t st) {
+static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool wide_tiles, void* ws, hipStream_t st) {
     const bool bytes = items[0].d.scheme == QAIL_W8_SYM_GROUP;   // all items of a call have the same code width
     const int Mpad = round_up(M, kRowPad);
     const int cus = gemm_max_blocks();
@@ -1033,7 +959,7 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, void*
     int prep_blocks = 0;
     for (int i = 0; i < n; ++i) {
         const qail_wdesc& d = items[i].d;
-        const int Kpad = round_up(d.K, kBK), G = d.K / d.group_size;
+        const int Kpad = round_up(d.K, kPadK), G = d.K / d.group_size;
         uint16_t* xh = reinterpret_cast<uint16_t*>(at);
         float* rscale = reinterpret_cast<float*>(xh + (size_t)Mpad * Kpad);
         float* wmul = rscale + Mpad;
@@ -1073,7 +999,7 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, void*
     int all[kGemmBatch];
     for (int i = 0; i < n; ++i) all[i] = i;
     deal(all, n, std::max(cus, n));
-    for (int i = 0; i < n; ++i) choose_tile<MB>(ga[i], share[i], n == 1, bytes, &wn[i], &split[i]);
+    for (int i = 0; i < n; ++i) choose_tile<MB>(ga[i], share[i], n == 1, !wide_tiles, &wn[i], &split[i]);
     // linears with the same tile width go out together, each group on the whole chip
     for (int w = 2; w >= 1; --w) {
         int idx[kGemmBatch], m = 0;
@@ -1084,43 +1010,42 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, void*
             deal(idx, m, std::max(cus, m));
             for (int j = 0; j < m; ++j) {
                 int w2;
-                choose_tile<MB>(ga[idx[j]], share[idx[j]], n == 1, bytes, &w2, &split[idx[j]]);
+                choose_tile<MB>(ga[idx[j]], share[idx[j]], n == 1, !wide_tiles, &w2, &split[idx[j]]);
             }
         }
         GemmArgs grp[kGemmBatch];
         int begin = 0;
         for (int j = 0; j < m; ++j) {
             GemmArgs& g = ga[idx[j]];
-            const int P = w == 2 ? plan_tiles<MB, 2>(g, split[idx[j]], share[idx[j]]) : plan_tiles<MB, 1>(g, split[idx[j]], share[idx[j]]);
+            const int sh = share[idx[j]];
+            const bool sp = split[idx[j]];
+            const int P = bytes ? (w == 2 ? plan_tiles<MB, 2, 8>(g, sp, sh) : plan_tiles<MB, 1, 8>(g, sp, sh))
+                                : (w == 2 ? plan_tiles<MB, 2, 4>(g, sp, sh) : plan_tiles<MB, 1, 4>(g, sp, sh));
             g.block_begin = begin;
             g.partial = slots + (size_t)2 * begin * (32 * MB) * (128 * w);
             begin += P;
             grp[j] = g;
         }
-        e = bytes ? launch_tile<MB, 1, 8>(grp, m, st)
+        e = bytes ? (w == 2 ? launch_tile<MB, 2, 8>(grp, m, st) : launch_tile<MB, 1, 8>(grp, m, st))
                   : (w == 2 ? launch_tile<MB, 2, 4>(grp, m, st) : launch_tile<MB, 1, 4>(grp, m, st));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-hipError_t launch_w4a16_gemm_f16_batch(const qail_w4a16_item* items, int count, int M, void* ws, hipStream_t st) {
+hipError_t launch_w4a16_gemm_f16_batch(const qail_w4a16_item* items, int count, int M, bool wide_tiles, void* ws, hipStream_t st) {
     for (int i0 = 0; i0 < count; i0 += kGemmBatch) {
         const int n = std::min(kGemmBatch, count - i0);
         hipError_t e;
         switch (tile_rows(M)) {
-            case 32: e = launch_chunk<1>(items + i0, n, M, ws, st); break;
-            case 64: e = launch_chunk<2>(items + i0, n, M, ws, st); break;
-            case 96: e = launch_chunk<3>(items + i0, n, M, ws, st); break;
-            default: e = launch_chunk<4>(items + i0, n, M, ws, st); break;
+            case 32: e = launch_chunk<1>(items + i0, n, M, wide_tiles, ws, st); break;
+            case 64: e = launch_chunk<2>(items + i0, n, M, wide_tiles, ws, st); break;
+            case 96: e = launch_chunk<3>(items + i0, n, M, wide_tiles, ws, st); break;
+            default: e = launch_chunk<4>(items + i0, n, M, wide_tiles, ws, st); break;
         }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-hipError_t launch_w4a16_gemm_f16(const qail_w4a16_item& it, int M, void* ws, hipStream_t st) {
-    return launch_w4a16_gemm_f16_batch(&it, 1, M, ws, st);
 }
 
 }  // namespace qail

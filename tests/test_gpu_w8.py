@@ -410,3 +410,30 @@ def test_w8a16_full_size_layer_batched_sampled(B, M):
         nx, nw = _w8_norms(xb[ms], q, s, 128)
         worst = max(worst, w4a16_norm_err(y, ref, nx, nw))
     assert worst <= TOL, worst
+
+
+@pytest.mark.parametrize("M", [33, 64, 96, 128, 200])
+def test_w8a16_matrix_cores_wide_and_narrow_tiles(B, M):
+    """The reported workspace has room for 256-column tiles; one with room for the slots of 128-column tiles
+    only is accepted too, a smaller one is not.  Whole tiles, ragged columns, K not a multiple of the step."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tile_rows = (M + 31) // 32 * 32 if M <= 96 else (96 if -(-M // 96) * 96 < -(-M // 128) * 128 else 128)
+    for i, (N, K, g) in enumerate([(1030, 4096, 128), (300, 2112, 64), (6200, 512, 256)]):
+        w = synth.llm_weight(N, K, 940 + i, outlier_frac=0.01)
+        xb = synth.llm_activation_bf16(M, K, 950 + i, outlier_frac=0.005)
+        q, s = O.quantize_w8_sym_group(w, g)
+        ref = O.w8a16_linear(xb, q, s, g)
+        nx, nw = _w8_norms(xb, q, s, g)
+        args = (dev(O.pack_bytes(q)), dev(s.view(np.uint16)), dev(xb))
+        wide = B.qail_w8a16_workspace(N, K, g, M)
+        if wide == 0:
+            continue   # the small-batch kernel's
+        narrow = wide - 2 * min(cus, 512) * tile_rows * 128 * 4
+        for nws in (wide, narrow):
+            y = torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda")
+            B.qail_w8a16_linear(N, K, g, *args, y, M, torch.empty(nws, dtype=torch.uint8, device="cuda"))
+            torch.cuda.synchronize()
+            assert w4a16_norm_err(host(y, np.uint16).reshape(M, N), ref, nx, nw) <= TOL, (N, K, nws)
+        with pytest.raises(B.QailError):
+            B.qail_w8a16_linear(N, K, g, *args, y, M, torch.empty(narrow - 256, dtype=torch.uint8, device="cuda"))
