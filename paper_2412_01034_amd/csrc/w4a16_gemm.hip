@@ -66,8 +66,8 @@ struct PrepItem {
     const uint16_t* x;
     const uint16_t* sc;
     uint16_t* xh;
-    float* rscale;
-    float* wmul;
+    uint16_t* rscale;   // the powers of two of the rows of x and of the weight rows: exact as bf16
+    uint16_t* wmul;
     int N, K, Kpad, G;
 };
 struct PrepBatch {
@@ -83,8 +83,8 @@ __global__ __launch_bounds__(256) void gemm_prep_kernel(const PrepBatch args) {
     const uint16_t* __restrict__ x = pi.x;
     const uint16_t* __restrict__ sc = pi.sc;
     uint16_t* __restrict__ xh = pi.xh;
-    float* __restrict__ rscale = pi.rscale;
-    float* __restrict__ wmul = pi.wmul;
+    uint16_t* __restrict__ rscale = pi.rscale;
+    uint16_t* __restrict__ wmul = pi.wmul;
     const int M = args.M, Mpad = args.Mpad, N = pi.N, K = pi.K, Kpad = pi.Kpad, G = pi.G;
     if ((int)blockIdx.x >= Mpad + (N + 31) / 32) return;   // the grid is as wide as the largest linear needs
     if ((int)blockIdx.x < Mpad) {
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void gemm_prep_kernel(const PrepBatch args) {
         uint4* dst = reinterpret_cast<uint4*>(xh + (size_t)m * Kpad);
         if (m >= M) {
             for (int i = t; i < Kpad / 8; i += 256) dst[i] = make_uint4(0, 0, 0, 0);
-            if (t == 0) rscale[m] = 0.f;
+            if (t == 0) rscale[m] = 0;
             return;
         }
         const uint4* src = reinterpret_cast<const uint4*>(x + (size_t)m * K);
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void gemm_prep_kernel(const PrepBatch args) {
         int p = mx == 0 ? 0 : 141 - e;
         p = p > 126 ? 126 : (p < -126 ? -126 : p);
         const float up = __builtin_bit_cast(float, (uint32_t)(127 + p) << 23);
-        if (t == 0) rscale[m] = __builtin_bit_cast(float, (uint32_t)(127 - p) << 23);
+        if (t == 0) rscale[m] = (uint16_t)((127 - p) << 7);
         auto rewrite = [&](const uint4 v) {
             const uint16_t b[8] = {(uint16_t)v.x, (uint16_t)(v.x >> 16), (uint16_t)v.y, (uint16_t)(v.y >> 16),
                                    (uint16_t)v.z, (uint16_t)(v.z >> 16), (uint16_t)v.w, (uint16_t)(v.w >> 16)};
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void gemm_prep_kernel(const PrepBatch args) {
         // scales are positive fp16, at least 2^-14 (a stored subnormal is treated as 2^-14)
         int e = (int)(mx >> 10) & 31;
         e = e < 1 ? 1 : e;
-        wmul[n] = __builtin_bit_cast(float, (uint32_t)(127 + e - 15) << 23);
+        wmul[n] = (uint16_t)((127 + e - 15) << 7);
     }
 }
 
@@ -225,6 +225,8 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t ld
 // chunk s of row r is kept at position s ^ swizzle(r), which makes the 16 lanes of a fragment read (16
 // consecutive rows, same s) hit 16 different positions of a 256-byte line and 8 consecutive ones 8
 // different ones of a 128-byte line: conflict-free.
+constexpr int kPow2Bytes = 768;   // powers of two of a tile: 256 columns, then 128 rows, bf16
+
 template <int kBits>
 struct Step {
     static constexpr int kBK = kBits == 4 ? 128 : 64;              // k per step
@@ -235,7 +237,10 @@ struct Step {
     static constexpr int kCodeLoads = kBK / 2 * kBits / 128;       // 16-byte pieces of a lane's codes of a step
     static constexpr int kLane = kCodeLoads * 1024 + (kBits == 4 ? 512 : 256);   // bytes per wave and column block: codes, scale words, zero words
     __device__ static __forceinline__ int swizzle(int r) { return kBits == 4 ? r & 15 : (r & 7) ^ ((r >> 3) & 1); }
-    static constexpr size_t lds(int rows, int col_blocks) { return (size_t)kStages * (rows * kRowBytes + col_blocks * kLane); }
+    static constexpr int kSegs = kStages + 1;                      // segments whose powers of two are in LDS
+    static constexpr size_t lds(int rows, int col_blocks) {
+        return (size_t)kStages * (rows * kRowBytes + col_blocks * kLane) + kSegs * kPow2Bytes;
+    }
 };
 
 struct GemmArgs {
@@ -243,15 +248,14 @@ struct GemmArgs {
     const uint16_t* sc;
     const uint32_t* zr;
     const uint16_t* xh;     // [Mpad][Kpad] fp16, scaled and permuted
-    const float* rscale;    // [Mpad]
-    const float* wmul;      // [N]
+    const uint16_t* pow2;   // bf16: [Mpad] of the rows of x, then [N] of the weight rows (from element wpow2 on)
     uint16_t* y;
-    int M, N, K, Kpad, g;
+    int M, N, K, Kpad, g, wpow2;
     // work decomposition: tiles are numbered with m running fastest.  The first `whole` tiles
     // are dealt whole, tile i to block i % P; the K steps of the others are dealt as units (one
     // K step of one tile): block b of P owns the units [b * units / P, (b + 1) * units / P)
     int Tm, tiles, steps, whole;
-    float* partial;  // [2 P][tile] fp32: sums of tiles whose K range is shared between blocks
+    float* partial;  // [2 P][tile] fp32: sums of tiles whose K range is shared between blocks, see slot_at()
     int block_begin, P;  // the linear is worked on by blocks [block_begin, block_begin + P) of the grid
 };
 
@@ -262,6 +266,8 @@ struct GemmBatch {
     int count;
 };
 
+// A slot holds a tile's sums as the MFMA lanes have them, 16 bytes of a lane at a time: piece
+// ((wave * MB + i) * WN + j) * 4 + q of lane (c, kb) is row 32 i + c, columns (WN wave + j) * 32 + 8 q + 4 kb + 0..3.
 // First unit of block b when `units` units are dealt to P blocks, and the block that owns unit u.
 __host__ __device__ inline long long first_unit(long long b, long long units, int P) { return b * units / P; }
 __host__ __device__ inline int owner_of(long long u, long long units, int P) { return (int)(((u + 1) * P - 1) / units); }
@@ -290,6 +296,20 @@ __host__ __device__ inline int owner_of(long long u, long long units, int P) { r
 // finished on the spot; otherwise its fp32 sums go to a slot of the workspace (two slots per
 // block: one for its first shared segment, one for any later one) and a second kernel adds the
 // slots of each such tile in K order, which keeps the result independent of timing.
+//
+// The segments of a block are one stream of steps: the loading waves go on with the next segment's steps
+// while the multiplying waves finish the last one, and the results leave from the registers (weights are
+// the MFMA's A operand, so a lane holds four neighbouring columns of one row), not through LDS, which is
+// busy with the next tile.  Nothing in the K loop waits for those stores.  With the ring drained at every
+// segment a tile of 128 x 256 paid 1.3 us of set-up, 4-6 us until its first step had landed and 4.7 us of
+// epilogue around 57 us of K loop at K = 4096, M = 1024; 18 of 128 us at M = 288.
+// One decoder layer: 60.0 -> 57.8 us at M = 48, 153.9 -> 149.8 at M = 288; 410 at M = 1024 either way, where
+// the chip is limited by power (1.80 GHz sustained of 2.4) and idle time was buying clock.
+// What the end of a segment needs, the powers of two of its rows and columns, is loaded with its first
+// step into one of kSegs slots: the step that is loaded first for segment q is loaded behind the barrier
+// of step kStages before it, and segments are at least one step long, so everybody has left segment
+// q - kSegs by then.
+
 // s_waitcnt immediate: vmcnt(n), lgkmcnt(0), expcnt untouched.
 __host__ __device__ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 
@@ -308,18 +328,17 @@ template <int MB, int WN, int kBits>
 __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const GemmBatch args) {
     typedef Step<kBits> S;
     constexpr int kBK = S::kBK, kStages = S::kStages, kRowBytes = S::kRowBytes, kCodeLoads = S::kCodeLoads, kBLane = S::kLane;
-    constexpr int kThreads = kGemmThreads;
     constexpr int kBM = 32 * MB;
     constexpr int kBN = 128 * WN;
     constexpr int kBufBytes = kBM * kRowBytes;    // one x tile
     constexpr int kBStage = 4 * WN * kBLane;      // one set of packed weights
-    constexpr int kCPitch = kBN * 2 + 16;         // bytes per row of the output staging tile
     extern __shared__ __attribute__((aligned(16))) unsigned char As[];  // [kStages][kBM][kRowBytes]
 
     const int t = threadIdx.x;
     const int lane = t % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const int c = lane & 31, kb = lane >> 5;
+    const int cwave = wave & 3;
     const bool loader = wave >= 4;   // wave-uniform
     int item = 0;
 #pragma unroll
@@ -367,28 +386,30 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         }
         vbid = before + ((bid - ((mine - q) & 7)) >> 3);
     }
+    // the block's next segment: K steps [ka, ka + steps) of the tile at (bm, bn); false: there is none
+    struct Seg {
+        int bm, bn, ka, steps;
+        bool first_shared;
+    };
     int wtile = vbid, unit = unit0;
-    for (;;) {
-    // ---- one segment: K steps [ka, ka + steps) of one tile
-    int tile, ka, steps;
-    bool first_shared = false;
+    auto next_segment = [&](Seg& sg) -> bool {
+    int tile;
+    sg.first_shared = false;
     if (wtile < ga.whole) {
         tile = wtile;
-        ka = 0;
-        steps = ga.steps;
+        sg.ka = 0;
+        sg.steps = ga.steps;
         wtile += P;
     } else if (unit < unit1) {
         const int tt = unit / ga.steps;
         tile = ga.whole + tt;
-        ka = unit - tt * ga.steps;
-        steps = min(ga.steps - ka, unit1 - unit);
-        first_shared = unit == unit0;
-        unit += steps;
+        sg.ka = unit - tt * ga.steps;
+        sg.steps = min(ga.steps - sg.ka, unit1 - unit);
+        sg.first_shared = unit == unit0;
+        unit += sg.steps;
     } else {
-        break;
+        return false;
     }
-    const bool whole = steps == ga.steps;
-    float* const pslot = ga.partial + (size_t)(2 * bid + (first_shared ? 0 : 1)) * (kBM * kBN);
     int tm = tile % ga.Tm, tn = tile / ga.Tm;
     if (pair_order && tile < ga.whole) {
         // (a last, partial column among the whole tiles keeps its order)
@@ -408,20 +429,15 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         tm = 2 * (xcd & 3) + (j & 1);
         tn = round * (P >> 3) + 2 * (j >> 1) + (xcd >> 2);
     }
-    const int bm = tm * kBM, bn = tn * kBN;
+    sg.bm = tm * kBM;
+    sg.bn = tn * kBN;
+    return true;
+    };
+    int total = unit1 - unit0;   // steps of all segments
+    for (int w = vbid; w < ga.whole; w += P) total += ga.steps;
 
-    // This lane's weight rows (WN 32-column blocks): where their scales begin, and their power of two.
     // All tensors here are below 4 GB (checked by the host), so addresses are a uniform base plus a
     // 32-bit offset.
-    uint32_t soff[WN];
-    float winv[WN];
-    const int cwave = wave & 3;   // (a loading wave's own values of these are not used)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-        const int n = min(bn + (cwave * WN + j) * 32 + c, ga.N - 1);
-        soff[j] = (uint32_t)n * (uint32_t)G * 2u;
-        winv[j] = __builtin_bit_cast(float, 0x7F000000u - __builtin_bit_cast(uint32_t, ga.wmul[n]));
-    }
     const uint32_t as_lds = __builtin_amdgcn_readfirstlane(lds_addr(As));
     // fragment read offset of this lane (row c of a 32-row block): its half of the step's k is the
     // chunks kSub * kb + jj, and sub-step jj < kSub folds in by an XOR of the low bits
@@ -432,93 +448,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     // tied up while the loads fly.  The group of a lane's k is tracked without divisions (the group
     // size is a multiple of 64, so they never straddle two groups).
     unsigned char* const Bs = As + kStages * kBufBytes;  // [kStages][4 waves][WN][kBLane]
-
-    // operands of the step being multiplied; ck / cgrp follow the consumed steps like lk / lgrp.
-    // A step's codes, scale word and zero word are read back from the per-lane FIFO (take_read) and
-    // turned into the expansion's constants (take_convert) in two parts, so that the reads can be in
-    // flight, and the conversions issue, under the MFMAs of the previous step's last sub-step.
-    uint32_t wq[WN][4 * kCodeLoads];
-    uint32_t tsw[WN], tzw[WN];
-    f16x2_t nz[WN], nz6[WN], s2[WN];
-    int ck = ka * kBK + kBK / 2 * kb, cgrp = ck / ga.g, ckin = ck - cgrp * ga.g;
-    auto take_read = [&](int stage) {
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            const unsigned char* src = Bs + stage * kBStage + (cwave * WN + j) * kBLane;
-#pragma unroll
-            for (int pc = 0; pc < kCodeLoads; ++pc) {
-                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(src + pc * 1024 + lane * 16);
-                wq[j][4 * pc] = v.x; wq[j][4 * pc + 1] = v.y; wq[j][4 * pc + 2] = v.z; wq[j][4 * pc + 3] = v.w;
-            }
-            tsw[j] = *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + lane * 4);
-            tzw[j] = kBits == 4 ? *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + 256 + lane * 4) : 0u;
-        }
-    };
-    auto take_convert = [&]() {
-        const bool v = ck < ga.K;
-        const uint32_t grp = v ? (uint32_t)cgrp : 0u;
-        // past the end of K the scale becomes 0 by a factor, in a register: as a conditional value the
-        // compiler turns it into a masked section, which nothing can be scheduled across
-        float live = v ? 1.f : 0.f;
-        asm volatile("" : "+v"(live));
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            // the scale's 2 bytes inside the aligned word that was fetched
-            const uint32_t sbits = (tsw[j] >> (8u * ((soff[j] + grp * 2u) & 2u))) & 0xFFFFu;
-            const float sf = (float)__builtin_bit_cast(_Float16, (uint16_t)sbits);
-            const float z = kBits == 4 ? (float)((tzw[j] >> (4u * (grp & 7u))) & 0xFu) : 128.f;   // bytes: the flip's 128
-            const _Float16 srel = (_Float16)(sf * (winv[j] * live));
-            const _Float16 a = (_Float16)(-1024.f - z), b = (_Float16)(-64.f - z);
-            nz[j] = f16x2_t{a, a};
-            nz6[j] = f16x2_t{b, b};
-            s2[j] = f16x2_t{srel, srel};
-        }
-        ck += kBK;
-        ckin += kBK;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int over = ckin >= ga.g;
-            ckin -= over * ga.g;
-            cgrp += over;
-        }
-    };
-
-    f32x16_t acc[MB][WN];
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    f16x8_t af[2][MB], bf[2][WN];
-    auto fetch = [&](int stage, int jj, int slot) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-            af[slot][i] = *reinterpret_cast<const f16x8_t*>(As + stage * kBufBytes + i * (32 * kRowBytes) + (aoff0 ^ (jj << 4)));
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            if constexpr (kBits == 4)
-                bf[slot][j] = expand_word(wq[j][jj], magic, nz[j], nz6[j], s2[j]);
-            else
-                bf[slot][j] = expand_bytes(wq[j][2 * jj], wq[j][2 * jj + 1], flip, magic, nz[j], s2[j]);
-        }
-    };
-    auto multiply = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int j = 0; j < WN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[slot][i], bf[slot][j], acc[i][j], 0, 0, 0);
-        // issue order: each MFMA is followed by one LDS read and a share of the vector
-        // operations that prepare the next sub-step
-#pragma unroll
-        for (int u = 0; u < MB * WN; ++u) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
-            __builtin_amdgcn_sched_group_barrier(0x002, ((kBits == 4 ? 13 : 14) * WN + MB * WN - 1) / (MB * WN), 0);  // VALU
-        }
-    };
+    unsigned char* const Ps = Bs + kStages * kBStage;    // [kSegs][kPow2Bytes]
 
     if (loader) {
         // ---- the loading waves: one barrier after the first step has landed, then one per step, as the
@@ -537,21 +467,44 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         const int share = xwave ? wave - 4 : 0;
         const int lr = lane / S::kChunks, lp = lane % S::kChunks;
         const uint32_t pitchb = (uint32_t)ga.Kpad * 2u;
-        const uint32_t xrow0 = (uint32_t)(bm + kRows * share + lr) * pitchb;
         uint32_t xsw[kPeriod];
 #pragma unroll
         for (int qm = 0; qm < kPeriod; ++qm) xsw[qm] = (uint32_t)((lp ^ S::swizzle(kRows * (kXWaves * qm + share) + lr)) * 16);
+        Seg sg;
+        int left = 0, pstep = 0, seg_slot = 0;   // steps of the segment still to load, the next one
+        uint32_t xrow0 = 0;
         uint32_t qo[kWBlocks], so[kWBlocks], zo[kWBlocks];
-#pragma unroll
-        for (int mm = 0; mm < kWBlocks; ++mm) {
-            const int n = min(bn + mm * 32 + c, ga.N - 1);
-            qo[mm] = (uint32_t)n * (uint32_t)kw * 4u;
-            so[mm] = (uint32_t)n * (uint32_t)G * 2u;
-            zo[mm] = (uint32_t)n * (uint32_t)zwords * 4u;
-        }
-        int lk = ka * kBK + kBK / 2 * kb, lgrp = lk / ga.g, lkin = lk - lgrp * ga.g;
-        int pstep = ka;
+        int lk = 0, lgrp = 0, lkin = 0;
         auto load_step = [&](int slot) {
+            if (left == 0) {
+                if (next_segment(sg)) {
+                    left = sg.steps;
+                    pstep = sg.ka;
+                    xrow0 = (uint32_t)(sg.bm + kRows * share + lr) * pitchb;
+#pragma unroll
+                    for (int mm = 0; mm < kWBlocks; ++mm) {
+                        const int n = min(sg.bn + mm * 32 + c, ga.N - 1);
+                        qo[mm] = (uint32_t)n * (uint32_t)kw * 4u;
+                        so[mm] = (uint32_t)n * (uint32_t)G * 2u;
+                        zo[mm] = (uint32_t)n * (uint32_t)zwords * 4u;
+                    }
+                    lk = sg.ka * kBK + kBK / 2 * kb;
+                    lgrp = lk / ga.g;
+                    lkin = lk - lgrp * ga.g;
+                    if (!xwave) {
+                        // the tile's powers of two, in front of its first step (the waits below then wait a
+                        // little longer than they have to, never too little): lanes 0-31 take 8 columns each,
+                        // lanes 32-47 8 rows.  Columns past N are whatever the workspace holds there; nothing
+                        // stored depends on them.
+                        const uint32_t at = lane < 32 ? (uint32_t)(ga.wpow2 + sg.bn + 8 * lane) : (uint32_t)(sg.bm + 8 * (lane - 32));
+                        if (lane < 32 + kBM / 8) dma16(ga.pow2, at * 2u, as_lds + kStages * (kBufBytes + kBStage) + (uint32_t)seg_slot * kPow2Bytes);
+                    }
+                    seg_slot = seg_slot == S::kSegs - 1 ? 0 : seg_slot + 1;
+                } else {
+                    left = 1 << 30;   // past the last segment: the last step's addresses again, which nothing reads
+                }
+            }
+            --left;
             const uint32_t slot_x = as_lds + (uint32_t)slot * kBufBytes + (uint32_t)share * 1024u;
             const uint32_t slot_w = as_lds + kStages * kBufBytes + (uint32_t)slot * kBStage;
             if (xwave) {
@@ -591,7 +544,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         else __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kWLoads));
         __syncthreads();
         int fill = kStages - 1;
-        for (int s = 0; s < steps; ++s) {
+        for (int s = 0; s < total; ++s) {
             // slot `fill` held step s - 1 and is free since the previous barrier
             load_step(fill);
             fill = fill == kStages - 1 ? 0 : fill + 1;
@@ -600,135 +553,242 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
             else __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kWLoads));
             __syncthreads();
         }
-    } else {
-    __syncthreads();
-    take_read(0);
-    take_convert();
-    fetch(0, 0, 0);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // nothing may still be writing LDS when the block ends
+        return;
+    }
 
-    for (int s0 = 0; s0 < steps; s0 += kStages) {
+    // operands of the step being multiplied; ck / cgrp follow the consumed steps like lk / lgrp.
+    // A step's codes, scale word and zero word are read back from the per-lane FIFO (take_read) and
+    // turned into the expansion's constants (take_convert) in two parts, so that the reads can be in
+    // flight, and the conversions issue, under the MFMAs of the previous step's last sub-step.
+    uint32_t wq[WN][4 * kCodeLoads];
+    uint32_t tsw[WN], tzw[WN];
+    f16x2_t nz[WN], nz6[WN], s2[WN];
+    int ck = 0, cgrp = 0, ckin = 0;
+    uint32_t odd[WN];    // parity of the position of a column's first scale
+    float winv[WN];      // one over the power of two of its largest
+    // the constants of segment sg, whose powers of two are in slot `seg_slot`
+    auto take_segment = [&](const Seg& sg, int seg_slot) {
+        ck = sg.ka * kBK + kBK / 2 * kb;
+        cgrp = ck / ga.g;
+        ckin = ck - cgrp * ga.g;
 #pragma unroll
-        for (int u = 0; u < kStages; ++u) {
-            if (s0 + u >= steps) break;
-            const int cur = u, nxt = (u + 1) % kStages;
+        for (int j = 0; j < WN; ++j) {
+            const int col = (cwave * WN + j) * 32 + c;
+            odd[j] = (uint32_t)(min(sg.bn + col, ga.N - 1) * G) & 1u;
+            const uint32_t pw = *reinterpret_cast<const uint16_t*>(Ps + seg_slot * kPow2Bytes + col * 2);
+            winv[j] = __builtin_bit_cast(float, 0x7F000000u - (pw << 16));
+        }
+    };
+    auto take_read = [&](uint32_t boff) {
 #pragma unroll
-            for (int jj = 0; jj < S::kSub - 1; ++jj) {
-                __builtin_amdgcn_sched_barrier(0);
-                fetch(cur, jj + 1, (jj + 1) & 1);
-                multiply(jj & 1);
+        for (int j = 0; j < WN; ++j) {
+            const unsigned char* src = Bs + boff + (cwave * WN + j) * kBLane;
+#pragma unroll
+            for (int pc = 0; pc < kCodeLoads; ++pc) {
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(src + pc * 1024 + lane * 16);
+                wq[j][4 * pc] = v.x; wq[j][4 * pc + 1] = v.y; wq[j][4 * pc + 2] = v.z; wq[j][4 * pc + 3] = v.w;
             }
-            __builtin_amdgcn_sched_barrier(0);
-            // The loading waves have seen step s + 1 land.  The wait covers this wave's LDS reads (lgkmcnt
-            // 0), so after the barrier slot `cur` is dead for everyone once the last sub-step is done
-            // (its operands are already in registers).
-            __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-            __syncthreads();
-            __builtin_amdgcn_sched_barrier(0);
-            // The last sub-step of this step (operands already in registers) with the next step's set-up under
-            // it: all LDS reads first (FIFO and A fragments), a few MFMAs while they are in flight, then
-            // the conversions and the first expansion shared out among the remaining MFMAs.
-            take_read(nxt);
-            take_convert();
-            fetch(nxt, 0, 0);
+            tsw[j] = *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + lane * 4);
+            tzw[j] = kBits == 4 ? *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + 256 + lane * 4) : 0u;
+        }
+    };
+    auto take_convert = [&]() {
+        const bool v = ck < ga.K;
+        const uint32_t grp = v ? (uint32_t)cgrp : 0u;
+        // past the end of K the scale becomes 0 by a factor, in a register: as a conditional value the
+        // compiler turns it into a masked section, which nothing can be scheduled across
+        float live = v ? 1.f : 0.f;
+        asm volatile("" : "+v"(live));
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+            // the scale's 2 bytes inside the aligned word that was fetched
+            const uint32_t sbits = (tsw[j] >> (16u * ((odd[j] + grp) & 1u))) & 0xFFFFu;
+            const float sf = (float)__builtin_bit_cast(_Float16, (uint16_t)sbits);
+            const float z = kBits == 4 ? (float)((tzw[j] >> (4u * (grp & 7u))) & 0xFu) : 128.f;   // bytes: the flip's 128
+            const _Float16 srel = (_Float16)(sf * (winv[j] * live));
+            const _Float16 a = (_Float16)(-1024.f - z), b = (_Float16)(-64.f - z);
+            nz[j] = f16x2_t{a, a};
+            nz6[j] = f16x2_t{b, b};
+            s2[j] = f16x2_t{srel, srel};
+        }
+        ck += kBK;
+        ckin += kBK;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int over = ckin >= ga.g;
+            ckin -= over * ga.g;
+            cgrp += over;
+        }
+    };
+
+    f32x16_t acc[MB][WN];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+
+    f16x8_t af[2][MB], bf[2][WN];
+    auto fetch = [&](uint32_t aoff, int jj, int slot) {
+        const unsigned char* src = As + aoff + (aoff0 ^ (jj << 4));
+#pragma unroll
+        for (int i = 0; i < MB; ++i) af[slot][i] = *reinterpret_cast<const f16x8_t*>(src + i * (32 * kRowBytes));
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+            if constexpr (kBits == 4)
+                bf[slot][j] = expand_word(wq[j][jj], magic, nz[j], nz6[j], s2[j]);
+            else
+                bf[slot][j] = expand_bytes(wq[j][2 * jj], wq[j][2 * jj + 1], flip, magic, nz[j], s2[j]);
+        }
+    };
+    auto multiply = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
+        // issue order: each MFMA is followed by one LDS read and a share of the vector
+        // operations that prepare the next sub-step
+#pragma unroll
+        for (int u = 0; u < MB * WN; ++u) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
+            __builtin_amdgcn_sched_group_barrier(0x002, ((kBits == 4 ? 13 : 14) * WN + MB * WN - 1) / (MB * WN), 0);  // VALU
+        }
+    };
+
+    // The end of a segment: lane (c, kb) has row 32 i + c and columns 8 q + 4 kb + 0..3 of every 32-column
+    // block in acc[i][j][4 q ..].
+    auto finish = [&](const Seg& sg, int seg_slot) {
+        if (sg.steps != ga.steps) {
+            // part of a tile's K: the raw sums go to this block's slot
+            float* const slot = ga.partial + (size_t)(2 * bid + (sg.first_shared ? 0 : 1)) * (kBM * kBN);
+            f32x4_t* const dst = reinterpret_cast<f32x4_t*>(slot) + cwave * (MB * WN * 4) * 64 + lane;
 #pragma unroll
             for (int i = 0; i < MB; ++i)
 #pragma unroll
                 for (int j = 0; j < WN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[1][i], bf[1][j], acc[i][j], 0, 0, 0);
-            constexpr int kLead = MB * WN < 4 ? 1 : 3;                     // MFMAs issued before any conversion
-            constexpr int kSetupValu = (kBits == 4 ? 13 + 16 : 14 + 12) * WN + 8;
-            __builtin_amdgcn_sched_group_barrier(0x100, WN * (kCodeLoads + (kBits == 4 ? 2 : 1)) + MB, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
-            if constexpr (MB * WN > kLead) {
 #pragma unroll
-                for (int u = 0; u < MB * WN - kLead; ++u) {
-                    __builtin_amdgcn_sched_group_barrier(0x002, (kSetupValu + MB * WN - kLead - 1) / (MB * WN - kLead), 0);
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    for (int q = 0; q < 4; ++q)
+                        dst[((i * WN + j) * 4 + q) * 64] = f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            return;
+        }
+        // y = acc * 2^-p(m) * 2^E(n), rounded once to bf16.  The halves of the wave exchange pieces, so that a
+        // lane stores eight neighbouring columns of its row.
+        const unsigned char* const pw = Ps + seg_slot * kPow2Bytes;
+        const bool vec_ok = (ga.N % 8) == 0;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+#pragma unroll
+            for (int qp = 0; qp < 2; ++qp) {
+                float wm[2][4];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint2 w2 = *reinterpret_cast<const uint2*>(pw + ((cwave * WN + j) * 32 + 16 * qp + 8 * h + 4 * kb) * 2);
+                    wm[h][0] = __builtin_bit_cast(float, w2.x << 16);
+                    wm[h][1] = __builtin_bit_cast(float, w2.x & 0xFFFF0000u);
+                    wm[h][2] = __builtin_bit_cast(float, w2.y << 16);
+                    wm[h][3] = __builtin_bit_cast(float, w2.y & 0xFFFF0000u);
+                }
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+                    const float rs = bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(pw + 512 + (32 * i + c) * 2));
+                    const f32x16_t& v = acc[i][j];
+                    uint32_t p[2][2];   // [which 8 columns][pair]
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const int r = 4 * (2 * qp + h) + 2 * e;
+                            p[h][e] = f32x2_to_bf16x2_rne(v[r] * rs * wm[h][2 * e], v[r + 1] * rs * wm[h][2 * e + 1]);
+                        }
+                    // lanes 32-63 of the first operand and lanes 0-31 of the second change places
+                    const auto a = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+                    const auto b = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+                    const u32x4_t o = {a[0], b[0], a[1], b[1]};
+                    const int m = sg.bm + 32 * i + c, n = sg.bn + (cwave * WN + j) * 32 + 16 * qp + 8 * kb;
+                    if (m < ga.M && n < ga.N) {
+                        uint16_t* dst = ga.y + (size_t)m * ga.N + n;
+                        if (vec_ok) {
+                            *reinterpret_cast<u32x4_t*>(dst) = o;
+                        } else {
+                            const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                if (n + e < ga.N) dst[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
+                        }
+                    }
                 }
             }
         }
-    }
-    }  // MFMA waves
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // nothing may still be writing LDS
-    __syncthreads();
+    };
 
-    if (!whole) {
-        // part of a tile's K: the raw sums go to this block's slot, tile-shaped [kBM][kBN],
-        // through LDS so that they leave as 16-byte pieces of full lines
-        constexpr int kPPitch = kBN + 4;  // floats per staged row
-        static_assert(kBM * kPPitch * 4 <= kStages * (kBufBytes + kBStage), "the fp32 tile fits in the ring");
-        float* const stage = reinterpret_cast<float*>(As) + (4 * kb) * kPPitch + cwave * WN * 32 + c;
-        if (!loader) {
+    Seg sg, ahead;
+    if (!next_segment(sg)) return;   // (every block has one)
+    bool more = next_segment(ahead);
+    int left = sg.steps, seg_slot = 0;
+    uint32_t acur = 0, bcur = 0;     // the step's slot
+    clear();
+    __syncthreads();
+    take_segment(sg, 0);
+    take_read(0);
+    take_convert();
+    fetch(0, 0, 0);
+    for (;;) {
+#pragma unroll
+        for (int jj = 0; jj < S::kSub - 1; ++jj) {
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(acur, jj + 1, (jj + 1) & 1);
+            multiply(jj & 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // The loading waves have seen step s + 1 land.  The wait covers this wave's LDS reads (lgkmcnt 0, not
+        // its stores), so after the barrier the step's slot is dead for everyone once the last sub-step is
+        // done (its operands are already in registers).
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(63));
+        __syncthreads();
+        acur = acur == (kStages - 1) * kBufBytes ? 0 : acur + kBufBytes;
+        bcur = bcur == (kStages - 1) * kBStage ? 0 : bcur + kBStage;
+        const bool last = --left == 0;
+        const int next_slot = seg_slot == S::kSegs - 1 ? 0 : seg_slot + 1;
+        if (last && more) take_segment(ahead, next_slot);
+        __builtin_amdgcn_sched_barrier(0);
+        // The last sub-step of this step (operands already in registers) with the next step's set-up under
+        // it: all LDS reads first (FIFO and A fragments), a few MFMAs while they are in flight, then
+        // the conversions and the first expansion shared out among the remaining MFMAs.
+        take_read(bcur);
+        take_convert();
+        fetch(acur, 0, 0);
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int j = 0; j < WN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[1][j], af[1][i], acc[i][j], 0, 0, 0);
+        constexpr int kLead = MB * WN < 4 ? 1 : 3;                     // MFMAs issued before any conversion
+        constexpr int kSetupValu = (kBits == 4 ? 13 + 16 : 14 + 12) * WN + 8;
+        __builtin_amdgcn_sched_group_barrier(0x100, WN * (kCodeLoads + (kBits == 4 ? 2 : 1)) + MB, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
+        if constexpr (MB * WN > kLead) {
 #pragma unroll
-                for (int i = 0; i < MB; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        stage[(i * 32 + 8 * (r / 4) + (r % 4)) * kPPitch + j * 32] = acc[i][j][r];
-        }
-        __syncthreads();
-        for (int idx = t; idx < kBM * (kBN / 4); idx += kThreads) {
-            const int row = idx / (kBN / 4), c4 = idx % (kBN / 4);
-            *reinterpret_cast<f32x4_t*>(pslot + row * kBN + c4 * 4) =
-                *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(As) + row * kPPitch + c4 * 4);
-        }
-        // the next segment counts its loads in flight exactly and reuses LDS
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-        __syncthreads();
-        continue;
-    }
-    // y = acc * 2^-p(m) * 2^E(n), rounded once to bf16, staged in LDS so that rows leave as
-    // 16-byte pieces of full lines.
-    if (!loader) {
-    float wm[WN];
-#pragma unroll
-    for (int j = 0; j < WN; ++j) wm[j] = ga.wmul[min(bn + (cwave * WN + j) * 32 + c, ga.N - 1)];
-    // the row factors of the lane's 16 MB rows, four neighbouring rows per load, all requested before
-    // the first is used (fetched where they are used, each load waited for the one before it: 4 MB
-    // round trips per tile)
-    f32x4_t rsv[MB][4];
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd)
-            rsv[i][qd] = *reinterpret_cast<const f32x4_t*>(ga.rscale + bm + i * 32 + 8 * qd + 4 * kb);
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            // registers r and r + 1 are two neighbouring rows of the lane's column
-            const int row = i * 32 + 8 * (r / 4) + 4 * kb + (r % 4);
-            const float rs0 = rsv[i][r / 4][r % 4], rs1 = rsv[i][r / 4][r % 4 + 1];
-#pragma unroll
-            for (int j = 0; j < WN; ++j) {
-                const int col = (cwave * WN + j) * 32 + c;
-                const uint32_t h = f32x2_to_bf16x2_rne(acc[i][j][r] * rs0 * wm[j], acc[i][j][r + 1] * rs1 * wm[j]);
-                *reinterpret_cast<uint16_t*>(As + row * kCPitch + col * 2) = (uint16_t)h;
-                *reinterpret_cast<uint16_t*>(As + (row + 1) * kCPitch + col * 2) = (uint16_t)(h >> 16);
+            for (int u = 0; u < MB * WN - kLead; ++u) {
+                __builtin_amdgcn_sched_group_barrier(0x002, (kSetupValu + MB * WN - kLead - 1) / (MB * WN - kLead), 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!last) continue;
+        finish(sg, seg_slot);
+        if (!more) break;
+        clear();
+        sg = ahead;
+        left = sg.steps;
+        seg_slot = next_slot;
+        more = next_segment(ahead);
     }
-    __syncthreads();
-    constexpr int kChunks = kBN / 8;  // 16-byte pieces per row
-    const bool vec_ok = (ga.N % 8) == 0;
-    for (int idx = t; idx < kBM * kChunks; idx += kThreads) {
-        const int row = idx / kChunks, ch = idx % kChunks;
-        const int m = bm + row, n = bn + ch * 8;
-        if (m >= ga.M || n >= ga.N) continue;
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(As + row * kCPitch + ch * 16);
-        uint16_t* dst = ga.y + (size_t)m * ga.N + n;
-        if (vec_ok && n + 8 <= ga.N) {
-            *reinterpret_cast<u32x4_t*>(dst) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int e = 0; e < 8 && n + e < ga.N; ++e) dst[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
-        }
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __syncthreads();  // the staging tile is about to be overwritten by the next segment's loads
-    }  // segments
 }
 
 // Adds up the slots of every tile whose K range was shared between blocks (in K order) and
@@ -772,10 +832,11 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
     }
 
     const int idx = blockIdx.y * 256 + t;
-    const int row = idx / (kBN / 4), c4 = idx % (kBN / 4);
-    const int m = (tile % ga.Tm) * kBM + row, n = (tile / ga.Tm) * kBN + c4 * 4;
+    const int piece = idx / 64, ilane = idx % 64;
+    const int q = piece % 4, j = piece / 4 % WN, i0 = piece / (4 * WN) % MB, w0 = piece / (4 * WN * MB);
+    const int m = (tile % ga.Tm) * kBM + 32 * i0 + ilane % 32, n = (tile / ga.Tm) * kBN + (w0 * WN + j) * 32 + 8 * q + 4 * (ilane / 32);
     if (m >= ga.M || n >= ga.N) return;
-    const float* src = ga.partial + row * kBN + c4 * 4;
+    const float* src = ga.partial + idx * 4;
     f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
     int i = 0;
     for (; i + 4 <= count; i += 4) {
@@ -786,11 +847,11 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
         for (int e = 0; e < 4; ++e) sum += v[e];
     }
     for (; i < count; ++i) sum += *reinterpret_cast<const f32x4_t*>(src + (size_t)slots[i] * (kBM * kBN));
-    const float rs = ga.rscale[m];
+    const float rs = bf16_bits_to_f32(ga.pow2[m]);
     uint16_t* dst = ga.y + (size_t)m * ga.N + n;
     uint16_t h[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = f32_to_bf16_rne(sum[e] * rs * ga.wmul[min(n + e, ga.N - 1)]);
+    for (int e = 0; e < 4; ++e) h[e] = f32_to_bf16_rne(sum[e] * rs * bf16_bits_to_f32(ga.pow2[ga.wpow2 + min(n + e, ga.N - 1)]));
     if ((ga.N % 4) == 0) {
         *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
     } else {
@@ -961,12 +1022,12 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool 
         const qail_wdesc& d = items[i].d;
         const int Kpad = round_up(d.K, kPadK), G = d.K / d.group_size;
         uint16_t* xh = reinterpret_cast<uint16_t*>(at);
-        float* rscale = reinterpret_cast<float*>(xh + (size_t)Mpad * Kpad);
-        float* wmul = rscale + Mpad;
+        uint16_t* rscale = xh + (size_t)Mpad * Kpad;
+        uint16_t* wmul = rscale + Mpad;
         at += gemm_head_bytes(d, M);
         pb.it[i] = PrepItem{items[i].x, items[i].scales, xh, rscale, wmul, d.N, d.K, Kpad, G};
-        ga[i] = GemmArgs{items[i].qweight, items[i].scales, items[i].zeros, xh, rscale, wmul, items[i].y,
-                         M, d.N, d.K, Kpad, d.group_size, 0, 0, 0, 0, nullptr, 0, 0};
+        ga[i] = GemmArgs{items[i].qweight, items[i].scales, items[i].zeros, xh, rscale, items[i].y,
+                         M, d.N, d.K, Kpad, d.group_size, Mpad, 0, 0, 0, 0, nullptr, 0, 0};
         prep_blocks = std::max(prep_blocks, Mpad + (d.N + 31) / 32);
     }
     for (int i = n; i < kGemmBatch; ++i) pb.it[i] = pb.it[n - 1];
