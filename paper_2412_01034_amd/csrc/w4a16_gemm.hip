@@ -32,7 +32,7 @@
 // 64 k deep instead of 128, so that a lane's share of it is two 16-byte pieces as well and the ring
 // (four slots of half the depth) fits LDS beside the wide tiles.  With 128-k steps only 128-column
 // tiles fitted, on which every MFMA costs one 1 KB fragment read, the LDS's full bandwidth: one
-// decoder layer at M = 288 took 210 us with them, 200 us now.
+// decoder layer at M = 288 took 213 us with them, 200 with this layout alone.
 //
 // MFMA operand layout (32x32x16, wave64): lane l supplies row (A) / column (B) l%32 and
 // the 8 consecutive k starting at 8*(l/32); it receives D[8*(r/4) + 4*(l/32) + r%4][l%32]
@@ -225,6 +225,11 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t ld
 // chunk s of row r is kept at position s ^ swizzle(r), which makes the 16 lanes of a fragment read (16
 // consecutive rows, same s) hit 16 different positions of a 256-byte line and 8 consecutive ones 8
 // different ones of a 128-byte line: conflict-free.
+// The codes of a step are 64 bytes per weight row and are fetched row by row (a load is 16 rows x 64 bytes:
+// with every lane fetching its own pieces it touched 32 rows twice, and one decoder layer of 8-bit weights at
+// M = 288, whose weight loads are the bottleneck, took 194 instead of 180 us); piece p (16 bytes) of row r is kept at position
+// p ^ code_swizzle(r) of the row's 64 bytes: conflict-free reads as above.
+__device__ __forceinline__ int code_swizzle(int r) { return ((r >> 2) & 3) ^ (r & 2); }
 constexpr int kPow2Bytes = 768;   // powers of two of a tile: 256 columns, then 128 rows, bf16
 
 template <int kBits>
@@ -235,11 +240,16 @@ struct Step {
     static constexpr int kRowBytes = 2 * kBK;
     static constexpr int kChunks = kRowBytes / 16;
     static constexpr int kCodeLoads = kBK / 2 * kBits / 128;       // 16-byte pieces of a lane's codes of a step
-    static constexpr int kLane = kCodeLoads * 1024 + (kBits == 4 ? 512 : 256);   // bytes per wave and column block: codes, scale words, zero words
+    static constexpr int kLane = kCodeLoads * 1024 + (kBits == 4 ? 512 : 0);   // bytes per wave and column block: codes, nibbles: scale words, zero words
     __device__ static __forceinline__ int swizzle(int r) { return kBits == 4 ? r & 15 : (r & 7) ^ ((r >> 3) & 1); }
     static constexpr int kSegs = kStages + 1;                      // segments whose powers of two are in LDS
+    // Bytes: a step lies inside one group, whose scale words (a tile's columns) are loaded once, with the
+    // group's first step, into one of kSegs slots (a group lasts at least a step, as a segment does).  Loaded
+    // with every step, for either half of the wave, they were a third of the weight loads (the layer above:
+    // 180 -> 169 us; at M = 1024 476 -> 461).
+    static constexpr int kScales = kBits == 4 ? 0 : 1024;          // bytes of such a slot
     static constexpr size_t lds(int rows, int col_blocks) {
-        return (size_t)kStages * (rows * kRowBytes + col_blocks * kLane) + kSegs * kPow2Bytes;
+        return (size_t)kStages * (rows * kRowBytes + col_blocks * kLane) + kSegs * (kPow2Bytes + kScales);
     }
 };
 
@@ -448,7 +458,9 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     // tied up while the loads fly.  The group of a lane's k is tracked without divisions (the group
     // size is a multiple of 64, so they never straddle two groups).
     unsigned char* const Bs = As + kStages * kBufBytes;  // [kStages][4 waves][WN][kBLane]
-    unsigned char* const Ps = Bs + kStages * kBStage;    // [kSegs][kPow2Bytes]
+    unsigned char* const Ps = Bs + kStages * kBStage;    // [kSegs][kPow2Bytes], then (bytes) [kSegs][kScales]
+    unsigned char* const Cs = Ps + S::kSegs * kPow2Bytes;
+    const int khalf = kBits == 4 ? kBK / 2 * kb : 0;     // first k of the lane's half, as far as groups are concerned
 
     if (loader) {
         // ---- the loading waves: one barrier after the first step has landed, then one per step, as the
@@ -459,7 +471,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         constexpr int kRows = 64 / S::kChunks;           // rows per 1 KB load
         constexpr int kXLoads = kBM / kRows / kXWaves;   // per x wave and step
         constexpr int kWBlocks = 4 * WN;
-        constexpr int kWLoads = kWBlocks * (kCodeLoads + (kBits == 4 ? 2 : 1));
+        constexpr int kWLoads = kWBlocks * (kCodeLoads + (kBits == 4 ? 2 : 0));   // ... and what starts a segment or a group
         constexpr int kPeriod = 16 / (kRows * kXWaves);  // loads of a wave after which the swizzle repeats
         static_assert(kBM % (kRows * kXWaves) == 0 && 16 % (kRows * kXWaves) == 0, "loads divide evenly");
         static_assert((kStages - 2) * kXLoads < 64 && (kStages - 2) * kWLoads < 64, "the waits' counts fit the load counter");
@@ -473,8 +485,12 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         Seg sg;
         int left = 0, pstep = 0, seg_slot = 0;   // steps of the segment still to load, the next one
         uint32_t xrow0 = 0;
-        uint32_t qo[kWBlocks], so[kWBlocks], zo[kWBlocks];
+        uint32_t qo[kWBlocks][kCodeLoads], so[kWBlocks], zo[kWBlocks];
+        const int crow = lane >> 2, cpiece = (lane & 3) ^ code_swizzle(crow);   // row of the 16, which 16 bytes of its 64
+        const uint32_t ck = (uint32_t)(cpiece * 128 / kBits);                   // ... and their first k
         int lk = 0, lgrp = 0, lkin = 0;
+        int group_slot = -1;     // bytes: the current group's scales
+        bool fresh = false;      // the next step is the first of a group
         auto load_step = [&](int slot) {
             if (left == 0) {
                 if (next_segment(sg)) {
@@ -484,11 +500,14 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
 #pragma unroll
                     for (int mm = 0; mm < kWBlocks; ++mm) {
                         const int n = min(sg.bn + mm * 32 + c, ga.N - 1);
-                        qo[mm] = (uint32_t)n * (uint32_t)kw * 4u;
+#pragma unroll
+                        for (int part = 0; part < kCodeLoads; ++part)
+                            qo[mm][part] = (uint32_t)min(sg.bn + mm * 32 + 16 * part + crow, ga.N - 1) * (uint32_t)kw * 4u + 16u * (uint32_t)cpiece;
                         so[mm] = (uint32_t)n * (uint32_t)G * 2u;
                         zo[mm] = (uint32_t)n * (uint32_t)zwords * 4u;
                     }
-                    lk = sg.ka * kBK + kBK / 2 * kb;
+                    lk = sg.ka * kBK + khalf;
+                    fresh = true;
                     lgrp = lk / ga.g;
                     lkin = lk - lgrp * ga.g;
                     if (!xwave) {
@@ -515,16 +534,28 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                           slot_x + qq * kXWaves * 1024);
             } else {
                 const bool v = lk < ga.K;
-                const uint32_t kc = v ? (uint32_t)lk : 0u;
+                const uint32_t k0 = (uint32_t)(pstep * kBK);
+                const uint32_t kc = k0 + ck < (uint32_t)ga.K ? k0 : 0u;   // past the end: any valid address, the scale becomes 0
                 const uint32_t grp = v ? (uint32_t)lgrp : 0u;
+                if (kBits == 8 && fresh) {
+                    group_slot = group_slot == S::kSegs - 1 ? 0 : group_slot + 1;
+                    fresh = false;
+#pragma unroll
+                    for (int q = 0; q < 2 * WN; ++q) {
+                        const uint32_t so64 = (uint32_t)min(sg.bn + 64 * q + lane, ga.N - 1) * (uint32_t)G * 2u;
+                        dma4(ga.sc, (so64 + grp * 2u) & ~3u, as_lds + (uint32_t)(Cs - As) + (uint32_t)group_slot * S::kScales + 256 * q);
+                    }
+                }
 #pragma unroll
                 for (int mm = 0; mm < kWBlocks; ++mm) {
                     const uint32_t dst = slot_w + mm * kBLane;
 #pragma unroll
                     for (int part = 0; part < kCodeLoads; ++part)
-                        dma16(ga.qw, qo[mm] + kc * kBits / 8 + 16 * part, dst + 1024 * part);
-                    dma4(ga.sc, (so[mm] + grp * 2u) & ~3u, dst + kCodeLoads * 1024);
-                    if (kBits == 4) dma4(ga.zr, zo[mm] + (grp / 8u) * 4u, dst + kCodeLoads * 1024 + 256);
+                        dma16(ga.qw, qo[mm][part] + kc * kBits / 8, dst + 1024 * part);
+                    if constexpr (kBits == 4) {
+                        dma4(ga.sc, (so[mm] + grp * 2u) & ~3u, dst + kCodeLoads * 1024);
+                        dma4(ga.zr, zo[mm] + (grp / 8u) * 4u, dst + kCodeLoads * 1024 + 256);
+                    }
                 }
             }
             ++pstep;
@@ -535,6 +566,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                 const int over = lkin >= ga.g;
                 lkin -= over * ga.g;
                 lgrp += over;
+                if (over) fresh = true;
             }
         };
 #pragma unroll
@@ -564,12 +596,14 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     uint32_t wq[WN][4 * kCodeLoads];
     uint32_t tsw[WN], tzw[WN];
     f16x2_t nz[WN], nz6[WN], s2[WN];
-    int ck = 0, cgrp = 0, ckin = 0;
+    int ck = 0, cgrp = 0, ckin = 0, group_slot = -1;
+    bool new_group = false;
     uint32_t odd[WN];    // parity of the position of a column's first scale
     float winv[WN];      // one over the power of two of its largest
     // the constants of segment sg, whose powers of two are in slot `seg_slot`
     auto take_segment = [&](const Seg& sg, int seg_slot) {
-        ck = sg.ka * kBK + kBK / 2 * kb;
+        ck = sg.ka * kBK + khalf;
+        new_group = true;
         cgrp = ck / ga.g;
         ckin = ck - cgrp * ga.g;
 #pragma unroll
@@ -581,15 +615,21 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         }
     };
     auto take_read = [&](uint32_t boff) {
+        if (kBits == 8 && new_group) {
+            group_slot = group_slot == S::kSegs - 1 ? 0 : group_slot + 1;
+            new_group = false;
+        }
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             const unsigned char* src = Bs + boff + (cwave * WN + j) * kBLane;
+            const unsigned char* row = src + c * 64;
 #pragma unroll
             for (int pc = 0; pc < kCodeLoads; ++pc) {
-                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(src + pc * 1024 + lane * 16);
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(row + (((2 * kb + pc) ^ code_swizzle(c)) << 4));
                 wq[j][4 * pc] = v.x; wq[j][4 * pc + 1] = v.y; wq[j][4 * pc + 2] = v.z; wq[j][4 * pc + 3] = v.w;
             }
-            tsw[j] = *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + lane * 4);
+            tsw[j] = kBits == 4 ? *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + lane * 4)
+                                : *reinterpret_cast<const uint32_t*>(Cs + group_slot * S::kScales + ((cwave * WN + j) * 32 + c) * 4);
             tzw[j] = kBits == 4 ? *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + 256 + lane * 4) : 0u;
         }
     };
@@ -619,6 +659,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
             const int over = ckin >= ga.g;
             ckin -= over * ga.g;
             cgrp += over;
+            if (over) new_group = true;
         }
     };
 
