@@ -11,6 +11,20 @@ namespace {
 
 constexpr int kRedBlocks = 1024;  // partial sums of the step gradient (workspace floats)
 
+// Results, and inputs that one training step reads once (weights, logits), pass the caches by: what they would
+// take there is what the next operator has to fetch again, the activations above all, which forward and
+// backward of the step quantiser both read.  4096 x 4096 weights 26.2 -> 21.5 us (results only); weights,
+// activations (6.4 M) and logits (256 x 32000) one after the other 79.1 -> 71.0 (results only) -> 65.6 us.  Sizes that
+// fit the caches gain nothing and lose nothing.  Activations are read the ordinary way: streamed, the backward
+// alone takes 16.5 instead of 15.1 us.
+__device__ __forceinline__ void store_once(float4* p, const float4 v) {
+    __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(p));
+}
+__device__ __forceinline__ float4 load_once(const float4* p) {
+    const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p));
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -77,7 +91,7 @@ __global__ __launch_bounds__(256) void fake_quant_w4_half_kernel(const float* __
         float lo = 0.f, hi = 0.f;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
-            v[u] = l + 32 * u < n4 ? src[l + 32 * u] : make_float4(0.f, 0.f, 0.f, 0.f);  // 0 leaves lo <= 0 <= hi alone
+            v[u] = l + 32 * u < n4 ? load_once(src + l + 32 * u) : make_float4(0.f, 0.f, 0.f, 0.f);  // 0 leaves lo <= 0 <= hi alone
             lo = fminf(fminf(lo, fminf(v[u].x, v[u].y)), fminf(v[u].z, v[u].w));
             hi = fmaxf(fmaxf(hi, fmaxf(v[u].x, v[u].y)), fmaxf(v[u].z, v[u].w));
         }
@@ -101,7 +115,7 @@ __global__ __launch_bounds__(256) void fake_quant_w4_half_kernel(const float* __
             r.y = (fminf(fmaxf(rintf(v[u].y / s) + z, 0.f), 15.f) - z) * s;
             r.z = (fminf(fmaxf(rintf(v[u].z / s) + z, 0.f), 15.f) - z) * s;
             r.w = (fminf(fmaxf(rintf(v[u].w / s) + z, 0.f), 15.f) - z) * s;
-            if (l + 32 * u < n4) dst[l + 32 * u] = r;
+            if (l + 32 * u < n4) store_once(dst + l + 32 * u, r);
         }
     }
 }
@@ -120,7 +134,7 @@ __global__ __launch_bounds__(256) void lsq_fwd_kernel(const float* __restrict__ 
         r.y = fminf(fmaxf(rintf(a.y / s), qn), qp) * s;
         r.z = fminf(fmaxf(rintf(a.z / s), qn), qp) * s;
         r.w = fminf(fmaxf(rintf(a.w / s), qn), qp) * s;
-        o4[i] = r;
+        store_once(o4 + i, r);
     }
     for (size_t i = n4 * 4 + first; i < n; i += stride) out[i] = fminf(fmaxf(rintf(v[i] / s), qn), qp) * s;
 }
@@ -149,7 +163,7 @@ __global__ __launch_bounds__(256) void lsq_bwd_kernel(const float* __restrict__ 
         one(a.y, d.y, g.y);
         one(a.z, d.z, g.z);
         one(a.w, d.w, g.w);
-        g4[i] = g;
+        store_once(g4 + i, g);
     }
     for (size_t i = n4 * 4 + first; i < n; i += stride) one(v[i], dout[i], dv[i]);
     const float tot = block_sum_256(acc, red);
@@ -200,7 +214,7 @@ __global__ __launch_bounds__(1024) void qbc_rows_reg_kernel(const float* __restr
         const int j = threadIdx.x + 1024 * u;
         d[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (j < n4) {
-            const float4 a = q4[j], b = f4[j];
+            const float4 a = load_once(q4 + j), b = load_once(f4 + j);
             d[u] = make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
         }
         acc = fmaf(d[u].x, d[u].x, acc);
@@ -223,7 +237,7 @@ __global__ __launch_bounds__(1024) void qbc_rows_reg_kernel(const float* __restr
 #pragma unroll
         for (int u = 0; u < kQbcPer; ++u) {
             const int j = threadIdx.x + 1024 * u;
-            if (j < n4) g4[j] = make_float4(d[u].x * k, d[u].y * k, d[u].z * k, d[u].w * k);
+            if (j < n4) store_once(g4 + j, make_float4(d[u].x * k, d[u].y * k, d[u].z * k, d[u].w * k));
         }
     }
 }
