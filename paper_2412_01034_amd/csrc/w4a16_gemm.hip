@@ -50,6 +50,8 @@ namespace {
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any_t __attribute__((ext_vector_type(2), aligned(2)));
 
 constexpr int kPadK = 128;              // rows of the fp16 copy of x are padded to this
 constexpr int kMaxGemmBlocks = 512;     // upper bound of the grid (the workspace has two slots per block)
@@ -315,6 +317,8 @@ __host__ __device__ inline int owner_of(long long u, long long units, int P) { r
 // epilogue around 57 us of K loop at K = 4096, M = 1024; 18 of 128 us at M = 288.
 // One decoder layer: 60.0 -> 57.8 us at M = 48, 153.9 -> 149.8 at M = 288; 410 at M = 1024 either way, where
 // the chip is limited by power (1.80 GHz sustained of 2.4) and idle time was buying clock.
+// That is also where it costs something: one 128-row tile per block (4096 x 4096 at M = 1024 launched alone)
+// 45.0 -> 47.7 us, the layer at M = 2048 771 -> 785.  Staging a block's last tile in LDS again did not help.
 // What the end of a segment needs, the powers of two of its rows and columns, is loaded with its first
 // step into one of kSegs slots: the step that is loaded first for segment q is loaded behind the barrier
 // of step kStages before it, and segments are at least one step long, so everybody has left segment
@@ -399,6 +403,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     // the block's next segment: K steps [ka, ka + steps) of the tile at (bm, bn); false: there is none
     struct Seg {
         int bm, bn, ka, steps;
+        int grp, kin;        // group of k = ka kBK, and the k of it that lie before
         bool first_shared;
     };
     int wtile = vbid, unit = unit0;
@@ -439,6 +444,8 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         tm = 2 * (xcd & 3) + (j & 1);
         tn = round * (P >> 3) + 2 * (j >> 1) + (xcd >> 2);
     }
+    sg.grp = sg.ka * kBK / ga.g;
+    sg.kin = sg.ka * kBK - sg.grp * ga.g;
     sg.bm = tm * kBM;
     sg.bn = tn * kBN;
     return true;
@@ -508,8 +515,9 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                     }
                     lk = sg.ka * kBK + khalf;
                     fresh = true;
-                    lgrp = lk / ga.g;
-                    lkin = lk - lgrp * ga.g;
+                    lkin = sg.kin + khalf;   // (less than two groups)
+                    lgrp = sg.grp + (lkin >= ga.g);
+                    lkin -= lkin >= ga.g ? ga.g : 0;
                     if (!xwave) {
                         // the tile's powers of two, in front of its first step (the waits below then wait a
                         // little longer than they have to, never too little): lanes 0-31 take 8 columns each,
@@ -598,21 +606,18 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     f16x2_t nz[WN], nz6[WN], s2[WN];
     int ck = 0, cgrp = 0, ckin = 0, group_slot = -1;
     bool new_group = false;
-    uint32_t odd[WN];    // parity of the position of a column's first scale
-    float winv[WN];      // one over the power of two of its largest
-    // the constants of segment sg, whose powers of two are in slot `seg_slot`
+    int bnext = 0, pnext = 0;   // columns of the step to be taken, and where its powers of two are
+    uint32_t tpw[WN];
     auto take_segment = [&](const Seg& sg, int seg_slot) {
         ck = sg.ka * kBK + khalf;
+        ckin = sg.kin + khalf;
+        cgrp = sg.grp;
+        const int over = ckin >= ga.g;
+        ckin -= over * ga.g;
+        cgrp += over;
         new_group = true;
-        cgrp = ck / ga.g;
-        ckin = ck - cgrp * ga.g;
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            const int col = (cwave * WN + j) * 32 + c;
-            odd[j] = (uint32_t)(min(sg.bn + col, ga.N - 1) * G) & 1u;
-            const uint32_t pw = *reinterpret_cast<const uint16_t*>(Ps + seg_slot * kPow2Bytes + col * 2);
-            winv[j] = __builtin_bit_cast(float, 0x7F000000u - (pw << 16));
-        }
+        bnext = sg.bn;
+        pnext = seg_slot * kPow2Bytes;
     };
     auto take_read = [&](uint32_t boff) {
         if (kBits == 8 && new_group) {
@@ -630,6 +635,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
             }
             tsw[j] = kBits == 4 ? *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + lane * 4)
                                 : *reinterpret_cast<const uint32_t*>(Cs + group_slot * S::kScales + ((cwave * WN + j) * 32 + c) * 4);
+            tpw[j] = *reinterpret_cast<const uint16_t*>(Ps + pnext + ((cwave * WN + j) * 32 + c) * 2);
             tzw[j] = kBits == 4 ? *reinterpret_cast<const uint32_t*>(src + kCodeLoads * 1024 + 256 + lane * 4) : 0u;
         }
     };
@@ -643,10 +649,14 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             // the scale's 2 bytes inside the aligned word that was fetched
-            const uint32_t sbits = (tsw[j] >> (16u * ((odd[j] + grp) & 1u))) & 0xFFFFu;
+            // (the parity of its position n G + grp)
+            const uint32_t n = (uint32_t)min(bnext + (cwave * WN + j) * 32 + c, ga.N - 1);
+            const uint32_t sbits = (tsw[j] >> (16u * (((n & (uint32_t)G) ^ grp) & 1u))) & 0xFFFFu;
             const float sf = (float)__builtin_bit_cast(_Float16, (uint16_t)sbits);
             const float z = kBits == 4 ? (float)((tzw[j] >> (4u * (grp & 7u))) & 0xFu) : 128.f;   // bytes: the flip's 128
-            const _Float16 srel = (_Float16)(sf * (winv[j] * live));
+            // one over the power of two of the column's largest scale
+            const float winv = __builtin_bit_cast(float, 0x7F000000u - (tpw[j] << 16));
+            const _Float16 srel = (_Float16)(sf * (winv * live));
             const _Float16 a = (_Float16)(-1024.f - z), b = (_Float16)(-64.f - z);
             nz[j] = f16x2_t{a, a};
             nz6[j] = f16x2_t{b, b};
@@ -720,56 +730,54 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         }
         // y = acc * 2^-p(m) * 2^E(n), rounded once to bf16.  The halves of the wave exchange pieces, so that a
         // lane stores eight neighbouring columns of its row.
+        // Row by row, so that the pieces of a line are stored one after the other.
         const unsigned char* const pw = Ps + seg_slot * kPow2Bytes;
-        const bool vec_ok = (ga.N % 8) == 0;
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
+        for (int i = 0; i < MB; ++i) {
+            const float rs = bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(pw + 512 + (32 * i + c) * 2));
+            const int m = sg.bm + 32 * i + c;
 #pragma unroll
-            for (int qp = 0; qp < 2; ++qp) {
-                float wm[2][4];
+            for (int j = 0; j < WN; ++j)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint2 w2 = *reinterpret_cast<const uint2*>(pw + ((cwave * WN + j) * 32 + 16 * qp + 8 * h + 4 * kb) * 2);
-                    wm[h][0] = __builtin_bit_cast(float, w2.x << 16);
-                    wm[h][1] = __builtin_bit_cast(float, w2.x & 0xFFFF0000u);
-                    wm[h][2] = __builtin_bit_cast(float, w2.y << 16);
-                    wm[h][3] = __builtin_bit_cast(float, w2.y & 0xFFFF0000u);
-                }
-#pragma unroll
-                for (int i = 0; i < MB; ++i) {
-                    const float rs = bf16_bits_to_f32(*reinterpret_cast<const uint16_t*>(pw + 512 + (32 * i + c) * 2));
+                for (int qp = 0; qp < 2; ++qp) {
                     const f32x16_t& v = acc[i][j];
                     uint32_t p[2][2];   // [which 8 columns][pair]
 #pragma unroll
-                    for (int h = 0; h < 2; ++h)
+                    for (int h = 0; h < 2; ++h) {
+                        const uint2 w2 = *reinterpret_cast<const uint2*>(pw + ((cwave * WN + j) * 32 + 16 * qp + 8 * h + 4 * kb) * 2);
+                        const float wm[4] = {__builtin_bit_cast(float, w2.x << 16), __builtin_bit_cast(float, w2.x & 0xFFFF0000u),
+                                             __builtin_bit_cast(float, w2.y << 16), __builtin_bit_cast(float, w2.y & 0xFFFF0000u)};
 #pragma unroll
                         for (int e = 0; e < 2; ++e) {
                             const int r = 4 * (2 * qp + h) + 2 * e;
-                            p[h][e] = f32x2_to_bf16x2_rne(v[r] * rs * wm[h][2 * e], v[r + 1] * rs * wm[h][2 * e + 1]);
+                            p[h][e] = f32x2_to_bf16x2_rne(v[r] * rs * wm[2 * e], v[r + 1] * rs * wm[2 * e + 1]);
                         }
+                    }
                     // lanes 32-63 of the first operand and lanes 0-31 of the second change places
                     const auto a = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
                     const auto b = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
                     const u32x4_t o = {a[0], b[0], a[1], b[1]};
-                    const int m = sg.bm + 32 * i + c, n = sg.bn + (cwave * WN + j) * 32 + 16 * qp + 8 * kb;
+                    const int n = sg.bn + (cwave * WN + j) * 32 + 16 * qp + 8 * kb;
                     if (m < ga.M && n < ga.N) {
                         uint16_t* dst = ga.y + (size_t)m * ga.N + n;
-                        if (vec_ok) {
-                            *reinterpret_cast<u32x4_t*>(dst) = o;
+                        if (n + 8 <= ga.N) {
+                            // (rows of y begin at any multiple of 2 bytes.  Stored value by value wherever N is
+                            // no multiple of 8, N = 8154 took 73 us at M = 442, K = 5888, against 61 now)
+                            *reinterpret_cast<u32x4_any_t*>(dst) = o;
                         } else {
                             const uint32_t w[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
-                            for (int e = 0; e < 8; ++e)
+                            for (int e = 0; e < 7; ++e)
                                 if (n + e < ga.N) dst[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
                         }
                     }
                 }
-            }
         }
     };
 
     Seg sg, ahead;
     if (!next_segment(sg)) return;   // (every block has one)
+    ahead = sg;
     bool more = next_segment(ahead);
     int left = sg.steps, seg_slot = 0;
     uint32_t acur = 0, bcur = 0;     // the step's slot
@@ -786,6 +794,8 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
             fetch(acur, jj + 1, (jj + 1) & 1);
             multiply(jj & 1);
         }
+#pragma unroll
+        for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(bf[1][j]));   // expanded here, not behind the barrier
         __builtin_amdgcn_sched_barrier(0);
         // The loading waves have seen step s + 1 land.  The wait covers this wave's LDS reads (lgkmcnt 0, not
         // its stores), so after the barrier the step's slot is dead for everyone once the last sub-step is
@@ -796,7 +806,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         bcur = bcur == (kStages - 1) * kBStage ? 0 : bcur + kBStage;
         const bool last = --left == 0;
         const int next_slot = seg_slot == S::kSegs - 1 ? 0 : seg_slot + 1;
-        if (last && more) take_segment(ahead, next_slot);
+        if (last) take_segment(ahead, next_slot);   // (past the last segment: the last again, which nothing uses)
         __builtin_amdgcn_sched_barrier(0);
         // The last sub-step of this step (operands already in registers) with the next step's set-up under
         // it: all LDS reads first (FIFO and A fragments), a few MFMAs while they are in flight, then
@@ -810,8 +820,8 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
             for (int j = 0; j < WN; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[1][j], af[1][i], acc[i][j], 0, 0, 0);
         constexpr int kLead = MB * WN < 4 ? 1 : 3;                     // MFMAs issued before any conversion
-        constexpr int kSetupValu = (kBits == 4 ? 13 + 16 : 14 + 12) * WN + 8;
-        __builtin_amdgcn_sched_group_barrier(0x100, WN * (kCodeLoads + (kBits == 4 ? 2 : 1)) + MB, 0);
+        constexpr int kSetupValu = (kBits == 4 ? 13 + 20 : 14 + 16) * WN + 8;
+        __builtin_amdgcn_sched_group_barrier(0x100, WN * (kCodeLoads + (kBits == 4 ? 3 : 2)) + MB, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
         if constexpr (MB * WN > kLead) {
 #pragma unroll
@@ -893,8 +903,8 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
     uint16_t h[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) h[e] = f32_to_bf16_rne(sum[e] * rs * bf16_bits_to_f32(ga.pow2[ga.wpow2 + min(n + e, ga.N - 1)]));
-    if ((ga.N % 4) == 0) {
-        *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+    if (n + 4 <= ga.N) {
+        *reinterpret_cast<u32x2_any_t*>(dst) = u32x2_any_t{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
     } else {
         for (int e = 0; e < 4 && n + e < ga.N; ++e) dst[e] = h[e];
     }

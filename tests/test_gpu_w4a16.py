@@ -558,3 +558,22 @@ def test_lora_changes_the_output_and_zero_adapter_does_not(B):
     plain = gpu_linear(B, qw, s, zw, synth.llm_activation_bf16(M, K, 778), g, N, K, M)
     assert np.array_equal(synth.bf16_bits_to_f32(base[0]), synth.bf16_bits_to_f32(plain))
     assert not np.array_equal(base[0], with_ad[0])
+
+
+@pytest.mark.parametrize("M,N,K", [(136, 1030, 512), (96, 517, 1024), (300, 1284, 512), (33, 131, 4096)])
+def test_gemm_ragged_columns(B, M, N, K):
+    """Rows of y that begin at no multiple of 16 bytes: whole tiles and tiles shared between blocks, the last
+    columns one by one."""
+    w = synth.llm_weight(N, K, 61 + N, outlier_frac=0.01)
+    xb = synth.llm_activation_bf16(M, K, 62 + N)
+    q, s, z = O.quantize_w4_asym_group(w, 128)
+    qw, zw = O.pack_w4a16(q, z)
+    import torch
+    y = torch.full((M * N + 8,), 0x7FC0, dtype=torch.int16, device="cuda")
+    B.qail_w4a16_linear(N, K, 128, dev(qw), dev(s.view(np.uint16)), dev(zw), dev(xb), y, M,
+                        ws_for(B, B.qail_w4a16_workspace(N, K, 128, M)))
+    torch.cuda.synchronize()
+    got = host(y, np.uint16)
+    assert np.all(got[M * N:] == 0x7FC0)
+    nx, nw = O.w4a16_row_norms(xb, qw, s, zw, 128)
+    assert w4a16_norm_err(got[:M * N].reshape(M, N), O.w4a16_linear(xb, qw, s, zw, 128), nx, nw) <= TOL
