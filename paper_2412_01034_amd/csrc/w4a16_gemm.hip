@@ -41,6 +41,7 @@
 
 #include <atomic>
 
+#include "gemm_tiles.h"
 #include "qail_internal.h"
 
 namespace qail {
@@ -236,9 +237,9 @@ constexpr int kPow2Bytes = 768;   // powers of two of a tile: 256 columns, then 
 
 template <int kBits>
 struct Step {
-    static constexpr int kBK = kBits == 4 ? 128 : 64;              // k per step
+    static constexpr int kBK = step_k(kBits);                     // k per step
     static constexpr int kSub = kBK / 16;                          // sub-steps: one MFMA per 32 x 32 block each
-    static constexpr int kStages = kBits == 4 ? 3 : 4;             // slots of the ring
+    static constexpr int kStages = ring_stages(kBits);            // slots of the ring
     static constexpr int kRowBytes = 2 * kBK;
     static constexpr int kChunks = kRowBytes / 16;
     static constexpr int kCodeLoads = kBK / 2 * kBits / 128;       // 16-byte pieces of a lane's codes of a step
@@ -494,7 +495,6 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         uint32_t xrow0 = 0;
         uint32_t qo[kWBlocks][kCodeLoads], so[kWBlocks], zo[kWBlocks];
         const int crow = lane >> 2, cpiece = (lane & 3) ^ code_swizzle(crow);   // row of the 16, which 16 bytes of its 64
-        const uint32_t ck = (uint32_t)(cpiece * 128 / kBits);                   // ... and their first k
         int lk = 0, lgrp = 0, lkin = 0;
         int group_slot = -1;     // bytes: the current group's scales
         bool fresh = false;      // the next step is the first of a group
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                         const int n = min(sg.bn + mm * 32 + c, ga.N - 1);
 #pragma unroll
                         for (int part = 0; part < kCodeLoads; ++part)
-                            qo[mm][part] = (uint32_t)min(sg.bn + mm * 32 + 16 * part + crow, ga.N - 1) * (uint32_t)kw * 4u + 16u * (uint32_t)cpiece;
+                            qo[mm][part] = code_offset((uint32_t)min(sg.bn + mm * 32 + 16 * part + crow, ga.N - 1), (uint32_t)kw, (uint32_t)cpiece);
                         so[mm] = (uint32_t)n * (uint32_t)G * 2u;
                         zo[mm] = (uint32_t)n * (uint32_t)zwords * 4u;
                     }
@@ -542,8 +542,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                           slot_x + qq * kXWaves * 1024);
             } else {
                 const bool v = lk < ga.K;
-                const uint32_t k0 = (uint32_t)(pstep * kBK);
-                const uint32_t kc = k0 + ck < (uint32_t)ga.K ? k0 : 0u;   // past the end: any valid address, the scale becomes 0
+                const uint32_t co = code_step_offset((uint32_t)(pstep * kBK), (uint32_t)cpiece, (uint32_t)ga.K, kBits);
                 const uint32_t grp = v ? (uint32_t)lgrp : 0u;
                 if (kBits == 8 && fresh) {
                     group_slot = group_slot == S::kSegs - 1 ? 0 : group_slot + 1;
@@ -551,7 +550,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
 #pragma unroll
                     for (int q = 0; q < 2 * WN; ++q) {
                         const uint32_t so64 = (uint32_t)min(sg.bn + 64 * q + lane, ga.N - 1) * (uint32_t)G * 2u;
-                        dma4(ga.sc, (so64 + grp * 2u) & ~3u, as_lds + (uint32_t)(Cs - As) + (uint32_t)group_slot * S::kScales + 256 * q);
+                        dma4(ga.sc, scale_word_offset(so64, grp), as_lds + (uint32_t)(Cs - As) + (uint32_t)group_slot * S::kScales + 256 * q);
                     }
                 }
 #pragma unroll
@@ -559,10 +558,10 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                     const uint32_t dst = slot_w + mm * kBLane;
 #pragma unroll
                     for (int part = 0; part < kCodeLoads; ++part)
-                        dma16(ga.qw, qo[mm][part] + kc * kBits / 8, dst + 1024 * part);
+                        dma16(ga.qw, qo[mm][part] + co, dst + 1024 * part);
                     if constexpr (kBits == 4) {
-                        dma4(ga.sc, (so[mm] + grp * 2u) & ~3u, dst + kCodeLoads * 1024);
-                        dma4(ga.zr, zo[mm] + (grp / 8u) * 4u, dst + kCodeLoads * 1024 + 256);
+                        dma4(ga.sc, scale_word_offset(so[mm], grp), dst + kCodeLoads * 1024);
+                        dma4(ga.zr, zero_word_offset(zo[mm], grp), dst + kCodeLoads * 1024 + 256);
                     }
                 }
             }
