@@ -54,11 +54,8 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_any_t __attribute__((ext_vector_type(2), aligned(2)));
 
-constexpr int kPadK = 128;              // rows of the fp16 copy of x are padded to this
 constexpr int kMaxGemmBlocks = 512;     // upper bound of the grid (the workspace has two slots per block)
 constexpr int kRowPad = 128;            // workspace rows are padded to this
-
-__host__ __device__ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 constexpr int kGemmBatch = 8;           // linears that can share one launch
 
@@ -264,12 +261,8 @@ struct GemmArgs {
     const uint16_t* pow2;   // bf16: [Mpad] of the rows of x, then [N] of the weight rows (from element wpow2 on)
     uint16_t* y;
     int M, N, K, Kpad, g, wpow2;
-    // work decomposition: tiles are numbered with m running fastest.  The first `whole` tiles
-    // are dealt whole, tile i to block i % P; the K steps of the others are dealt as units (one
-    // K step of one tile): block b of P owns the units [b * units / P, (b + 1) * units / P)
-    int Tm, tiles, steps, whole;
-    float* partial;  // [2 P][tile] fp32: sums of tiles whose K range is shared between blocks, see slot_at()
-    int block_begin, P;  // the linear is worked on by blocks [block_begin, block_begin + P) of the grid
+    TilePlan tp;
+    float* partial;  // [2 P][tile] fp32: sums of tiles whose K range is shared between blocks
 };
 
 // Up to kGemmBatch linears share a launch: each gets a share of the grid and is dealt to its
@@ -281,9 +274,6 @@ struct GemmBatch {
 
 // A slot holds a tile's sums as the MFMA lanes have them, 16 bytes of a lane at a time: piece
 // ((wave * MB + i) * WN + j) * 4 + q of lane (c, kb) is row 32 i + c, columns (WN wave + j) * 32 + 8 q + 4 kb + 0..3.
-// First unit of block b when `units` units are dealt to P blocks, and the block that owns unit u.
-__host__ __device__ inline long long first_unit(long long b, long long units, int P) { return b * units / P; }
-__host__ __device__ inline int owner_of(long long u, long long units, int P) { return (int)(((u + 1) * P - 1) / units); }
 
 // Block tile (32 * MB) x (128 * WN): 4 waves side by side along n, each (32 * MB) x (32 * WN).
 //
@@ -358,9 +348,9 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     int item = 0;
 #pragma unroll
     for (int i = 1; i < kGemmBatch; ++i)
-        if (i < args.count && (int)blockIdx.x >= args.it[i].block_begin) item = i;
+        if (i < args.count && (int)blockIdx.x >= args.it[i].tp.block_begin) item = i;
     const GemmArgs ga = args.it[item];
-    const int bid = (int)blockIdx.x - ga.block_begin, P = ga.P;   // this block among the linear's own
+    const int bid = (int)blockIdx.x - ga.tp.block_begin;   // this block among the linear's own
     const int G = ga.K / ga.g, zwords = (G + 7) / 8, kw = ga.K / (32 / kBits);
 
     uint32_t magic = kBits == 4 ? 0x64006400u : 0x64646464u;
@@ -368,91 +358,26 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     uint32_t flip = 0x80808080u;
     asm volatile("" : "+v"(flip));
 
-    const long long units = (long long)(ga.tiles - ga.whole) * ga.steps;
-    const int unit0 = (int)first_unit(bid, units, P);
-    const int unit1 = (int)first_unit(bid + 1, units, P);
-    // Whole tiles are numbered with m running fastest, so consecutive tiles share their weight columns.
-    // Where the x of all row tiles fits an L2 beside the weights passing through (2.5 MB), the blocks of
-    // an XCD take consecutive tiles: workgroup b of the launch runs on XCD b mod 8, so this block's rank
-    // among its linear's blocks is counted XCD by XCD.  A weight tile is then fetched by one or two L2s
-    // instead of one per row tile.  Measured on a decoder layer's four linears as one launch: 2 % faster
-    // with three row tiles (M = 272, 288), 3-5 % slower with two (M = 160 .. 256), which stay as they
-    // were.  (Taller linears: see the dealing of eight row tiles below.)
-    int vbid = bid;
-    const bool x_fits_l2 = ga.Tm >= 3 && (long long)ga.Tm * kBM * ga.Kpad * 2 <= 2560 * 1024;
-    // Taller linears with an even number of row tiles, where the x of two row tiles fits: the same
-    // ranks, and the whole tiles are walked pair of row tiles by pair of row tiles (inside a pair column
-    // by column), so that an XCD's consecutive tiles are two row tiles of a few columns.
-    // Only where a round of the linear's blocks stays inside a pair (a share of a launch: all XCDs then
-    // share the pair's x at the same time and each has weight columns of its own; a linear on the whole
-    // grid has several pairs at once and is 7-15 % slower this way, see the dealing of eight row tiles).
-    const int whole_cols = ga.whole / ga.Tm;
-    // Measured on a decoder layer's four linears as one launch: 0.4 / 1.1 / 1.4 % faster with 4 / 8 / 16 row
-    // tiles, 1.1 % slower with 6, which keeps the launch order.
-    const bool pair_order = !x_fits_l2 && ga.Tm >= 4 && (ga.Tm & 3) == 0 && 2ll * kBM * ga.Kpad * 2 <= 2560 * 1024 &&
-                            P <= 2 * whole_cols;
-    if (x_fits_l2 || pair_order) {
-        const int q = ga.block_begin & 7, mine = (q + bid) & 7;
-        int before = 0;
-        for (int x = 0; x < 8; ++x) {
-            const int first = (x - q) & 7;   // the first of the linear's blocks on XCD x
-            const int count = first < P ? (P - first + 7) >> 3 : 0;
-            if (x < mine) before += count;
-        }
-        vbid = before + ((bid - ((mine - q) & 7)) >> 3);
-    }
+    TileDealer dealer(ga.tp, bid, kBM, ga.Kpad);
     // the block's next segment: K steps [ka, ka + steps) of the tile at (bm, bn); false: there is none
     struct Seg {
         int bm, bn, ka, steps;
         int grp, kin;        // group of k = ka kBK, and the k of it that lie before
         bool first_shared;
     };
-    int wtile = vbid, unit = unit0;
     auto next_segment = [&](Seg& sg) -> bool {
-    int tile;
-    sg.first_shared = false;
-    if (wtile < ga.whole) {
-        tile = wtile;
-        sg.ka = 0;
-        sg.steps = ga.steps;
-        wtile += P;
-    } else if (unit < unit1) {
-        const int tt = unit / ga.steps;
-        tile = ga.whole + tt;
-        sg.ka = unit - tt * ga.steps;
-        sg.steps = min(ga.steps - sg.ka, unit1 - unit);
-        sg.first_shared = unit == unit0;
-        unit += sg.steps;
-    } else {
-        return false;
-    }
-    int tm = tile % ga.Tm, tn = tile / ga.Tm;
-    if (pair_order && tile < ga.whole) {
-        // (a last, partial column among the whole tiles keeps its order)
-        if (tile < whole_cols * ga.Tm) {
-            const int pair = tile / (2 * whole_cols), rem = tile - pair * 2 * whole_cols;
-            tm = 2 * pair + (rem & 1);
-            tn = rem >> 1;
-        }
-    } else if (ga.Tm == 8 && !x_fits_l2 && (P & 15) == 0 && (ga.block_begin & 7) == 0 && tile < ga.whole) {
-        // Whole tiles of a linear that is eight row tiles high and has the grid to itself: in launch order
-        // the eight row tiles that share a weight tile would sit on eight XCDs and every L2 would fetch
-        // every weight column.  A round's P tiles (P / 8 columns) are dealt instead so that an XCD works on
-        // two row tiles (their x fits its L2) and on every other column: a weight tile is then fetched by
-        // four L2s, not eight.
-        const int round = tile / P, idx = tile - round * P;
-        const int xcd = idx & 7, j = idx >> 3;
-        tm = 2 * (xcd & 3) + (j & 1);
-        tn = round * (P >> 3) + 2 * (j >> 1) + (xcd >> 2);
-    }
-    sg.grp = sg.ka * kBK / ga.g;
-    sg.kin = sg.ka * kBK - sg.grp * ga.g;
-    sg.bm = tm * kBM;
-    sg.bn = tn * kBN;
-    return true;
+        TileDealer::Segment d;
+        if (!dealer.next(d)) return false;
+        sg.ka = d.ka;
+        sg.steps = d.steps;
+        sg.first_shared = d.first_shared;
+        sg.grp = sg.ka * kBK / ga.g;
+        sg.kin = sg.ka * kBK - sg.grp * ga.g;
+        sg.bm = d.tm * kBM;
+        sg.bn = d.tn * kBN;
+        return true;
     };
-    int total = unit1 - unit0;   // steps of all segments
-    for (int w = vbid; w < ga.whole; w += P) total += ga.steps;
+    const int total = dealer.total_steps();
 
     // All tensors here are below 4 GB (checked by the host), so addresses are a uniform base plus a
     // 32-bit offset.
@@ -535,7 +460,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
             const uint32_t slot_x = as_lds + (uint32_t)slot * kBufBytes + (uint32_t)share * 1024u;
             const uint32_t slot_w = as_lds + kStages * kBufBytes + (uint32_t)slot * kBStage;
             if (xwave) {
-                const uint32_t k0b = (uint32_t)(min(pstep, ga.steps - 1) * kBK) * 2u;
+                const uint32_t k0b = (uint32_t)(min(pstep, ga.tp.steps - 1) * kBK) * 2u;
 #pragma unroll
                 for (int qq = 0; qq < kXLoads; ++qq)
                     dma16(ga.xh, xrow0 + (uint32_t)(qq * kXWaves * kRows) * pitchb + xsw[qq % kPeriod] + k0b,
@@ -714,7 +639,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     // The end of a segment: lane (c, kb) has row 32 i + c and columns 8 q + 4 kb + 0..3 of every 32-column
     // block in acc[i][j][4 q ..].
     auto finish = [&](const Seg& sg, int seg_slot) {
-        if (sg.steps != ga.steps) {
+        if (sg.steps != ga.tp.steps) {
             // part of a tile's K: the raw sums go to this block's slot
             float* const slot = ga.partial + (size_t)(2 * bid + (sg.first_shared ? 0 : 1)) * (kBM * kBN);
             f32x4_t* const dst = reinterpret_cast<f32x4_t*>(slot) + cwave * (MB * WN * 4) * 64 + lane;
@@ -850,11 +775,12 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
     static_assert((kBM * kBN / 4) % 256 == 0, "tiles split into whole pieces");
     const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
     const GemmArgs ga = args.it[blockIdx.z];
-    const int P = ga.P;
-    if ((int)blockIdx.x >= ga.tiles - ga.whole) return;   // the grid is as wide as the largest tail
-    const int tile = ga.whole + blockIdx.x;
-    const long long units = (long long)(ga.tiles - ga.whole) * ga.steps;
-    const long long u_first = (long long)blockIdx.x * ga.steps, u_last = u_first + ga.steps - 1;
+    const TilePlan tp = ga.tp;
+    const int P = tp.P;
+    if ((int)blockIdx.x >= tp.tiles - tp.whole) return;   // the grid is as wide as the largest tail
+    const int tile = tp.whole + blockIdx.x;
+    const long long units = (long long)(tp.tiles - tp.whole) * tp.steps;
+    const long long u_first = (long long)blockIdx.x * tp.steps, u_last = u_first + tp.steps - 1;
     const int b_lo = owner_of(u_first, units, P), b_hi = owner_of(u_last, units, P);
     if (b_lo == b_hi) return;  // one block had the whole tile and has finished it
 
@@ -869,7 +795,7 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
         if (b <= b_hi) {
             const long long fu = first_unit(b, units, P);
             // a block's first shared segment is in its slot 0, a later one in slot 1
-            if (fu != first_unit(b + 1, units, P)) sl = 2 * b + ((int)blockIdx.x == (int)(fu / ga.steps) ? 0 : 1);
+            if (fu != first_unit(b + 1, units, P)) sl = 2 * b + ((int)blockIdx.x == (int)(fu / tp.steps) ? 0 : 1);
         }
         const unsigned long long have = __ballot(sl >= 0);
         if (lane == 0) wave_count[wave] = __popcll(have);
@@ -884,7 +810,7 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
     const int idx = blockIdx.y * 256 + t;
     const int piece = idx / 64, ilane = idx % 64;
     const int q = piece % 4, j = piece / 4 % WN, i0 = piece / (4 * WN) % MB, w0 = piece / (4 * WN * MB);
-    const int m = (tile % ga.Tm) * kBM + 32 * i0 + ilane % 32, n = (tile / ga.Tm) * kBN + (w0 * WN + j) * 32 + 8 * q + 4 * (ilane / 32);
+    const int m = (tile % tp.Tm) * kBM + 32 * i0 + ilane % 32, n = (tile / tp.Tm) * kBN + (w0 * WN + j) * 32 + 8 * q + 4 * (ilane / 32);
     if (m >= ga.M || n >= ga.N) return;
     const float* src = ga.partial + idx * 4;
     f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
@@ -911,23 +837,7 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
 
 int gemm_max_blocks() { return device_cu_count() < kMaxGemmBlocks ? device_cu_count() : kMaxGemmBlocks; }
 
-// Fills in the work decomposition of one linear on `cus` blocks; returns the blocks it uses.
-template <int MB, int WN, int kBits>
-int plan_tiles(GemmArgs& ga, bool split_tail, int cus) {
-    constexpr int kBM = 32 * MB, kBN = 128 * WN;
-    ga.Tm = (ga.M + kBM - 1) / kBM;
-    ga.tiles = ga.Tm * ((ga.N + kBN - 1) / kBN);
-    ga.steps = (ga.K + Step<kBits>::kBK - 1) / Step<kBits>::kBK;
-    ga.whole = split_tail ? ga.tiles / cus * cus : ga.tiles;
-    const int tail = ga.tiles - ga.whole;
-    const long long units = (long long)tail * ga.steps;
-    int P = ga.whole >= cus ? cus : ga.whole;
-    if (tail > 0 && P < cus) P = units < cus ? (int)units : cus;  // here whole == 0
-    ga.P = P;
-    return P;
-}
-
-// One launch for `n` linears that use the same tile, each on its own blocks (ga[i].block_begin, P set).
+// One launch for `n` linears that use the same tile, each on its own blocks (its plan).
 template <int MB, int WN, int kBits>
 hipError_t launch_tile(const GemmArgs* gas, int n, hipStream_t st) {
     constexpr int kBM = 32 * MB, kBN = 128 * WN;
@@ -947,12 +857,13 @@ hipError_t launch_tile(const GemmArgs* gas, int n, hipStream_t st) {
     for (int i = 0; i < kGemmBatch; ++i) {
         gb.it[i] = gas[i < n ? i : n - 1];
         if (i < n) {
-            grid += gas[i].P;
+            const TilePlan& tp = gas[i].tp;
+            grid += tp.P;
             // the second kernel is only needed when some block boundary falls inside a tile
-            const int tail = gas[i].tiles - gas[i].whole;
-            const long long units = (long long)tail * gas[i].steps;
+            const int tail = tp.tiles - tp.whole;
+            const long long units = (long long)tail * tp.steps;
             bool shared = false;
-            for (int b = 1; b < gas[i].P && tail > 0 && !shared; ++b) shared = first_unit(b, units, gas[i].P) % gas[i].steps != 0;
+            for (int b = 1; b < tp.P && tail > 0 && !shared; ++b) shared = first_unit(b, units, tp.P) % tp.steps != 0;
             if (shared && tail > max_tail) max_tail = tail;
         }
     }
@@ -965,48 +876,6 @@ hipError_t launch_tile(const GemmArgs* gas, int n, hipStream_t st) {
         e = hipGetLastError();
     }
     return e;
-}
-
-// Tile width and the treatment of the last, incomplete round of tiles, for a linear that has
-// `cus` blocks to itself.
-template <int MB>
-void choose_tile(const GemmArgs& ga, int cus, bool alone, bool narrow_only, int* wn_out, bool* split_out) {
-    // Measured on the four linears of a 7B decoder layer at M = 288 and 1024 (256 CUs), one launch each:
-    //   * a round or more of wide tiles: wide tiles, and the incomplete last round is dealt in
-    //     K steps only when it is short (a fuller one is cheaper left as it is: blocks that
-    //     share tiles pay for slots and a second kernel, and a chip that is not full clocks higher);
-    //   * between half a round and a round of wide tiles: wide tiles, whole;
-    //   * less: narrow tiles (twice as many), dealt in K steps when K is long or the tiles are few.
-    // A linear that shares the launch with others has only its share of the blocks, which it must
-    // keep busy to the end because the others cannot use them: less than a round of wide tiles is
-    // dealt in K steps, and as narrow tiles when M is a single tile high (measured 3-6 % faster than
-    // wide ones at M = 17 .. 128, 2-9 % slower at M = 200 and 288).
-    const int t2 = ((ga.M + 32 * MB - 1) / (32 * MB)) * ((ga.N + 255) / 256);
-    int wn = 2;
-    bool split = false;
-    if (ga.N <= 128 || narrow_only) {
-        wn = 1;
-        split = ga.Kpad / kPadK >= 64;
-    } else if (t2 >= cus) {
-        split = (t2 % cus) * 5 <= cus * 2;
-    } else if (!alone) {
-        wn = ga.M <= 32 * MB ? 1 : 2;
-        split = true;
-    } else if (t2 * 2 <= cus) {
-        wn = 1;
-        // in K steps when K is long, or when whole narrow tiles would leave half of the CUs idle
-        // (measured on single linears at M = 48 .. 288: the out projection 27 -> 19 us at M = 64,
-        // 37 -> 25 us at M = 128; with more tiles than that the shared tiles cost more than they give)
-        split = ga.Kpad / kPadK >= 64 || (t2 * 4 <= cus && ga.Kpad / kPadK >= 16);
-    }
-    *wn_out = wn;
-    *split_out = split;
-}
-
-// tile height: the multiple of 32 rows (at most 128) that pads M least
-int tile_rows(int M) {
-    if (M <= 96) return round_up(M, 32);
-    return round_up(M, 96) < round_up(M, 128) ? 96 : 128;
 }
 
 }  // namespace
@@ -1077,7 +946,7 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool 
         at += gemm_head_bytes(d, M);
         pb.it[i] = PrepItem{items[i].x, items[i].scales, xh, rscale, wmul, d.N, d.K, Kpad, G};
         ga[i] = GemmArgs{items[i].qweight, items[i].scales, items[i].zeros, xh, rscale, items[i].y,
-                         M, d.N, d.K, Kpad, d.group_size, Mpad, 0, 0, 0, 0, nullptr, 0, 0};
+                         M, d.N, d.K, Kpad, d.group_size, Mpad, TilePlan{}, nullptr};
         prep_blocks = std::max(prep_blocks, Mpad + (d.N + 31) / 32);
     }
     for (int i = n; i < kGemmBatch; ++i) pb.it[i] = pb.it[n - 1];
@@ -1110,7 +979,7 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool 
     int all[kGemmBatch];
     for (int i = 0; i < n; ++i) all[i] = i;
     deal(all, n, std::max(cus, n));
-    for (int i = 0; i < n; ++i) choose_tile<MB>(ga[i], share[i], n == 1, !wide_tiles, &wn[i], &split[i]);
+    for (int i = 0; i < n; ++i) choose_tile(32 * MB, M, ga[i].N, ga[i].Kpad, share[i], n == 1, !wide_tiles, &wn[i], &split[i]);
     // linears with the same tile width go out together, each group on the whole chip
     for (int w = 2; w >= 1; --w) {
         int idx[kGemmBatch], m = 0;
@@ -1121,20 +990,17 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool 
             deal(idx, m, std::max(cus, m));
             for (int j = 0; j < m; ++j) {
                 int w2;
-                choose_tile<MB>(ga[idx[j]], share[idx[j]], n == 1, !wide_tiles, &w2, &split[idx[j]]);
+                choose_tile(32 * MB, M, ga[idx[j]].N, ga[idx[j]].Kpad, share[idx[j]], n == 1, !wide_tiles, &w2, &split[idx[j]]);
             }
         }
         GemmArgs grp[kGemmBatch];
         int begin = 0;
         for (int j = 0; j < m; ++j) {
             GemmArgs& g = ga[idx[j]];
-            const int sh = share[idx[j]];
-            const bool sp = split[idx[j]];
-            const int P = bytes ? (w == 2 ? plan_tiles<MB, 2, 8>(g, sp, sh) : plan_tiles<MB, 1, 8>(g, sp, sh))
-                                : (w == 2 ? plan_tiles<MB, 2, 4>(g, sp, sh) : plan_tiles<MB, 1, 4>(g, sp, sh));
-            g.block_begin = begin;
+            g.tp = plan_tiles(M, g.N, g.K, 32 * MB, 128 * w, step_k(bytes ? 8 : 4), split[idx[j]], share[idx[j]]);
+            g.tp.block_begin = begin;
             g.partial = slots + (size_t)2 * begin * (32 * MB) * (128 * w);
-            begin += P;
+            begin += g.tp.P;
             grp[j] = g;
         }
         e = bytes ? (w == 2 ? launch_tile<MB, 2, 8>(grp, m, st) : launch_tile<MB, 1, 8>(grp, m, st))

@@ -1,6 +1,7 @@
 // Walks through the index arithmetic of the matrix-core GEMM (csrc/gemm_tiles.h) on the host.
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
 #include "gemm_tiles.h"
 
@@ -42,6 +43,52 @@ void loads(int bits, uint32_t N, uint32_t K, uint32_t g) {
     }
 }
 
+// Every K step of every output tile is dealt to exactly one block, and nothing else is.
+void dealing(const TilePlan& tp, int tile_m, int Kpad, const char* what, int M, int N) {
+    const int cols = tp.tiles / tp.Tm;
+    static std::vector<unsigned char> seen;
+    seen.assign((size_t)tp.tiles * tp.steps, 0);
+    for (int b = 0; b < tp.P; ++b) {
+        TileDealer dealer(tp, b, tile_m, Kpad);
+        int total = dealer.total_steps(), shared = 0;
+        CHECK(total > 0, "%s M %d N %d: block %d of %d has no work", what, M, N, b, tp.P);
+        TileDealer::Segment sg;
+        while (dealer.next(sg)) {
+            total -= sg.steps;
+            CHECK(sg.tm >= 0 && sg.tm < tp.Tm && sg.tn >= 0 && sg.tn < cols, "%s M %d N %d: block %d works on tile (%d, %d) of %d x %d", what, M, N, b,
+                  sg.tm, sg.tn, tp.Tm, cols);
+            CHECK(sg.ka >= 0 && sg.steps >= 1 && sg.ka + sg.steps <= tp.steps, "%s M %d N %d: steps %d + %d of %d", what, M, N, sg.ka, sg.steps, tp.steps);
+            // a block has two slots for sums of parts of a tile: its first shared segment's and one more
+            if (sg.steps != tp.steps && !sg.first_shared) ++shared;
+            for (int s = sg.ka; s < sg.ka + sg.steps; ++s) {
+                unsigned char& c = seen[((size_t)sg.tn * tp.Tm + sg.tm) * tp.steps + s];
+                CHECK(c == 0, "%s M %d N %d: tile (%d, %d) step %d dealt twice", what, M, N, sg.tm, sg.tn, s);
+                c = 1;
+            }
+        }
+        CHECK(total == 0 && shared <= 1, "%s M %d N %d: block %d, %d steps left over, %d shared segments", what, M, N, b, total, shared);
+    }
+    for (size_t i = 0; i < seen.size(); ++i)
+        CHECK(seen[i], "%s M %d N %d: tile (%d, %d) step %d dealt to nobody", what, M, N, (int)(i / tp.steps % tp.Tm), (int)(i / tp.steps / tp.Tm),
+              (int)(i % tp.steps));
+}
+
+// Plans as the launcher makes them, for a linear alone and for shares of the grid that begin anywhere.
+void planned(int M, int N, int K, int cus) {
+    const int rows = tile_rows(M), Kpad = round_up(K, kPadK);
+    const int shares[][2] = {{cus, 0}, {cus / 2, 0}, {cus / 2, cus / 2}, {cus / 4 + 3, 5}, {cus / 16, 8}, {1, 3}};
+    for (int bits : {4, 8})
+        for (const auto& sh : shares)
+            for (bool narrow_only : {false, true}) {
+                int wn;
+                bool split;
+                choose_tile(rows, M, N, Kpad, sh[0], sh[0] == cus, narrow_only, &wn, &split);
+                TilePlan tp = plan_tiles(M, N, K, rows, 128 * wn, step_k(bits), split, sh[0]);
+                tp.block_begin = sh[1];
+                dealing(tp, rows, Kpad, bits == 4 ? "nibbles" : "bytes", M, N);
+            }
+}
+
 }  // namespace
 
 int main() {
@@ -50,6 +97,13 @@ int main() {
             for (uint32_t g = 64; g <= K; g += 64)
                 for (uint32_t N : {1u, 2u, 7u, 128u, 129u, 260u, 4096u})
                     if (K % g == 0) loads(bits, N, K, g);
+    // every width of the linears a model may have, at every tile height and number of row tiles up to sixteen
+    for (int cus : {256, 304, 64})
+        for (int M : {17, 33, 96, 128, 129, 288, 320, 384, 512, 640, 768, 897, 1000, 1024, 1536, 2048})
+            for (int N = cus == 256 && M > 896 && M <= 1024 ? 128 : 384; N <= 24000; N += M > 896 && M <= 1024 ? 256 : 1280) planned(M, N, 1536, cus);
+    for (int N : {2, 100, 128, 130, 11008, 11520, 12544, 32000})
+        for (int K : {64, 192, 1024, 4096, 11008})
+            for (int M : {17, 200, 1024}) planned(M, N, K, 256);
     std::printf("gemm tiles: ok\n");
     return 0;
 }

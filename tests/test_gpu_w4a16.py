@@ -577,3 +577,31 @@ def test_gemm_ragged_columns(B, M, N, K):
     assert np.all(got[M * N:] == 0x7FC0)
     nx, nw = O.w4a16_row_norms(xb, qw, s, zw, 128)
     assert w4a16_norm_err(got[:M * N].reshape(M, N), O.w4a16_linear(xb, qw, s, zw, 128), nx, nw) <= TOL
+
+
+@pytest.mark.parametrize("M,linears", [(1024, (11520,)), (897, (12032,)), (1024, (11008, 11008))])
+def test_gemm_eight_row_tiles_and_an_odd_last_round(B, M, linears):
+    """Eight row tiles over a number of columns whose last round is incomplete, whole, and an odd number of columns
+    wide: every output is written, and those of the last columns agree with the oracle."""
+    import torch
+    K, g, n_ref = 1536, 128, 600
+    ents, keep = [], []
+    for i, N in enumerate(linears):
+        w = synth.llm_weight(N, K, 71 + i, outlier_frac=0.01)
+        xb = synth.llm_activation_bf16(M, K, 73 + i)
+        qb, sb, zb = B.qail_packed_sizes(N, K, g, B.QAIL_W4_ASYM_GROUP)
+        qw, sc, zr = (torch.zeros(b // 2, dtype=torch.int16, device="cuda") for b in (qb, sb, zb))
+        B.qail_quantize_weights(dev(w), g, B.QAIL_W4_ASYM_GROUP, qw, sc, zr)
+        torch.cuda.synchronize()
+        ents.append(dict(N=N, K=K, group_size=g, qweight=qw, scales=sc, zeros=zr, x=dev(xb),
+                         y=torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda")))
+        keep.append((w[-n_ref:], xb))
+    items = B.make_w4a16_items(ents, M)
+    B.qail_w4a16_linear_batch(items, len(ents), M, ws_for(B, B.qail_w4a16_batch_workspace(items, len(ents), M)))
+    torch.cuda.synchronize()
+    for e, (w, xb) in zip(ents, keep):
+        y = host(e["y"], np.uint16).reshape(M, e["N"])
+        assert np.all(y != 0x7FC0), np.argwhere(y == 0x7FC0)[:3]
+        qw, s, zw = oracle_pack(w, g)
+        nx, nw = O.w4a16_row_norms(xb, qw, s, zw, g)
+        assert w4a16_norm_err(y[:, -n_ref:], O.w4a16_linear(xb, qw, s, zw, g), nx, nw) <= TOL

@@ -437,3 +437,24 @@ def test_w8a16_matrix_cores_wide_and_narrow_tiles(B, M):
             assert w4a16_norm_err(host(y, np.uint16).reshape(M, N), ref, nx, nw) <= TOL, (N, K, nws)
         with pytest.raises(B.QailError):
             B.qail_w8a16_linear(N, K, g, *args, y, M, torch.empty(narrow - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("M,N", [(1024, 11520), (897, 12032)])
+def test_w8a16_eight_row_tiles_and_an_odd_last_round(B, M, N):
+    """Eight row tiles over a number of columns whose last round is incomplete, whole, and an odd number of columns
+    wide: every output is written, and those of the last columns agree with the oracle."""
+    import torch
+    K, g, n_ref = 1536, 128, 600
+    w = synth.llm_weight(N, K, 81, outlier_frac=0.01)
+    xb = synth.llm_activation_bf16(M, K, 82)
+    qw = torch.zeros(N * K // 4, dtype=torch.int32, device="cuda")
+    sc = torch.zeros(N * (K // g), dtype=torch.int16, device="cuda")
+    B.qail_quantize_weights(dev(w), g, B.QAIL_W8_SYM_GROUP, qw, sc, None)
+    y = torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda")
+    B.qail_w8a16_linear(N, K, g, qw, sc, dev(xb), y, M, w8_ws(B, N, K, g, M))
+    torch.cuda.synchronize()
+    y = host(y, np.uint16).reshape(M, N)
+    assert np.all(y != 0x7FC0), np.argwhere(y == 0x7FC0)[:3]
+    q, s = O.quantize_w8_sym_group(w[-n_ref:], g)
+    nx, nw = _w8_norms(xb, q, s, g)
+    assert w4a16_norm_err(y[:, -n_ref:], O.w8a16_linear(xb, q, s, g), nx, nw) <= TOL
