@@ -157,13 +157,19 @@ inline TilePlan plan_tiles(int M, int N, int K, int rows, int cols, int step_k, 
     const int tail = tp.tiles - tp.whole;
     const long long units = (long long)tail * tp.steps;
     tp.P = tp.whole >= cus ? cus : tp.whole;
-    if (tail > 0 && tp.P < cus) tp.P = units < cus ? (int)units : cus;  // here whole == 0
+    if (tail > 0 && tp.P < cus) {   // here whole == 0
+        // Blocks that share a tile take at least 128 k of it, and 256 k of byte codes: a block's sums cost the second
+        // kernel as much however short its part is.  Bytes, one / two / four 64-k steps per block: 128 x 11008 at
+        // M = 40 24.3 / 18.8 / 16.8 us, 512 x 4096 at M = 96 19.7 / 15.6 / 14.4, 1024 x 4096 at M = 128 17.7 / 17.7 / 15.5.
+        const long long parts = step_k == 64 && units / 4 > tail ? units / 4 : step_k == 64 ? tail : units;
+        tp.P = parts < cus ? (int)parts : cus;
+    }
     return tp;
 }
 
 // Tile width and the treatment of the last, incomplete round of tiles, for a linear that has
 // `cus` blocks to itself.
-inline void choose_tile(int rows, int M, int N, int Kpad, int cus, bool alone, bool narrow_only, int* wn_out, bool* split_out) {
+inline void choose_tile(int bits, int rows, int M, int N, int Kpad, int cus, bool alone, bool narrow_only, int* wn_out, bool* split_out) {
     // Measured on the four linears of a 7B decoder layer at M = 288 and 1024 (256 CUs), one launch each:
     //   * a round or more of wide tiles: wide tiles, and the incomplete last round is dealt in
     //     K steps only when it is short (a fuller one is cheaper left as it is: blocks that
@@ -174,12 +180,21 @@ inline void choose_tile(int rows, int M, int N, int Kpad, int cus, bool alone, b
     // keep busy to the end because the others cannot use them: less than a round of wide tiles is
     // dealt in K steps, and as narrow tiles when M is a single tile high (measured 3-6 % faster than
     // wide ones at M = 17 .. 128, 2-9 % slower at M = 200 and 288).
-    const int t2 = ((M + rows - 1) / rows) * ((N + 255) / 256);
+    //
+    // Bytes, narrow tiles: their steps are half as deep and two blocks that share a tile part with at least
+    // four of them each (see plan_tiles), so sharing pays from shorter K on.  Measured on single linears of
+    // N = 64 .. 22016 and K = 1024 .. 11008 at M = 34 .. 1024, whole / shared: 64 x 4096 at M = 40 30.8 / 12.6 us,
+    // 128 x 4096 at M = 288 37.9 / 15.1, 4096 x 4096 at M = 288 38.5 / 29.7 and, above the line, M = 640 43.6 / 45.9;
+    // 2048 x 1024 at M = 96 15.2 / 13.4 and, above the line, 4096 x 1024 at M = 96 15.0 / 16.3, M = 640 17.8 / 21.7;
+    // 4096 x 11008 at M = 640 109.5 / 91.1.
+    const int Tm = (M + rows - 1) / rows, t1 = Tm * ((N + 127) / 128), t2 = Tm * ((N + 255) / 256), k128 = Kpad / kPadK;
+    const bool few_bytes = k128 >= 64 || (t1 * 2 <= cus && k128 >= 16) || (t1 * 16 <= cus && k128 >= 8);
     int wn = 2;
     bool split = false;
     if (N <= 128 || narrow_only) {
         wn = 1;
-        split = Kpad / kPadK >= 64;
+        if (bits == 4) split = k128 >= 64;
+        else split = t1 >= cus ? (t1 % cus) * 5 <= cus * 2 : !alone || few_bytes;
     } else if (t2 >= cus) {
         split = (t2 % cus) * 5 <= cus * 2;
     } else if (!alone) {
@@ -190,7 +205,7 @@ inline void choose_tile(int rows, int M, int N, int Kpad, int cus, bool alone, b
         // in K steps when K is long, or when whole narrow tiles would leave half of the CUs idle
         // (measured on single linears at M = 48 .. 288: the out projection 27 -> 19 us at M = 64,
         // 37 -> 25 us at M = 128; with more tiles than that the shared tiles cost more than they give)
-        split = Kpad / kPadK >= 64 || (t2 * 4 <= cus && Kpad / kPadK >= 16);
+        split = bits == 8 ? few_bytes : k128 >= 64 || (t2 * 4 <= cus && k128 >= 16);
     }
     *wn_out = wn;
     *split_out = split;

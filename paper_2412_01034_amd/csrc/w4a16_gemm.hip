@@ -979,7 +979,7 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool 
     int all[kGemmBatch];
     for (int i = 0; i < n; ++i) all[i] = i;
     deal(all, n, std::max(cus, n));
-    for (int i = 0; i < n; ++i) choose_tile(32 * MB, M, ga[i].N, ga[i].Kpad, share[i], n == 1, !wide_tiles, &wn[i], &split[i]);
+    for (int i = 0; i < n; ++i) choose_tile(bytes ? 8 : 4, 32 * MB, M, ga[i].N, ga[i].Kpad, share[i], n == 1, !wide_tiles, &wn[i], &split[i]);
     // linears with the same tile width go out together, each group on the whole chip
     for (int w = 2; w >= 1; --w) {
         int idx[kGemmBatch], m = 0;
@@ -990,7 +990,7 @@ static hipError_t launch_chunk(const qail_w4a16_item* items, int n, int M, bool 
             deal(idx, m, std::max(cus, m));
             for (int j = 0; j < m; ++j) {
                 int w2;
-                choose_tile(32 * MB, M, ga[idx[j]].N, ga[idx[j]].Kpad, share[idx[j]], n == 1, !wide_tiles, &w2, &split[idx[j]]);
+                choose_tile(bytes ? 8 : 4, 32 * MB, M, ga[idx[j]].N, ga[idx[j]].Kpad, share[idx[j]], n == 1, !wide_tiles, &w2, &split[idx[j]]);
             }
         }
         GemmArgs grp[kGemmBatch];

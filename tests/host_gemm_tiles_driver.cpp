@@ -82,11 +82,21 @@ void planned(int M, int N, int K, int cus) {
             for (bool narrow_only : {false, true}) {
                 int wn;
                 bool split;
-                choose_tile(rows, M, N, Kpad, sh[0], sh[0] == cus, narrow_only, &wn, &split);
+                choose_tile(bits, rows, M, N, Kpad, sh[0], sh[0] == cus, narrow_only, &wn, &split);
                 TilePlan tp = plan_tiles(M, N, K, rows, 128 * wn, step_k(bits), split, sh[0]);
                 tp.block_begin = sh[1];
                 dealing(tp, rows, Kpad, bits == 4 ? "nibbles" : "bytes", M, N);
             }
+}
+
+// Byte codes: a linear of a few tiles and a K worth sharing keeps a good part of the chip busy, also where only
+// narrow tiles have room.
+void byte_parts(int M, int N, int K, bool narrow_only, int least) {
+    int wn;
+    bool split;
+    choose_tile(8, tile_rows(M), M, N, round_up(K, kPadK), 256, true, narrow_only, &wn, &split);
+    const TilePlan tp = plan_tiles(M, N, K, tile_rows(M), 128 * wn, step_k(8), split, 256);
+    CHECK(tp.P >= least, "M %d N %d K %d: %d blocks", M, N, K, tp.P);
 }
 
 }  // namespace
@@ -104,6 +114,13 @@ int main() {
     for (int N : {2, 100, 128, 130, 11008, 11520, 12544, 32000})
         for (int K : {64, 192, 1024, 4096, 11008})
             for (int M : {17, 200, 1024}) planned(M, N, K, 256);
+    for (bool narrow_only : {false, true}) {
+        byte_parts(288, 128, 4096, narrow_only, 48);    // three tiles of 64 steps
+        byte_parts(40, 64, 4096, narrow_only, 16);
+        byte_parts(40, 4096, 4096, narrow_only, 256);
+        byte_parts(96, 2048, 1024, narrow_only, 64);
+        byte_parts(288, 4096, 11008, narrow_only, 192);
+    }
     std::printf("gemm tiles: ok\n");
     return 0;
 }
