@@ -308,8 +308,9 @@ struct GemmBatch {
 // epilogue around 57 us of K loop at K = 4096, M = 1024; 18 of 128 us at M = 288.
 // One decoder layer: 60.0 -> 57.8 us at M = 48, 153.9 -> 149.8 at M = 288; 410 at M = 1024 either way, where
 // the chip is limited by power (1.80 GHz sustained of 2.4) and idle time was buying clock.
-// That is also where it costs something: one 128-row tile per block (4096 x 4096 at M = 1024 launched alone)
-// 45.0 -> 47.7 us, the layer at M = 2048 771 -> 785.  Staging a block's last tile in LDS again did not help.
+// With one 128-row tile per block there is nothing to overlap, and it still costs a little where such tiles are
+// wide: 4096 x 11008 at M = 2048 180.8 -> 183.3 us, the layer at M = 2048 773 -> 777.  Staging a block's last tile in
+// LDS again did not help.
 // What the end of a segment needs, the powers of two of its rows and columns, is loaded with its first
 // step into one of kSegs slots: the step that is loaded first for segment q is loaded behind the barrier
 // of step kStages before it, and segments are at least one step long, so everybody has left segment
@@ -626,8 +627,13 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
 #pragma unroll
             for (int j = 0; j < WN; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
-        // issue order: each MFMA is followed by one LDS read and a share of the vector
-        // operations that prepare the next sub-step
+        // issue order: the address of the next sub-step's fragments, then each MFMA followed by one LDS read
+        // and a share of the vector operations that prepare the next sub-step.  (The address has a place of
+        // its own because the reads wait for it: inside the first share it comes after the first read's place,
+        // the pattern cannot be kept, and the reads gather behind the last MFMA, where the next sub-step waits
+        // for them.  128-column tiles: 4096 x 4096 at M = 640 / 1024 40.2 / 47.2 -> 34.2 / 43.0 us, 4096 x 11008
+        // at M = 1024 117 -> 104.7, 2048 x 1024 at M = 96 .. 1024 8-10 % less.)
+        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
 #pragma unroll
         for (int u = 0; u < MB * WN; ++u) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
@@ -754,6 +760,11 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             }
         }
+        // 256-column tiles: the next step's first fragments are expanded here, under the MFMAs; left alone the
+        // compiler moves that behind the branch, to the start of the next step (layer at M = 1024 / 2048 396.7 / 780.1
+        // -> 395.3 / 776.9 us, bytes at M = 1024 454 -> 449; 128-column tiles are 0.5-1 % slower with it).  On the
+        // 128 x 256 nibble tile it costs 8 bytes of scratch per lane, stored and read back outside the K loop.
+        if constexpr (WN == 2) asm volatile("" : "+v"(bf[0][0]), "+v"(bf[0][1]));
         __builtin_amdgcn_sched_barrier(0);
         if (!last) continue;
         finish(sg, seg_slot);
