@@ -11,16 +11,22 @@ namespace {
 
 constexpr int kRedBlocks = 1024;  // partial sums of the step gradient (workspace floats)
 
-// Results, and inputs that one training step reads once (weights, logits), pass the caches by: what they would
-// take there is what the next operator has to fetch again, the activations above all, which forward and
-// backward of the step quantiser both read.  4096 x 4096 weights 26.2 -> 21.5 us (results only); weights,
-// activations (6.4 M) and logits (256 x 32000) one after the other 79.1 -> 71.0 (results only) -> 65.6 us.  Sizes that
-// fit the caches gain nothing and lose nothing.  Activations are read the ordinary way: streamed, the backward
-// alone takes 16.5 instead of 15.1 us.
-__device__ __forceinline__ void store_once(float4* p, const float4 v) {
-    __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(p));
-}
+// Weights and logits are read once per training step; from kStreamFrom bytes (read and written by the call) on
+// they are read past the caches, where they would push out what other operators read again.  us, plain /
+// streamed, with a cast of the result to bf16 behind the call and inputs that no cache holds: fake quantiser, 134 MB
+// 42.1 / 40.2, 34 MB 14.4 / 13.9, 8 MB (below the line) 6.3 / 6.4; QBC, 98 MB 32.2 / 27.0, 25 MB 15.4 / 14.8, 12 MB 11.8 / 11.3,
+// 6 MB (below) 10.1 / 11.5; with inputs just written the two are within 4 % of each other either way.
+// Activations are read the ordinary way: streamed, the backward alone takes 16.5 instead of 15.1 us.
+// Results are stored the ordinary way, at every size: the next operator reads them.  Stored past the caches the four
+// operators alone take 65.4 instead of 73.9 us (4096 x 4096 weights, 6.4 M activations, 256 x 32000 logits: the
+// backward then finds the activations in a cache, which it does not behind a whole network), but with
+// a reader behind each 164 instead of 160; the forward with a product behind it 38.5 / 35.1, the backward with an
+// elementwise one 28.9 / 27.5, the fake quantiser of 512 x 1024 weights with an fp32 product 13.1 / 11.7.
+constexpr size_t kStreamFrom = (size_t)12 << 20;
+
+template <bool kStream>
 __device__ __forceinline__ float4 load_once(const float4* p) {
+    if constexpr (!kStream) return *p;
     const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p));
     return make_float4(v[0], v[1], v[2], v[3]);
 }
@@ -80,7 +86,7 @@ __global__ __launch_bounds__(256) void fake_quant_w4_kernel(const float* __restr
 
 // The same for groups of at most 128 * kPer values: half a wave per group, the group held in
 // registers (read once), a block walks over groups 8 at a time.
-template <int kPer>
+template <int kPer, bool kStream>
 __global__ __launch_bounds__(256) void fake_quant_w4_half_kernel(const float* __restrict__ w, float* __restrict__ out,
                                                                  long long ngroups, int g) {
     const int half = threadIdx.x / 32, l = threadIdx.x % 32;
@@ -91,7 +97,7 @@ __global__ __launch_bounds__(256) void fake_quant_w4_half_kernel(const float* __
         float lo = 0.f, hi = 0.f;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
-            v[u] = l + 32 * u < n4 ? load_once(src + l + 32 * u) : make_float4(0.f, 0.f, 0.f, 0.f);  // 0 leaves lo <= 0 <= hi alone
+            v[u] = l + 32 * u < n4 ? load_once<kStream>(src + l + 32 * u) : make_float4(0.f, 0.f, 0.f, 0.f);  // 0 leaves lo <= 0 <= hi alone
             lo = fminf(fminf(lo, fminf(v[u].x, v[u].y)), fminf(v[u].z, v[u].w));
             hi = fmaxf(fmaxf(hi, fmaxf(v[u].x, v[u].y)), fmaxf(v[u].z, v[u].w));
         }
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(256) void fake_quant_w4_half_kernel(const float* __
             r.y = (fminf(fmaxf(rintf(v[u].y / s) + z, 0.f), 15.f) - z) * s;
             r.z = (fminf(fmaxf(rintf(v[u].z / s) + z, 0.f), 15.f) - z) * s;
             r.w = (fminf(fmaxf(rintf(v[u].w / s) + z, 0.f), 15.f) - z) * s;
-            if (l + 32 * u < n4) store_once(dst + l + 32 * u, r);
+            if (l + 32 * u < n4) dst[l + 32 * u] = r;
         }
     }
 }
@@ -134,7 +140,7 @@ __global__ __launch_bounds__(256) void lsq_fwd_kernel(const float* __restrict__ 
         r.y = fminf(fmaxf(rintf(a.y / s), qn), qp) * s;
         r.z = fminf(fmaxf(rintf(a.z / s), qn), qp) * s;
         r.w = fminf(fmaxf(rintf(a.w / s), qn), qp) * s;
-        store_once(o4 + i, r);
+        o4[i] = r;
     }
     for (size_t i = n4 * 4 + first; i < n; i += stride) out[i] = fminf(fmaxf(rintf(v[i] / s), qn), qp) * s;
 }
@@ -163,7 +169,7 @@ __global__ __launch_bounds__(256) void lsq_bwd_kernel(const float* __restrict__ 
         one(a.y, d.y, g.y);
         one(a.z, d.z, g.z);
         one(a.w, d.w, g.w);
-        store_once(g4 + i, g);
+        g4[i] = g;
     }
     for (size_t i = n4 * 4 + first; i < n; i += stride) one(v[i], dout[i], dv[i]);
     const float tot = block_sum_256(acc, red);
@@ -200,6 +206,7 @@ __global__ __launch_bounds__(256) void qbc_rows_kernel(const float* __restrict__
 // The same with 1024 threads per row and the row's differences held in registers (D a multiple
 // of 4, at most 32768): the logits are read once.
 constexpr int kQbcPer = 8;   // 16-byte pieces per thread
+template <bool kStream>
 __global__ __launch_bounds__(1024) void qbc_rows_reg_kernel(const float* __restrict__ lq, const float* __restrict__ lf, int D,
                                                             float inv_b, float* __restrict__ dist, float* __restrict__ grad) {
     __shared__ float red[16];
@@ -214,7 +221,7 @@ __global__ __launch_bounds__(1024) void qbc_rows_reg_kernel(const float* __restr
         const int j = threadIdx.x + 1024 * u;
         d[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (j < n4) {
-            const float4 a = load_once(q4 + j), b = load_once(f4 + j);
+            const float4 a = load_once<kStream>(q4 + j), b = load_once<kStream>(f4 + j);
             d[u] = make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
         }
         acc = fmaf(d[u].x, d[u].x, acc);
@@ -237,7 +244,7 @@ __global__ __launch_bounds__(1024) void qbc_rows_reg_kernel(const float* __restr
 #pragma unroll
         for (int u = 0; u < kQbcPer; ++u) {
             const int j = threadIdx.x + 1024 * u;
-            if (j < n4) store_once(g4 + j, make_float4(d[u].x * k, d[u].y * k, d[u].z * k, d[u].w * k));
+            if (j < n4) g4[j] = make_float4(d[u].x * k, d[u].y * k, d[u].z * k, d[u].w * k);
         }
     }
 }
@@ -249,10 +256,10 @@ hipError_t launch_fake_quant_w4(const qail_wdesc& d, const float* w, float* out,
     if (d.group_size <= 256) {
         long long blocks = (ngroups + 7) / 8;
         if (blocks > 4096) blocks = 4096;
-        if (d.group_size <= 128)
-            hipLaunchKernelGGL(fake_quant_w4_half_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, w, out, ngroups, d.group_size);
-        else
-            hipLaunchKernelGGL(fake_quant_w4_half_kernel<2>, dim3((unsigned)blocks), dim3(256), 0, st, w, out, ngroups, d.group_size);
+        const bool stream = (size_t)d.N * d.K * 8 >= kStreamFrom;
+        auto* const kernel = d.group_size <= 128 ? (stream ? fake_quant_w4_half_kernel<1, true> : fake_quant_w4_half_kernel<1, false>)
+                                                 : (stream ? fake_quant_w4_half_kernel<2, true> : fake_quant_w4_half_kernel<2, false>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, out, ngroups, d.group_size);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(fake_quant_w4_kernel, dim3((unsigned)((ngroups + 3) / 4)), dim3(256), 0, st, w, out, ngroups,
@@ -280,9 +287,11 @@ hipError_t launch_lsq_bwd(const float* v, const float* dout, size_t n, const flo
 
 hipError_t launch_qbc(const float* lq, const float* lf, int B, int D, float* loss, float* grad, float* ws, hipStream_t st) {
     const bool aligned = ((reinterpret_cast<uintptr_t>(lq) | reinterpret_cast<uintptr_t>(lf) | reinterpret_cast<uintptr_t>(grad)) & 15u) == 0;
-    if (D % 4 == 0 && D <= 1024 * 4 * kQbcPer && aligned)
-        hipLaunchKernelGGL(qbc_rows_reg_kernel, dim3(B), dim3(1024), 0, st, lq, lf, D, 1.0f / (float)B, ws, grad);
-    else
+    if (D % 4 == 0 && D <= 1024 * 4 * kQbcPer && aligned) {
+        const bool stream = (size_t)B * D * (grad ? 12 : 8) >= kStreamFrom;
+        hipLaunchKernelGGL(stream ? qbc_rows_reg_kernel<true> : qbc_rows_reg_kernel<false>, dim3(B), dim3(1024), 0, st, lq, lf, D,
+                           1.0f / (float)B, ws, grad);
+    } else
         hipLaunchKernelGGL(qbc_rows_kernel, dim3(B), dim3(256), 0, st, lq, lf, D, 1.0f / (float)B, ws, grad);
     hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, ws, B, 1.0f / (float)B, loss);
     return hipGetLastError();

@@ -127,3 +127,34 @@ def test_training_operators_at_the_benchmark_sizes(B):
     assert abs(float(loss.item()) - l_ref) <= 2e-6 * l_ref
     gh = host(grad, np.float32).reshape(Bn, D).astype(np.float64)
     assert np.all(np.abs(gh - g_ref) <= 2e-6 * np.abs(g_ref).max())
+
+
+@pytest.mark.parametrize("g", [64, 128, 256])
+@pytest.mark.parametrize("N", [1535, 1536, 1537])
+def test_fake_quant_w4_on_both_sides_of_the_streaming_size(B, N, g):
+    """1536 x 1024 values (12 MiB read and written) are the first that are read past the caches."""
+    import torch
+    K = 1024
+    w = synth.llm_weight(N, K, 90 + N, outlier_frac=0.01)
+    out = torch.full((N * K,), float("nan"), dtype=torch.float32, device="cuda")
+    B.qail_fake_quant_w4(dev(w), g, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(out, np.float32).reshape(N, K), O.fake_quant_w4_group(w, g))
+
+
+@pytest.mark.parametrize("Bn", [255, 256, 257, 383, 385])
+def test_qbc_loss_on_both_sides_of_the_streaming_size(B, Bn):
+    """256 x 4096 logits of either policy and the gradient are 12 MiB, 384 x 4096 without the gradient."""
+    import torch
+    D = 4096
+    rng = np.random.default_rng(Bn)
+    lq, lf = (rng.standard_normal((Bn, D)).astype(np.float32) for _ in range(2))
+    l_ref, g_ref = O.qbc_loss(lq, lf)
+    loss = torch.zeros(2, dtype=torch.float32, device="cuda")
+    grad = torch.full((Bn, D), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(Bn, dtype=torch.float32, device="cuda")
+    B.qail_qbc_loss(dev(lq), dev(lf), loss[:1], grad, ws)
+    B.qail_qbc_loss(dev(lq), dev(lf), loss[1:], None, ws)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(host(loss, np.float32) - l_ref) <= 2e-6 * l_ref)
+    assert np.all(np.abs(host(grad, np.float32).reshape(Bn, D).astype(np.float64) - g_ref) <= 2e-6 * np.abs(g_ref).max())
