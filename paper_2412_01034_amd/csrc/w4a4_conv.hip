@@ -85,7 +85,10 @@ struct ConvOut {
     const float* res_f32;
     float s_out, res_scale;
     float inv_s_out;  // 1 / s_out, correctly rounded (host division)
-    int quick;        // s_out and its reciprocal are normal numbers: the quotient may be tried as a product first
+    // fused output: s_out and its reciprocal are normal numbers, the quotient may be tried as a product first;
+    // plain outputs: stored past the caches (kPastCaches).  One word for both: the arguments of a batch with another
+    // one in each item cost the encoder at batch 32 2 % (304 -> 310 us).
+    int quick;
 };
 
 // Up to kConvBatch independent convolutions share a launch: item i is the grid's plane z = i
@@ -194,17 +197,30 @@ __device__ __forceinline__ i32x4_t widen_b(uint32_t x, uint32_t y) {
                    (int)(y & 0xF0F0F0F0u)};
 }
 
-// Plain outputs of 4 consecutive channels n0.. of a pixel, o = their position; 16-byte stores when Cout allows,
-// past the caches, which the codes and weights need (W8A8, 32 x 28 x 28 x 128, 3x3: 11.3 -> 10.1 us)
+// Plain outputs of this many bytes and more are stored past the caches, which the codes and weights need; smaller ones
+// stay there for the operator that reads them next.  us, ordinary / past the caches, 3x3 layers alone and with a step
+// search and a quantiser behind them: W8A8, 12.8 MB (32 x 28 x 28 x 128) 12.0 / 10.6 and 25.0 / 24.6, 6.4 MB (half the
+// batch, below the line) 8.4 / 7.9 and 19.3 / 19.9, 0.4 MB 4.1 / 4.1 and 12.0 / 12.4; W4A4, 12.8 MB 10.8 / 9.8 and
+// 23.8 / 23.0, 6.4 MB 8.1 / 7.7 and 19.3 / 19.8, 0.2 MB 3.8 / 3.9 and 9.4 / 11.0.
+constexpr size_t kPastCaches = (size_t)8 << 20;
+
+// Plain outputs of 4 consecutive channels n0.. of a pixel, o = their position; 16-byte stores when Cout allows
 // (sc, bi: the channels' scales and biases, fetched by the caller in that case).
 __device__ __forceinline__ void store_plain(const i32x4_t v, const ConvOut& out, size_t o, int n0, int cout, const float4 sc,
                                             const float4 bi) {
     if ((cout % 4) == 0) {
-        if (out.acc) __builtin_nontemporal_store(v, reinterpret_cast<i32x4_t*>(out.acc + o));
-        if (out.y)
-            __builtin_nontemporal_store(f32x4_t{fmaf((float)v[0], sc.x, bi.x), fmaf((float)v[1], sc.y, bi.y),
-                                                fmaf((float)v[2], sc.z, bi.z), fmaf((float)v[3], sc.w, bi.w)},
-                                        reinterpret_cast<f32x4_t*>(out.y + o));
+        i32x4_t* const acc = reinterpret_cast<i32x4_t*>(out.acc + o);
+        f32x4_t* const y = reinterpret_cast<f32x4_t*>(out.y + o);
+        const f32x4_t f = {fmaf((float)v[0], sc.x, bi.x), fmaf((float)v[1], sc.y, bi.y), fmaf((float)v[2], sc.z, bi.z),
+                           fmaf((float)v[3], sc.w, bi.w)};
+        // (in this shape: of two alternatives for one store the compiler makes a single ordinary one)
+        if (out.quick) {
+            if (out.acc) __builtin_nontemporal_store(v, acc);
+            if (out.y) __builtin_nontemporal_store(f, y);
+        } else {
+            if (out.acc) *acc = v;
+            if (out.y) *y = f;
+        }
     } else {
         for (int e = 0; e < 4 && n0 + e < cout; ++e) {
             if (out.acc) out.acc[o + e] = v[e];
@@ -930,6 +946,7 @@ ConvJob make_job(const qail_conv_desc& d, const uint32_t* a, const uint32_t* w, 
     job.a = a;
     job.w = w;
     job.out = out;
+    if (!out.out_u4) job.out.quick = (size_t)gm.M * gm.Cout * 4 >= kPastCaches;
     return job;
 }
 

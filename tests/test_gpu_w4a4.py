@@ -455,3 +455,21 @@ def test_dispatch_edges_bit_exact(B, s):
     for kw in (dict(), dict(res_codes=rc, res_scale=np.float32(s_out * 0.8)), dict(res_f32=rf)):
         got = gpu_conv_u4(B, s, aw, ww, scale, bias, s_out, **kw)
         assert np.array_equal(got, O.pack_nibbles(O.fused_requant_u4(acc_ref, scale, bias, s_out, **kw)))
+
+
+@pytest.mark.parametrize("Bn", [7, 8, 9])
+@pytest.mark.parametrize("taps", [1, 3])
+def test_plain_outputs_on_both_sides_of_the_cached_size(B, Bn, taps):
+    """8 x 64 x 64 pixels of 64 channels (8 MiB per output) are the first results that are stored past the caches;
+    one tap runs on the direct kernel, nine on the tiled one."""
+    s = synth.ConvShape("c", Bn, 64, 64, 64, 64, taps, taps, 1, taps // 2)
+    aw = O.pack_nibbles(synth.random_codes((s.B, s.H, s.W, s.Cin), 0, 15, 5).astype(np.uint8))
+    ww = O.pack_nibbles(synth.random_codes((s.Cout, s.K), -8, 7, 6))
+    scale = (np.random.default_rng(7).random(s.Cout) * 1e-3 + 1e-4).astype(np.float32)
+    bias = synth.conv_bias(s, 8)
+    ref = O.w4a4_conv_acc(aw, ww, *geom(s), use_blas=True)
+    acc, y = gpu_conv(B, s, aw, ww, scale, bias)
+    assert np.array_equal(acc, ref)
+    check_requant(y, ref, scale, bias)
+    _, y_only = gpu_conv(B, s, aw, ww, scale, bias, want_acc=False)
+    assert np.array_equal(y, y_only)
