@@ -965,8 +965,9 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     auto blocks = [&](int bm, int bn) {
         return (long long)((gm.M + bm - 1) / bm) * ((gm.Cout + bn - 1) / bn);
     };
-    long long all64 = 0, all16 = 0;
+    long long all64 = 0, all32 = 0, all16 = 0;
     for (int i = 0; i < n; ++i) {
+        all32 += (long long)((jobs[i].gm.M + 31) / 32) * ((jobs[i].gm.Cout + 31) / 32);
         all64 += (long long)((jobs[i].gm.M + 63) / 64) * ((jobs[i].gm.Cout + 63) / 64);
         all16 += (long long)((jobs[i].gm.M + 15) / 16) * ((jobs[i].gm.Cout + 15) / 16);
     }
@@ -977,11 +978,18 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     // images 4.7 / 5.3, 4.6 / 5.0, 4.9 / 6.6, 5.4 / 8.4; eight images 7.0 / 5.7 (28 k tile steps, above the
     // line), 5.4 / 5.1 (above), 6.7 / 6.8 (above), 6.5 / 8.5.  8-bit, 72 steps, four images 8.0 / 8.3, eight
     // 9.9 / 8.5 (above the line).
+    // With few K steps the direct kernel is bound by its blocks, not by its steps, so their number has a limit of
+    // its own: three and a half 32 x 32 blocks per CU.  3x3 layers of 3 steps, 784 / 1176 blocks 4.9 / 5.5, 6.2 / 5.7 (above);
+    // 1x1 layers (plain output) of 1 step, 392 / 784 / 1568 / 3136 blocks 4.1 / 4.8, 4.9 / 5.0, 7.0 / 5.6, 10.3 / 8.0 (the last
+    // two above).  The tiled kernel's set-up is shorter for one tap, and its epilogue for fused outputs: there
+    // 784 blocks are 5.1 / 4.8 already, and with 8-bit codes or fused outputs 12.5 k tile steps 5.3 / 5.2, 5.8 / 5.5.
     const long long cus = device_cu_count(), work = all16 * ksteps;
     if (all16 <= cus && work <= 120 * cus) return launch_direct<kBits, 1, 1, 8, 2>(jobs, n, st);
     if (all16 <= 2 * cus && work <= 120 * cus) return launch_direct<kBits, 1, 2, 8, 2>(jobs, n, st);
     if (all16 <= 4 * cus && work <= (kBits == 4 ? 120 : 96) * cus) return launch_direct<kBits, 2, 2, 8, 1>(jobs, n, st);
-    if (work <= 64 * cus) return launch_direct<kBits, 2, 2, 4, 1>(jobs, n, st);
+    const bool one_tap = gm.KH * gm.KW == 1, fused = jobs[lead].out.out_u4 != nullptr;
+    if (2 * all32 <= (one_tap && fused ? 5 : 7) * cus && work <= (one_tap && (fused || kBits == 8) ? 44 : 64) * cus)
+        return launch_direct<kBits, 2, 2, 4, 1>(jobs, n, st);
     const bool wide = gm.Cout > 64;
     // (the 128 x 128 tile already from one and a half blocks per CU: at batch 256 it takes the
     // 512 -> 512 layers from 45.7 to 37.6 us against the 128 x 64 tile)

@@ -460,8 +460,7 @@ def test_dispatch_edges_bit_exact(B, s):
 @pytest.mark.parametrize("Bn", [7, 8, 9])
 @pytest.mark.parametrize("taps", [1, 3])
 def test_plain_outputs_on_both_sides_of_the_cached_size(B, Bn, taps):
-    """8 x 64 x 64 pixels of 64 channels (8 MiB per output) are the first results that are stored past the caches;
-    one tap runs on the direct kernel, nine on the tiled one."""
+    """8 x 64 x 64 pixels of 64 channels (8 MiB per output) are the first results that are stored past the caches."""
     s = synth.ConvShape("c", Bn, 64, 64, 64, 64, taps, taps, 1, taps // 2)
     aw = O.pack_nibbles(synth.random_codes((s.B, s.H, s.W, s.Cin), 0, 15, 5).astype(np.uint8))
     ww = O.pack_nibbles(synth.random_codes((s.Cout, s.K), -8, 7, 6))
@@ -473,3 +472,22 @@ def test_plain_outputs_on_both_sides_of_the_cached_size(B, Bn, taps):
     check_requant(y, ref, scale, bias)
     _, y_only = gpu_conv(B, s, aw, ww, scale, bias, want_acc=False)
     assert np.array_equal(y, y_only)
+
+
+@pytest.mark.parametrize("taps", [1, 3])
+@pytest.mark.parametrize("per_cu", [2.5, 3.5])
+@pytest.mark.parametrize("more", [0, 1])
+def test_few_steps_on_both_sides_of_the_direct_kernels_limits(B, taps, per_cu, more):
+    """One or three K steps and as many 32 x 32 blocks as the direct kernel takes at most (2.5 per CU with one tap and
+    fused outputs, 3.5 otherwise), and one block more."""
+    import torch
+    blocks = int(per_cu * torch.cuda.get_device_properties(0).multi_processor_count) + more
+    s = synth.ConvShape("d", 1, 32, blocks, 32, 32, taps, taps, 1, taps // 2)
+    aw, ww, scale, bias = quantised_inputs(s, 600 + taps)
+    ref = O.w4a4_conv_acc(aw, ww, *geom(s), use_blas=True)
+    acc, y = gpu_conv(B, s, aw, ww, scale, bias)
+    assert np.array_equal(acc, ref)
+    check_requant(y, ref, scale, bias)
+    s_out = np.float32(O.requant(ref, scale, bias).max() / 20.0)
+    assert np.array_equal(gpu_conv_u4(B, s, aw, ww, scale, bias, s_out),
+                          O.pack_nibbles(O.fused_requant_u4(ref, scale, bias, s_out)))
