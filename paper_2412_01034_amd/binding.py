@@ -155,9 +155,16 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# The handle of a device's current stream without a Stream object around it (2 us less per call); torch keeps it for
+# itself, so a torch without it gets the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    """The handle of torch's current stream on the current device, without a Stream object around it."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """The handle of torch's current stream on the current device."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _need(t: torch.Tensor, nbytes: int, what: str) -> None:

@@ -243,3 +243,23 @@ def test_binding_refuses_host_tensors(B):
     with pytest.raises(ValueError):
         B.qail_quantize_weights(t, 32, B.QAIL_W4_ASYM_GROUP, torch.zeros(128, dtype=torch.int32),
                                 torch.zeros(32, dtype=torch.float16), torch.zeros(16, dtype=torch.int32))
+
+
+def test_stream_handle_without_torchs_own_accessor(B, monkeypatch):
+    import torch
+
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    assert B._stream() == 1234
+
+
+@pytest.mark.gpu
+def test_stream_handle_is_the_current_streams(B):
+    import torch
+    side = torch.cuda.Stream()
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert B._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
