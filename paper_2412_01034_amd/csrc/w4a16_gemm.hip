@@ -5,16 +5,16 @@
 // the one W4A16 kernel bound by the matrix pipe rather than by HBM.  The design goal is
 // to keep vector-ALU and LDS work per MFMA low:
 //
-//   * The weights never pass through LDS.  A wave owns 64 columns n; lane (c, kb) loads
-//     the 8 packed words (64 consecutive k) of row n = c of a 128-k step straight from
-//     global memory and expands one word into the 8 fp16 values one
-//     v_mfma_f32_32x32x16_f16 needs from it as B operand:  0x6400 | q is the fp16 number
+//   * The weights are in LDS as packed codes only.  A wave owns 32 or 64 columns n; lane (c, kb) reads
+//     the 8 packed words (64 consecutive k) of row n = c of a 128-k step back from LDS, where a
+//     loading wave has put them, and expands one word into the 8 fp16 values one
+//     v_mfma_f32_32x32x16_f16 needs from it as A operand:  0x6400 | q is the fp16 number
 //     1024 + q and 0x6400 | (q << 4) is 1024 + 16 q, so a v_and_or_b32 yields two codes,
 //     one packed add (or fma with 1/16) removes the offset together with the zero-point
 //     exactly, and one packed multiply applies the scale: 13 vector operations per word,
 //     used by BM / 32 MFMAs.
-//   * Only the activations are staged in LDS, once per block, and every wave reads the
-//     whole tile: one 16-byte LDS read per two MFMAs.
+//   * The activations are staged in LDS once per block, ready for the MFMAs, and every wave reads the
+//     whole tile: one 16-byte LDS read per two MFMAs (on 256-column tiles).
 //   * fp16 holds every bf16 significand but not its range, so a small kernel first
 //     rewrites x per row as fp16 scaled by a power of two (largest magnitude in
 //     [2^14, 2^15)), with the k order inside each group of 8 that the expansion above
@@ -36,7 +36,7 @@
 //
 // MFMA operand layout (32x32x16, wave64): lane l supplies row (A) / column (B) l%32 and
 // the 8 consecutive k starting at 8*(l/32); it receives D[8*(r/4) + 4*(l/32) + r%4][l%32]
-// for r = 0..15.  A = activations (rows m), B = weights (columns n).
+// for r = 0..15.  A = weights (columns n), B = activations (rows m).
 #include <algorithm>
 
 #include <atomic>
@@ -386,11 +386,12 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     // fragment read offset of this lane (row c of a 32-row block): its half of the step's k is the
     // chunks kSub * kb + jj, and sub-step jj < kSub folds in by an XOR of the low bits
     const int aoff0 = c * kRowBytes + (((S::kSub * kb) ^ S::swizzle(c)) << 4);
-    // The packed weights of a step: the lane's kBK / 2 k (two 16-byte pieces per column block) plus the
-    // 4-byte words holding its group's scale and zero-point.  Each lane only ever reads back its own
-    // slots, so LDS is a per-lane FIFO here and no registers (and no compiler-inserted load waits) are
-    // tied up while the loads fly.  The group of a lane's k is tracked without divisions (the group
-    // size is a multiple of 64, so they never straddle two groups).
+    // The packed weights of a step and column block: 64 bytes of codes of each of its 32 rows, row by row, of which
+    // a lane reads the two 16-byte pieces with its kBK / 2 k, and (nibbles) per lane the 4-byte words that hold
+    // its group's scale and zero-point.  What a lane reads was fetched by other lanes of a loading wave: it is
+    // complete once that wave has waited for the step and the step's barrier has been passed, and only
+    // then.  No registers (and no compiler-inserted load waits) are tied up while the loads fly.  The group of a
+    // lane's k is tracked without divisions (the group size is a multiple of 64, so they never straddle two groups).
     unsigned char* const Bs = As + kStages * kBufBytes;  // [kStages][4 waves][WN][kBLane]
     unsigned char* const Ps = Bs + kStages * kBStage;    // [kSegs][kPow2Bytes], then (bytes) [kSegs][kScales]
     unsigned char* const Cs = Ps + S::kSegs * kPow2Bytes;
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
     }
 
     // operands of the step being multiplied; ck / cgrp follow the consumed steps like lk / lgrp.
-    // A step's codes, scale word and zero word are read back from the per-lane FIFO (take_read) and
+    // A step's codes, scale word and zero word are read back from the ring (take_read) and
     // turned into the expansion's constants (take_convert) in two parts, so that the reads can be in
     // flight, and the conversions issue, under the MFMAs of the previous step's last sub-step.
     uint32_t wq[WN][4 * kCodeLoads];
@@ -739,7 +740,7 @@ __global__ __launch_bounds__(kGemmThreads) void w4a16_gemm_f16_kernel(const Gemm
         if (last) take_segment(ahead, next_slot);   // (past the last segment: the last again, which nothing uses)
         __builtin_amdgcn_sched_barrier(0);
         // The last sub-step of this step (operands already in registers) with the next step's set-up under
-        // it: all LDS reads first (FIFO and A fragments), a few MFMAs while they are in flight, then
+        // it: all LDS reads first (codes, constants, x fragments), a few MFMAs while they are in flight, then
         // the conversions and the first expansion shared out among the remaining MFMAs.
         take_read(bcur);
         take_convert();
