@@ -197,11 +197,11 @@ __device__ __forceinline__ i32x4_t widen_b(uint32_t x, uint32_t y) {
                    (int)(y & 0xF0F0F0F0u)};
 }
 
-// Plain outputs of this many bytes and more are stored past the caches, which the codes and weights need; smaller ones
-// stay there for the operator that reads them next.  us, ordinary / past the caches, 3x3 layers alone and with a step
-// search and a quantiser behind them: W8A8, 12.8 MB (32 x 28 x 28 x 128) 12.0 / 10.6 and 25.0 / 24.6, 6.4 MB (half the
-// batch, below the line) 8.4 / 7.9 and 19.3 / 19.9, 0.4 MB 4.1 / 4.1 and 12.0 / 12.4; W4A4, 12.8 MB 10.8 / 9.8 and
-// 23.8 / 23.0, 6.4 MB 8.1 / 7.7 and 19.3 / 19.8, 0.2 MB 3.8 / 3.9 and 9.4 / 11.0.
+// Plain outputs of this many bytes and more (int32 and fp32 together) are stored past the caches, which the codes
+// and weights need; smaller ones stay there for the operator that reads them next.  us, ordinary / past the caches,
+// 3x3 layers alone and with a step search and a quantiser behind them: W8A8, 12.8 MB (32 x 28 x 28 x 128)
+// 12.0 / 10.6 and 25.0 / 24.6, 6.4 MB (half the batch, below the line) 8.4 / 7.9 and 19.3 / 19.9, 0.4 MB 4.1 / 4.1 and
+// 12.0 / 12.4; W4A4, 12.8 MB 10.8 / 9.8 and 23.8 / 23.0, 6.4 MB 8.1 / 7.7 and 19.3 / 19.8, 0.2 MB 3.8 / 3.9 and 9.4 / 11.0.
 constexpr size_t kPastCaches = (size_t)8 << 20;
 
 // Plain outputs of 4 consecutive channels n0.. of a pixel, o = their position; 16-byte stores when Cout allows
@@ -946,7 +946,7 @@ ConvJob make_job(const qail_conv_desc& d, const uint32_t* a, const uint32_t* w, 
     job.a = a;
     job.w = w;
     job.out = out;
-    if (!out.out_u4) job.out.quick = (size_t)gm.M * gm.Cout * 4 >= kPastCaches;
+    if (!out.out_u4) job.out.quick = (size_t)gm.M * gm.Cout * ((out.acc ? 4 : 0) + (out.y ? 4 : 0)) >= kPastCaches;
     return job;
 }
 

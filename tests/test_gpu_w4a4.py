@@ -457,10 +457,11 @@ def test_dispatch_edges_bit_exact(B, s):
         assert np.array_equal(got, O.pack_nibbles(O.fused_requant_u4(acc_ref, scale, bias, s_out, **kw)))
 
 
-@pytest.mark.parametrize("Bn", [7, 8, 9])
+@pytest.mark.parametrize("Bn", [3, 4, 5, 7, 8, 9])
 @pytest.mark.parametrize("taps", [1, 3])
 def test_plain_outputs_on_both_sides_of_the_cached_size(B, Bn, taps):
-    """8 x 64 x 64 pixels of 64 channels (8 MiB per output) are the first results that are stored past the caches."""
+    """8 x 64 x 64 pixels of 64 channels in one output, or 4 x 64 x 64 in two (8 MiB), are the first results that are
+    stored past the caches."""
     s = synth.ConvShape("c", Bn, 64, 64, 64, 64, taps, taps, 1, taps // 2)
     aw = O.pack_nibbles(synth.random_codes((s.B, s.H, s.W, s.Cin), 0, 15, 5).astype(np.uint8))
     ww = O.pack_nibbles(synth.random_codes((s.Cout, s.K), -8, 7, 6))
