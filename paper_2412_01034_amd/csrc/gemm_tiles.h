@@ -161,7 +161,8 @@ inline TilePlan plan_tiles(int M, int N, int K, int rows, int cols, int step_k, 
         // Blocks that share a tile take at least 128 k of it, and 256 k of byte codes: a block's sums cost the second
         // kernel as much however short its part is.  Bytes, one / two / four 64-k steps per block: 128 x 11008 at
         // M = 40 24.3 / 18.8 / 16.8 us, 512 x 4096 at M = 96 19.7 / 15.6 / 14.4, 1024 x 4096 at M = 128 17.7 / 17.7 / 15.5.
-        const long long parts = step_k == 64 && units / 4 > tail ? units / 4 : step_k == 64 ? tail : units;
+        long long parts = units;
+        if (step_k == 64) parts = units / 4 > tail ? units / 4 : tail;
         tp.P = parts < cus ? (int)parts : cus;
     }
     return tp;

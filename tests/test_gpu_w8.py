@@ -458,3 +458,27 @@ def test_w8a16_eight_row_tiles_and_an_odd_last_round(B, M, N):
     q, s = O.quantize_w8_sym_group(w[-n_ref:], g)
     nx, nw = _w8_norms(xb, q, s, g)
     assert w4a16_norm_err(y[:, -n_ref:], O.w8a16_linear(xb, q, s, g), nx, nw) <= TOL
+
+
+@pytest.mark.parametrize("M", [34, 96, 130, 288])
+@pytest.mark.parametrize("N,K", [(64, 4160), (130, 4096), (520, 1088), (2100, 1024)])
+def test_w8a16_few_tiles_share_their_k(B, M, N, K):
+    """One linear of few tiles: K is shared between blocks, in parts of four steps and more, with the reported
+    workspace and with one that has room for 128-column tiles only; steps that four does not divide, ragged columns."""
+    import torch
+    g = 64
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tile_rows = (M + 31) // 32 * 32 if M <= 96 else (96 if -(-M // 96) * 96 < -(-M // 128) * 128 else 128)
+    w = synth.llm_weight(N, K, 1940 + N, outlier_frac=0.01)
+    xb = synth.llm_activation_bf16(M, K, 1950 + N, outlier_frac=0.005)
+    q, s = O.quantize_w8_sym_group(w, g)
+    ref = O.w8a16_linear(xb, q, s, g)
+    nx, nw = _w8_norms(xb, q, s, g)
+    args = (dev(O.pack_bytes(q)), dev(s.view(np.uint16)), dev(xb))
+    wide = B.qail_w8a16_workspace(N, K, g, M)
+    narrow = wide - (2 * min(cus, 512) * tile_rows * 128 * 4 if N > 128 else 0)
+    for nws in (wide, narrow):
+        y = torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda")
+        B.qail_w8a16_linear(N, K, g, *args, y, M, torch.empty(nws, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        assert w4a16_norm_err(host(y, np.uint16).reshape(M, N), ref, nx, nw) <= TOL, nws
