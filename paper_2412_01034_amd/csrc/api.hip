@@ -287,6 +287,12 @@ int qail_w4a16_linear_batch(const qail_w4a16_item* items, int32_t count, int32_t
             i = j;
             continue;
         }
+        int taken = 0;
+        if (launch_midm_if_better(items + i, count - i, M, false, st, &taken) != hipSuccess) return QAIL_ERR_HIP;
+        if (taken > 0) {
+            i += taken;
+            continue;
+        }
         while (j < count && smallm_supports(items[j].d, M) && !decode4_supports(items[j].d, M)) ++j;
         if (j > i) {
             if (launch_w4a16_smallm(items + i, j - i, M, st) != hipSuccess) return QAIL_ERR_HIP;
@@ -621,6 +627,14 @@ int qail_w8a16_linear_batch(const qail_w8a16_item* items, int32_t count, int32_t
             continue;
         }
         qail_w4a16_item run[8];
+        int taken = 0;
+        for (j = i; j < count && j - i < 8; ++j) run[j - i] = as_gemm_item(items[j]);
+        if (launch_midm_if_better(run, j - i, M, true, st, &taken) != hipSuccess) return QAIL_ERR_HIP;
+        if (taken > 0) {
+            i += taken;
+            continue;
+        }
+        j = i;
         while (j < count && j - i < 8 && smallm_w8_supports(items[j].d, M)) {
             run[j - i] = as_gemm_item(items[j]);
             ++j;

@@ -73,6 +73,11 @@ hipError_t launch_w4a16_smallm(const qail_w4a16_item* items, int count, int M, h
 // 8-bit weights at 2 <= M <= 16 on the same kernel (group size 128); items in the W4A16 record, zeros unused
 bool smallm_w8_supports(const qail_wdesc& d, int M);
 hipError_t launch_w8a16_smallm(const qail_w4a16_item* items, int count, int M, hipStream_t st);
+// Passes over K that the small-batch kernel makes for M rows of x.
+int smallm_passes(int M, int K);
+// 5 <= M <= 64 at group size 128 or 64 (8-bit: 128), one pass over K: launches the leading items of the list where that is
+// faster than the kernels above and below, and says how many (0: none).  8-bit items as above; no workspace.
+hipError_t launch_midm_if_better(const qail_w4a16_item* items, int count, int M, bool b8, hipStream_t st, int* taken);
 // Compute units of the current device (256 when none can be asked); the launchers size their grids by it.
 int device_cu_count();
 

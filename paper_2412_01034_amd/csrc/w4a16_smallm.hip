@@ -948,6 +948,12 @@ hipError_t sm_launch_chunk(const qail_w4a16_item* items, int count, int M, hipSt
 
 }  // namespace
 
+int smallm_passes(int M, int K) {
+    int rows, steps;
+    sm_plan(M, K / kStepK, &rows, &steps);
+    return (K / kStepK + steps - 1) / steps;
+}
+
 bool smallm_supports(const qail_wdesc& d, int M) {
     const int spg = d.group_size / kStepK;
     if (M > 16) return M <= 32 && d.K % kStepK == 0 && sm_one_group_per_step(d);   // two row blocks: that kernel only

@@ -1,0 +1,90 @@
+"""The kernel for medium batches (5 <= M <= 64): one pass over K, x staged step by step, K parts added in LDS.
+
+Lists and shapes at its edges: row blocks full and ragged, columns that end inside a tile, one step of K and step counts
+that the K parts do not divide, blocks of one tile and of several, both group sizes, bytes; against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import qail_oracle as O
+from paper_2412_01034_amd import synth
+
+from .helpers import dev, ensure_built, host, w4a16_norm_err, ws_for
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-3                          # of the norm product: fp32 sums, one rounding to bf16 (2^-9 of a value far below that product)
+TOL_TINY_K = 2.0 ** -8 * 1.01       # few k: a dot product may be almost aligned, the output's rounding alone counts
+
+
+@pytest.fixture(scope="module")
+def B():
+    return ensure_built()
+
+
+def make(B, bits, N, K, g, M, seed):
+    import torch
+    w = synth.llm_weight(N, K, seed, outlier_frac=0.01)
+    xb = synth.llm_activation_bf16(M, K, seed + 1, outlier_frac=0.005)
+    e = dict(N=N, K=K, group_size=g, x=dev(xb), y=torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda"))
+    nx = np.sqrt((O.bf16_bits_to_f64(xb) ** 2).sum(axis=1))
+    if bits == 4:
+        q, s, z = O.quantize_w4_asym_group(w, g)
+        qw, zw = O.pack_w4a16(q, z)
+        e.update(qweight=dev(qw), scales=dev(s.view(np.uint16)), zeros=dev(zw))
+        return e, O.w4a16_linear(xb, qw, s, zw, g), O.w4a16_row_norms(xb, qw, s, zw, g)
+    q, s = O.quantize_w8_sym_group(w, g)
+    e.update(qweight=dev(O.pack_bytes(q)), scales=dev(s.view(np.uint16)))
+    wh = q.astype(np.float64) * np.repeat(s.astype(np.float64), g, axis=1)
+    return e, O.w8a16_linear(xb, q, s, g), (nx, np.sqrt((wh ** 2).sum(axis=1)))
+
+
+def run(B, bits, ents, M):
+    import torch
+    if bits == 4:
+        items = B.make_w4a16_items(ents, M)
+        B.qail_w4a16_linear_batch(items, len(ents), M, ws_for(B, B.qail_w4a16_batch_workspace(items, len(ents), M)))
+    else:
+        items = B.make_w8a16_items(ents, M)
+        B.qail_w8a16_linear_batch(items, len(ents), M, ws_for(B, B.qail_w8a16_batch_workspace(items, len(ents), M)))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M", [5, 16, 17, 31, 33, 48, 49, 64])
+@pytest.mark.parametrize("bits,shapes", [
+    (4, [(300, 128, 64)]),                                              # one step of K
+    (4, [(33, 384, 64), (1000, 640, 64), (7, 2816, 64)]),               # 3, 5 and 22 steps, ragged columns
+    (4, [(4200, 1024, 64), (520, 1024, 128), (70, 2048, 128)]),         # group sizes in launches of their own
+    (4, [(300, 11008, 128), (1030, 256, 128)]),                         # 86 steps: four parts do not divide them
+    (4, [(9000, 512, 128), (4100, 768, 128)]),                          # blocks of several tiles
+    (8, [(1030, 11008, 128), (77, 256, 128)]),
+    (8, [(9000, 768, 128), (300, 512, 128)]),
+])
+def test_lists_and_edges(B, bits, shapes, M):
+    made = [make(B, bits, N, K, g, M, 3000 + 10 * i + M) for i, (N, K, g) in enumerate(shapes)]
+    ents = [m[0] for m in made]
+    run(B, bits, ents, M)
+    first = [host(e["y"], np.uint16).copy() for e in ents]
+    for e in ents:
+        e["y"].fill_(0x7FC0)
+    run(B, bits, ents, M)
+    for (e, ref, (nx, nw)), y0 in zip(made, first):
+        y = host(e["y"], np.uint16)
+        assert np.array_equal(y, y0), "run to run"
+        tol = TOL if e["K"] >= 512 else TOL_TINY_K
+        assert w4a16_norm_err(y.reshape(M, e["N"]), ref, nx, nw) <= tol, (e["N"], e["K"], e["group_size"])
+
+
+@pytest.mark.parametrize("bits,g,M", [(4, 64, 16), (4, 64, 33), (4, 128, 40), (8, 128, 50)])
+def test_rows_do_not_reach_each_other(B, bits, g, M):
+    """A row of x that holds infinities and NaN gives NaN in its own results only; a row of zeros gives zeros."""
+    N, K = 300, 1024
+    e, ref, (nx, nw) = make(B, bits, N, K, g, M, 4000 + M)
+    x = e["x"].view(M, K)
+    x[3] = 0x7F80                   # +inf
+    x[4] = 0x7FC0                   # NaN
+    x[2] = 0
+    run(B, bits, [e], M)
+    y = (host(e["y"], np.uint16).reshape(M, N).astype(np.uint32) << 16).view(np.float32)
+    assert np.all(np.isnan(y[3]) | np.isinf(y[3])) and np.all(np.isnan(y[4])) and np.all(y[2] == 0)
+    rest = [m for m in range(M) if m not in (2, 3, 4)]
+    assert w4a16_norm_err(host(e["y"], np.uint16).reshape(M, N)[rest], ref[rest], nx[rest], nw) <= TOL
