@@ -172,6 +172,18 @@ def _need(t: torch.Tensor, nbytes: int, what: str) -> None:
         raise ValueError(f"{what}: {t.numel() * t.element_size()} bytes given, {nbytes} needed")
 
 
+def _arg(t: torch.Tensor, nbytes: int, what: str) -> int:
+    """The address of a required tensor of at least `nbytes` bytes: _need and _ptr in one (a call is a few microseconds of
+    such questions, 4096 x 4096 at M = 1 takes 4.5 on the GPU)."""
+    if t.nbytes < nbytes:
+        raise ValueError(f"{what}: {t.nbytes} bytes given, {nbytes} needed")
+    if not t.is_cuda:
+        raise ValueError("device tensor expected")
+    if not t.is_contiguous():
+        raise ValueError("contiguous tensor expected")
+    return t.data_ptr()
+
+
 def qail_version() -> int:
     return int(lib().qail_version())
 
@@ -242,15 +254,14 @@ def qail_w4a16_linear(N: int, K: int, group_size: int, qweight: torch.Tensor, sc
     """x: bf16 [M, K]; y: bf16 [M, N]; both device tensors (torch.bfloat16 or a
     16-bit integer view of the same bits)."""
     G = K // group_size
-    _need(qweight, N * K // 2, "qweight")
-    _need(scales, N * G * 2, "scales")
-    _need(zeros, N * ((G + 7) // 8) * 4, "zeros")
-    _need(x, M * K * 2, "x")
-    _need(y, M * N * 2, "y")
-    d = qail_wdesc(N, K, group_size, QAIL_W4_ASYM_GROUP)
-    wsb = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib().qail_w4a16_linear(ctypes.byref(d), _ptr(qweight), _ptr(scales), _ptr(zeros), _ptr(x),
-                                   _ptr(y), M, _ptr(workspace), wsb, _stream()), "qail_w4a16_linear")
+    q, s = _arg(qweight, N * K // 2, "qweight"), _arg(scales, N * G * 2, "scales")
+    z = _arg(zeros, N * ((G + 7) // 8) * 4, "zeros")
+    xa, ya = _arg(x, M * K * 2, "x"), _arg(y, M * N * 2, "y")
+    ws, wsb = (None, 0) if workspace is None else (_ptr(workspace), workspace.nbytes)
+    status = (_lib or lib()).qail_w4a16_linear(ctypes.byref(qail_wdesc(N, K, group_size, QAIL_W4_ASYM_GROUP)), q, s, z, xa, ya,
+                                               M, ws, wsb, _stream())
+    if status:
+        raise QailError(status, "qail_w4a16_linear")
 
 
 def make_w4a16_items(entries: Sequence[dict], M: int):

@@ -263,3 +263,18 @@ def test_stream_handle_is_the_current_streams(B):
     assert B._stream() == torch.cuda.current_stream().cuda_stream
     with torch.cuda.stream(side):
         assert B._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+
+
+def test_linear_refuses_short_and_host_tensors(B):
+    """The linear call asks each tensor once for size, place and layout: short ones and host tensors are refused as ever."""
+    import torch
+    N, K, g, M = 16, 256, 128, 1
+    ok = dict(qweight=torch.zeros(N * K // 8, dtype=torch.int32), scales=torch.zeros(N * 2, dtype=torch.float16),
+              zeros=torch.zeros(N, dtype=torch.int32), x=torch.zeros((M, K), dtype=torch.bfloat16), y=torch.zeros((M, N), dtype=torch.bfloat16))
+    with pytest.raises(ValueError, match="device tensor"):
+        B.qail_w4a16_linear(N, K, g, *ok.values(), M)
+    for short in ok:
+        args = dict(ok)
+        args[short] = ok[short].reshape(-1)[1:]
+        with pytest.raises(ValueError):
+            B.qail_w4a16_linear(N, K, g, *args.values(), M)
