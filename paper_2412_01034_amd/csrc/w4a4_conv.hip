@@ -17,8 +17,9 @@
 //
 // MFMA operand layout (32x32x32 int8, wave64): lane l supplies row (A) / column
 // (B) l%32 and the 16 consecutive k starting at 16*(l/32); register r of its 16
-// results is D[8*(r/4) + 4*(l/32) + r%4][l%32].  A = activations (rows m),
-// B = weights (columns n).  The 16x16x64 form has the same operand volume per
+// results is D[8*(r/4) + 4*(l/32) + r%4][l%32].  A = weights (channels n),
+// B = activations (pixels m), so that a lane has four neighbouring channels of one
+// pixel at a time.  The 16x16x64 form has the same operand volume per
 // multiply-add but a wave issuing nothing else reaches only 0.6 of the matrix
 // rate with it (2.7 against 4.5 POP/s over the chip, measured), the 32x32x32 form all of it.
 //
@@ -28,6 +29,12 @@
 // (half the LDS traffic of int8); the load unit writes the tiles of the next two steps
 // straight into a ring of three LDS slots, one barrier per step.
 // Zero padding costs nothing: code 0 of the unsigned activations is the value 0.
+//
+// Where a launch's time goes (time stamps of a block, 3x3 layers of 64 / 128 / 256 / 512 channels at batch 32, us):
+// set-up to the first loads 0.96 / 0.68 / 0.60 / 0.60, their landing 0.3-0.6, K loop 3.4 / 3.9 / 3.6 / 5.4 (blocks that
+// share their unit with more others up to 5.5 / 5.2 / 5.7 / 5.5), epilogue 2.0 / 1.8 / 0.84 / 1.08; first to last stamp
+// 9.9 / 8.5 / 8.3 / 8.1, and 1.5 to 2 more to the next launch.  The loop is bound by vector issue (widening) and, with
+// 64 x 64 tiles, by what a unit takes in from L2 (300 KB a block), the epilogue by its operations per element.
 #include "qail_internal.h"
 #include <algorithm>
 #include <cmath>
@@ -45,6 +52,7 @@ struct ConvGeom {
     // x * magic is x / d for every x the kernel divides.
     uint32_t mg_ohow, mg_ow, mg_cw, mg_kw;
     int fastdiv;
+    uint32_t row_taps;   // bit kh KW for every row kh of the filter
 };
 
 // x / d as the high word of x * ceil(2^32 / d): with e = d * magic - 2^32 (0 <= e < d) the product
@@ -114,33 +122,36 @@ __device__ __forceinline__ float fused_value(int acc, float scale, float bias, f
 #pragma clang fp contract(off)
     float t = (float)acc * scale;
     t = t + bias;
-    t = t + r;
-    return fmaxf(t, 0.f);
+    return t + r;   // the ReLU is part of the clamps below
 }
 __device__ __forceinline__ float fused_code(float t, float s_out) {
-    return fminf(__builtin_rintf(t / s_out), 15.f);
+    return fminf(__builtin_rintf(fmaxf(t, 0.f) / s_out), 15.f);
 }
 // The same code without the division wherever that is provably the same: u = t * fl(1 / s) is
 // within 1.5 * 2^-23 (relative) of fl(t / s), so below 16 the two differ by less than 2^-18 and
 // round to the same integer unless u lies within 2^-17 of a half-integer, i.e. |u - rint(u)|
 // (an exact difference) exceeds 1/2 - 2^-17; `worst` keeps the largest such distance of a word and
-// the caller divides when it is that large.  From 15.6 upwards both round to 16 or more and the
-// code is 15 either way.  (The ReLU stays in front of the quotient: behind it, one median-of-three
-// would do for both clamps, but negative values would then reach the tie test, and with round
-// steps, where ties are exact and common, nearly every wave would divide.)
+// the caller divides when it is that large.  u is clamped to 0 .. 15 first (one median-of-three, which makes 0 of a
+// NaN as the ReLU does): from 15 upwards the quotient is at least 15 - 2^-18 and the code 15, below 0 the ReLU makes it
+// 0, and the clamped values are no ties, so that negative and large values do not make their waves divide.
 __device__ __forceinline__ float fused_code_quick(float t, float inv_s, float& worst) {
 #pragma clang fp contract(off)
-    const float u = t * inv_s;
+    const float u = __builtin_amdgcn_fmed3f(t * inv_s, 0.f, 15.f);
     const float q = __builtin_rintf(u);
     worst = fmaxf(worst, __builtin_fabsf(u - q));
-    return fminf(q, 15.f);
+    return q;
 }
-// Eight codes (small non-negative integers held as floats) -> one packed word, code e in nibble e.
+// Eight codes (small non-negative integers held as floats) -> one packed word, code e in nibble e: a code is
+// converted into its byte of the even or the odd codes' word (11 operations per output element up to here, 14 with a
+// shift and an or per code and the clamps one by one: 1 % of the body at batch 32).
 __device__ __forceinline__ uint32_t pack_codes(const float (&q)[8]) {
-    uint32_t word = 0;
+    uint32_t even = 0, odd = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) word |= (uint32_t)q[e] << (4 * e);
-    return word;
+    for (int e = 0; e < 4; ++e) {
+        even = __builtin_amdgcn_cvt_pk_u8_f32(q[2 * e], e, even);
+        odd = __builtin_amdgcn_cvt_pk_u8_f32(q[2 * e + 1], e, odd);
+    }
+    return even | (odd << 4);
 }
 
 // 8 consecutive channels of one output pixel -> one packed word; sc / bi: their scales and
@@ -166,10 +177,11 @@ __device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
 }
 // Shortcut values of 8 channels from a word of 4-bit codes (each times its step: one rounding).
 __device__ __forceinline__ void shortcut_from_codes(uint32_t rw, float res_scale, float (&r)[8]) {
+    const uint32_t even = rw & 0x0F0F0F0Fu, odd = (rw >> 4) & 0x0F0F0F0Fu;   // a byte converts to float in one operation
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
 #pragma clang fp contract(off)
-        r[e] = res_scale * (float)((rw >> (4 * e)) & 0xFu);
+        r[e] = res_scale * (float)((((e & 1) ? odd : even) >> (8 * (e / 2))) & 0xFFu);
     }
 }
 __device__ __forceinline__ uint32_t fused_word(const int (&acc)[8], const ConvOut& o, size_t m, int n0, int cout) {
@@ -322,11 +334,13 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
             const int oh = div_by(rem, gm.OW, gm.mg_ow, gm.fastdiv), ow = rem - oh * gm.OW;
             const int ih0 = oh * gm.stride - gm.pad, iw0 = ow * gm.stride - gm.pad;
             abase[i] = ((b * gm.H + ih0) * gm.W + iw0) * cw * 4;
-            // taps inside the image: kw in [kw_lo, kw_hi) for every kh in [kh_lo, kh_hi)
-            const int kw_lo = max(0, -iw0), kw_hi = min(gm.KW, gm.W - iw0);
-            const int kh_lo = max(0, -ih0), kh_hi = min(gm.KH, gm.H - ih0);
-            const uint32_t cols = kw_hi > kw_lo ? (0xFFFFFFFFu >> (32 - (kw_hi - kw_lo))) << kw_lo : 0u;
-            for (int kh = kh_lo; kh < kh_hi; ++kh) amask[i] |= cols << (kh * gm.KW);
+            // taps inside the image: kw in [kw_lo, kw_hi) for every kh in [kh_lo, kh_hi); at most 32 taps, and the product
+            // copies the bits of a row (fewer than KW + 1) to every row kept
+            const int kw_lo = max(0, -iw0), kw_n = min(gm.KW, gm.W - iw0) - kw_lo;
+            const int kh_lo = max(0, -ih0), kh_n = min(gm.KH, gm.H - ih0) - kh_lo;
+            if (kw_n > 0 && kh_n > 0)
+                amask[i] = ((0xFFFFFFFFu >> (32 - kw_n)) << kw_lo) *
+                           (gm.row_taps & ((0xFFFFFFFFu >> (32 - kh_n * gm.KW)) << (kh_lo * gm.KW)));
         }
     }
     uint32_t bbase[kLB];
@@ -336,32 +350,24 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
         bbase[i] = n < gm.Cout ? (uint32_t)n * kwords * 4 : kOut;
     }
 
-    // Where a K step's chunks come from is the same for every row and every block: a table in
-    // LDS, built once, holds for (step, chunk) the byte offset of the chunk from a pixel's
-    // (ih0, iw0, 0), its offset inside a filter row, and its tap; steps past the end of K are
-    // marked invalid (their loads read nothing and write zeros).
-    {
-        const int entries = (steps + kStages) * KS * 4;
-        for (int e = t; e < entries; e += kThreads) {
-            const int kw0 = (e >> 2) * kStepWords + (e & 3) * 4;   // first word of the chunk
-            uint2 v = make_uint2(0u, 0xFFFFFFFFu);
-            if (kw0 < kwords) {
-                const int tap = div_by(kw0, cw, gm.mg_cw, gm.fastdiv), cword = kw0 - tap * cw;
-                const int kh = div_by(tap, gm.KW, gm.mg_kw, gm.fastdiv), kwi = tap - kh * gm.KW;
-                v.x = (uint32_t)(((kh * gm.W + kwi) * cw + cword) * 4);
-                v.y = (uint32_t)(kw0 * 4) | ((uint32_t)tap << 26);
-            }
-            steptab[e] = v;
+    // Where a K step's chunks come from is the same for every row and every block: for (step, chunk) the byte offset of
+    // the chunk from a pixel's (ih0, iw0, 0), its offset inside a filter row, and its tap; steps past the end of K are
+    // marked invalid (their loads read nothing and write zeros).  The steps of the ring's first fill are worked out by
+    // each lane for itself, so that their loads leave at once; the others come from a table in LDS, built once
+    // while those loads are in flight (the body at batch 32: 0.7 %).
+    auto entry = [&](int step, int ch) {
+        const int kw0 = step * kStepWords + ch * 4;   // first word of the chunk
+        uint2 v = make_uint2(0u, 0xFFFFFFFFu);
+        if (kw0 < kwords) {
+            const int tap = div_by(kw0, cw, gm.mg_cw, gm.fastdiv), cword = kw0 - tap * cw;
+            const int kh = div_by(tap, gm.KW, gm.mg_kw, gm.fastdiv), kwi = tap - kh * gm.KW;
+            v.x = (uint32_t)(((kh * gm.W + kwi) * cw + cword) * 4);
+            v.y = (uint32_t)(kw0 * 4) | ((uint32_t)tap << 26);
         }
-    }
-    __syncthreads();
-    int pstep = 0;
-    uint2 pent = steptab[grp * 4 + chunk];  // entry of the next step to plan, read one step ahead
+        return v;
+    };
     uint32_t poff[kL];
-    auto plan = [&]() {
-        const uint2 e = pent;
-        ++pstep;
-        pent = steptab[(pstep * KS + grp) * 4 + chunk];
+    auto place = [&](const uint2 e) {
         const bool kin = (e.y >> 31) == 0;
         const uint32_t tap = (e.y >> 26) & 31u, kw4 = e.y & 0x03FFFFFFu;
 #pragma unroll
@@ -371,6 +377,14 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
         }
 #pragma unroll
         for (int i = 0; i < kLB; ++i) poff[kLA + i] = kin ? bbase[i] + kw4 : kOut;
+    };
+    int pstep = kStages - 1;
+    uint2 pent;   // entry of the next step to plan, read one step ahead
+    auto plan = [&]() {
+        const uint2 e = pent;
+        ++pstep;
+        pent = steptab[(pstep * KS + grp) * 4 + chunk];
+        place(e);
     };
     auto issue = [&](int i, int slot) {
         if (i < kLA)
@@ -438,7 +452,7 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
             for (int i = 0; i < kUM; ++i)
 #pragma unroll
                 for (int j = 0; j < kUN; ++j)
-                    acc[i][j][h % kAccs] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[reg][i][h], bf[reg][j][h],
+                    acc[i][j][h % kAccs] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[reg][j][h], af[reg][i][h],
                                                                                  acc[i][j][h % kAccs], 0, 0, 0);
         // issue order: the LDS reads and the widening of the next fragments go between the MFMAs
         constexpr int kM = 2 * kUM * kUN, kF = 2 * (kUM + kUN);   // MFMAs, operand fragments
@@ -455,13 +469,50 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     // steps 0 and 1 up front, then step s + 2 during step s
 #pragma unroll
     for (int p = 0; p < kStages - 1; ++p) {
-        plan();
+        place(entry(p * KS + grp, chunk));
 #pragma unroll
         for (int i = 0; i < kL; ++i) issue(i, p);
     }
+    for (int e = t; e < (steps + kStages) * KS * 4; e += kThreads) steptab[e] = entry(e >> 2, e & 3);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kL));
     __syncthreads();
+    pent = steptab[(pstep * KS + grp) * 4 + chunk];
     fetch(0, 0, 0);
+
+    // What the epilogue needs of scales, biases and shortcut is requested here, behind the ring's first steps: requested at
+    // the end, where the multiplying has stopped, it cost every launch a trip to memory (ResNet-34 body at batch 32, with the staging in
+    // 16-byte pieces below: 1 to 2 % of 310 us).
+    // A thread writes the same columns in every iteration of the epilogue's store loops (the block's
+    // thread count is a multiple of the pieces per row).
+    constexpr int kWordsPerRow = BN / 8, kQuadsPerRow = BN / 4;
+    static_assert(kThreads % kWordsPerRow == 0 && kThreads % kQuadsPerRow == 0, "columns fixed per thread");
+    constexpr int kItF = (kPassRows * kWordsPerRow + kThreads - 1) / kThreads;
+    const int n0f = bn + (t % kWordsPerRow) * 8, n0q = bn + (t % kQuadsPerRow) * 4;
+    const bool vec = (gm.Cout % 4) == 0;
+    float scf[8], bif[8];
+    float4 scq = make_float4(0.f, 0.f, 0.f, 0.f), biq = scq;
+    uint32_t rwf[kPasses][kItF];
+    const bool fused = kBits == 4 && out.out_u4;   // (bytes have plain outputs only)
+    if (fused) {
+        if (n0f < gm.Cout) {
+            load8(out.scale + n0f, scf);
+            load8(out.bias + n0f, bif);
+        }
+        if (out.res_u4) {
+#pragma unroll
+            for (int pass = 0; pass < kPasses; ++pass)
+#pragma unroll
+                for (int it = 0; it < kItF; ++it) {
+                    const int idx = t + it * kThreads;
+                    const int m = bm + pass * kPassRows + idx / kWordsPerRow;
+                    rwf[pass][it] = (idx < kPassRows * kWordsPerRow && m < gm.M && n0f < gm.Cout)
+                                        ? out.res_u4[(size_t)m * (gm.Cout / 8) + n0f / 8] : 0u;
+                }
+        }
+    } else if (out.y && vec && n0q < gm.Cout) {
+        scq = *reinterpret_cast<const float4*>(out.scale + n0q);
+        biq = *reinterpret_cast<const float4*>(out.bias + n0q);
+    }
 
     if constexpr (kBits == 4) {
         for (int s0 = 0; s0 < steps; s0 += kStages) {
@@ -510,58 +561,33 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     __syncthreads();
 
     // Epilogue: the accumulators (all rows at once if they fit, else half the rows at a time)
-    // are staged in LDS (pitch BN + 4 words: conflict-free for the writes below) and leave as
-    // whole pieces of rows.
+    // are staged in LDS (pitch BN + 4 words: the 16-byte writes of eight neighbouring pixels fall on different banks) and
+    // leave as whole pieces of rows.
     int32_t* const stage = reinterpret_cast<int32_t*>(smem);
-    // A thread writes the same columns in every iteration of the store loops below (the block's
-    // thread count is a multiple of the pieces per row), so their scales and biases are fetched
-    // once, here, and the shortcut words of a pass before its barrier: a load inside the store
-    // loop would wait out its full latency in every iteration, behind the previous store.
-    constexpr int kWordsPerRow = BN / 8, kQuadsPerRow = BN / 4;
-    static_assert(kThreads % kWordsPerRow == 0 && kThreads % kQuadsPerRow == 0, "columns fixed per thread");
-    constexpr int kItF = (kPassRows * kWordsPerRow + kThreads - 1) / kThreads;
-    const int n0f = bn + (t % kWordsPerRow) * 8, n0q = bn + (t % kQuadsPerRow) * 4;
-    const bool vec = (gm.Cout % 4) == 0;
-    float scf[8], bif[8];
-    float4 scq = make_float4(0.f, 0.f, 0.f, 0.f), biq = scq;
-    if (out.out_u4) {
-        if (n0f < gm.Cout) {
-            load8(out.scale + n0f, scf);
-            load8(out.bias + n0f, bif);
-        }
-    } else if (out.y && vec && n0q < gm.Cout) {
-        scq = *reinterpret_cast<const float4*>(out.scale + n0q);
-        biq = *reinterpret_cast<const float4*>(out.bias + n0q);
-    }
 #pragma unroll
     for (int pass = 0; pass < kPasses; ++pass) {
         if (pass) __syncthreads();  // the previous pass has been read
-        uint32_t rwf[kItF];
-        if (out.out_u4 && out.res_u4) {
-#pragma unroll
-            for (int it = 0; it < kItF; ++it) {
-                const int idx = t + it * kThreads;
-                const int m = bm + pass * kPassRows + idx / kWordsPerRow;
-                rwf[it] = (idx < kPassRows * kWordsPerRow && m < gm.M && n0f < gm.Cout)
-                              ? out.res_u4[(size_t)m * (gm.Cout / 8) + n0f / 8] : 0u;
-            }
-        }
         if (kPasses == 1 || wm == pass) {
             const int rbase = kPasses == 1 ? wm * (BM / 2) : 0;
-            // 32 x 32 accumulator: register r of lane (c32, hi) is row 8 (r / 4) + 4 hi + r % 4, column c32
+            // register r of lane (r32, kh) is pixel r32, channel 8 (r / 4) + 4 kh + r % 4 of the wave's 32 x 32 block
 #pragma unroll
             for (int i = 0; i < kUM; ++i)
 #pragma unroll
                 for (int j = 0; j < kUN; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int v = kAccs == 2 ? acc[i][j][0][r] + acc[i][j][kAccs - 1][r] : acc[i][j][0][r];
-                        stage[(rbase + i * 32 + 8 * (r / 4) + 4 * kh + (r % 4)) * kSPitch + wn * (BN / 2) + j * 32 + r32] =
-                            kBits == 4 ? v >> 4 : v;  // 4-bit: the accumulator is 16 * result
+                    for (int q = 0; q < 4; ++q) {
+                        i32x4_t v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int r = 4 * q + e;
+                            v[e] = kAccs == 2 ? acc[i][j][0][r] + acc[i][j][kAccs - 1][r] : acc[i][j][0][r];
+                            if (kBits == 4) v[e] >>= 4;  // 4-bit: the accumulator is 16 * result
+                        }
+                        *reinterpret_cast<i32x4_t*>(&stage[(rbase + i * 32 + r32) * kSPitch + wn * (BN / 2) + j * 32 + 8 * q + 4 * kh]) = v;
                     }
         }
         __syncthreads();
-        if (out.out_u4) {
+        if (fused) {
             // fused output: 8 consecutive channels of a pixel -> one packed word
 #pragma unroll
             for (int it = 0; it < kItF; ++it) {
@@ -580,7 +606,7 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
                 const int av[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
                 float r[8];
                 if (out.res_u4) {
-                    shortcut_from_codes(rwf[it], out.res_scale, r);
+                    shortcut_from_codes(rwf[pass][it], out.res_scale, r);
                 } else if (out.res_f32) {
                     load8(out.res_f32 + (size_t)m * gm.Cout + n0, r);
                 } else {
@@ -935,6 +961,8 @@ ConvJob make_job(const qail_conv_desc& d, const uint32_t* a, const uint32_t* w, 
         gm.mg_cw = div_magic(cw, (uint64_t)gm.KH * gm.KW * cw, ok);
         gm.mg_kw = div_magic((uint32_t)gm.KW, (uint64_t)gm.KH * gm.KW, ok);
         gm.fastdiv = ok ? 1 : 0;
+        gm.row_taps = 0;
+        for (long long b = 0; b < (long long)gm.KH * gm.KW && b < 32; b += gm.KW) gm.row_taps |= 1u << b;
     }
     const size_t cwb = (size_t)gm.Cin / kPerWord * 4;  // bytes per pixel
     const bool fits32 = (size_t)gm.B * gm.H * gm.W * cwb < 0xFFFFFFF0ull &&
