@@ -45,6 +45,18 @@ struct TilePlan {
 __host__ __device__ inline long long first_unit(long long b, long long units, int P) { return b * units / P; }
 __host__ __device__ inline int owner_of(long long u, long long units, int P) { return (int)(((u + 1) * P - 1) / units); }
 
+// The same for the second kernel, which starts with five of them: P is at most kMaxGemmBlocks, so below kUnits32 units every
+// product fits 32 bits (only a K of a million reaches that line), and a 32-bit division is a sixth of the 64-bit one's
+// 150 instructions, most of which wait for the one before.
+constexpr int kMaxGemmBlocks = 512;     // upper bound of the grid (the workspace has two slots per block)
+constexpr long long kUnits32 = (1ll << 32) / kMaxGemmBlocks;
+__host__ __device__ inline int first_unit_quick(int b, long long units, int P) {
+    return units < kUnits32 ? (int)((uint32_t)b * (uint32_t)units / (uint32_t)P) : (int)first_unit(b, units, P);
+}
+__host__ __device__ inline int owner_of_quick(int u, long long units, int P) {
+    return units < kUnits32 ? (int)((((uint32_t)u + 1u) * (uint32_t)P - 1u) / (uint32_t)units) : owner_of(u, units, P);
+}
+
 // The segments (a tile and a range of its K steps) of one block, one after the other: its whole tiles, then
 // its units.  tile_m: rows of a tile; Kpad: padded length of a row of x (fp16).
 struct TileDealer {

@@ -99,9 +99,21 @@ void byte_parts(int M, int N, int K, bool narrow_only, int least) {
     CHECK(tp.P >= least, "M %d N %d K %d: %d blocks", M, N, K, tp.P);
 }
 
+// The second kernel's arithmetic agrees with the general one on both sides of the line between them.
+void quick_units() {
+    for (long long units : {1ll, 2ll, 63ll, 1376ll, 4096ll, kUnits32 - 1, kUnits32, kUnits32 + 1, (1ll << 27) - 5})
+        for (int P : {1, 2, 7, 114, 255, 256, 304, kMaxGemmBlocks}) {
+            for (int b = 0; b <= P; ++b)
+                CHECK(first_unit_quick(b, units, P) == (int)first_unit(b, units, P), "units %lld P %d block %d", units, P, b);
+            for (long long u : {0ll, 1ll, units / 3, units / 2, units - 2, units - 1})
+                if (u >= 0 && u < units) CHECK(owner_of_quick((int)u, units, P) == owner_of(u, units, P), "units %lld P %d unit %lld", units, P, u);
+        }
+}
+
 }  // namespace
 
 int main() {
+    quick_units();
     for (int bits : {4, 8})
         for (uint32_t K = 64; K <= 2048; K += 64)
             for (uint32_t g = 64; g <= K; g += 64)
