@@ -109,6 +109,28 @@ int check_item(const qail_w4a16_item& it, int M) {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? QAIL_OK : QAIL_ERR_HIP; }
 
+// Linears of the matrix-core GEMM that share launches lie side by side in the workspace: eight at a time, counted from
+// the start of their run (consecutive items that the GEMM can take).  The workspace is sized by these groups, so the
+// launches keep to them, also where another kernel has taken some of a run's items: what is left of a
+// group needs no more than the group, but groups counted afresh from the first item left could need more than any that was
+// sized (four of 256 x 256 and eight of 4096 x 10880: 45 MB for 8 + 4 of them, 56 MB for the last eight together).
+class GemmGroups {
+   public:
+    // Where the group that holds item i ends, or i if the GEMM does not take it; to be asked in the order of the items.
+    template <class Takes>
+    int end(int i, int count, const Takes& takes) {
+        for (; at_ < i; ++at_)
+            if (!takes(at_)) run_ = at_ + 1;
+        const int full = run_ + ((i - run_) / kGemmGroup + 1) * kGemmGroup;
+        int j = i;
+        while (j < count && j < full && takes(j)) ++j;
+        return j;
+    }
+
+   private:
+    int at_ = 0, run_ = 0;   // no item before run_ is in the run that reaches at_
+};
+
 }  // namespace
 
 extern "C" {
@@ -204,20 +226,14 @@ static bool takes_gemm(const qail_wdesc& d, int M) {
     return M > 1 && !decode4_supports(d, M) && !smallm_supports(d, M) && gemm_f16_supports(d, M);
 }
 
-// Workspace of a batch: consecutive linears of the matrix-core GEMM share launches and lie side
-// by side in it; runs follow each other on the stream and reuse it.
+// Workspace of a batch: groups follow each other on the stream and reuse it.
 static size_t batch_need(const qail_w4a16_item* items, int count, int M) {
     size_t need = 0;
-    int i = 0;
-    while (i < count) {
-        int j = i;
-        while (j < count && takes_gemm(items[j].d, M)) ++j;
-        if (j > i) {
-            need = std::max(need, gemm_f16_batch_workspace(items + i, j - i, M));
-            i = j;
-        } else {
-            ++i;
-        }
+    GemmGroups groups;
+    for (int i = 0; i < count;) {
+        const int j = groups.end(i, count, [&](int e) { return takes_gemm(items[e].d, M); });
+        if (j > i) need = std::max(need, gemm_f16_batch_workspace(items + i, j - i, M));
+        i = std::max(j, i + 1);
     }
     return need;
 }
@@ -277,6 +293,7 @@ int qail_w4a16_linear_batch(const qail_w4a16_item* items, int32_t count, int32_t
         }
         return QAIL_OK;
     }
+    GemmGroups groups;
     int i = 0;
     while (i < count) {
         // runs of items one of the streaming kernels takes go out together
@@ -299,7 +316,7 @@ int qail_w4a16_linear_batch(const qail_w4a16_item* items, int32_t count, int32_t
             i = j;
             continue;
         }
-        while (j < count && takes_gemm(items[j].d, M)) ++j;
+        j = groups.end(i, count, [&](int e) { return takes_gemm(items[e].d, M); });
         if (j > i) {
             if (launch_w4a16_gemm_f16_batch(items + i, j - i, M, true, workspace, st) != hipSuccess) return QAIL_ERR_HIP;
             i = j;
@@ -555,23 +572,16 @@ int check_w8_item(const qail_w8a16_item& it, int M) {
     return QAIL_OK;
 }
 
-// Workspace of a batch: runs of consecutive items that go to the GEMM share launches, eight at a time.
+// Workspace of a batch, as for 4-bit weights.
 size_t w8_batch_need(const qail_w8a16_item* items, int count, int M, bool wide_tiles) {
     size_t need = 0;
-    int i = 0;
-    while (i < count) {
-        int j = i;
-        qail_w4a16_item run[8];
-        while (j < count && j - i < 8 && w8_takes_gemm(items[j].d, M)) {
-            run[j - i] = as_gemm_item(items[j]);
-            ++j;
-        }
-        if (j > i) {
-            need = std::max(need, gemm_f16_batch_workspace(run, j - i, M, wide_tiles));
-            i = j;
-        } else {
-            ++i;
-        }
+    GemmGroups groups;
+    for (int i = 0; i < count;) {
+        const int j = groups.end(i, count, [&](int e) { return w8_takes_gemm(items[e].d, M); });
+        qail_w4a16_item group[kGemmGroup];
+        for (int e = i; e < j; ++e) group[e - i] = as_gemm_item(items[e]);
+        if (j > i) need = std::max(need, gemm_f16_batch_workspace(group, j - i, M, wide_tiles));
+        i = std::max(j, i + 1);
     }
     return need;
 }
@@ -617,6 +627,7 @@ int qail_w8a16_linear_batch(const qail_w8a16_item* items, int32_t count, int32_t
         if (reinterpret_cast<uintptr_t>(workspace) & 255u) return QAIL_ERR_ALIGN;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
+    GemmGroups groups;
     int i = 0;
     while (i < count) {
         int j = i;
@@ -626,16 +637,16 @@ int qail_w8a16_linear_batch(const qail_w8a16_item* items, int32_t count, int32_t
             i = j;
             continue;
         }
-        qail_w4a16_item run[8];
+        qail_w4a16_item run[kGemmGroup];
         int taken = 0;
-        for (j = i; j < count && j - i < 8; ++j) run[j - i] = as_gemm_item(items[j]);
+        for (j = i; j < count && j - i < kGemmGroup; ++j) run[j - i] = as_gemm_item(items[j]);
         if (launch_midm_if_better(run, j - i, M, true, st, &taken) != hipSuccess) return QAIL_ERR_HIP;
         if (taken > 0) {
             i += taken;
             continue;
         }
         j = i;
-        while (j < count && j - i < 8 && smallm_w8_supports(items[j].d, M)) {
+        while (j < count && j - i < kGemmGroup && smallm_w8_supports(items[j].d, M)) {
             run[j - i] = as_gemm_item(items[j]);
             ++j;
         }
@@ -644,10 +655,8 @@ int qail_w8a16_linear_batch(const qail_w8a16_item* items, int32_t count, int32_t
             i = j;
             continue;
         }
-        while (j < count && j - i < 8 && w8_takes_gemm(items[j].d, M)) {
-            run[j - i] = as_gemm_item(items[j]);
-            ++j;
-        }
+        j = groups.end(i, count, [&](int e) { return w8_takes_gemm(items[e].d, M); });
+        for (int e = i; e < j; ++e) run[e - i] = as_gemm_item(items[e]);
         if (j > i) {
             if (launch_w4a16_gemm_f16_batch(run, j - i, M, wide_tiles, workspace, st) != hipSuccess) return QAIL_ERR_HIP;
             i = j;

@@ -84,6 +84,7 @@ int device_cu_count();
 // fp16-MFMA GEMM for M > 16; needs gemm_f16_workspace() bytes of 256-byte aligned device memory.
 bool gemm_f16_supports(const qail_wdesc& d, int M);
 size_t gemm_f16_workspace(const qail_wdesc& d, int M);
+constexpr int kGemmGroup = 8;   // linears that can share its launches
 // Several such linears (all supported, same M and code width) in shared launches, each on a share of the
 // blocks; needs gemm_f16_batch_workspace() bytes.  wide_tiles = false: 128-column tiles only, whose slots
 // take half the workspace.

@@ -56,7 +56,7 @@ typedef uint32_t u32x2_any_t __attribute__((ext_vector_type(2), aligned(2)));
 
 constexpr int kRowPad = 128;            // workspace rows are padded to this
 
-constexpr int kGemmBatch = 8;           // linears that can share one launch
+constexpr int kGemmBatch = kGemmGroup;  // linears that can share one launch
 
 // ---------------------------------------------------------------------------------------
 // Preparation, for up to kGemmBatch linears at once (blockIdx.y): blocks [0, rows) rewrite one

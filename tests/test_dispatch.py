@@ -1,0 +1,74 @@
+"""What a list of linears launches, asked of the built library on a machine without a GPU (tests/host_dispatch_driver.cpp):
+the workspace that every launch of the matrix-core GEMM lays out against the one that the call asked for."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+from .helpers import ensure_built
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not found")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """ask(lists) -> for each list (bits, M, [(N, K, group size), ...]): the workspace asked for and the launches, each as
+    (kernel, blocks, workspace of its items as a list of their own, items)."""
+    exe = str(tmp_path_factory.mktemp("dispatch") / "host_dispatch_driver")
+    r = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-host-only", "-Wno-unused-command-line-argument", "-rdynamic",
+                        "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host_dispatch_driver.cpp"), "-o", exe, "-ldl"],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-4000:]
+    lib = ensure_built().LIB_PATH
+
+    def ask(lists):
+        text = "\n".join("w%d %d %d " % (bits, M, len(shapes)) + " ".join("%d %d %d" % s for s in shapes) for bits, M, shapes in lists)
+        r = subprocess.run([exe, lib], input=text + "\n", stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-4000:]
+        out, lines = [], iter(r.stdout.splitlines())
+        for bits, M, shapes in lists:
+            word, status, need, n = next(lines).split()
+            assert word == "list" and status == "0", (bits, M, shapes, status)
+            launches = []
+            for _ in range(int(n)):
+                kernel, blocks, own, *items = next(lines).split()
+                launches.append((kernel, int(blocks), int(own), [int(i) for i in items]))
+            out.append((int(need), launches))
+        return out
+
+    return ask
+
+
+def mixed_lists():
+    """Lists in which several kernels take items: what one of them leaves is another's."""
+    lists = [(4, 48, [(256, 256, 128)] * 4 + [(4096, 10880, 128)] * 8),   # 85 groups of 128: the GEMM's alone
+             (8, 48, [(256, 256, 128)] * 3 + [(4096, 10880, 128)] * 6),
+             (4, 24, [(512, 512, 64)] * 2 + [(4096, 11008, 256)] * 9)]
+    rng = random.Random(5)
+    for _ in range(400):
+        bits = rng.choice((4, 4, 8))
+        shapes = []
+        while len(shapes) < rng.choice((3, 9, 12, 20, 40)):
+            g = rng.choice((64, 128, 128, 128, 256) if bits == 4 else (64, 128, 128, 256))
+            N, K = 16 * rng.randint(1, 400), g * rng.randint(1, 11008 // g)
+            shapes += [(N, K, g)] * rng.randint(1, 6)
+        lists.append((bits, rng.choice((5, 8, 16, 17, 24, 32, 33, 40, 48, 49, 64, 65, 130)), shapes))
+    return lists
+
+
+def test_gemm_launches_fit_the_workspace_asked_for(ask):
+    lists = mixed_lists()
+    gemm = beside = 0
+    for (bits, M, shapes), (need, launches) in zip(lists, ask(lists)):
+        for kernel, _, own, items in launches:
+            if kernel == "gemm_prep_kernel":
+                assert 1 <= len(items) <= 8
+                assert own <= need, (bits, M, shapes, items)
+                gemm += 1
+                beside += any(k.startswith("midm") for k, *_ in launches)
+    assert gemm > 300 and beside > 100   # the lists are of the kind meant

@@ -88,3 +88,22 @@ def test_rows_do_not_reach_each_other(B, bits, g, M):
     assert np.all(np.isnan(y[3]) | np.isinf(y[3])) and np.all(np.isnan(y[4])) and np.all(y[2] == 0)
     rest = [m for m in range(M) if m not in (2, 3, 4)]
     assert w4a16_norm_err(host(e["y"], np.uint16).reshape(M, N)[rest], ref[rest], nx[rest], nw) <= TOL
+
+
+@pytest.mark.parametrize("bits,shapes", [(4, [(256, 256, 128)] * 4 + [(520, 10880, 128)] * 8),
+                                         (8, [(256, 256, 128)] * 3 + [(520, 10880, 128)] * 6)])
+def test_lists_shared_with_the_matrix_core_gemm_stay_in_their_workspace(B, bits, shapes):
+    """This kernel takes the first linears, the GEMM (85 groups) the others: it writes nothing past the workspace asked for."""
+    import torch
+    M, past = 48, 16 << 20
+    made = [make(B, bits, N, K, g, M, 5000 + 10 * i) for i, (N, K, g) in enumerate(shapes)]
+    ents = [m[0] for m in made]
+    name = "w4a16" if bits == 4 else "w8a16"
+    items = getattr(B, f"make_{name}_items")(ents, M)
+    need = getattr(B, f"qail_{name}_batch_workspace")(items, len(ents), M)
+    ws = torch.full((need + past,), 0x5A, dtype=torch.uint8, device="cuda")
+    getattr(B, f"qail_{name}_linear_batch")(items, len(ents), M, ws[:need])
+    torch.cuda.synchronize()
+    assert bool((ws[need:] == 0x5A).all())
+    for e, ref, (nx, nw) in made:
+        assert w4a16_norm_err(host(e["y"], np.uint16).reshape(M, e["N"]), ref, nx, nw) <= (TOL if e["K"] >= 512 else TOL_TINY_K)
