@@ -11,14 +11,16 @@
 //     does not depend on timing.
 //   * Packed codes go from HBM straight into registers, D steps (of 128 k) ahead: a wave-wide
 //     load is 16 rows x 64 bytes, a lane's 16 bytes are the B operands of four
-//     v_mfma_f32_16x16x32_bf16 (0x4300 | q is bf16 128 + q).  A weight is expanded once and used
+//     v_mfma_f32_16x16x32_bf16 (0x3B80 | q is bf16 (128 + q) 2^-15).  A weight is expanded once and used
 //     by all row blocks of the wave.
 //   * x passes through the same registers, as far ahead (loads return in order: x fetched later
 //     than the codes beside it would drain their ring), into a double buffer of LDS, one 128-k
 //     step of every K part at a time, one barrier per step.  Its sums over each group, which the
 //     offset form needs,
 //         sum_k x (q - z) s = s * ( sum_k x (q + 128)  -  (128 + z) * sum_k x ),
-//     come from four MFMAs against ones on the way.  Nothing is rounded before the fp32 sums.
+//     come from four MFMAs against ones on the way.  Nothing is rounded before the fp32 sums.  Codes and ones carry a
+//     factor of 2^-15 (bytes: 2^-24), taken back at the end (with the scale): a group's 128 products of x with
+//     up to 255 stay finite for every finite x; without the factor an x beyond 2e36 (bytes: 1e34) gave NaN.
 //   * The block's scales and zero-points are copied to LDS once: as loads beside the codes they
 //     would cost as much as the codes.
 //
@@ -170,7 +172,7 @@ __device__ __forceinline__ void md_block(const MdArgs& args, const MdItem& it, u
         ++ix;
         if (++px == n_max) px = 0;
     };
-    uint32_t ones = kMode != kNib64 || (li & 1) == (kb >> 1) ? 0x3F803F80u : 0u;   // groups of 64: the sums of one in the even columns, of the other in the odd ones
+    uint32_t ones = kMode != kNib64 || (li & 1) == (kb >> 1) ? (kBytes ? 0x33803380u : 0x38003800u) : 0u;   // groups of 64: the sums of one in the even columns, of the other in the odd ones
     asm volatile("" : "+v"(ones));
     const u32x4_t ones4 = {ones, ones, ones, ones};
     auto put_x = [&](const u32x4_t (&v)[NL], int buf) {
@@ -252,7 +254,7 @@ __device__ __forceinline__ void md_block(const MdArgs& args, const MdItem& it, u
     for (int j = 0; j < 4; ++j)
         aoff[j] = (uint32_t)(kw * kRB * 4096 + li * 256 + ((pbase ^ li ^ kPiece[j]) << 4));
     const uint32_t soff = (uint32_t)(kw * kRB * (kGroups * 64) + kb * 16);
-    uint32_t magic = 0x43004300u;
+    uint32_t magic = 0x3B803B80u;
     asm volatile("" : "+v"(magic));
 
     f32x4_t acc[C][kRB];
@@ -263,13 +265,16 @@ __device__ __forceinline__ void md_block(const MdArgs& args, const MdItem& it, u
 
     int pc = rot;   // the step being multiplied
     auto expand = [&](uint32_t w0, uint32_t w1) {
-        if constexpr (kBytes) {   // eight signed bytes b = q + 128 -> bf16
+        if constexpr (kBytes) {   // eight signed bytes b = q + 128 -> bf16 b 2^-24: as the bits of an fp16 number, a byte is that subnormal
             const uint32_t w[2] = {w0 ^ 0x80808080u, w1 ^ 0x80808080u};
             u32x4_t o;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const uint32_t f0 = __builtin_bit_cast(uint32_t, (float)(w[h] & 0xFFu)), f1 = __builtin_bit_cast(uint32_t, (float)((w[h] >> 8) & 0xFFu));
-                const uint32_t f2 = __builtin_bit_cast(uint32_t, (float)((w[h] >> 16) & 0xFFu)), f3 = __builtin_bit_cast(uint32_t, (float)(w[h] >> 24));
+                uint32_t f0, f1, f2, f3;   // (the compiler takes a mask and a conversion for byte 2)
+                asm("v_cvt_f32_f16_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(f0) : "v"(w[h]));
+                asm("v_cvt_f32_f16_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1" : "=v"(f1) : "v"(w[h]));
+                asm("v_cvt_f32_f16_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(f2) : "v"(w[h]));
+                asm("v_cvt_f32_f16_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3" : "=v"(f3) : "v"(w[h]));
                 o[2 * h] = __builtin_amdgcn_perm(f1, f0, 0x07060302u);
                 o[2 * h + 1] = __builtin_amdgcn_perm(f3, f2, 0x07060302u);
             }
@@ -329,6 +334,7 @@ __device__ __forceinline__ void md_block(const MdArgs& args, const MdItem& it, u
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     float s = (float)*reinterpret_cast<const _Float16*>(stab + srow[c] + (uint32_t)g * 2u);
+                    if (kBytes) s *= 0x1p24f;
                     asm volatile("" : "+v"(s));   // widened once, not in every multiply-add
                     float zn = -128.f;
                     if constexpr (!kBytes) {
@@ -381,6 +387,7 @@ done:
         f32x4_t v = {0.f, 0.f, 0.f, 0.f};
         for (int p = 0; p < Wk; ++p) v += *reinterpret_cast<const f32x4_t*>(red + (((src + p) * cmax + c) * kRB + R) * 256 + lane * 4);
         const int n = (tile0 + t) * 16 + li;
+        if (!kBytes) v *= 0x1p15f;
         const uint32_t lo = f32x2_to_bf16x2_rne(v[0], v[1]), hi = f32x2_to_bf16x2_rne(v[2], v[3]);
         const uint16_t o[4] = {(uint16_t)lo, (uint16_t)(lo >> 16), (uint16_t)hi, (uint16_t)(hi >> 16)};
         if (n < N)

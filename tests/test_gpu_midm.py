@@ -107,3 +107,32 @@ def test_lists_shared_with_the_matrix_core_gemm_stay_in_their_workspace(B, bits,
     assert bool((ws[need:] == 0x5A).all())
     for e, ref, (nx, nw) in made:
         assert w4a16_norm_err(host(e["y"], np.uint16).reshape(M, e["N"]), ref, nx, nw) <= (TOL if e["K"] >= 512 else TOL_TINY_K)
+
+
+@pytest.mark.parametrize("bits,g,M", [(4, 64, 16), (4, 64, 40), (4, 128, 40), (8, 128, 40), (8, 128, 50)])
+def test_rows_of_any_size(B, bits, g, M):
+    """Rows of x from 2^-110 to just below the largest bf16 number: no sum on the way overflows or falls out of fp32's range."""
+    import torch
+    N, K = 300, 1024
+    # 2^-10: the weights (their scales are fp16 numbers below 2^-14, exact in the oracle), so that results are representable
+    w = synth.llm_weight(N, K, 6000) * np.float32(2.0 ** -10)
+    rng = np.random.default_rng(6001)
+    x = rng.uniform(0.5, 1.99, size=(M, K)) * np.where(rng.random((M, K)) < 0.05, -1.0, 1.0)   # mostly of one sign: the offset's sums grow with K
+    x *= 2.0 ** np.linspace(-110, 127, M).round()[:, None]
+    xb = synth.f32_to_bf16_bits(x.astype(np.float32))
+    assert np.isfinite(O.bf16_bits_to_f64(xb)).all()
+    e = dict(N=N, K=K, group_size=g, x=dev(xb), y=torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda"))
+    nx = np.sqrt((O.bf16_bits_to_f64(xb) ** 2).sum(axis=1))
+    if bits == 4:
+        q, s, z = O.quantize_w4_asym_group(w, g)
+        qw, zw = O.pack_w4a16(q, z)
+        e.update(qweight=dev(qw), scales=dev(s.view(np.uint16)), zeros=dev(zw))
+        ref, (_, nw) = O.w4a16_linear(xb, qw, s, zw, g), O.w4a16_row_norms(xb, qw, s, zw, g)
+    else:
+        q, s = O.quantize_w8_sym_group(w, g)
+        e.update(qweight=dev(O.pack_bytes(q)), scales=dev(s.view(np.uint16)))
+        ref = O.w8a16_linear(xb, q, s, g)
+        nw = np.sqrt(((q.astype(np.float64) * np.repeat(s.astype(np.float64), g, axis=1)) ** 2).sum(axis=1))
+    run(B, bits, [e], M)
+    y = host(e["y"], np.uint16).reshape(M, N)
+    assert w4a16_norm_err(y, ref, nx, nw) <= TOL
