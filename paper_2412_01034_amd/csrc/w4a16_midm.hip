@@ -493,7 +493,9 @@ const void* md_kernel(int rb) {
 int md_mode(const qail_wdesc& d, bool b8) { return b8 ? kByte128 : d.group_size == 64 ? kNib64 : kNib128; }
 
 // The division of a launch: tiles per block of each item.  Starting from one, the block that would still be the shortest
-// with another tile gets it, until one block per CU is enough (or no block can grow: more rounds then).
+// with another tile gets it, until one block per CU is enough.  Lists that do not get there (a block has at most four column
+// tiles a wave) are left to the other kernels: a second round of blocks, mostly a nearly empty one, costs as much as the first
+// (152064 x 3584 in groups of 64 at M = 8 94 us there, 130 in two rounds; bytes at M = 32 155 against 191).
 struct MdDivision {
     MdShape s;
     MdPlan plan[kMdMaxItems];
@@ -504,15 +506,14 @@ struct MdDivision {
 bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, MdDivision* v) {
     v->s.mode = md_mode(items[0].d, b8);
     v->s.rb = (M + 15) / 16;   // at most 4
-    const int cus = device_cu_count();
+    const int cus = std::min(device_cu_count(), kMdMaxBlocks);
     int nt[kMdMaxItems], used = 0;
     MdPlan next[kMdMaxItems];
     for (int i = 0; i < count; ++i) {
         v->tiles[i] = (items[i].d.N + 15) / 16;
         // (fewer tiles than this a block need not try: one block per CU could not serve the item alone)
-        nt[i] = std::max(1, v->tiles[i] / cus);
+        nt[i] = std::max(1, (v->tiles[i] + cus - 1) / cus);
         v->plan[i] = md_plan(v->s, items[i].d.K, nt[i]);
-        while (v->plan[i].us < 0.f && nt[i] > 1) v->plan[i] = md_plan(v->s, items[i].d.K, --nt[i]);
         if (v->plan[i].us < 0.f) return false;
         next[i] = md_plan(v->s, items[i].d.K, nt[i] + 1);
         used += (v->tiles[i] + nt[i] - 1) / nt[i];
@@ -521,7 +522,7 @@ bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, MdDivisi
         int best = -1;
         for (int i = 0; i < count; ++i)
             if (next[i].us >= 0.f && nt[i] < v->tiles[i] && (best < 0 || next[i].us < next[best].us)) best = i;
-        if (best < 0) break;
+        if (best < 0) return false;
         used -= (v->tiles[best] + nt[best] - 1) / nt[best];
         v->plan[best] = next[best];
         ++nt[best];
@@ -536,7 +537,6 @@ bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, MdDivisi
         if (most != nt[i]) v->plan[i] = md_plan(v->s, items[i].d.K, most);
         v->us = std::max(v->us, v->plan[i].us);
     }
-    v->us *= (float)((used + cus - 1) / cus);
     return true;
 }
 
@@ -615,9 +615,6 @@ hipError_t launch_midm_if_better(const qail_w4a16_item* items, int count, int M,
     while (n < count && n < kMdMaxItems && items[n].d.group_size == items[0].d.group_size && md_supports(items[n].d, M, b8)) ++n;
     MdDivision v;
     if (n == 0 || !md_divide(items, n, M, b8, &v) || !md_better(items, n, M, v)) return hipSuccess;
-    int blocks = 0;
-    for (int i = 0; i < n; ++i) blocks += v.blocks[i];
-    if (n > 1 && blocks > kMdMaxBlocks) return hipSuccess;   // the block-to-item table is too short
     *taken = n;
     return md_launch(items, n, M, v, st);
 }

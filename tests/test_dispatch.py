@@ -1,5 +1,6 @@
 """What a list of linears launches, asked of the built library on a machine without a GPU (tests/host_dispatch_driver.cpp):
-the workspace that every launch of the matrix-core GEMM lays out against the one that the call asked for."""
+the workspace that every launch of the matrix-core GEMM lays out against the one that the call asked for, and which
+kernels serve which lists."""
 import os
 import random
 import shutil
@@ -72,3 +73,13 @@ def test_gemm_launches_fit_the_workspace_asked_for(ask):
                 gemm += 1
                 beside += any(k.startswith("midm") for k, *_ in launches)
     assert gemm > 300 and beside > 100   # the lists are of the kind meant
+
+
+@pytest.mark.parametrize("bits,g,shapes", [(4, 64, [(152064, 3584)]), (4, 128, [(152064, 3584)]), (8, 128, [(152064, 3584)]), (8, 128, [(128256, 4096)]),
+                                           (4, 64, [(140000, 512)]), (4, 64, [(22016, 4096), (4096, 11008)] * 8), (4, 128, [(1 << 21, 1024)])])
+def test_medium_batch_kernel_has_one_block_per_unit_at_most(ask, bits, g, shapes):
+    """Lists that its blocks (256 compute units) cannot serve in one round are other kernels': a second round costs as much as the first."""
+    lists = [(bits, M, [(N, K, g) for N, K in shapes]) for M in (5, 8, 16, 17, 32, 33, 48, 64)]
+    for (_, M, _), (_, launches) in zip(lists, ask(lists)):
+        for kernel, blocks, _, _ in launches:
+            assert not kernel.startswith("midm") or blocks <= 256, (M, kernel, blocks)
