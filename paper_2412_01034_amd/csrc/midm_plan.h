@@ -1,0 +1,188 @@
+// Division of labour of the medium-batch kernel (w4a16_midm.hip): which lists of linears it takes, how many tiles a block
+// owns and how its waves share them.  Apart from the kernel, so that the host can walk through it.
+#ifndef QAIL_MIDM_PLAN_H
+#define QAIL_MIDM_PLAN_H
+
+#include <algorithm>
+
+#include "qail_internal.h"
+
+namespace qail {
+
+constexpr int kMdWaves = 8;
+constexpr int kMdStepK = 128;
+constexpr int kMdMaxItems = 16;
+constexpr int kMdMaxBlocks = 2048;   // blocks of a launch
+constexpr size_t kMdLds = 160 * 1024;
+
+enum MdMode { kNib128 = 0, kNib64 = 1, kByte128 = 2 };
+
+struct MdItem {
+    const uint32_t* qw;
+    const uint16_t* sc;
+    const uint32_t* zr;
+    const uint16_t* x;
+    uint16_t* y;
+    int N, K;
+    int block_begin;             // first block of the grid that works on this item
+    int tiles_base, tiles_rem;   // block b of the item owns tiles_base tiles, one more if b < tiles_rem
+    uint8_t wkl;                 // log2 of the K parts
+    uint8_t tiles_per_wave;      // column tiles of the wave that has most
+    uint16_t table;              // LDS offset of the scales, in 64-byte units
+};
+
+struct MdArgs {
+    MdItem it[kMdMaxItems];
+    uint32_t item_of_block[kMdMaxBlocks / 8];   // 4 bits per block
+    int M;
+};
+
+// Column tiles of wave `wave` in a block of nt tiles: one more in the first waves where they do not come out even.
+__host__ __device__ inline int md_wave_tiles(int nt, int wkl, int wave) {
+    const int wc = kMdWaves >> wkl;
+    return (nt - (wave >> wkl) + wc - 1) >> (3 - wkl);
+}
+
+// Loads of x per wave and step: four per K part and row block, dealt to eight waves; p = log2 of the K parts.
+constexpr int md_loads(int rb, int p) { return ((rb << p) + 1) / 2; }
+
+// Steps fetched ahead, by what they cost in registers: each is C (bytes: 2 C) loads of codes and NL of x.
+constexpr int md_depth(int mode, int rb, int c, int nl) {
+    const int per_step = (c * (mode == kByte128 ? 2 : 1) + nl) * 4;
+    const int room = 256 - 80 - 8 * c * rb - 8 * rb - (mode == kNib64 ? 4 * c + 28 : 0);   // beside the sums, the operands and the addresses
+    return room / per_step >= 6 ? 6 : room / per_step < 2 ? 2 : room / per_step;
+}
+// What fits the registers.
+constexpr bool md_variant(int mode, int rb, int c, int nl) { return c <= 4 && c * rb <= (mode == kNib64 ? 9 : 12) && nl <= 8 && (nl <= 4 || c <= 2); }
+
+// How an item is divided when its blocks own up to nt tiles.
+struct MdPlan {
+    float us;      // what such a block takes
+    int wkl, c;
+    size_t lds, table;
+};
+
+struct MdShape {
+    int mode, rb;   // 16-row blocks of x
+};
+
+// The time of a block, fitted to 120 (shape, M) pairs: the launch with its start and end, and per step a barrier, the x that a
+// wave stages and the tiles of the two waves of a SIMD.  A block that streams its codes at its share of the memory's rate
+// (20 KB a microsecond) takes no less.
+inline MdPlan md_plan(const MdShape& s, int K, int nt) {
+    MdPlan best;
+    best.us = -1.f;
+    const int S = K / kMdStepK, groups = s.mode == kNib64 ? 2 : 1, G = S * groups;
+    const bool bytes = s.mode == kByte128;
+    const size_t tables = (size_t)nt * 16 * (G * 2 + (bytes ? 0 : (G + 7) / 8 * 4));
+    const float stream = (float)nt * 16.f * (float)K * (bytes ? 1.f : 0.5f) / 20000.f;
+    for (int wkl = 0; (1 << wkl) <= S && wkl <= 3; ++wkl) {
+        const int wc = kMdWaves >> wkl, c = (nt + wc - 1) / wc, nl = md_loads(s.rb, wkl);
+        if (!md_variant(s.mode, s.rb, c, nl)) continue;
+        const size_t table = (((size_t)s.rb << wkl) * (2 * 4096 + 2 * groups * 64) + 63) / 64 * 64;
+        const size_t lds = std::max(table + tables, (size_t)kMdWaves * c * s.rb * 1024);
+        if (lds > kMdLds) continue;
+        const float tiles = c + (float)nt / wc;   // of the wave that has most and of an average one: a SIMD has two waves
+        const float step = 0.5f + 0.03f * s.rb * nl + 0.065f * s.rb * tiles * (groups == 2 ? 1.5f : 1.f);
+        const float us = 6.5f + std::max((float)((S + (1 << wkl) - 1) >> wkl) * step, stream);
+        if (best.us < 0.f || us < best.us) {
+            best.us = us;
+            best.wkl = wkl;
+            best.c = c;
+            best.lds = lds;
+            best.table = table;
+        }
+    }
+    return best;
+}
+
+inline int md_mode(const qail_wdesc& d, bool b8) { return b8 ? kByte128 : d.group_size == 64 ? kNib64 : kNib128; }
+
+// The division of a launch: tiles per block of each item.  Starting from one, the block that would still be the shortest
+// with another tile gets it, until one block per CU is enough.  Lists that do not get there (a block has at most four column
+// tiles a wave) are left to the other kernels: a second round of blocks, mostly a nearly empty one, costs as much as the first
+// (152064 x 3584 in groups of 64 at M = 8 94 us there, 130 in two rounds; bytes at M = 32 155 against 191).
+struct MdDivision {
+    MdShape s;
+    MdPlan plan[kMdMaxItems];
+    int tiles[kMdMaxItems], blocks[kMdMaxItems];
+    float us;
+};
+
+inline bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, MdDivision* v) {
+    v->s.mode = md_mode(items[0].d, b8);
+    v->s.rb = (M + 15) / 16;   // at most 4
+    const int cus = std::min(device_cu_count(), kMdMaxBlocks);
+    int nt[kMdMaxItems], used = 0;
+    MdPlan next[kMdMaxItems];
+    for (int i = 0; i < count; ++i) {
+        v->tiles[i] = (items[i].d.N + 15) / 16;
+        // (fewer tiles than this a block need not try: one block per CU could not serve the item alone)
+        nt[i] = std::max(1, (v->tiles[i] + cus - 1) / cus);
+        v->plan[i] = md_plan(v->s, items[i].d.K, nt[i]);
+        if (v->plan[i].us < 0.f) return false;
+        next[i] = md_plan(v->s, items[i].d.K, nt[i] + 1);
+        used += (v->tiles[i] + nt[i] - 1) / nt[i];
+    }
+    while (used > cus) {
+        int best = -1;
+        for (int i = 0; i < count; ++i)
+            if (next[i].us >= 0.f && nt[i] < v->tiles[i] && (best < 0 || next[i].us < next[best].us)) best = i;
+        if (best < 0) return false;
+        used -= (v->tiles[best] + nt[best] - 1) / nt[best];
+        v->plan[best] = next[best];
+        ++nt[best];
+        used += (v->tiles[best] + nt[best] - 1) / nt[best];
+        next[best] = md_plan(v->s, items[best].d.K, nt[best] + 1);
+    }
+    v->us = 0.f;
+    for (int i = 0; i < count; ++i) {
+        v->blocks[i] = (v->tiles[i] + nt[i] - 1) / nt[i];
+        // the tiles as the blocks share them evenly
+        const int most = (v->tiles[i] + v->blocks[i] - 1) / v->blocks[i];
+        if (most != nt[i]) v->plan[i] = md_plan(v->s, items[i].d.K, most);
+        v->us = std::max(v->us, v->plan[i].us);
+    }
+    return true;
+}
+
+// Whether the division beats the kernels that took these items before, by what was measured of both (layers of several
+// widths in one call and single linears of 500 to 24000 rows and 1024 to 11008 k, M = 5 .. 64):
+//   * groups of 128 and bytes up to M = 32: the small-batch kernel loses where its x takes several passes over K, so the
+//     passes of an item, weighted by its bytes, decide.  Nibbles up to M = 16 from two passes on (4096 x 11008 at M = 16
+//     19.4 -> 16.0 us; one pass, 4096 x 4096: 9.0 against 9.5), above from 1.3 (M = 24, the 7B layer 43.7 -> 37.6; one pass,
+//     2048 x 2048: 8.0 against 9.3), bytes from 1.2 (the layer at M = 8 / 32 51.9 -> 44.6 / 63.0 -> 51.4; one pass,
+//     4096 x 4096 at M = 8: 9.4 against 10.2);
+//   * otherwise the matrix-core GEMM, which takes 13.5 us, 1.3 per further item and a microsecond per 3 MB, measured on the
+//     low side: M = 48 the layer 56.0 -> 44.2, with bytes 71.8 -> 56.9; one 4096 x 11008, whose K the GEMM divides among
+//     blocks, 22.9 against 33.7.  Groups of 64 stay below 49 rows (the layer at M = 32 / 48 53.9 -> 44.1 / 61.8 -> 59.1,
+//     at M = 64 62.8 against 66.6) and need no comparison up to 16 (52.9 -> 41.5; 4096 x 4096 14.9 -> 9.9).
+inline bool md_better(const qail_w4a16_item* items, int count, int M, const MdDivision& v) {
+    if (v.s.mode == kNib64 && (M <= 16 || M > 48)) return M <= 16;
+    double bytes = 0, passes = 0;
+    for (int i = 0; i < count; ++i) {
+        const double b = (double)items[i].d.N * items[i].d.K * (v.s.mode == kByte128 ? 1.0 : 0.5);
+        bytes += b;
+        if (M <= 32 && v.s.mode != kNib64) passes += b * smallm_passes(M, items[i].d.K);
+    }
+    if (M <= 32 && v.s.mode != kNib64) return passes >= bytes * (v.s.mode == kByte128 ? 1.2 : M <= 16 ? 2.0 : 1.3);
+    const double more = v.s.mode == kByte128 ? 0.0 : std::max(0.0, bytes - 60.0e6) / 9.0e6;   // nibbles: a larger share of it expansion
+    return v.us <= 13.5 + 1.3 * (count - 1) + bytes / 3.0e6 + more;
+}
+
+inline bool md_supports(const qail_wdesc& d, int M, bool b8) {
+    if (M < 5 || M > 64 || d.K % kMdStepK != 0 || (d.group_size != 128 && (b8 || d.group_size != 64))) return false;
+    if ((d.K / d.group_size) % 2 != 0) return false;   // the scales of a row are whole words
+    return (unsigned long long)d.N * d.K / (b8 ? 1 : 2) <= 0x7FFFFFFFull && (unsigned long long)M * d.K * 2 <= 0x7FFFFFFFull;
+}
+
+// How many of the leading items of the list the kernel takes (0: none), and their division.
+inline int md_take(const qail_w4a16_item* items, int count, int M, bool b8, MdDivision* v) {
+    int n = 0;   // items of one group size share a launch
+    while (n < count && n < kMdMaxItems && items[n].d.group_size == items[0].d.group_size && md_supports(items[n].d, M, b8)) ++n;
+    return n > 0 && md_divide(items, n, M, b8, v) && md_better(items, n, M, *v) ? n : 0;
+}
+
+}  // namespace qail
+
+#endif
