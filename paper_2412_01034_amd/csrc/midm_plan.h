@@ -147,16 +147,18 @@ inline bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, M
 }
 
 // Whether the division beats the kernels that took these items before, by what was measured of both (layers of several
-// widths in one call and single linears of 500 to 24000 rows and 1024 to 11008 k, M = 5 .. 64):
+// widths in one call and single linears of 500 to 65000 rows and 256 to 28672 k, M = 5 .. 64; us, new buffers from call to call):
 //   * groups of 128 and bytes up to M = 32: the small-batch kernel loses where its x takes several passes over K, so the
 //     passes of an item, weighted by its bytes, decide.  Nibbles up to M = 16 from two passes on (4096 x 11008 at M = 16
-//     19.4 -> 16.0 us; one pass, 4096 x 4096: 9.0 against 9.5), above from 1.3 (M = 24, the 7B layer 43.7 -> 37.6; one pass,
-//     2048 x 2048: 8.0 against 9.3), bytes from 1.2 (the layer at M = 8 / 32 51.9 -> 44.6 / 63.0 -> 51.4; one pass,
-//     4096 x 4096 at M = 8: 9.4 against 10.2);
-//   * otherwise the matrix-core GEMM, which takes 13.5 us, 1.3 per further item and a microsecond per 3 MB, measured on the
-//     low side: M = 48 the layer 56.0 -> 44.2, with bytes 71.8 -> 56.9; one 4096 x 11008, whose K the GEMM divides among
-//     blocks, 22.9 against 33.7.  Groups of 64 stay below 49 rows (the layer at M = 32 / 48 53.9 -> 44.1 / 61.8 -> 59.1,
-//     at M = 64 62.8 against 66.6) and need no comparison up to 16 (52.9 -> 41.5; 4096 x 4096 14.9 -> 9.9).
+//     20.9 -> 17.5; one pass, 4096 x 4096: 8.7 against 9.5), as long as there are 200 MB or less for each pass that is saved: over the
+//     rest of the stream that kernel is 2 to 3 % faster (428 MB and 2.6 passes at M = 8 105 against 111; 3.4 passes at M = 16
+//     116 -> 111).  Above M = 16 from 1.3 (M = 24, the 7B layer 42.8 -> 37.8; one pass, 2048 x 2048: a fifth slower), bytes from
+//     1.2 (the layer at M = 8 / 32 53.0 -> 44.3 / 64.0 -> 49.3; one pass, 4096 x 4096 at M = 8: a tenth slower);
+//   * otherwise the matrix-core GEMM, which takes 13.5 us, 1.3 per further item and a microsecond per 3 MB (bytes: 3.3; at 3.0
+//     8192 x 28672 at M = 48 went from 80 to 83), measured on the low side: M = 48 the layer 56.2 -> 45.2, with bytes 73.9 -> 54.5;
+//     one 4096 x 11008, whose K the GEMM divides among blocks, 23.3 against 31.6.  Groups of 64 stay below 49 rows (the layer
+//     at M = 32 / 48 54.7 -> 46.7 / 62.6 -> 56.9, at M = 64 63.1 against 66.2) and need no comparison up to 16
+//     (54.5 -> 40.8; 4096 x 4096 14.5 -> 9.6).
 inline bool md_better(const qail_w4a16_item* items, int count, int M, const MdDivision& v) {
     if (v.s.mode == kNib64 && (M <= 16 || M > 48)) return M <= 16;
     double bytes = 0, passes = 0;
@@ -165,9 +167,12 @@ inline bool md_better(const qail_w4a16_item* items, int count, int M, const MdDi
         bytes += b;
         if (M <= 32 && v.s.mode != kNib64) passes += b * smallm_passes(M, items[i].d.K);
     }
-    if (M <= 32 && v.s.mode != kNib64) return passes >= bytes * (v.s.mode == kByte128 ? 1.2 : M <= 16 ? 2.0 : 1.3);
+    if (M <= 32 && v.s.mode != kNib64) {
+        if (v.s.mode == kNib128 && M <= 16) return passes >= 2.0 * bytes && (passes / bytes - 1.0) * 2.0e8 >= bytes;
+        return passes >= bytes * (v.s.mode == kByte128 ? 1.2 : 1.3);
+    }
     const double more = v.s.mode == kByte128 ? 0.0 : std::max(0.0, bytes - 60.0e6) / 9.0e6;   // nibbles: a larger share of it expansion
-    return v.us <= 13.5 + 1.3 * (count - 1) + bytes / 3.0e6 + more;
+    return v.us <= 13.5 + 1.3 * (count - 1) + bytes / (v.s.mode == kByte128 ? 3.3e6 : 3.0e6) + more;
 }
 
 inline bool md_supports(const qail_wdesc& d, int M, bool b8) {

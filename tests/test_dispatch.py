@@ -83,3 +83,17 @@ def test_medium_batch_kernel_has_one_block_per_unit_at_most(ask, bits, g, shapes
     for (_, M, _), (_, launches) in zip(lists, ask(lists)):
         for kernel, blocks, _, _ in launches:
             assert not kernel.startswith("midm") or blocks <= 256, (M, kernel, blocks)
+
+
+WIDE = [(10240, 8192), (8192, 8192), (57344, 8192), (8192, 28672)]   # 428 MB of nibbles
+
+
+@pytest.mark.parametrize("bits,M,shapes,medium", [
+    (4, 8, WIDE, False), (4, 10, WIDE, False), (4, 16, WIDE, True),       # saved passes against a slower stream
+    (4, 7, [(4096, 4096)], False), (4, 16, [(4096, 11008)], True),
+    (8, 48, [(8192, 28672)], False), (8, 48, [(22016, 4096)], True),      # against the matrix-core GEMM
+    (4, 48, [(12288, 4096), (4096, 4096), (22016, 4096), (4096, 11008)], True), (4, 48, [(4096, 11008)], False),
+])
+def test_medium_batch_kernel_is_taken_where_it_was_faster(ask, bits, M, shapes, medium):
+    [(_, launches)] = ask([(bits, M, [(N, K, 128) for N, K in shapes])])
+    assert [k.startswith("midm") for k, *_ in launches] == ([True] if medium else [False] * len(launches)), launches
