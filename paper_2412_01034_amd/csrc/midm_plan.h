@@ -53,6 +53,7 @@ constexpr int md_depth(int mode, int rb, int c, int nl) {
     return room / per_step >= 6 ? 6 : room / per_step < 2 ? 2 : room / per_step;
 }
 // What fits the registers.
+constexpr int kMdMostTiles = 4 * kMdWaves;   // of a block, times its K parts
 constexpr bool md_variant(int mode, int rb, int c, int nl) { return c <= 4 && c * rb <= (mode == kNib64 ? 9 : 12) && nl <= 8 && (nl <= 4 || c <= 2); }
 
 // How an item is divided when its blocks own up to nt tiles.
@@ -75,23 +76,18 @@ inline MdPlan md_plan(const MdShape& s, int K, int nt) {
     const int S = K / kMdStepK, groups = s.mode == kNib64 ? 2 : 1, G = S * groups;
     const bool bytes = s.mode == kByte128;
     const size_t tables = (size_t)nt * 16 * (G * 2 + (bytes ? 0 : (G + 7) / 8 * 4));
-    const float stream = (float)nt * 16.f * (float)K * (bytes ? 1.f : 0.5f) / 20000.f;
-    for (int wkl = 0; (1 << wkl) <= S && wkl <= 3; ++wkl) {
-        const int wc = kMdWaves >> wkl, c = (nt + wc - 1) / wc, nl = md_loads(s.rb, wkl);
+    const float stream = (float)nt * (float)K * (bytes ? 16.f / 20000.f : 8.f / 20000.f);
+    // (more K parts have more column tiles a wave: past kMdMostTiles there is no variant)
+    for (int wkl = 0; wkl <= 3 && (1 << wkl) <= S && nt << wkl <= kMdMostTiles; ++wkl) {
+        const int c = ((nt << wkl) + kMdWaves - 1) / kMdWaves, nl = md_loads(s.rb, wkl);
         if (!md_variant(s.mode, s.rb, c, nl)) continue;
         const size_t table = (((size_t)s.rb << wkl) * (2 * 4096 + 2 * groups * 64) + 63) / 64 * 64;
         const size_t lds = std::max(table + tables, (size_t)kMdWaves * c * s.rb * 1024);
         if (lds > kMdLds) continue;
-        const float tiles = c + (float)nt / wc;   // of the wave that has most and of an average one: a SIMD has two waves
-        const float step = 0.5f + 0.03f * s.rb * nl + 0.065f * s.rb * tiles * (groups == 2 ? 1.5f : 1.f);
+        const float tiles = (float)c + (float)(nt << wkl) * (1.f / kMdWaves);   // of the wave that has most and of an average one: a SIMD has two waves
+        const float step = 0.5f + 0.03f * (float)(s.rb * nl) + 0.065f * (float)s.rb * tiles * (groups == 2 ? 1.5f : 1.f);
         const float us = 6.5f + std::max((float)((S + (1 << wkl) - 1) >> wkl) * step, stream);
-        if (best.us < 0.f || us < best.us) {
-            best.us = us;
-            best.wkl = wkl;
-            best.c = c;
-            best.lds = lds;
-            best.table = table;
-        }
+        if (best.us < 0.f || us < best.us) best = MdPlan{us, wkl, c, lds, table};
     }
     return best;
 }
@@ -146,7 +142,9 @@ inline bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, M
     return true;
 }
 
-// Whether the division beats the kernels that took these items before, by what was measured of both (layers of several
+inline double md_bytes(const qail_wdesc& d, int mode) { return (double)d.N * d.K * (mode == kByte128 ? 1.0 : 0.5); }
+
+// Whether the kernel beats those that took these items before, by what was measured of both (layers of several
 // widths in one call and single linears of 500 to 65000 rows and 256 to 28672 k, M = 5 .. 64; us, new buffers from call to call):
 //   * groups of 128 and bytes up to M = 32: the small-batch kernel loses where its x takes several passes over K, so the
 //     passes of an item, weighted by its bytes, decide.  Nibbles up to M = 16 from two passes on (4096 x 11008 at M = 16
@@ -159,20 +157,19 @@ inline bool md_divide(const qail_w4a16_item* items, int count, int M, bool b8, M
 //     one 4096 x 11008, whose K the GEMM divides among blocks, 23.3 against 31.6.  Groups of 64 stay below 49 rows (the layer
 //     at M = 32 / 48 54.7 -> 46.7 / 62.6 -> 56.9, at M = 64 63.1 against 66.2) and need no comparison up to 16
 //     (54.5 -> 40.8; 4096 x 4096 14.5 -> 9.6).
-inline bool md_better(const qail_w4a16_item* items, int count, int M, const MdDivision& v) {
-    if (v.s.mode == kNib64 && (M <= 16 || M > 48)) return M <= 16;
-    double bytes = 0, passes = 0;
-    for (int i = 0; i < count; ++i) {
-        const double b = (double)items[i].d.N * items[i].d.K * (v.s.mode == kByte128 ? 1.0 : 0.5);
-        bytes += b;
-        if (M <= 32 && v.s.mode != kNib64) passes += b * smallm_passes(M, items[i].d.K);
-    }
-    if (M <= 32 && v.s.mode != kNib64) {
-        if (v.s.mode == kNib128 && M <= 16) return passes >= 2.0 * bytes && (passes / bytes - 1.0) * 2.0e8 >= bytes;
-        return passes >= bytes * (v.s.mode == kByte128 ? 1.2 : 1.3);
-    }
-    const double more = v.s.mode == kByte128 ? 0.0 : std::max(0.0, bytes - 60.0e6) / 9.0e6;   // nibbles: a larger share of it expansion
-    return v.us <= 13.5 + 1.3 * (count - 1) + bytes / (v.s.mode == kByte128 ? 3.3e6 : 3.0e6) + more;
+enum class MdAnswer { no, yes, by_time };
+inline MdAnswer md_wanted(const qail_w4a16_item* items, int count, int M, int mode, double bytes) {   // what needs no division
+    if (mode == kNib64) return M <= 16 ? MdAnswer::yes : M > 48 ? MdAnswer::no : MdAnswer::by_time;
+    if (M > 32) return MdAnswer::by_time;
+    double passes = 0;
+    for (int i = 0; i < count; ++i) passes += md_bytes(items[i].d, mode) * smallm_passes(M, items[i].d.K);
+    passes /= bytes;
+    const bool better = mode == kByte128 ? passes >= 1.2 : M > 16 ? passes >= 1.3 : passes >= 2.0 && (passes - 1.0) * 2.0e8 >= bytes;
+    return better ? MdAnswer::yes : MdAnswer::no;
+}
+inline bool md_beats_gemm(float us, int count, int mode, double bytes) {
+    const double more = mode == kByte128 ? 0.0 : std::max(0.0, bytes - 60.0e6) / 9.0e6;   // nibbles: a larger share of it expansion
+    return us <= 13.5 + 1.3 * (count - 1) + bytes / (mode == kByte128 ? 3.3e6 : 3.0e6) + more;
 }
 
 inline bool md_supports(const qail_wdesc& d, int M, bool b8) {
@@ -185,7 +182,13 @@ inline bool md_supports(const qail_wdesc& d, int M, bool b8) {
 inline int md_take(const qail_w4a16_item* items, int count, int M, bool b8, MdDivision* v) {
     int n = 0;   // items of one group size share a launch
     while (n < count && n < kMdMaxItems && items[n].d.group_size == items[0].d.group_size && md_supports(items[n].d, M, b8)) ++n;
-    return n > 0 && md_divide(items, n, M, b8, v) && md_better(items, n, M, *v) ? n : 0;
+    if (n == 0) return 0;
+    const int mode = md_mode(items[0].d, b8);
+    double bytes = 0;
+    for (int i = 0; i < n; ++i) bytes += md_bytes(items[i].d, mode);
+    const MdAnswer answer = md_wanted(items, n, M, mode, bytes);   // (before the division: the search for one takes microseconds)
+    if (answer == MdAnswer::no || !md_divide(items, n, M, b8, v)) return 0;
+    return answer == MdAnswer::yes || md_beats_gemm(v->us, n, mode, bytes) ? n : 0;
 }
 
 }  // namespace qail
