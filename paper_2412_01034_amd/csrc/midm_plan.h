@@ -46,15 +46,24 @@ __host__ __device__ inline int md_wave_tiles(int nt, int wkl, int wave) {
 // Loads of x per wave and step: four per K part and row block, dealt to eight waves; p = log2 of the K parts.
 constexpr int md_loads(int rb, int p) { return ((rb << p) + 1) / 2; }
 
-// Steps fetched ahead, by what they cost in registers: each is C (bytes: 2 C) loads of codes and NL of x.
+// Steps fetched ahead, by what they cost in registers: each is C (bytes: 2 C) loads of codes and NL of x.  Three variants
+// have a step less than that leaves room for: with it the compiler spilled four to eight registers, inside the loop (4096 x 11008
+// at M = 32 24.6 -> 22.0 us without, 12288 x 4096 of bytes at M = 56 25.4 -> 22.1).
 constexpr int md_depth(int mode, int rb, int c, int nl) {
     const int per_step = (c * (mode == kByte128 ? 2 : 1) + nl) * 4;
     const int room = 256 - 80 - 8 * c * rb - 8 * rb - (mode == kNib64 ? 4 * c + 28 : 0);   // beside the sums, the operands and the addresses
-    return room / per_step >= 6 ? 6 : room / per_step < 2 ? 2 : room / per_step;
+    const bool less = (mode == kNib128 && ((rb == 2 && c == 1 && nl == 8) || (rb == 4 && c == 1 && nl == 8))) ||
+                      (mode == kByte128 && rb == 4 && c == 2 && nl == 8);
+    return (room / per_step >= 6 ? 6 : room / per_step < 2 ? 2 : room / per_step) - (less ? 1 : 0);
 }
-// What fits the registers.
 constexpr int kMdMostTiles = 4 * kMdWaves;   // of a block, times its K parts
-constexpr bool md_variant(int mode, int rb, int c, int nl) { return c <= 4 && c * rb <= (mode == kNib64 ? 9 : 12) && nl <= 8 && (nl <= 4 || c <= 2); }
+// The variants there are: what fits the registers, of that what some list makes use of.  Groups of 64 are the GEMM's above
+// M = 48.  Many tiles of bytes and few rows of x wait for HBM with one K part as with several.
+constexpr bool md_variant(int mode, int rb, int c, int p) {
+    const int nl = md_loads(rb, p);
+    return c <= 4 && c * rb <= (mode == kNib64 ? 9 : 12) && nl <= 8 && (nl <= 4 || c <= 2) && (mode != kNib64 || rb <= 3) &&
+           (mode != kByte128 || p == 0 || c <= rb + 1);
+}
 
 // How an item is divided when its blocks own up to nt tiles.
 struct MdPlan {
@@ -80,7 +89,7 @@ inline MdPlan md_plan(const MdShape& s, int K, int nt) {
     // (more K parts have more column tiles a wave: past kMdMostTiles there is no variant)
     for (int wkl = 0; wkl <= 3 && (1 << wkl) <= S && nt << wkl <= kMdMostTiles; ++wkl) {
         const int c = ((nt << wkl) + kMdWaves - 1) / kMdWaves, nl = md_loads(s.rb, wkl);
-        if (!md_variant(s.mode, s.rb, c, nl)) continue;
+        if (!md_variant(s.mode, s.rb, c, wkl)) continue;
         const size_t table = (((size_t)s.rb << wkl) * (2 * 4096 + 2 * groups * 64) + 63) / 64 * 64;
         const size_t lds = std::max(table + tables, (size_t)kMdWaves * c * s.rb * 1024);
         if (lds > kMdLds) continue;

@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kMdThreads, 2) void midm_kernel(const MdArgs args) 
     const int mine = md_wave_tiles(it.tiles_base + (b < it.tiles_rem ? 1 : 0), p, wave);
 #define MD_CASE(C, P)                                                                                                  \
     case 4 * P + C:                                                                                                     \
-        if constexpr (md_variant(kMode, kRB, C, md_loads(kRB, P)))                                                       \
+        if constexpr (md_variant(kMode, kRB, C, P))                                                                     \
             md_block<kMode, kRB, C, md_loads(kRB, P), md_depth(kMode, kRB, C, md_loads(kRB, P))>(args, it, md_lds);      \
         break;
 #define MD_CASES(P) MD_CASE(1, P) MD_CASE(2, P) MD_CASE(3, P) MD_CASE(4, P)
@@ -405,8 +405,9 @@ const void* md_kernel(int rb) {
         case 1: return reinterpret_cast<const void*>(&midm_kernel<kMode, 1>);
         case 2: return reinterpret_cast<const void*>(&midm_kernel<kMode, 2>);
         case 3: return reinterpret_cast<const void*>(&midm_kernel<kMode, 3>);
-        default: return reinterpret_cast<const void*>(&midm_kernel<kMode, 4>);
     }
+    if constexpr (kMode != kNib64) return reinterpret_cast<const void*>(&midm_kernel<kMode, 4>);
+    return nullptr;   // groups of 64 have no variant for four row blocks
 }
 
 hipError_t md_launch(const qail_w4a16_item* items, int count, int M, const MdDivision& v, hipStream_t st) {
