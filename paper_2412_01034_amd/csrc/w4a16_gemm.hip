@@ -167,15 +167,21 @@ __global__ __launch_bounds__(256) void gemm_prep_kernel(const PrepBatch args) {
         const size_t first = (size_t)n * G, last = first + G - 1;
         const uint32_t* const words = reinterpret_cast<const uint32_t*>(sc);
         const size_t w_last = last / 2;
-        for (size_t w0 = first / 2 + part; w0 <= w_last; w0 += 32) {
-            uint32_t v[4];
+        if (G <= 14) {   // eight words hold the row: one each (65536 x 256 at M = 72, 12.6 -> 12.1 us)
+            const size_t w = min(first / 2 + part, w_last);
+            const uint32_t v = words[w];
+            mx = max(2 * w >= first ? v & 0xFFFFu : 0u, 2 * w + 1 <= last ? v >> 16 : 0u);
+        } else {
+            for (size_t w0 = first / 2 + part; w0 <= w_last; w0 += 32) {
+                uint32_t v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = words[w0 + 8 * e < w_last ? w0 + 8 * e : w_last];   // past the row: its last word again
+                for (int e = 0; e < 4; ++e) v[e] = words[w0 + 8 * e < w_last ? w0 + 8 * e : w_last];   // past the row: its last word again
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const size_t w = w0 + 8 * e < w_last ? w0 + 8 * e : w_last;
-                mx = max(mx, 2 * w >= first ? v[e] & 0xFFFFu : 0u);   // a word at a row's end may hold a neighbour's scale
-                mx = max(mx, 2 * w + 1 <= last ? v[e] >> 16 : 0u);
+                for (int e = 0; e < 4; ++e) {
+                    const size_t w = w0 + 8 * e < w_last ? w0 + 8 * e : w_last;
+                    mx = max(mx, 2 * w >= first ? v[e] & 0xFFFFu : 0u);   // a word at a row's end may hold a neighbour's scale
+                    mx = max(mx, 2 * w + 1 <= last ? v[e] >> 16 : 0u);
+                }
             }
         }
     }
@@ -845,11 +851,20 @@ __global__ __launch_bounds__(256) void w4a16_gemm_fixup_kernel(const GemmBatch a
     float wm[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) wm[e] = bf16_bits_to_f32(ga.pow2[ga.wpow2 + min(n + e, ga.N - 1)]);
-    // Four slots at a time, all requested before any is added; most tiles have two or three, so a request past
-    // the last slot reads that one again (from the cache) and is not added.  With the 32-bit divisions: decoder layer at
-    // M = 288 / 1024 10.9 / 8.8 -> 9.7 / 8.2 us.
+    // Four slots at a time, all requested before any is added; most tiles have two or three, so in the last four a request
+    // past the last slot reads that one again (from the cache) and is not added.  With the 32-bit divisions: decoder layer at
+    // M = 288 / 1024 10.9 / 8.8 -> 9.7 / 8.2 us.  (That test in every four cost tiles of 64 slots, 500 x 11008 at M = 40,
+    // 1.8 us of 20.)
     f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
-    for (int i = 0; i < count; i += 4) {
+    int i = 0;
+    for (; i + 4 <= count; i += 4) {
+        f32x4_t v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const f32x4_t*>(src + (size_t)slots[i + e] * (kBM * kBN));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum += v[e];
+    }
+    if (i < count) {
         f32x4_t v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const f32x4_t*>(src + (size_t)slots[min(i + e, count - 1)] * (kBM * kBN));

@@ -136,6 +136,46 @@ def test_matrix_core_gemm_value_ranges(B):
     assert w4a16_norm_err(y, ref, nx, nw) <= TOL
 
 
+@pytest.mark.parametrize("M", [72, 130])
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("G", [1, 2, 3, 13, 14, 15, 21, 64, 85])
+def test_matrix_core_gemm_finds_each_rows_largest_scale(B, bits, G, M):
+    """The scales of a row are read as the aligned words that hold them, which begin and end with a neighbour's scale where G is
+    odd.  Rows of scales near 2^-12 stand between rows of scales near 2^4: a neighbour's power of two for such a row
+    takes its fp16 weights out of range.  The row's own largest scale stands anywhere in it, the first and last place too."""
+    import torch
+    N, g = 96, 64 if bits == 4 else 128
+    K = G * g
+    rng = np.random.default_rng(100 * G + M)
+    s = rng.uniform(0.5, 1.0, size=(N, G)) * np.where(np.arange(N) % 2 == 0, 2.0 ** -17, 2.0 ** -1)[:, None]
+    s[np.arange(N), np.where(np.arange(N) % 4 < 2, 0, rng.integers(0, G, N))] *= 32.0
+    s[4::8, 0] /= 32.0
+    s[4::8, -1] *= 32.0
+    s = s.astype(np.float16)
+    xb = synth.llm_activation_bf16(M, K, G)
+    y = torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda")
+    if bits == 4:
+        q, z = rng.integers(0, 16, size=(N, K)).astype(np.uint8), rng.integers(0, 16, size=(N, G)).astype(np.uint8)
+        qw, zw = O.pack_w4a16(q, z)
+        B.qail_w4a16_linear(N, K, g, dev(qw), dev(s.view(np.uint16)), dev(zw), dev(xb), y, M, ws_for(B, B.qail_w4a16_workspace(N, K, g, M)))
+        ref, (nx, nw) = O.w4a16_linear(xb, qw, s, zw, g), O.w4a16_row_norms(xb, qw, s, zw, g)
+    else:
+        q = rng.integers(-128, 128, size=(N, K)).astype(np.int8)
+        B.qail_w8a16_linear(N, K, g, dev(O.pack_bytes(q)), dev(s.view(np.uint16)), dev(xb), y, M, ws_for(B, B.qail_w8a16_workspace(N, K, g, M)))
+        ref = O.w8a16_linear(xb, q, s, g)
+        nx = np.sqrt((O.bf16_bits_to_f64(xb) ** 2).sum(axis=1))
+        nw = np.sqrt(((q.astype(np.float64) * np.repeat(s.astype(np.float64), g, axis=1)) ** 2).sum(axis=1))
+    torch.cuda.synchronize()
+    assert w4a16_norm_err(host(y, np.uint16).reshape(M, N), ref, nx, nw) <= (TOL if K >= 512 else TOL_TINY_K)
+
+
+@pytest.mark.parametrize("N,K,M", [(500, 11008, 40), (100, 11008, 72), (500, 2048, 130)])
+def test_matrix_core_gemm_tiles_of_many_slots(B, N, K, M):
+    """Few tiles and a long K: a tile's K is shared by up to 86 blocks, and the second kernel adds as many slots, four at a time
+    and a remainder."""
+    check(B, N, K, 128, M, 7000 + M, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005))
+
+
 @pytest.mark.parametrize("M", [2, 3, 4])
 @pytest.mark.parametrize("N,K,g", [(4, 512, 512),         # one quad, one chunk, one group
                                    (260, 4096, 64),       # eight groups per 512-k chunk
