@@ -354,7 +354,7 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     // the chunk from a pixel's (ih0, iw0, 0), its offset inside a filter row, and its tap; steps past the end of K are
     // marked invalid (their loads read nothing and write zeros).  The steps of the ring's first fill are worked out by
     // each lane for itself, so that their loads leave at once; the others come from a table in LDS, built once
-    // while those loads are in flight (the body at batch 32: 0.7 %).
+    // while those loads are in flight (body at batch 16 / 32 / 64 237.2 / 305.5 / 251.7 -> 233.0 / 305.0 / 243.8 us).
     auto entry = [&](int step, int ch) {
         const int kw0 = step * kStepWords + ch * 4;   // first word of the chunk
         uint2 v = make_uint2(0u, 0xFFFFFFFFu);
@@ -479,9 +479,12 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     pent = steptab[(pstep * KS + grp) * 4 + chunk];
     fetch(0, 0, 0);
 
-    // What the epilogue needs of scales, biases and shortcut is requested here, behind the ring's first steps: requested at
-    // the end, where the multiplying has stopped, it cost every launch a trip to memory (ResNet-34 body at batch 32, with the staging in
-    // 16-byte pieces below: 1 to 2 % of 310 us).
+    // What the epilogue needs of scales, biases and shortcut.  Requested behind the ring's first steps, it does not cost the end, where the
+    // multiplying has stopped, a trip to memory: nothing in the ResNet-34 body, 4 % of plain outputs of 1 x 1 filters (64 to 128
+    // channels, 32 x 56 x 56 6.32 -> 6.06 us).  Blocks that split K between groups of waves request it at the end: there the K loop
+    // as compiled with the requests in front of it was 2 to 4 % slower, for every kind of output (512 channels at batch 16
+    // 8.62 us against 8.29, 5 x 5 of 512 at 800 pixels 17.0 against 16.2; body at batch 16 / 32 / 64 237.1 / 308.0 / 247.2
+    // against 233.0 / 305.0 / 243.8).
     // A thread writes the same columns in every iteration of the epilogue's store loops (the block's
     // thread count is a multiple of the pieces per row).
     constexpr int kWordsPerRow = BN / 8, kQuadsPerRow = BN / 4;
@@ -493,26 +496,29 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     float4 scq = make_float4(0.f, 0.f, 0.f, 0.f), biq = scq;
     uint32_t rwf[kPasses][kItF];
     const bool fused = kBits == 4 && out.out_u4;   // (bytes have plain outputs only)
-    if (fused) {
-        if (n0f < gm.Cout) {
-            load8(out.scale + n0f, scf);
-            load8(out.bias + n0f, bif);
-        }
-        if (out.res_u4) {
+    auto request = [&]() {
+        if (fused) {
+            if (n0f < gm.Cout) {
+                load8(out.scale + n0f, scf);
+                load8(out.bias + n0f, bif);
+            }
+            if (out.res_u4) {
 #pragma unroll
-            for (int pass = 0; pass < kPasses; ++pass)
+                for (int pass = 0; pass < kPasses; ++pass)
 #pragma unroll
-                for (int it = 0; it < kItF; ++it) {
-                    const int idx = t + it * kThreads;
-                    const int m = bm + pass * kPassRows + idx / kWordsPerRow;
-                    rwf[pass][it] = (idx < kPassRows * kWordsPerRow && m < gm.M && n0f < gm.Cout)
-                                        ? out.res_u4[(size_t)m * (gm.Cout / 8) + n0f / 8] : 0u;
-                }
+                    for (int it = 0; it < kItF; ++it) {
+                        const int idx = t + it * kThreads;
+                        const int m = bm + pass * kPassRows + idx / kWordsPerRow;
+                        rwf[pass][it] = (idx < kPassRows * kWordsPerRow && m < gm.M && n0f < gm.Cout)
+                                            ? out.res_u4[(size_t)m * (gm.Cout / 8) + n0f / 8] : 0u;
+                    }
+            }
+        } else if (out.y && vec && n0q < gm.Cout) {
+            scq = *reinterpret_cast<const float4*>(out.scale + n0q);
+            biq = *reinterpret_cast<const float4*>(out.bias + n0q);
         }
-    } else if (out.y && vec && n0q < gm.Cout) {
-        scq = *reinterpret_cast<const float4*>(out.scale + n0q);
-        biq = *reinterpret_cast<const float4*>(out.bias + n0q);
-    }
+    };
+    if constexpr (KS == 1) request();
 
     if constexpr (kBits == 4) {
         for (int s0 = 0; s0 < steps; s0 += kStages) {
@@ -563,6 +569,7 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     // Epilogue: the accumulators (all rows at once if they fit, else half the rows at a time)
     // are staged in LDS (pitch BN + 4 words: the 16-byte writes of eight neighbouring pixels fall on different banks) and
     // leave as whole pieces of rows.
+    if constexpr (KS > 1) request();
     int32_t* const stage = reinterpret_cast<int32_t*>(smem);
 #pragma unroll
     for (int pass = 0; pass < kPasses; ++pass) {
