@@ -4,8 +4,10 @@
 // are found by looking for them in its arguments.
 //
 // One list per line of standard input: "w4" or "w8", M, the number of items, then N, K and group size of each.  Answer:
-// "list <status> <workspace asked for>", then one line per launch:
-// "<kernel> <blocks> <workspace that its items ask for as a list of their own> <item> <item> ...".
+// "list <status> <workspace asked for> <launches>", then one line per launch:
+// "<kernel> <blocks> <workspace that its items ask for as a list of their own> <item> <item> ...", for the medium-batch kernel
+// with the variants that its waves run after a bar, as "<column tiles>.<log2 of the K parts>".  First of all:
+// "variants <mode>,<row blocks>,<column tiles>,<log2 of the K parts> ...", those that are compiled.
 #include <cxxabi.h>
 #include <dlfcn.h>
 #include <stdio.h>
@@ -13,12 +15,11 @@
 #include <string.h>
 
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
-#include <hip/hip_runtime.h>
-
-#include "qail.h"
+#include "midm_plan.h"
 
 namespace {
 
@@ -29,6 +30,7 @@ struct Launch {
     std::string kernel;
     unsigned blocks;
     std::vector<int> items;
+    std::set<std::pair<int, int>> variants;
 };
 std::map<const void*, std::string>& names() {
     static std::map<const void*, std::string> m;
@@ -42,7 +44,8 @@ hipStream_t next_stream;
 // The records of the items stand first in a launch's only argument (or its arguments are a lone item's own).
 size_t record_bytes(const std::string& kernel) {
     if (kernel.find("gemm_prep_kernel") != std::string::npos) return 8 * 56;
-    if (kernel.find("midm_kernel") != std::string::npos || kernel.find("smallm") != std::string::npos) return 16 * 64;
+    if (kernel.find("midm_kernel") != std::string::npos) return sizeof(qail::MdArgs::it);
+    if (kernel.find("smallm") != std::string::npos) return 16 * 64;
     return 0;
 }
 
@@ -93,6 +96,13 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, 
         if (!seen[i]) l.items.push_back(i);
         seen[i] = true;
     }
+    if (l.kernel.find("midm_kernel") != std::string::npos) {
+        const qail::MdArgs& a = *static_cast<const qail::MdArgs*>(args[0]);
+        for (const qail::MdItem& it : a.it)
+            for (int more = 0; more < 2; ++more)   // blocks of tiles_base tiles and of one more
+                for (int wave = 0; wave < qail::kMdWaves && (it.tiles_base + more > 0) && (more == 0 || it.tiles_rem > 0); ++wave)
+                    l.variants.insert({std::max(1, qail::md_wave_tiles(it.tiles_base + more, it.wkl, wave)), it.wkl});
+    }
     launches.push_back(l);
     return hipSuccess;
 }
@@ -127,6 +137,13 @@ int main(int argc, char** argv) {
     FN(qail_w8a16_batch_workspace);
     FN(qail_w8a16_linear_batch);
 #undef FN
+    printf("variants");
+    for (int mode = 0; mode < 3; ++mode)
+        for (int rb = 1; rb <= 4; ++rb)
+            for (int c = 1; c <= 4; ++c)
+                for (int p = 0; p < 4; ++p)
+                    if (qail::md_variant(mode, rb, c, p)) printf(" %d,%d,%d,%d", mode, rb, c, p);
+    printf("\n");
     char kind[8];
     int M, count;
     while (scanf("%7s %d %d", kind, &M, &count) == 3) {
@@ -167,6 +184,8 @@ int main(int argc, char** argv) {
         for (const Launch& l : launches) {
             printf("%s %u %zu", l.kernel.c_str(), l.blocks, asked(l.items));
             for (int i : l.items) printf(" %d", i);
+            if (!l.variants.empty()) printf(" |");
+            for (const auto& v : l.variants) printf(" %d.%d", v.first, v.second);
             printf("\n");
         }
     }

@@ -9,6 +9,7 @@ import subprocess
 import pytest
 
 from .helpers import ensure_built
+from .midm_lists import EDGE_M, EDGES, LISTS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -19,10 +20,11 @@ pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not fou
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     """ask(lists) -> for each list (bits, M, [(N, K, group size), ...]): the workspace asked for and the launches, each as
-    (kernel, blocks, workspace of its items as a list of their own, items)."""
+    (kernel, blocks, workspace of its items as a list of their own, items).  ask.variants: those of the medium-batch kernel that
+    are compiled, ask.run: those that lists asked so far run, each as (mode, row blocks, column tiles of a wave, log2 of the K parts)."""
     exe = str(tmp_path_factory.mktemp("dispatch") / "host_dispatch_driver")
     r = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-host-only", "-Wno-unused-command-line-argument", "-rdynamic",
-                        "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host_dispatch_driver.cpp"), "-o", exe, "-ldl"],
+                        "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2412_01034_amd", "csrc"), os.path.join(ROOT, "tests", "host_dispatch_driver.cpp"), "-o", exe, "-ldl"],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout[-4000:]
     lib = ensure_built().LIB_PATH
@@ -32,16 +34,22 @@ def ask(tmp_path_factory):
         r = subprocess.run([exe, lib], input=text + "\n", stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
         assert r.returncode == 0, r.stderr[-4000:]
         out, lines = [], iter(r.stdout.splitlines())
+        ask.variants = {tuple(int(n) for n in v.split(",")) for v in next(lines).split()[1:]}
         for bits, M, shapes in lists:
             word, status, need, n = next(lines).split()
             assert word == "list" and status == "0", (bits, M, shapes, status)
             launches = []
             for _ in range(int(n)):
-                kernel, blocks, own, *items = next(lines).split()
+                line, _, variants = next(lines).partition("|")
+                kernel, blocks, own, *items = line.split()
+                if variants:
+                    mode, rb = kernel[len("midm_kernel<"):-1].split(",")
+                    ask.run |= {(int(mode), int(rb), *(int(n) for n in v.split("."))) for v in variants.split()}
                 launches.append((kernel, int(blocks), int(own), [int(i) for i in items]))
             out.append((int(need), launches))
         return out
 
+    ask.run = set()
     return ask
 
 
@@ -97,3 +105,19 @@ WIDE = [(10240, 8192), (8192, 8192), (57344, 8192), (8192, 28672)]   # 428 MB of
 def test_medium_batch_kernel_is_taken_where_it_was_faster(ask, bits, M, shapes, medium):
     [(_, launches)] = ask([(bits, M, [(N, K, 128) for N, K in shapes])])
     assert [k.startswith("midm") for k, *_ in launches] == ([True] if medium else [False] * len(launches)), launches
+
+
+def test_lists_of_the_gpu_test_run_every_variant(ask):
+    """Each is one launch of the medium-batch kernel, and no variant is compiled that none of them runs."""
+    ask.run.clear()
+    for (bits, M, shapes), (_, launches) in zip(LISTS, ask(LISTS)):
+        assert [k.split("<")[0] for k, *_ in launches] == ["midm_kernel"], (bits, M, shapes, launches)
+    assert ask.run == ask.variants
+
+
+def test_edge_lists_of_the_gpu_test_reach_the_kernel_where_they_say(ask):
+    lists = [(bits, M, shapes) for bits, shapes, _ in EDGES for M in EDGE_M]
+    answers = iter(ask(lists))
+    for bits, shapes, taken in EDGES:
+        got = tuple(M for M in EDGE_M if any(k.startswith("midm") for k, *_ in next(answers)[1]))
+        assert got == taken, (bits, shapes)

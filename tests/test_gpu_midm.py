@@ -1,7 +1,8 @@
 """The kernel for medium batches (5 <= M <= 64): one pass over K, x staged step by step, K parts added in LDS.
 
 Lists and shapes at its edges: row blocks full and ragged, columns that end inside a tile, one step of K and step counts
-that the K parts do not divide, blocks of one tile and of several, both group sizes, bytes; against the oracle."""
+that the K parts do not divide, blocks of one tile and of several, both group sizes, bytes; and lists that run every compiled
+variant between them (tests/midm_lists.py, which tests/test_dispatch.py holds against the library).  Against the oracle."""
 import numpy as np
 import pytest
 
@@ -9,6 +10,7 @@ from oracle import qail_oracle as O
 from paper_2412_01034_amd import synth
 
 from .helpers import dev, ensure_built, host, w4a16_norm_err, ws_for
+from .midm_lists import EDGE_M, EDGES, LISTS
 
 pytestmark = pytest.mark.gpu
 
@@ -49,16 +51,8 @@ def run(B, bits, ents, M):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("M", [5, 16, 17, 31, 33, 48, 49, 64])
-@pytest.mark.parametrize("bits,shapes", [
-    (4, [(300, 128, 64)]),                                              # one step of K
-    (4, [(33, 384, 64), (1000, 640, 64), (7, 2816, 64)]),               # 3, 5 and 22 steps, ragged columns
-    (4, [(4200, 1024, 64), (520, 1024, 128), (70, 2048, 128)]),         # group sizes in launches of their own
-    (4, [(300, 11008, 128), (1030, 256, 128)]),                         # 86 steps: four parts do not divide them
-    (4, [(9000, 512, 128), (4100, 768, 128)]),                          # blocks of several tiles
-    (8, [(1030, 11008, 128), (77, 256, 128)]),
-    (8, [(9000, 768, 128), (300, 512, 128)]),
-])
+@pytest.mark.parametrize("M", EDGE_M)
+@pytest.mark.parametrize("bits,shapes", [(bits, shapes) for bits, shapes, _ in EDGES])
 def test_lists_and_edges(B, bits, shapes, M):
     made = [make(B, bits, N, K, g, M, 3000 + 10 * i + M) for i, (N, K, g) in enumerate(shapes)]
     ents = [m[0] for m in made]
@@ -72,6 +66,46 @@ def test_lists_and_edges(B, bits, shapes, M):
         assert np.array_equal(y, y0), "run to run"
         tol = TOL if e["K"] >= 512 else TOL_TINY_K
         assert w4a16_norm_err(y.reshape(M, e["N"]), ref, nx, nw) <= tol, (e["N"], e["K"], e["group_size"])
+
+
+@pytest.mark.parametrize("bits,M,shapes", LISTS)
+def test_every_variant(B, bits, M, shapes):
+    """Random codes, scales and zero-points (every bit pattern of a code word is a weight).  All results are written and repeat bit
+    for bit; the oracle is asked for a column out of every tile, as far as six million weights of an item go."""
+    import torch
+    rng = np.random.default_rng(M + sum(N + K for N, K, _ in shapes))
+    gen = torch.Generator(device="cuda").manual_seed(int(rng.integers(1 << 30)))
+    ents = []
+    for N, K, g in shapes:
+        G = K // g
+        x = synth.llm_activation_bf16(M, K, int(rng.integers(1 << 30)), outlier_frac=0.005)
+        ents.append(dict(N=N, K=K, group_size=g, x=dev(x), y=torch.full((M * N,), 0x7FC0, dtype=torch.int16, device="cuda"),
+                         qweight=torch.randint(-2 ** 31, 2 ** 31, (N, K * bits // 32), dtype=torch.int32, device="cuda", generator=gen),
+                         scales=(torch.rand((N, G), device="cuda", generator=gen) * 1e-2 + 1e-3).half(),
+                         zeros=torch.randint(-2 ** 31, 2 ** 31, (N, (G + 7) // 8), dtype=torch.int32, device="cuda", generator=gen)))
+    run(B, bits, ents, M)
+    first = [e["y"].clone() for e in ents]
+    for e in ents:
+        e["y"].fill_(0x7FC0)
+    run(B, bits, ents, M)
+    for e, y0 in zip(ents, first):
+        N, K, g = e["N"], e["K"], e["group_size"]
+        assert torch.equal(e["y"], y0), "run to run"
+        assert bool(torch.isfinite(y0.view(torch.bfloat16)).all())
+        tiles = rng.permutation((N + 15) // 16)[:max(1, 6_000_000 // K)]
+        n = np.unique(np.r_[0, N - 1, np.minimum(16 * tiles + rng.integers(0, 16, tiles.size), N - 1)])
+        pick = torch.from_numpy(n).cuda()
+        q, s, z = (host(e[k][pick], d) for k, d in (("qweight", np.uint32), ("scales", np.float16), ("zeros", np.uint32)))
+        xb = host(e["x"], np.uint16).reshape(M, K)
+        nx = np.sqrt((O.bf16_bits_to_f64(xb) ** 2).sum(axis=1))
+        if bits == 4:
+            ref, (_, nw) = O.w4a16_linear(xb, q, s, z, g), O.w4a16_row_norms(xb, q, s, z, g)
+        else:
+            codes = q.view(np.int8).reshape(n.size, K)
+            ref = O.w8a16_linear(xb, codes, s, g)
+            nw = np.sqrt(((codes.astype(np.float64) * np.repeat(s.astype(np.float64), g, axis=1)) ** 2).sum(axis=1))
+        y = host(y0, np.uint16).reshape(M, N)[:, n]
+        assert w4a16_norm_err(y, ref, nx, nw) <= (TOL if K >= 512 else TOL_TINY_K), (N, K)
 
 
 @pytest.mark.parametrize("bits,g,M", [(4, 64, 16), (4, 64, 33), (4, 128, 40), (8, 128, 50)])
