@@ -35,11 +35,12 @@ def _run_linear(B, t):
 def test_replays_match_eager(B):
     import torch
     # one case per W4A16 kernel: M = 1 stream, four-row stream, small batch (one and two blocks of 16 rows of
-    # x, the latter with K in several passes; the kernel for other group sizes), matrix-core GEMM with tiles
+    # x; the kernel for other group sizes), medium batch (M = 27 at K = 11008), matrix-core GEMM with tiles
     # shared between blocks (K = 8192: 64 steps), and a convolution
     lin = [_linear_case(B, 256, 4096, 128, 1, 11), _linear_case(B, 64, 11008, 128, 4, 12),
            _linear_case(B, 80, 4096, 128, 16, 13), _linear_case(B, 300, 8192, 128, 100, 14),
-           _linear_case(B, 100, 11008, 128, 27, 15), _linear_case(B, 72, 2048, 256, 9, 16)]
+           _linear_case(B, 100, 11008, 128, 27, 15), _linear_case(B, 72, 2048, 256, 9, 16),
+           _linear_case(B, 100, 1024, 128, 27, 17)]
     s = synth.ConvShape("graph", B=2, H=14, W=14, Cin=64, Cout=64, KH=3, KW=3, stride=1, pad=1)
     rng = np.random.default_rng(5)
     a = dev(rng.integers(0, 2 ** 32, size=s.B * s.H * s.W * s.Cin // 8, dtype=np.uint64).astype(np.uint32))

@@ -112,10 +112,11 @@ def test_matrix_core_gemm_work_split(B, M, N, K, g):
     check(B, N, K, g, M, 5 * M + N, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005), tol=TOL)
 
 
-def test_matrix_core_gemm_value_ranges(B):
+@pytest.mark.parametrize("M", [40, 72])   # (40: the medium-batch kernel's, on the same inputs)
+def test_matrix_core_gemm_value_ranges(B, M):
     # rows of x and rows of W spanning 60 binades each: the per-row powers of two that keep the
     # fp16 operands in range must come back out exactly
-    N, K, g, M = 96, 1024, 128, 40
+    N, K, g = 96, 1024, 128
     rng = np.random.default_rng(123)
     w = synth.llm_weight(N, K, 31) * (2.0 ** rng.integers(-8, 18, size=(N, 1))).astype(np.float32)
     x = rng.standard_normal((M, K)).astype(np.float32) * (2.0 ** rng.integers(-30, 30, size=(M, 1))).astype(np.float32)

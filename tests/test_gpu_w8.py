@@ -254,11 +254,12 @@ def test_w8a16_batch_on_the_matrix_cores(B, M):
         assert w4a16_norm_err(y.reshape(M, e["N"]), ref, nx, nw) <= tol, (e["N"], e["K"])
 
 
-def test_w8a16_closed_forms_on_the_matrix_cores(B):
+@pytest.mark.parametrize("M", [40, 72])   # (40: the medium-batch kernel's, on the same inputs)
+def test_w8a16_closed_forms_on_the_matrix_cores(B, M):
     # all codes c, s = 1, x = 1 -> y = K * c exactly (K * 127 = 130048 = 127 * 2^10 is a bf16 number);
     # one-hot x reads single weights: q * s rounded to fp16 (exact here: 8-bit q, s a power of two)
     import torch
-    N, K, g, M = 96, 1024, 128, 40
+    N, K, g = 96, 1024, 128
     for c in (-128, -1, 1, 127):
         q = np.full((N, K), c, np.int8)
         s = np.ones((N, K // g), np.float16)
