@@ -294,7 +294,7 @@ def main():
         stack_bytes_w = 32 * sum(linear_bytes(N, K, 0) for _, N, K in shapes)
         for M in (1, 4, 16, 32, 64):
             io = dec if M == 1 else with_io(M)
-            nws = B.qail_w4a16_batch_workspace(io[0][0], 4, M)   # M > 32: the matrix-core GEMM's
+            nws = B.qail_w4a16_batch_workspace(io[0][0], 4, M)   # M > 32: sized for the matrix-core GEMM
             wsk = torch.empty(nws, dtype=torch.uint8, device="cuda") if nws else None
 
             def walk():
@@ -658,7 +658,7 @@ def main():
                                        "us_per_layer_one_launch_per_linear": round(tl8 * 1e6, 2),
                                        "note": f"{L8} distinct layers cycled"}
         # the same layer at M > 1, one batched call per layer: the small-batch streaming kernel with byte
-        # weights up to M = 16, the byte-code instantiation of the matrix-core GEMM above
+        # weights at M = 4, the medium-batch kernel at M = 16, the byte-code instantiation of the matrix-core GEMM above
         w8m = {}
         for M8 in (4, 16, 288, 1024):
             xs8 = [dev(synth.llm_activation_bf16(M8, K, synth.seed_for(1, i, 1))) for i, (_, N, K) in enumerate(shapes)]
@@ -679,7 +679,7 @@ def main():
             w8m[f"M={M8}"] = {"us_per_layer": round(tm * 1e6, 1), "TFLOPs": round(tf8, 1),
                               "frac_f16_peak": round(tf8 / BF16_PEAK_TFLOPS, 4),
                               "GBps_weights": round((b8 - sum(2 * (N + K) for _, N, K in shapes)) / tm / 1e9, 1),
-                              "kernel": "small-batch stream" if M8 <= 16 else "matrix-core GEMM"}
+                              "kernel": {4: "small-batch stream", 16: "medium-batch kernel"}.get(M8, "matrix-core GEMM")}
             del its, xs8, ws8
         extra["w8a16_layer_batched"] = w8m
         del w8ls, it8

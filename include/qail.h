@@ -140,7 +140,8 @@ int qail_quantize_act_u4(const float* a, size_t n, const float* s_a, uint32_t* a
 
 /* Bytes of device scratch the call below needs for this (d, M).  0 for the streaming
  * kernels (M <= 16 on shapes they take, M <= 32 at group_size 128 with an even number of
- * groups per row); for the matrix-core GEMM it holds an fp16 copy
+ * groups per row); for shapes of the matrix-core GEMM it holds (also at M <= 64, where another
+ * kernel may be faster for them and uses none) an fp16 copy
  * of x (rows padded to a multiple of 128, K to a multiple of 128), one float per padded
  * row and per output column, and two tile-shaped fp32 slots per block of the grid (one
  * block per compute unit) for output tiles whose K range is shared between blocks (tens
@@ -153,8 +154,11 @@ int qail_w4a16_workspace(const qail_wdesc* d, int32_t M, size_t* bytes);
  * in fp32 and rounded once to bf16 (nearest even).  M = 1 (decode) is served by a
  * bandwidth-bound streaming kernel, 2 <= M <= 4 by the same stream with four rows of x,
  * up to M = 16 (M = 32 at group_size 128 with an even number of groups per row) by a
- * weight-streaming MFMA kernel (x and codes exact in the products),
- * larger M (prefill) by an fp16 MFMA kernel that expands the codes in registers
+ * weight-streaming MFMA kernel (x and codes exact in the products; an x beyond 2e36 may
+ * overflow a sum of codes times x on the way),
+ * 5 <= M <= 64 at group_size 128 or 64 with K % 128 == 0 and an even number of groups per row, where
+ * that was measured to be faster, by a kernel with one pass over K (the same products, any finite x),
+ * larger M (prefill) and other shapes by an fp16 MFMA kernel that expands the codes in registers
  * ((q - z) * s rounded once to fp16, x rescaled per row by a power of two).
  * workspace may be NULL when the query returns 0; otherwise a missing or short one
  * is QAIL_ERR_WORKSPACE and a misaligned one QAIL_ERR_ALIGN. */
@@ -336,8 +340,8 @@ int qail_w8a8_gemm(const qail_conv_desc* d, const uint32_t* a_s8, const uint32_t
  * fp32 accumulation, one rounding.  M = 1 runs a bandwidth-bound streaming kernel (K % 16 == 0,
  * group_size % 16 == 0, K + K/g <= 16384).  2 <= M <= 32 at group_size 128 with an even number
  * of groups per row (N * K below 2 GB) runs the small-batch streaming kernel of
- * qail_w4a16_linear with byte weights (x and q exact in the products, fp32 accumulation, no
- * workspace).  Other M > 1 runs on the fp16 matrix cores (the kernel of
+ * qail_w4a16_linear with byte weights, or, as 33 <= M <= 64 of these shapes, its kernel with one pass over K
+ * where that is faster (x and q exact in the products, fp32 accumulation; M <= 32 needs no workspace).  Other M > 1 runs on the fp16 matrix cores (the kernel of
  * qail_w4a16_linear for M > 16 with byte codes: K % 64 == 0, group_size % 64 == 0, an even
  * number of scales; (q * s) is rounded once to fp16 before the fp32 accumulation) and needs the
  * workspace the query below reports, 256-byte aligned.  Shapes outside both go to a plain

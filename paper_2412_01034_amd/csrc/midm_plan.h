@@ -163,9 +163,9 @@ inline double md_bytes(const qail_wdesc& d, int mode) { return (double)d.N * d.K
 //     1.2 (the layer at M = 8 / 32 53.0 -> 44.3 / 64.0 -> 49.3; one pass, 4096 x 4096 at M = 8: a tenth slower);
 //   * otherwise the matrix-core GEMM, which takes 13.5 us, 1.3 per further item and a microsecond per 3 MB (bytes: 3.3; at 3.0
 //     8192 x 28672 at M = 48 went from 80 to 83), measured on the low side: M = 48 the layer 56.2 -> 45.2, with bytes 73.9 -> 54.5;
-//     one 4096 x 11008, whose K the GEMM divides among blocks, 23.3 against 31.6.  Groups of 64 stay below 49 rows (the layer
-//     at M = 32 / 48 54.7 -> 46.7 / 62.6 -> 56.9, at M = 64 63.1 against 66.2) and need no comparison up to 16
-//     (54.5 -> 40.8; 4096 x 4096 14.5 -> 9.6).
+//     one 4096 x 11008, whose K the GEMM divides among blocks, 23.3 against 31.6.  Groups of 64 stay below 49 rows (layers of
+//     1024 to 2048 channels at M = 48 a third faster, most single linears at M = 49 slower) and need no comparison up to 16 (the
+//     7B layer 54.5 -> 40.8; 4096 x 4096 14.5 -> 9.6; at M = 32 54.7 -> 46.7).
 enum class MdAnswer { no, yes, by_time };
 inline MdAnswer md_wanted(const qail_w4a16_item* items, int count, int M, int mode, double bytes) {   // what needs no division
     if (mode == kNib64) return M <= 16 ? MdAnswer::yes : M > 48 ? MdAnswer::no : MdAnswer::by_time;

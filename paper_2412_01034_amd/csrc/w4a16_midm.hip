@@ -25,11 +25,13 @@
 //     would cost as much as the codes.
 //
 // What bounds it: issue and latency inside a step (at M = 48 12 tiles a block with no loads take
-// 30 us of the 38 that 100 MB of codes take; the codes alone 24), then HBM.  The layer of a 7B
-// model in one call, before (smallm / GEMM) -> now, us: M = 24 / 32 / 48 / 64 43.7 / 45.2 / 56.0 /
-// 56.4 -> 37.6 / 39.6 / 44.2 / 51.7; groups of 64 M = 8 / 32 / 48 53.1 / 53.9 / 61.8 -> 40.9 /
-// 44.1 / 59.1; bytes M = 8 / 32 / 48 51.9 / 63.0 / 71.8 -> 44.6 / 51.4 / 56.9.  Measured and not
-// kept: codes fetched with the pieces of a row in neighbouring lanes (22 instead of 66 cycles of
+// 30 us of the 39 that the 100 MB of codes of a 7B model's layer take from the last-level cache; the
+// codes alone 24), then HBM.  That layer in one call, new buffers from call to call, before
+// (smallm / GEMM) -> now, us: M = 24 / 32 / 48 44.3 / 45.9 / 56.9 -> 38.5 / 39.1 / 45.4; groups of 64
+// M = 8 / 16 / 32 54.0 / 54.2 / 54.7 -> 40.2 / 40.9 / 46.7; bytes M = 8 / 32 / 48 / 64 52.3 / 64.7 / 74.6 /
+// 75.4 -> 42.6 / 50.0 / 58.8 / 66.7.  (Nibbles from M = 49 on are the GEMM's there: the plan's model has 61 us for
+// 54.)  The very first pass over buffers that nothing has read gains nothing: M = 48 71 to 76 us
+// with either kernel, four runs.  Measured and not kept: codes fetched with the pieces of a row in neighbouring lanes (22 instead of 66 cycles of
 // the address unit per load) and turned through LDS, the offset as the MFMAs' start value and the
 // zero-points as fp32 MFMAs, tile-outer order, a third buffer of x: none faster.
 #include <string.h>
