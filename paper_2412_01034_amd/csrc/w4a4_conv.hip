@@ -23,18 +23,17 @@
 // multiply-add but a wave issuing nothing else reaches only 0.6 of the matrix
 // rate with it (2.7 against 4.5 POP/s over the chip, measured), the 32x32x32 form all of it.
 //
-// Tiling: a block of 4 waves (2 x 2) owns a BM x BN output tile and walks K in
+// Tiling: a block of 4 to 16 waves owns an output tile of 64 x 64 to 128 x 128 and walks K in
 // steps of 128 codes (16 packed words per row; K is ordered (kh, kw, c), so a step
 // is a run of channels of one or two filter taps).  Nibbles stay packed in LDS
-// (half the LDS traffic of int8); the load unit writes the tiles of the next two steps
-// straight into a ring of three LDS slots, one barrier per step.
+// (half the LDS traffic of int8); the load unit writes the tiles of the next one or two steps
+// straight into a ring of LDS slots, one barrier per step.
 // Zero padding costs nothing: code 0 of the unsigned activations is the value 0.
 //
-// Where a launch's time goes (time stamps of a block, 3x3 layers of 64 / 128 / 256 / 512 channels at batch 32, us):
-// set-up to the first loads 0.96 / 0.68 / 0.60 / 0.60, their landing 0.3-0.6, K loop 3.4 / 3.9 / 3.6 / 5.4 (blocks that
-// share their unit with more others up to 5.5 / 5.2 / 5.7 / 5.5), epilogue 2.0 / 1.8 / 0.84 / 1.08; first to last stamp
-// 9.9 / 8.5 / 8.3 / 8.1, and 1.5 to 2 more to the next launch.  The loop is bound by vector issue (widening) and, with
-// 64 x 64 tiles, by what a unit takes in from L2 (300 KB a block), the epilogue by its operations per element.
+// Where a launch's time goes (3x3 layers of 64 / 128 / 256 / 512 channels with a shortcut at batch 32, 5 / 9 / 18 / 36 K steps,
+// launches one after the other): 10.4 / 8.9 / 8.8 / 8.8 us, of which 7.0 / 5.3 / 4.9 / 4.5 are there with a single step (launch
+// cadence 2.4, operands' first trip to memory, epilogue).  The loop is bound by vector issue (widening) and, with
+// 64 x 64 tiles, by what a unit takes in from L2 (300 KB a block).
 #include "qail_internal.h"
 #include <algorithm>
 #include <cmath>
@@ -93,7 +92,7 @@ struct ConvOut {
     const float* res_f32;
     float s_out, res_scale;
     float inv_s_out;  // 1 / s_out, correctly rounded (host division)
-    // fused output: s_out and its reciprocal are normal numbers, the quotient may be tried as a product first;
+    // fused output: s_out is far from the ends of the range, the quotient may be tried as a product first;
     // plain outputs: stored past the caches (kPastCaches).  One word for both: the arguments of a batch with another
     // one in each item cost the encoder at batch 32 2 % (304 -> 310 us).
     int quick;
@@ -141,62 +140,69 @@ __device__ __forceinline__ float fused_code_quick(float t, float inv_s, float& w
     worst = fmaxf(worst, __builtin_fabsf(u - q));
     return q;
 }
-// Eight codes (small non-negative integers held as floats) -> one packed word, code e in nibble e: a code is
+// N codes (small non-negative integers held as floats) -> nibbles 0 .. N - 1 of a word: a code is
 // converted into its byte of the even or the odd codes' word (11 operations per output element up to here, 14 with a
 // shift and an or per code and the clamps one by one: 1 % of the body at batch 32).
-__device__ __forceinline__ uint32_t pack_codes(const float (&q)[8]) {
+template <int N>
+__device__ __forceinline__ uint32_t pack_codes(const float (&q)[N]) {
     uint32_t even = 0, odd = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < N / 2; ++e) {
         even = __builtin_amdgcn_cvt_pk_u8_f32(q[2 * e], e, even);
         odd = __builtin_amdgcn_cvt_pk_u8_f32(q[2 * e + 1], e, odd);
     }
     return even | (odd << 4);
 }
 
-// 8 consecutive channels of one output pixel -> one packed word; sc / bi: their scales and
-// biases, r: their shortcut values (0 without a shortcut: t + 0 == t).
-__device__ __forceinline__ uint32_t fused_pack(const int (&acc)[8], const float (&sc)[8], const float (&bi)[8],
-                                               const float (&r)[8], const ConvOut& o) {
-    float t[8];
+// N neighbouring channels of one output pixel -> their codes; sc / bi: the channels' scales and biases, r: their
+// shortcut values (0 without a shortcut: t + 0 == t).
+template <int N>
+__device__ __forceinline__ void fused_codes(const int (&acc)[N], const float (&sc)[N], const float (&bi)[N], const float (&r)[N],
+                                            const ConvOut& o, float (&q)[N]) {
+    float t[N];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) t[e] = fused_value(acc[e], sc[e], bi[e], r[e]);
-    float q[8];
+    for (int e = 0; e < N; ++e) t[e] = fused_value(acc[e], sc[e], bi[e], r[e]);
     float worst = o.quick ? 0.f : 1.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) q[e] = fused_code_quick(t[e], o.inv_s_out, worst);
+    for (int e = 0; e < N; ++e) q[e] = fused_code_quick(t[e], o.inv_s_out, worst);
     if (__builtin_expect(!(worst <= 0.5f - 0x1p-17f), 0)) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = fused_code(t[e], o.s_out);
+        for (int e = 0; e < N; ++e) q[e] = fused_code(t[e], o.s_out);
     }
-    return pack_codes(q);
 }
-__device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
-    const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+template <int N>
+__device__ __forceinline__ void load_floats(const float* p, float (&v)[N]) {   // 16-byte aligned
+#pragma unroll
+    for (int e = 0; e < N; e += 4) {
+        const float4 a = *reinterpret_cast<const float4*>(p + e);
+        v[e] = a.x; v[e + 1] = a.y; v[e + 2] = a.z; v[e + 3] = a.w;
+    }
 }
-// Shortcut values of 8 channels from a word of 4-bit codes (each times its step: one rounding).
-__device__ __forceinline__ void shortcut_from_codes(uint32_t rw, float res_scale, float (&r)[8]) {
+// Shortcut values of N channels from a word of 4-bit codes (each times its step: one rounding).
+template <int N>
+__device__ __forceinline__ void shortcut_from_codes(uint32_t rw, float res_scale, float (&r)[N]) {
     const uint32_t even = rw & 0x0F0F0F0Fu, odd = (rw >> 4) & 0x0F0F0F0Fu;   // a byte converts to float in one operation
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < N; ++e) {
 #pragma clang fp contract(off)
         r[e] = res_scale * (float)((((e & 1) ? odd : even) >> (8 * (e / 2))) & 0xFFu);
     }
 }
 __device__ __forceinline__ uint32_t fused_word(const int (&acc)[8], const ConvOut& o, size_t m, int n0, int cout) {
     float sc[8], bi[8], r[8];
-    load8(o.scale + n0, sc);
-    load8(o.bias + n0, bi);
+    load_floats(o.scale + n0, sc);
+    load_floats(o.bias + n0, bi);
     if (o.res_u4) {
         shortcut_from_codes(o.res_u4[m * (size_t)(cout / 8) + n0 / 8], o.res_scale, r);
     } else if (o.res_f32) {
-        load8(o.res_f32 + m * (size_t)cout + n0, r);
+        load_floats(o.res_f32 + m * (size_t)cout + n0, r);
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) r[e] = 0.f;
     }
-    return fused_pack(acc, sc, bi, r, o);
+    float q[8];
+    fused_codes(acc, sc, bi, r, o, q);
+    return pack_codes(q);
 }
 
 // Two words of codes as MFMA operand bytes: activations as they are, weights times 16.
@@ -260,138 +266,202 @@ __device__ __forceinline__ void dma16(u32x4_t rsrc, uint32_t off, uint32_t lds) 
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(lds), "v"(off), "s"(rsrc) : "memory", "m0");
 }
+__device__ __forceinline__ void dma4(u32x4_t rsrc, uint32_t off, uint32_t lds) {   // lane l's 4 bytes at lds + 4 l
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :: "s"(lds), "v"(off), "s"(rsrc) : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+    return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p);
+}
 __host__ __device__ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }  // lgkmcnt 0 too
 
-constexpr int kStages = 3;  // ring of K steps in LDS: step s + 2 is loaded while step s is multiplied
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float v) {   // v of another lane of the row
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kCtrl, 0xF, 0xF, false));
+}
+
 constexpr int kMaxSteps = 128;  // rows of the step table (K steps plus the ring's look-ahead)
 
-// Tiling: a block of 4 waves (2 x 2) owns a BM x BN output tile and walks K in steps of 128
-// codes (64 B per row; K is ordered (kh, kw, c) and Cin % 32 == 0, so every 16-byte chunk lies
+// Tiling: a block owns a BM x BN output tile, WM x WN waves side by side with 32 UM x 32 UN of it each, and walks K in
+// steps of 128 codes (64 B per row; K is ordered (kh, kw, c) and Cin % 32 == 0, so every 16-byte chunk lies
 // inside one filter tap).  Rows are unpadded in LDS; chunk c of row r is kept at position
 // c ^ swz(r), swz(r) = ((r / 4) % 4) ^ (r & 2), chosen through the loading lane's address: the
 // 16-byte fragment reads of 8 consecutive rows then fall into 8 different 16-byte columns of
 // a 128-byte line, and those of 16 consecutive rows into 16 different ones of a 256-byte line.
 //
-// KS > 1: KS groups of 4 waves share the tile and split K between them (group g takes steps
-// g, g + KS, ...), each with its own ring; their int32 partial tiles are added in the epilogue
-// (integer sums: exact in any order).  For the deep layers of a small batch, which have few
-// tiles and long K, this puts several waves on every SIMD instead of one.
+// KS > 1: KS groups of WM x WN waves share the tile and split K between them (group g takes steps
+// g, g + KS, ...), each with its own ring of ST slots; the waves with the same part of the tile then hand each other pieces of
+// it through LDS, so that each finishes one KS-th (integer sums: exact in any order).
+//
+// What bounds it is the number of vector instructions: a lone wave on a SIMD issues one per 8 cycles, two or more
+// one per 4.5 together (a loop of MFMAs and ANDs: 30 / 16 ns per 8 of them), and at batch 32 a SIMD has two to four waves for
+// the whole launch.  So what a row or a step needs is worked out once per block, into tables (a row's address and taps,
+// a step's offsets; by every lane for the rows it loads: 3 to 6 % slower); the weights' addresses need no test (rows past Cout load the
+// last one, steps past the end the last one, and neither reaches a result); halves of a K step past the end of K are not
+// multiplied (64 channels: 4.5 steps, not 5); the fused epilogue works from the registers, in units of the output step (see
+// there); the ring has two slots where three would leave room for fewer blocks on a unit.  Before, every lane worked out its
+// own rows, the sums went through LDS and the epilogue took 11 operations per element (now 7, with a shortcut 9 instead
+// of 13).  3x3 layers with a shortcut, before / now: 64 channels, 56 x 56, batch 32 / 64 / 256 12.0 / 10.3, 18.3 / 15.7,
+// 60.2 / 50.7 us; 96 to 160 channels, 17 x 40 x 43 14.3 / 10.6; 256, 14 x 14, batch 48 13.5 / 10.8.
 //
 // kBits = 8 is the W8A8 variant of the same kernel (Sec. 5.4): bytes are MFMA operands as they
 // are, a K step is 64 codes and one MFMA deep, nothing is widened and nothing shifted back.
 //
 // The tile at rows bm.., columns bn.. of one convolution; the two kernels below call it.
-template <int BM, int BN, int KS, int kBits>
-__device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_t* __restrict__ a,
-                                               const uint32_t* __restrict__ w, const ConvOut& out, const int bm,
-                                               const int bn) {
-    constexpr int kLA = BM / 64;   // wave-wide loads per wave and step for the activation tile
-    constexpr int kLB = BN / 64;   // ... for the weight tile
+template <int UM, int UN, int WM, int WN, int KS, int ST, int kBits>
+__device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_t* __restrict__ a, const uint32_t* __restrict__ w,
+                                               const ConvOut& out, const int bm, const int bn) {
+    constexpr int G = WM * WN;                       // waves of a K group
+    constexpr int BM = 32 * UM * WM, BN = 32 * UN * WN;
+    constexpr int kThreads = 64 * G * KS;
+    constexpr int kLA = BM / (16 * G);   // wave-wide loads per wave and step for the activation tile
+    constexpr int kLB = BN / (16 * G);   // ... for the weight tile
     constexpr int kL = kLA + kLB;
-    constexpr int kUM = BM / 64;   // 32 x 32 MFMA tiles per wave along m
-    constexpr int kUN = BN / 64;   // ... along n
-    constexpr int kAccs = kUM * kUN == 1 ? 2 : 1;  // a lone tile alternates between two accumulators (no dependent pair)
     constexpr int kStageBytes = (BM + BN) * 64;
-    constexpr int kSPitch = BN + 4;  // words per row of the int32 staging tile of the epilogue
-    constexpr int kPasses = BM * kSPitch * 4 <= kStages * kStageBytes ? 1 : 2;  // epilogue passes over the rows
-    constexpr int kPassRows = BM / kPasses;
-    constexpr int kGroupBytes = kStages * kStageBytes > kPassRows * kSPitch * 4 ? kStages * kStageBytes
-                                                                                 : kPassRows * kSPitch * 4;
-    constexpr int kThreads = 256 * KS;
-    __shared__ __attribute__((aligned(16))) unsigned char smem_all[KS * kGroupBytes];
+    constexpr int kQuads = 4 * UM * UN, kOwn = kQuads / KS;   // a wave's tile in pieces of 32 pixels x 8 channels, and how many it finishes
+    constexpr int kHandBytes = (KS - 1) * kQuads * 1024 * G / KS;   // handed over per group
+    constexpr int kGroupBytes = ST * kStageBytes > kHandBytes ? ST * kStageBytes : kHandBytes;
+    static_assert(BM % (16 * G) == 0 && BN % (16 * G) == 0 && BM <= kThreads && BN % 64 == 0, "loads and tables divide evenly");
+    static_assert(kQuads % KS == 0 && (kOwn == 1 || kOwn % 2 == 0), "a wave finishes one piece or pairs of them");
+    static_assert((KS - 1) * kQuads * 1024 * G <= KS * kGroupBytes && kStageBytes % 16 == 0 && kGroupBytes % 16 == 0, "pieces fit the rings");
+    static_assert(ST == 2 || ST == 3, "slots of a ring");
+    __shared__ __attribute__((aligned(16))) unsigned char ring[KS * kGroupBytes];
+    // scales, biases; fused: the same in units of the output step (bytes keep them in registers, and their blocks of three
+    // slots and 128 x 64 or 64 x 128 to 40 KB, so that four fit a unit)
+    __shared__ __attribute__((aligned(16))) float chan[4][kBits == 4 ? BN : 1];
+    __shared__ float limit[kBits == 4 ? BN / 8 : 1];             // fused: how far from an integer a quick quotient may be
     __shared__ uint2 steptab[kMaxSteps * 4];
+    __shared__ __attribute__((aligned(16))) unsigned char resid[kBits == 4 ? BM * BN / 2 : 16];   // the tile of the shortcut's codes
 
     const int t = threadIdx.x;
     const int lane = t % kWave;
     const int wave_all = __builtin_amdgcn_readfirstlane(t / kWave);
-    const int grp = wave_all / 4, wave = wave_all % 4;   // K group, wave inside the group
-    unsigned char* const smem = smem_all + grp * kGroupBytes;
-    const int wm = wave / 2, wn = wave % 2;
+    const int grp = wave_all / G, wave = wave_all % G;   // K group, wave inside the group
+    unsigned char* const smem = ring + grp * kGroupBytes;
+    const int wm = wave / WN, wn = wave % WN;
     const int cw = gm.Cin / (32 / kBits);      // words per pixel
-    const int kwords = gm.KH * gm.KW * cw;     // words per filter
+    const int kwords = gm.KH * gm.KW * cw;     // words per filter (a multiple of 4)
     const int gsteps = (kwords + kStepWords - 1) / kStepWords;   // K steps of the whole problem
     const int steps = (gsteps + KS - 1) / KS;                     // ... of one group (the same for all)
+    const bool fused = kBits == 4 && out.out_u4;                  // (bytes have plain outputs only)
 
     const u32x4_t ra = make_rsrc_words(a, (uint32_t)((size_t)gm.B * gm.H * gm.W * cw * 4));
     const u32x4_t rw = make_rsrc_words(w, (uint32_t)((size_t)gm.Cout * kwords * 4));
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)smem);
+    const uint32_t lds0 = lds_address(smem);
 
-    // Loader geometry: load i of this wave fills rows (4 i + wave) * 16 + lane / 4, position
+    // Scales and biases first: wave c takes channels 64 c .. 64 c + 63 and, for fused outputs, works on them below.
+    if (kBits == 4 && wave_all < BN / 64 && out.scale && out.bias) {
+        const u32x4_t rs = make_rsrc_words(out.scale, (uint32_t)gm.Cout * 4), rb = make_rsrc_words(out.bias, (uint32_t)gm.Cout * 4);
+        const uint32_t c0 = lds_address(&chan[0][0]) + wave_all * 256;
+        dma4(rs, (uint32_t)(bn + t) * 4u, c0);
+        dma4(rb, (uint32_t)(bn + t) * 4u, c0 + BN * 4);
+    }
+
+    // Loader geometry: load i of this wave fills rows (G i + wave) * 16 + lane / 4, position
     // lane % 4, with the chunk that belongs there.
     const int lrow = lane >> 2;
     const int chunk = (lane & 3) ^ ((lrow >> 2) & 3) ^ (lrow & 2);  // which 16 bytes of a step this lane fetches
-    int abase[kLA];       // byte offset of (b, ih0, iw0, 0); may be negative at the border
-    uint32_t amask[kLA];  // bit tap = the tap's pixel is inside the image
+    // Weights: rows past Cout load the last one (their results are not stored), steps past the end of K the last one
+    // (not multiplied).  A chunk past the end of K inside the last step is the next row's first or lies past the tensor: the
+    // activations it meets are zeros.
+    uint32_t bbase[kLB];
 #pragma unroll
-    for (int i = 0; i < kLA; ++i) {
-        const int m = bm + (4 * i + wave) * 16 + lrow;
-        abase[i] = 0;
-        amask[i] = 0;
+    for (int i = 0; i < kLB; ++i)
+        bbase[i] = (uint32_t)min(bn + (G * i + wave) * 16 + lrow, gm.Cout - 1) * (uint32_t)(kwords * 4) + chunk * 16;
+    auto issue_w = [&](int step, int slot) {
+        const uint32_t k4 = (uint32_t)min(step, gsteps - 1) * (kStepWords * 4);
+#pragma unroll
+        for (int i = 0; i < kLB; ++i) dma16(rw, bbase[i] + k4, lds0 + slot * kStageBytes + BM * 64 + (G * i + wave) * 1024);
+    };
+    issue_w(grp, 0);
+    issue_w(KS + grp, 1);
+
+    // Where a pixel is: byte offset of (b, ih0, iw0, 0), which may be negative at the border, and a bit per tap that
+    // lies outside the image (all of them for rows past the end).
+    auto pixel = [&](int m) {
+        uint2 v = make_uint2(0u, 0xFFFFFFFFu);
         if (m < gm.M) {
             const int b = div_by(m, gm.OH * gm.OW, gm.mg_ohow, gm.fastdiv);
             const int rem = m - b * (gm.OH * gm.OW);
             const int oh = div_by(rem, gm.OW, gm.mg_ow, gm.fastdiv), ow = rem - oh * gm.OW;
             const int ih0 = oh * gm.stride - gm.pad, iw0 = ow * gm.stride - gm.pad;
-            abase[i] = ((b * gm.H + ih0) * gm.W + iw0) * cw * 4;
+            v.x = (uint32_t)(((b * gm.H + ih0) * gm.W + iw0) * cw * 4);
             // taps inside the image: kw in [kw_lo, kw_hi) for every kh in [kh_lo, kh_hi); at most 32 taps, and the product
             // copies the bits of a row (fewer than KW + 1) to every row kept
             const int kw_lo = max(0, -iw0), kw_n = min(gm.KW, gm.W - iw0) - kw_lo;
             const int kh_lo = max(0, -ih0), kh_n = min(gm.KH, gm.H - ih0) - kh_lo;
             if (kw_n > 0 && kh_n > 0)
-                amask[i] = ((0xFFFFFFFFu >> (32 - kw_n)) << kw_lo) *
-                           (gm.row_taps & ((0xFFFFFFFFu >> (32 - kh_n * gm.KW)) << (kh_lo * gm.KW)));
+                v.y = ~(((0xFFFFFFFFu >> (32 - kw_n)) << kw_lo) *
+                        (gm.row_taps & ((0xFFFFFFFFu >> (32 - kh_n * gm.KW)) << (kh_lo * gm.KW))));
         }
-    }
-    uint32_t bbase[kLB];
-#pragma unroll
-    for (int i = 0; i < kLB; ++i) {
-        const int n = bn + (4 * i + wave) * 16 + lrow;
-        bbase[i] = n < gm.Cout ? (uint32_t)n * kwords * 4 : kOut;
-    }
-
-    // Where a K step's chunks come from is the same for every row and every block: for (step, chunk) the byte offset of
-    // the chunk from a pixel's (ih0, iw0, 0), its offset inside a filter row, and its tap; steps past the end of K are
-    // marked invalid (their loads read nothing and write zeros).  The steps of the ring's first fill are worked out by
-    // each lane for itself, so that their loads leave at once; the others come from a table in LDS, built once
-    // while those loads are in flight (body at batch 16 / 32 / 64 237.2 / 305.5 / 251.7 -> 233.0 / 305.0 / 243.8 us).
+        return v;
+    };
+    // Where a K step's chunks come from is the same for every row: for (step, chunk) the byte offset of the chunk from a
+    // pixel's (ih0, iw0, 0) and its tap.  Chunks past the end of K get tap 31, which is outside the image for every row:
+    // there are such chunks only where K is no whole number of steps, i.e. with fewer than 32 taps (32 of them are
+    // 128 words or more).  Steps past the end repeat the last one.
     auto entry = [&](int step, int ch) {
-        const int kw0 = step * kStepWords + ch * 4;   // first word of the chunk
-        uint2 v = make_uint2(0u, 0xFFFFFFFFu);
+        const int kw0 = min(step, gsteps - 1) * kStepWords + ch * 4;   // first word of the chunk
+        uint2 v = make_uint2(0u, 31u);
         if (kw0 < kwords) {
             const int tap = div_by(kw0, cw, gm.mg_cw, gm.fastdiv), cword = kw0 - tap * cw;
             const int kh = div_by(tap, gm.KW, gm.mg_kw, gm.fastdiv), kwi = tap - kh * gm.KW;
             v.x = (uint32_t)(((kh * gm.W + kwi) * cw + cword) * 4);
-            v.y = (uint32_t)(kw0 * 4) | ((uint32_t)tap << 26);
+            v.y = (uint32_t)tap;
         }
         return v;
     };
-    uint32_t poff[kL];
-    auto place = [&](const uint2 e) {
-        const bool kin = (e.y >> 31) == 0;
-        const uint32_t tap = (e.y >> 26) & 31u, kw4 = e.y & 0x03FFFFFFu;
+    // (the rows' table is in the third slot of a ring, which is empty until the K loop, where there is one)
+    __shared__ uint2 rows_apart[ST == 3 ? 1 : BM];
+    uint2* const rowtab = ST == 3 ? reinterpret_cast<uint2*>(ring + 2 * kStageBytes) : rows_apart;
+    if (t < BM) rowtab[t] = pixel(bm + t);
+    for (int e = kThreads - 1 - t; e < (steps + 3) * KS * 4; e += kThreads) steptab[e] = entry(e >> 2, e & 3);
+    __syncthreads();
+    uint32_t abase[kLA], aout[kLA];
+#pragma unroll
+    for (int i = 0; i < kLA; ++i) {
+        const uint2 v = rowtab[(G * i + wave) * 16 + lrow];
+        abase[i] = v.x;
+        aout[i] = v.y;
+    }
+    const uint2 e0 = steptab[grp * 4 + chunk], e1 = steptab[(KS + grp) * 4 + chunk];
+    auto issue_a = [&](const uint2 e, int slot) {
 #pragma unroll
         for (int i = 0; i < kLA; ++i) {
-            const bool in = kin && ((amask[i] >> tap) & 1u);
-            poff[i] = in ? (uint32_t)(abase[i] + (int)e.x) : kOut;
+            const uint32_t miss = (uint32_t)__builtin_amdgcn_sbfe((int)aout[i], e.y, 1);   // 0, or all ones: an offset past every buffer
+            dma16(ra, (abase[i] + e.x) | (miss << 4), lds0 + slot * kStageBytes + (G * i + wave) * 1024);
         }
-#pragma unroll
-        for (int i = 0; i < kLB; ++i) poff[kLA + i] = kin ? bbase[i] + kw4 : kOut;
     };
-    int pstep = kStages - 1;
-    uint2 pent;   // entry of the next step to plan, read one step ahead
-    auto plan = [&]() {
-        const uint2 e = pent;
-        ++pstep;
-        pent = steptab[(pstep * KS + grp) * 4 + chunk];
-        place(e);
-    };
-    auto issue = [&](int i, int slot) {
-        if (i < kLA)
-            dma16(ra, poff[i], lds0 + slot * kStageBytes + (4 * i + wave) * 1024);
-        else
-            dma16(rw, poff[i], lds0 + slot * kStageBytes + BM * 64 + (4 * (i - kLA) + wave) * 1024);
-    };
+    issue_a(e0, 0);
+    if constexpr (kBits == 4) {
+        // the shortcut's codes go into LDS behind the first step: they then cost the end, where the multiplying has stopped, no
+        // trip to memory, and the loop no registers
+        if (fused && out.res_u4) {
+            const u32x4_t rr = make_rsrc_words(out.res_u4, (uint32_t)((size_t)gm.M * gm.Cout / 2));
+            const uint32_t r0 = lds_address(resid);
+            if (gm.Cout % 32 == 0) {   // 32 channels of a pixel per lane (16 bytes that are inside the tensor or not as a whole)
+                constexpr int kPer = BN / 32;
+                for (int c = wave_all; c < BM * kPer / 64; c += G * KS) {
+                    const int m = bm + (c * 64 + lane) / kPer, n = bn + lane % kPer * 32;
+                    dma16(rr, m < gm.M && n < gm.Cout ? (uint32_t)m * (uint32_t)(gm.Cout / 2) + (uint32_t)(n / 2) : kOut, r0 + c * 1024);
+                }
+            } else {
+                constexpr int kPer = BN / 8;
+                for (int c = wave_all; c < BM * kPer / 64; c += G * KS) {
+                    const int m = bm + (c * 64 + lane) / kPer, n = bn + lane % kPer * 8;
+                    dma4(rr, m < gm.M && n < gm.Cout ? (uint32_t)m * (uint32_t)(gm.Cout / 2) + (uint32_t)(n / 2) : kOut, r0 + c * 256);
+                }
+            }
+        }
+    }
+    issue_a(e1, 1);
+    // (bytes: columns fixed per thread, see the stores)
+    const int nq = (t % (BN / 4)) * 4;
+    float4 sc = make_float4(0.f, 0.f, 0.f, 0.f), bi = sc;
+    if (kBits == 8 && out.y && gm.Cout % 4 == 0 && bn + nq < gm.Cout) {
+        sc = *reinterpret_cast<const float4*>(out.scale + bn + nq);
+        bi = *reinterpret_cast<const float4*>(out.bias + bn + nq);
+    }
 
     // Fragment reads for the 32 x 32 x 32 MFMA (a wave issuing only 16 x 16 x 64 ones reaches 0.6 of
     // the matrix rate, measured): lane (r32, kh) supplies 16 codes of row r32 to each MFMA, as
@@ -406,29 +476,27 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
 #pragma unroll
     for (int u = 0; u < 2; ++u) foff[u] = r32 * 64 + (((2 * u + kh) ^ swz) << 4);
 
-    i32x16_t acc[kUM][kUN][kAccs];
+    i32x16_t acc[UM][UN];
 #pragma unroll
-    for (int i = 0; i < kUM; ++i)
+    for (int i = 0; i < UM; ++i)
 #pragma unroll
-        for (int j = 0; j < kUN; ++j)
+        for (int j = 0; j < UN; ++j)
 #pragma unroll
-            for (int c = 0; c < kAccs; ++c)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][c][r] = 0;
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
-    i32x4_t af[2][kUM][2], bf[2][kUN][2];
+    i32x4_t af[2][UM][2], bf[2][UN][2];
     auto fetch = [&](int slot, int sub, int reg) {
-        const unsigned char* As = smem + slot * kStageBytes + wm * (BM / 2) * 64;
-        const unsigned char* Bs = smem + slot * kStageBytes + BM * 64 + wn * (BN / 2) * 64;
+        const unsigned char* As = smem + slot * kStageBytes + wm * (32 * UM) * 64;
+        const unsigned char* Bs = smem + slot * kStageBytes + BM * 64 + wn * (32 * UN) * 64;
         if constexpr (kBits == 4) {
 #pragma unroll
-            for (int i = 0; i < kUM; ++i) {
+            for (int i = 0; i < UM; ++i) {
                 const uint4 p = *reinterpret_cast<const uint4*>(As + foff[sub] + i * 32 * 64);
                 af[reg][i][0] = widen_a(p.x, p.y);
                 af[reg][i][1] = widen_a(p.z, p.w);
             }
 #pragma unroll
-            for (int j = 0; j < kUN; ++j) {
+            for (int j = 0; j < UN; ++j) {
                 const uint4 p = *reinterpret_cast<const uint4*>(Bs + foff[sub] + j * 32 * 64);
                 bf[reg][j][0] = widen_b(p.x, p.y);
                 bf[reg][j][1] = widen_b(p.z, p.w);
@@ -437,10 +505,10 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                for (int i = 0; i < kUM; ++i)
+                for (int i = 0; i < UM; ++i)
                     af[reg][i][h] = *reinterpret_cast<const i32x4_t*>(As + foff[h] + i * 32 * 64);
 #pragma unroll
-                for (int j = 0; j < kUN; ++j)
+                for (int j = 0; j < UN; ++j)
                     bf[reg][j][h] = *reinterpret_cast<const i32x4_t*>(Bs + foff[h] + j * 32 * 64);
             }
         }
@@ -449,14 +517,13 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int i = 0; i < kUM; ++i)
+            for (int i = 0; i < UM; ++i)
 #pragma unroll
-                for (int j = 0; j < kUN; ++j)
-                    acc[i][j][h % kAccs] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[reg][j][h], af[reg][i][h],
-                                                                                 acc[i][j][h % kAccs], 0, 0, 0);
+                for (int j = 0; j < UN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[reg][j][h], af[reg][i][h], acc[i][j], 0, 0, 0);
         // issue order: the LDS reads and the widening of the next fragments go between the MFMAs
-        constexpr int kM = 2 * kUM * kUN, kF = 2 * (kUM + kUN);   // MFMAs, operand fragments
-        constexpr int kR = kBits == 4 ? kF / 2 : kF;               // LDS reads (4-bit: one per two fragments)
+        constexpr int kM = 2 * UM * UN, kF = 2 * (UM + UN);   // MFMAs, operand fragments
+        constexpr int kR = kBits == 4 ? kF / 2 : kF;           // LDS reads (4-bit: one per two fragments)
         constexpr int kRead = (kR + kM - 1) / kM;
 #pragma unroll
         for (int u = 0; u < kM; ++u) {
@@ -466,194 +533,278 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
         }
     };
 
-    // steps 0 and 1 up front, then step s + 2 during step s
-#pragma unroll
-    for (int p = 0; p < kStages - 1; ++p) {
-        place(entry(p * KS + grp, chunk));
-#pragma unroll
-        for (int i = 0; i < kL; ++i) issue(i, p);
+    // Fused output, in units of the output step: u = (16 acc) c1 + c0 + shortcut with c1 = fl(scale fl(1 / s)) / 16 and
+    // c0 = fl(bias fl(1 / s)) takes two roundings where the reference (fused_value, fused_code) takes three and a division.  With e = 2^-24
+    // and B, C the magnitudes of bias and shortcut over s, the two differ by less than e (3 |acc scale / s| + 2 B + 3 C + the
+    // partial sums) <= 8 e (|u| + B + C), so where u (clamped to 0 .. 15) is further than 2^-21 (16 + B + C), and an eighth
+    // more for the terms of second order, from a half-integer, both round to the same code; `limit` keeps one half minus that
+    // for each word of eight channels.  Nothing overflows on either path as long as c1, B and C are small against 2^100 and s
+    // is between 2^-100 and 2^100 (quick).  Other words are worked out as the reference does.
+    if (fused && t < BN) {   // (whole waves, each with what it loaded itself: in flight behind it are two steps, and at most the shortcut)
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kL) : "memory");
+        const float inv = out.inv_s_out, c1 = chan[0][t] * inv, c0 = chan[1][t] * inv;
+        chan[2][t] = c1 * 0.0625f;
+        chan[3][t] = c0;
+        // 2^100 stands for what may not be quick at all, a NaN among it
+        float bias = __builtin_fabsf(c1) < 0x1p100f && __builtin_fabsf(c0) < 0x1p100f ? __builtin_fabsf(c0) : 0x1p100f;
+        bias = fmaxf(bias, dpp<0xB1>(bias));    // the word's eight lanes: neighbours, pairs, quads
+        bias = fmaxf(bias, dpp<0x4E>(bias));
+        bias = fmaxf(bias, dpp<0x141>(bias));
+        const float lim = 0.5f - 0x1.2p-21f * (16.f + bias + (out.res_u4 ? 15.f * __builtin_fabsf(out.res_scale * inv) : 0.f));
+        if (t % 8 == 0) limit[t / 8] = out.quick && lim > 0.25f ? lim : -1.f;
     }
-    for (int e = t; e < (steps + kStages) * KS * 4; e += kThreads) steptab[e] = entry(e >> 2, e & 3);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kL));
+
+    // in flight: weights of steps 0 and 1, pixels of step 0, the shortcut, pixels of step 1
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kLA));
     __syncthreads();
-    pent = steptab[(pstep * KS + grp) * 4 + chunk];
+    int pstep = 2;
+    uint2 pent = steptab[(pstep * KS + grp) * 4 + chunk];   // the next step to load, its entry read one step ahead
     fetch(0, 0, 0);
 
-    // What the epilogue needs of scales, biases and shortcut.  Requested behind the ring's first steps, it does not cost the end, where the
-    // multiplying has stopped, a trip to memory: nothing in the ResNet-34 body, 4 % of plain outputs of 1 x 1 filters (64 to 128
-    // channels, 32 x 56 x 56 6.32 -> 6.06 us).  Blocks that split K between groups of waves request it at the end: there the K loop
-    // as compiled with the requests in front of it was 2 to 4 % slower, for every kind of output (512 channels at batch 16
-    // 8.62 us against 8.29, 5 x 5 of 512 at 800 pixels 17.0 against 16.2; body at batch 16 / 32 / 64 237.1 / 308.0 / 247.2
-    // against 233.0 / 305.0 / 243.8).
-    // A thread writes the same columns in every iteration of the epilogue's store loops (the block's
-    // thread count is a multiple of the pieces per row).
-    constexpr int kWordsPerRow = BN / 8, kQuadsPerRow = BN / 4;
-    static_assert(kThreads % kWordsPerRow == 0 && kThreads % kQuadsPerRow == 0, "columns fixed per thread");
-    constexpr int kItF = (kPassRows * kWordsPerRow + kThreads - 1) / kThreads;
-    const int n0f = bn + (t % kWordsPerRow) * 8, n0q = bn + (t % kQuadsPerRow) * 4;
-    const bool vec = (gm.Cout % 4) == 0;
-    float scf[8], bif[8];
-    float4 scq = make_float4(0.f, 0.f, 0.f, 0.f), biq = scq;
-    uint32_t rwf[kPasses][kItF];
-    const bool fused = kBits == 4 && out.out_u4;   // (bytes have plain outputs only)
-    auto request = [&]() {
-        if (fused) {
-            if (n0f < gm.Cout) {
-                load8(out.scale + n0f, scf);
-                load8(out.bias + n0f, bif);
-            }
-            if (out.res_u4) {
-#pragma unroll
-                for (int pass = 0; pass < kPasses; ++pass)
-#pragma unroll
-                    for (int it = 0; it < kItF; ++it) {
-                        const int idx = t + it * kThreads;
-                        const int m = bm + pass * kPassRows + idx / kWordsPerRow;
-                        rwf[pass][it] = (idx < kPassRows * kWordsPerRow && m < gm.M && n0f < gm.Cout)
-                                            ? out.res_u4[(size_t)m * (gm.Cout / 8) + n0f / 8] : 0u;
-                    }
-            }
-        } else if (out.y && vec && n0q < gm.Cout) {
-            scq = *reinterpret_cast<const float4*>(out.scale + n0q);
-            biq = *reinterpret_cast<const float4*>(out.bias + n0q);
-        }
+    // slot of step s + 2: with three slots step s - 1 had it, whose last reads were issued before the previous barrier; with
+    // two step s itself, whose last reads every wave has issued (and waited for) at the step's barrier
+    auto refill = [&](int slot) {
+        const uint2 e = pent;
+        issue_w(pstep * KS + grp, slot);
+        ++pstep;
+        pent = steptab[(pstep * KS + grp) * 4 + chunk];
+        issue_a(e, slot);
     };
-    if constexpr (KS == 1) request();
-
+    // in flight at a step's wait: step s + 1 and, with three slots, step s + 2
     if constexpr (kBits == 4) {
-        for (int s0 = 0; s0 < steps; s0 += kStages) {
+        const int halves = (kwords + kStepWords / 2 - 1) / (kStepWords / 2);   // half-steps of the whole problem
+        for (int s0 = 0; s0 < steps; s0 += ST) {
 #pragma unroll
-            for (int u = 0; u < kStages; ++u) {
+            for (int u = 0; u < ST; ++u) {
                 if (s0 + u >= steps) break;
-                const int cur = u, nxt = (u + 1) % kStages, fill = (u + 2) % kStages;
+                const int cur = u, nxt = (u + 1) % ST, fill = (u + 2) % ST;
+                const int left = halves - 2 * ((s0 + u) * KS + grp);
                 __builtin_amdgcn_sched_barrier(0);
                 fetch(cur, 1, 1);
-                multiply(0);
+                if (KS == 1 || left > 0) multiply(0);
                 __builtin_amdgcn_sched_barrier(0);
-                // slot `fill` held step s - 1, whose last reads were issued before the previous barrier
-                plan();
-#pragma unroll
-                for (int i = 0; i < kL; ++i) issue(i, fill);
-                // in flight: step s + 1 (issued one step ago) and step s + 2 (just issued)
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm(kL));
+                if (ST == 3) refill(fill);
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(ST == 3 ? kL : 0));
                 __syncthreads();
+                if (ST == 2) refill(fill);
                 __builtin_amdgcn_sched_barrier(0);
                 fetch(nxt, 0, 0);
-                multiply(1);
+                if (left > 1) multiply(1);
             }
         }
     } else {
-        // one MFMA step per K step: the operand registers alternate with the step's parity, so
-        // the ring of three is unrolled twice
-        for (int s0 = 0; s0 < steps; s0 += 2 * kStages) {
+        // one MFMA step per K step: the operand registers alternate with the step's parity, so a ring of three is unrolled twice
+        constexpr int kTurn = ST % 2 ? 2 * ST : ST;
+        for (int s0 = 0; s0 < steps; s0 += kTurn) {
 #pragma unroll
-            for (int u = 0; u < 2 * kStages; ++u) {
+            for (int u = 0; u < kTurn; ++u) {
                 if (s0 + u >= steps) break;
-                const int nxt = (u + 1) % kStages, fill = (u + 2) % kStages, reg = u & 1;
+                const int nxt = (u + 1) % ST, fill = (u + 2) % ST, reg = u & 1;
+                const int left = gsteps - ((s0 + u) * KS + grp);
                 __builtin_amdgcn_sched_barrier(0);
-                plan();
-#pragma unroll
-                for (int i = 0; i < kL; ++i) issue(i, fill);
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm(kL));
+                if (ST == 3) refill(fill);
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(ST == 3 ? kL : 0));
                 __syncthreads();
+                if (ST == 2) refill(fill);
                 __builtin_amdgcn_sched_barrier(0);
                 fetch(nxt, 0, reg ^ 1);
-                multiply(reg);
+                if (KS == 1 || left > 0) multiply(reg);
             }
         }
     }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // nothing may still be writing LDS
-    __syncthreads();
 
-    // Epilogue: the accumulators (all rows at once if they fit, else half the rows at a time)
-    // are staged in LDS (pitch BN + 4 words: the 16-byte writes of eight neighbouring pixels fall on different banks) and
-    // leave as whole pieces of rows.
-    if constexpr (KS > 1) request();
-    int32_t* const stage = reinterpret_cast<int32_t*>(smem);
+    // Epilogue.  Piece p of the wave's tile: block (i, j), quad q (registers 4 q ..: channels 8 q + 4 kh + 0..3 of pixel r32); two neighbouring
+    // pieces are quads q and q + 2 of a block.
+    auto piece = [&](int o, int& i, int& j, int& q) {   // the wave's own piece o
+        const int p = KS == 1 ? o : grp * kOwn + o;
+        i = p / (4 * UN);
+        j = p / 4 % UN;
+        q = p % 4 / 2 + 2 * (p % 2);
+    };
+    auto quad = [&](int p) {
+        const i32x16_t& v = acc[p / (4 * UN)][p / 4 % UN];
+        const int at = 4 * (p % 4 / 2 + 2 * (p % 2));
+        return i32x4_t{v[at], v[at + 1], v[at + 2], v[at + 3]};
+    };
+    // What a lane has of own piece o once the halves of the wave have changed places (see below): its first channel and row in the tile.
+    constexpr int kE = kOwn == 1 ? 4 : 8;   // channels of a lane at a time
+    auto at_lane = [&](int o, int& nl, int& row) {
+        int i, j, q;
+        piece(o, i, j, q);
+        nl = (wn * UN + j) * 32 + 8 * q + (kE == 8 ? 16 * kh : 4 * kh);
+        row = (wm * UM + i) * 32 + r32;
+    };
+    const bool res_codes = out.res_u4 != nullptr, res_floats = out.res_f32 != nullptr;
+    float r[4 * kOwn];   // a real-valued shortcut, requested before the pieces change hands where K is split
+    auto request = [&](int o) {
+        int nl, row;
+        at_lane(o, nl, row);
+        const bool in = bm + row < gm.M && bn + nl < gm.Cout;
 #pragma unroll
-    for (int pass = 0; pass < kPasses; ++pass) {
-        if (pass) __syncthreads();  // the previous pass has been read
-        if (kPasses == 1 || wm == pass) {
-            const int rbase = kPasses == 1 ? wm * (BM / 2) : 0;
-            // register r of lane (r32, kh) is pixel r32, channel 8 (r / 4) + 4 kh + r % 4 of the wave's 32 x 32 block
+        for (int e = 0; e < kE; e += 4) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (in) v = *reinterpret_cast<const float4*>(out.res_f32 + (size_t)(bm + row) * gm.Cout + bn + nl + e);
+            r[4 * o + e] = v.x; r[4 * o + e + 1] = v.y; r[4 * o + e + 2] = v.z; r[4 * o + e + 3] = v.w;
+        }
+    };
+    if (KS > 1 && fused && res_floats) {
 #pragma unroll
-            for (int i = 0; i < kUM; ++i)
+        for (int o = 0; o < kOwn; o += kE / 4) request(o);
+    }
+    i32x4_t own[kOwn];
+    if constexpr (KS == 1) {
 #pragma unroll
-                for (int j = 0; j < kUN; ++j)
+        for (int o = 0; o < kOwn; ++o) own[o] = quad(o);
+    } else {
+        __syncthreads();   // the rings have been read
+        unsigned char* const hand = ring + wave * ((KS - 1) * kQuads * 1024) + lane * 16;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        i32x4_t v;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int r = 4 * q + e;
-                            v[e] = kAccs == 2 ? acc[i][j][0][r] + acc[i][j][kAccs - 1][r] : acc[i][j][0][r];
-                            if (kBits == 4) v[e] >>= 4;  // 4-bit: the accumulator is 16 * result
-                        }
-                        *reinterpret_cast<i32x4_t*>(&stage[(rbase + i * 32 + r32) * kSPitch + wn * (BN / 2) + j * 32 + 8 * q + 4 * kh]) = v;
-                    }
+        for (int p = 0; p < kQuads; ++p) {
+            const int owner = p / kOwn;
+            if (owner != grp)
+                *reinterpret_cast<i32x4_t*>(hand + ((owner * (KS - 1) + (grp < owner ? grp : grp - 1)) * kOwn + p % kOwn) * 1024) = quad(p);
         }
         __syncthreads();
-        if (fused) {
-            // fused output: 8 consecutive channels of a pixel -> one packed word
 #pragma unroll
-            for (int it = 0; it < kItF; ++it) {
-                const int idx = t + it * kThreads;
-                if (idx >= kPassRows * kWordsPerRow) break;
-                const int row = idx / kWordsPerRow, wd = idx % kWordsPerRow;
-                const int m = bm + pass * kPassRows + row, n0 = n0f;
-                if (m >= gm.M || n0 >= gm.Cout) continue;
-                i32x4_t v0 = {0, 0, 0, 0}, v1 = {0, 0, 0, 0};
+        for (int g = 0; g < KS; ++g)
+            if (grp == g) {
 #pragma unroll
-                for (int g = 0; g < KS; ++g) {
-                    const int32_t* sg = reinterpret_cast<const int32_t*>(smem_all + g * kGroupBytes);
-                    v0 += *reinterpret_cast<const i32x4_t*>(&sg[row * kSPitch + wd * 8]);
-                    v1 += *reinterpret_cast<const i32x4_t*>(&sg[row * kSPitch + wd * 8 + 4]);
-                }
-                const int av[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                float r[8];
-                if (out.res_u4) {
-                    shortcut_from_codes(rwf[pass][it], out.res_scale, r);
-                } else if (out.res_f32) {
-                    load8(out.res_f32 + (size_t)m * gm.Cout + n0, r);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) r[e] = 0.f;
-                }
-                out.out_u4[(size_t)m * (gm.Cout / 8) + n0 / 8] = fused_pack(av, scf, bif, r, out);
+                for (int o = 0; o < kOwn; ++o) own[o] = quad(g * kOwn + o);
             }
-        } else {
-            // plain outputs: 4 consecutive channels per thread, 16-byte stores when Cout allows
-            for (int idx = t; idx < kPassRows * kQuadsPerRow; idx += kThreads) {
-                const int row = idx / kQuadsPerRow, qd = idx % kQuadsPerRow;
-                const int m = bm + pass * kPassRows + row, n0 = bn + qd * 4;
-                if (m >= gm.M || n0 >= gm.Cout) continue;
-                i32x4_t v = {0, 0, 0, 0};
 #pragma unroll
-                for (int g = 0; g < KS; ++g)
-                    v += *reinterpret_cast<const i32x4_t*>(
-                        &reinterpret_cast<const int32_t*>(smem_all + g * kGroupBytes)[row * kSPitch + qd * 4]);
-                store_plain(v, out, (size_t)m * gm.Cout + n0, n0, gm.Cout, scq, biq);
+        for (int s = 0; s < KS - 1; ++s)
+#pragma unroll
+            for (int o = 0; o < kOwn; ++o)
+                own[o] += *reinterpret_cast<const i32x4_t*>(hand + ((grp * (KS - 1) + s) * kOwn + o) * 1024);
+    }
+
+    if (fused) {
+        const float cr = out.res_scale * out.inv_s_out;
+#pragma unroll
+        for (int o = 0; o < kOwn; o += kE / 4) {
+            int nl, row;
+            at_lane(o, nl, row);
+            int av[kE];
+            // Two pieces: the halves of the wave change places, so that lanes 0-31 have the eight channels of quad q, the
+            // others those of quad q + 2.  (Four channels at a time, with their packed codes changing places, was 2-3 % slower.)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (kE == 8) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)own[o][e], (unsigned)own[o + 1][e], false, false);
+                    av[e] = (int)sw[0];
+                    av[4 + e] = (int)sw[1];
+                } else {
+                    av[e] = own[o][e];
+                }
+            }
+            const int nw = kE == 8 ? nl : nl - 4 * kh, m = bm + row, n0 = bn + nw;   // (the lane's word begins at nw)
+            const bool in = m < gm.M && n0 < gm.Cout;
+            float c1[kE], c0[kE], u[kE], q[kE], worst = 0.f, lim = limit[nl / 8];
+            load_floats(&chan[2][nl], c1);
+            load_floats(&chan[3][nl], c0);
+#pragma unroll
+            for (int e = 0; e < kE; ++e) u[e] = fmaf((float)av[e], c1[e], c0[e]);
+            uint32_t rw8 = 0;
+            if (res_codes) {
+                rw8 = *reinterpret_cast<const uint32_t*>(resid + row * (BN / 2) + nw / 2);
+                if (kE == 4) rw8 >>= 16 * kh;
+                const uint32_t even = rw8 & 0x0F0F0F0Fu, odd = (rw8 >> 4) & 0x0F0F0F0Fu;   // a byte converts to float in one operation
+#pragma unroll
+                for (int e = 0; e < kE; ++e)
+                    u[e] = fmaf((float)((((e & 1) ? odd : even) >> (8 * (e / 2))) & 0xFFu), cr, u[e]);
+            } else if (res_floats) {
+                if constexpr (KS == 1) request(o);
+                float top = 0.f;
+#pragma unroll
+                for (int e = 0; e < kE; ++e) {
+                    u[e] = fmaf(r[4 * o + e], out.inv_s_out, u[e]);
+                    top = fmaxf(top, __builtin_fabsf(r[4 * o + e]));
+                }
+                lim -= 0x1.2p-21f * (top * out.inv_s_out);   // (C above; below zero nothing is quick)
+            }
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+                u[e] = __builtin_amdgcn_fmed3f(u[e], 0.f, 15.f);   // (0 of a NaN, as the ReLU makes of it)
+                q[e] = __builtin_rintf(u[e]);
+                worst = fmaxf(worst, __builtin_fabsf(u[e] - q[e]));
+            }
+            if (__builtin_expect(!(worst <= lim), 0)) {
+                float sc[kE], bi[kE], sh[kE];
+                load_floats(&chan[0][nl], sc);
+                load_floats(&chan[1][nl], bi);
+                shortcut_from_codes(rw8, res_codes ? out.res_scale : 0.f, sh);
+                int ex[kE];
+#pragma unroll
+                for (int e = 0; e < kE; ++e) {
+                    ex[e] = av[e] >> 4;   // 4-bit: the accumulator is 16 * result
+                    if (res_floats) sh[e] = r[4 * o + e];
+                }
+                fused_codes(ex, sc, bi, sh, out, q);
+            }
+            uint32_t word = pack_codes(q);
+            if constexpr (kE == 4) {   // lanes 0-31 take the four channels of lanes 32-63 as well
+                const auto sw = __builtin_amdgcn_permlane32_swap(word, word, false, false);
+                word |= sw[1] << 16;
+            }
+            if (in && (kE == 8 || kh == 0)) out.out_u4[(uint32_t)m * (uint32_t)(gm.Cout / 8) + (uint32_t)n0 / 8u] = word;
+        }
+    } else {
+        // Plain outputs leave as whole pieces of rows, through LDS (pitch BN + 4 words: the 16-byte writes of eight neighbouring
+        // pixels fall on different banks), as many blocks of 32 rows at a time as the rings hold.  Stored from the registers, 32
+        // bytes of each of 32 rows at a time, 12.8 MB took 30 us instead of 11.
+        constexpr int kPitch = BN + 4, kFit = KS * kGroupBytes / (32 * kPitch * 4), kBlocks = UM * WM;
+        constexpr int kAtOnce = kFit < kBlocks ? kFit : kBlocks;
+        static_assert(kAtOnce >= 1 && kBlocks % kAtOnce == 0 && kThreads % (BN / 4) == 0, "whole turns; columns fixed per thread");
+        int32_t* const stage = reinterpret_cast<int32_t*>(ring);
+        const int n = bn + nq;
+        if (kBits == 4 && out.y) {
+            sc = *reinterpret_cast<const float4*>(&chan[0][nq]);
+            bi = *reinterpret_cast<const float4*>(&chan[1][nq]);
+        }
+#pragma unroll
+        for (int b0 = 0; b0 < kBlocks; b0 += kAtOnce) {
+            __syncthreads();   // the rings, the pieces handed over or the rows before have been read
+#pragma unroll
+            for (int o = 0; o < kOwn; ++o) {
+                int i, j, qd;
+                piece(o, i, j, qd);
+                const int rb = wm * UM + i - b0;
+                if (kAtOnce == kBlocks || (rb >= 0 && rb < kAtOnce)) {
+                    i32x4_t v = own[o];
+                    if (kBits == 4) v >>= 4;
+                    *reinterpret_cast<i32x4_t*>(&stage[(rb * 32 + r32) * kPitch + (wn * UN + j) * 32 + 8 * qd + 4 * kh]) = v;
+                }
+            }
+            __syncthreads();
+            for (int row = t / (BN / 4); row < kAtOnce * 32; row += kThreads / (BN / 4)) {
+                const int m = bm + b0 * 32 + row;
+                if (m >= gm.M || n >= gm.Cout) continue;
+                store_plain(*reinterpret_cast<const i32x4_t*>(&stage[row * kPitch + nq]), out, (size_t)m * gm.Cout + n, n, gm.Cout, sc, bi);
             }
         }
     }
 }
 
+// Waves on a SIMD that the registers have to leave room for: as many as the blocks that fit LDS bring, at most four.
+constexpr int conv_waves(int um_un, int waves, int slots) { return waves == 16 ? 4 : um_un >= 4 ? 2 : slots == 3 ? 3 : 4; }
+
 // One convolution per launch: grid (column tiles, row tiles).
-template <int BM, int BN, int KS, int kBits>
-__global__ __launch_bounds__(256 * KS, (KS > 1 ? 1 : (BM * BN >= 128 * 128 ? 2 : 4))) void w4a4_conv_kernel(
+template <int UM, int UN, int WM, int WN, int KS, int ST, int kBits>
+__global__ __launch_bounds__(64 * WM * WN * KS, conv_waves(UM * UN, WM * WN * KS, ST)) void w4a4_conv_kernel(
     const ConvGeom gm, const uint32_t* __restrict__ a, const uint32_t* __restrict__ w, const ConvOut out) {
-    w4a4_conv_tile<BM, BN, KS, kBits>(gm, a, w, out, blockIdx.y * BM, blockIdx.x * BN);
+    w4a4_conv_tile<UM, UN, WM, WN, KS, ST, kBits>(gm, a, w, out, blockIdx.y * (32 * UM * WM), blockIdx.x * (32 * UN * WN));
 }
 
 // Several per launch: item i is the grid's plane z = i.
-template <int BM, int BN, int KS, int kBits>
-__global__ __launch_bounds__(256 * KS, (KS > 1 ? 1 : (BM * BN >= 128 * 128 ? 2 : 4))) void w4a4_conv_batch_kernel(
-    const ConvBatch args) {
+template <int UM, int UN, int WM, int WN, int KS, int ST, int kBits>
+__global__ __launch_bounds__(64 * WM * WN * KS, conv_waves(UM * UN, WM * WN * KS, ST)) void w4a4_conv_batch_kernel(const ConvBatch args) {
+    constexpr int BM = 32 * UM * WM, BN = 32 * UN * WN;
     const ConvItem& it = args.it[blockIdx.z];
     const ConvGeom gm = it.gm;
     if ((int)blockIdx.x * BN >= gm.Cout || (int)blockIdx.y * BM >= gm.M) return;   // the grid fits the largest item
-    w4a4_conv_tile<BM, BN, KS, kBits>(gm, it.a, it.w, it.out, blockIdx.y * BM, blockIdx.x * BN);
+    w4a4_conv_tile<UM, UN, WM, WN, KS, ST, kBits>(gm, it.a, it.w, it.out, blockIdx.y * BM, blockIdx.x * BN);
 }
 
 // The same convolution for few output pixels (one or a few frames), where a tile grid leaves most of the
@@ -760,10 +911,10 @@ __device__ __forceinline__ void conv_direct_tile(const ConvGeom& gm, const uint3
     float sc[8], bi[8], res[8];
     uint32_t resw = 0;
     if (out.out_u4 && finishf) {
-        load8(out.scale + nf, sc);
-        load8(out.bias + nf, bi);
+        load_floats(out.scale + nf, sc);
+        load_floats(out.bias + nf, bi);
         if (out.res_u4) resw = out.res_u4[(size_t)mf * (gm.Cout / 8) + nf / 8];
-        else if (out.res_f32) load8(out.res_f32 + (size_t)mf * gm.Cout + nf, res);
+        else if (out.res_f32) load_floats(out.res_f32 + (size_t)mf * gm.Cout + nf, res);
     } else if (out.y && finishq && (gm.Cout % 4) == 0) {
         scq = *reinterpret_cast<const float4*>(out.scale + nq);
         biq = *reinterpret_cast<const float4*>(out.bias + nq);
@@ -800,7 +951,9 @@ __device__ __forceinline__ void conv_direct_tile(const ConvGeom& gm, const uint3
 #pragma unroll
             for (int e = 0; e < 8; ++e) res[e] = 0.f;
         }
-        out.out_u4[(size_t)mf * (gm.Cout / 8) + nf / 8] = fused_pack(q, sc, bi, res, out);
+        float code[8];
+        fused_codes(q, sc, bi, res, out, code);
+        out.out_u4[(size_t)mf * (gm.Cout / 8) + nf / 8] = pack_codes(code);
     } else {
         if (!finishq) return;
         i32x4_t v = *reinterpret_cast<const i32x4_t*>(&sums[(t / kQuadsPerRow) * kPitch + (t % kQuadsPerRow) * 4]);
@@ -909,8 +1062,9 @@ struct ConvJob {
 };
 
 // One launch of the tiled kernel for n jobs (n <= kConvBatch) that share a tile configuration.
-template <int kBits, int BM, int BN, int KS = 1>
+template <int kBits, int UM, int UN, int WM, int WN, int KS, int ST>
 void launch_tiled(const ConvJob* jobs, int n, hipStream_t st) {
+    constexpr int BM = 32 * UM * WM, BN = 32 * UN * WN, kThreads = 64 * WM * WN * KS;
     ConvBatch cb;
     int ny = 0, nx = 0;
     for (int i = 0; i < kConvBatch; ++i) {
@@ -922,9 +1076,9 @@ void launch_tiled(const ConvJob* jobs, int n, hipStream_t st) {
         }
     }
     if (kBits == 4 && n > 1)
-        hipLaunchKernelGGL((w4a4_conv_batch_kernel<BM, BN, KS, 4>), dim3(nx, ny, n), dim3(256 * KS), 0, st, cb);
+        hipLaunchKernelGGL((w4a4_conv_batch_kernel<UM, UN, WM, WN, KS, ST, 4>), dim3(nx, ny, n), dim3(kThreads), 0, st, cb);
     else
-        hipLaunchKernelGGL((w4a4_conv_kernel<BM, BN, KS, kBits>), dim3(nx, ny, 1), dim3(256 * KS), 0, st, jobs[0].gm,
+        hipLaunchKernelGGL((w4a4_conv_kernel<UM, UN, WM, WN, KS, ST, kBits>), dim3(nx, ny, 1), dim3(kThreads), 0, st, jobs[0].gm,
                            jobs[0].a, jobs[0].w, jobs[0].out);
 }
 
@@ -977,7 +1131,7 @@ ConvJob make_job(const qail_conv_desc& d, const uint32_t* a, const uint32_t* w, 
                         (size_t)gm.M * gm.Cout * 4 < 0xFFFFFFF0ull;
     job.ksteps = (gm.KH * gm.KW * (gm.Cin / kPerWord) + kStepWords - 1) / kStepWords;
     // a 16-byte chunk (32 or 16 codes) must lie inside one filter tap
-    job.tiled = d.Cin % (4 * kPerWord) == 0 && d.KH * d.KW <= 32 && fits32 && job.ksteps + 4 * (kStages + 1) <= kMaxSteps;
+    job.tiled = d.Cin % (4 * kPerWord) == 0 && d.KH * d.KW <= 32 && fits32 && job.ksteps + 16 <= kMaxSteps;
     job.a = a;
     job.w = w;
     job.out = out;
@@ -985,9 +1139,8 @@ ConvJob make_job(const qail_conv_desc& d, const uint32_t* a, const uint32_t* w, 
     return job;
 }
 
-// Launches n jobs the tiled kernel can run (n <= kConvBatch) as one grid.  The tile is chosen for
-// the job with the longest K (the one that decides how long the launch takes); whether K is split
-// between groups of waves depends on how many blocks all jobs together put on a CU.
+// Launches n jobs the tiled kernel can run (n <= kConvBatch) as one grid.  The tile is chosen for the job with the most
+// work (the one that decides how long the launch takes), as if it had as many more tiles as the others are worth in its K steps.
 template <int kBits>
 void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     int lead = 0;
@@ -995,15 +1148,10 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
         if ((long long)jobs[i].ksteps * jobs[i].gm.M > (long long)jobs[lead].ksteps * jobs[lead].gm.M) lead = i;
     const ConvGeom& gm = jobs[lead].gm;
     const int ksteps = jobs[lead].ksteps;
-    // the largest tile that still gives every CU about two blocks
-    const long long want = 2LL * device_cu_count();
-    auto blocks = [&](int bm, int bn) {
-        return (long long)((gm.M + bm - 1) / bm) * ((gm.Cout + bn - 1) / bn);
-    };
-    long long all64 = 0, all32 = 0, all16 = 0;
+    long long all64 = 0, all32 = 0, all16 = 0;   // (all64: in tiles of the lead)
     for (int i = 0; i < n; ++i) {
         all32 += (long long)((jobs[i].gm.M + 31) / 32) * ((jobs[i].gm.Cout + 31) / 32);
-        all64 += (long long)((jobs[i].gm.M + 63) / 64) * ((jobs[i].gm.Cout + 63) / 64);
+        all64 += (long long)((jobs[i].gm.M + 63) / 64) * ((jobs[i].gm.Cout + 63) / 64) * jobs[i].ksteps / ksteps;
         all16 += (long long)((jobs[i].gm.M + 15) / 16) * ((jobs[i].gm.Cout + 15) / 16);
     }
     // Few 16 x 16 tiles: the direct kernel, whose tile and K split grow with them.  It reads every operand
@@ -1025,15 +1173,37 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     const bool one_tap = gm.KH * gm.KW == 1, fused = jobs[lead].out.out_u4 != nullptr;
     if (2 * all32 <= (one_tap && fused ? 5 : 7) * cus && work <= (one_tap && (fused || kBits == 8) ? 44 : 64) * cus)
         return launch_direct<kBits, 2, 2, 4, 1>(jobs, n, st);
-    const bool wide = gm.Cout > 64;
-    // (the 128 x 128 tile already from one and a half blocks per CU: at batch 256 it takes the
-    // 512 -> 512 layers from 45.7 to 37.6 us against the 128 x 64 tile)
-    if (wide && 4 * blocks(128, 128) >= 3 * want) launch_tiled<kBits, 128, 128>(jobs, n, st);
-    else if (blocks(128, 64) >= want) launch_tiled<kBits, 128, 64>(jobs, n, st);
-    else if (wide && blocks(64, 128) >= want / 2) launch_tiled<kBits, 64, 128>(jobs, n, st);
-    else if (all64 <= device_cu_count() && ksteps >= 16) launch_tiled<kBits, 64, 64, 4>(jobs, n, st);
-    else if (all64 <= 2 * device_cu_count() && ksteps >= 8) launch_tiled<kBits, 64, 64, 2>(jobs, n, st);
-    else launch_tiled<kBits, 64, 64>(jobs, n, st);
+    // The tiled kernel's shapes, by the number t of 64 x 64 tiles per CU and the K steps (sweep of 96 convolutions with plain,
+    // 4-bit and, W8A8, plain outputs; us).  Up to one tile per CU K is split between groups of four waves with 32 x 32 each,
+    // four groups where it is long (36 steps 8.4, two groups 9.0; 18 steps 7.0 / 6.7; bytes 72 steps 8.0 / 8.5, 36 steps 6.4 /
+    // 6.2).  Up to three the same waves without a split as long as K is short (9 steps, t = 2.3, 7.9; split with 64 x 32 each 8.3),
+    // with one where it is long (18 steps, t = 1.5 / 2.7 8.7 / 11.1 against 9.3 / 11.7; at t = 2.3 12.3 against 10.9, which is the
+    // other way round up to 24 steps; 36 steps, t = 2.3 12.6 / 13.9).  Above that four waves with 64 x 32 or 32 x 64 each, whichever pads
+    // the channels less, a ring of three where all blocks fit a CU with it (t <= 6; t = 4.6, 5 steps 12.7 / 12.8, t = 3.8 9.0 / 9.4, t =
+    // 6.1 11.7 / 10.7), and from t = 6 on 128 x 128 where that pads no more (t = 6.1, 9 steps 12.8, 128 x 64 15.0; 18 steps, t = 12.2 20.4 /
+    // 22.3), unless there are only a step or two (1x1, 128 -> 512 channels 12.9, 64 x 128 10.9).  Bytes, which have no widening and so
+    // load more per unit of time, keep two slots for 64 x 128 (t = 4.6, 36 steps 11.2, three 14.8) and for up to three blocks of 128 x 128 a CU (t = 6.1,
+    // 18 steps 12.6 / 14.2; above, t = 12.2, 28.5 / 24.6), and three for 128 x 64 (t = 24.5 33.0 / 38.6).
+    const bool fits128 = (gm.Cout + 127) / 128 * 2 == (gm.Cout + 63) / 64;   // tiles 128 wide pad no more than tiles 64 wide
+    if constexpr (kBits == 4) {
+        if (all64 <= cus) return ksteps >= 24 ? launch_tiled<4, 1, 1, 2, 2, 4, 3>(jobs, n, st) : launch_tiled<4, 1, 1, 2, 2, 2, 3>(jobs, n, st);
+        if (all64 < 3 * cus) {
+            if (ksteps <= 14 || (all64 > 2 * cus && 2 * all64 <= 5 * cus && ksteps < 24)) return launch_tiled<4, 1, 1, 2, 2, 1, 2>(jobs, n, st);
+            return launch_tiled<4, 2, 1, 1, 2, 2, 2>(jobs, n, st);
+        }
+        if (fits128 && all64 >= 6 * cus && ksteps > 2) return launch_tiled<4, 2, 2, 2, 2, 1, 2>(jobs, n, st);
+        if (all64 <= 6 * cus) return fits128 ? launch_tiled<4, 1, 2, 2, 2, 1, 3>(jobs, n, st) : launch_tiled<4, 2, 1, 2, 2, 1, 3>(jobs, n, st);
+        return fits128 ? launch_tiled<4, 1, 2, 2, 2, 1, 2>(jobs, n, st) : launch_tiled<4, 2, 1, 2, 2, 1, 2>(jobs, n, st);
+    } else {
+        if (all64 <= cus) return ksteps >= 24 ? launch_tiled<8, 1, 1, 2, 2, 4, 3>(jobs, n, st) : launch_tiled<8, 1, 1, 2, 2, 2, 3>(jobs, n, st);
+        if (all64 < 3 * cus) {
+            if (ksteps <= (4 * all64 <= 7 * cus ? 12 : 20)) return launch_tiled<8, 1, 1, 2, 2, 1, 2>(jobs, n, st);
+            if (4 * all64 <= 7 * cus) return launch_tiled<8, 2, 1, 1, 2, 2, 2>(jobs, n, st);
+        }
+        if (!fits128) return launch_tiled<8, 2, 1, 2, 2, 1, 3>(jobs, n, st);
+        if (all64 < 6 * cus || ksteps <= 2) return launch_tiled<8, 1, 2, 2, 2, 1, 2>(jobs, n, st);
+        return all64 <= 12 * cus ? launch_tiled<8, 2, 2, 2, 2, 1, 2>(jobs, n, st) : launch_tiled<8, 2, 2, 2, 2, 1, 3>(jobs, n, st);
+    }
 }
 
 template <int kBits>
@@ -1061,7 +1231,7 @@ hipError_t launch_conv(const qail_conv_desc& d, const uint32_t* a, const uint32_
 ConvOut fused_out(const float* scale, const float* bias, float s_out, const uint32_t* res_u4, float res_scale,
                   const float* res_f32, uint32_t* out_u4) {
     const float inv = 1.0f / s_out;
-    const int quick = std::isnormal(s_out) && std::isnormal(inv) && s_out > 0.f;
+    const int quick = s_out >= 0x1p-100f && s_out <= 0x1p100f;   // (a normal number, and so is its reciprocal)
     return ConvOut{nullptr, scale, bias, nullptr, out_u4, res_u4, res_f32, s_out, res_scale, inv, quick};
 }
 }  // namespace

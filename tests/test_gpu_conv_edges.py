@@ -62,3 +62,77 @@ def test_set_up_and_epilogue_edges(B, s):
             want = O.fused_requant_u4(ref, scale, np.where(np.isnan(bias), -np.inf, bias), s_out, **kw)   # the ReLU makes 0 of a NaN
         assert len(np.unique(want)) >= 12
         assert np.array_equal(host(out, np.uint32).reshape(s.M, s.Cout // 8)[rows], O.pack_nibbles(want))
+
+
+# Every shape of the tiled kernel, with tiles that are cut off in both directions and a K that is no whole number of
+# steps.  Columns: K split between groups of waves or not, waves' own tile, slots of the ring.
+VARIANTS = [
+    ("four groups", 4, (12, 20, 21, 352, 72, 3, 1, 1)),
+    ("two groups of four waves", 4, (12, 20, 21, 224, 72, 3, 1, 1)),
+    ("32 x 32 a wave", 4, (24, 28, 29, 96, 72, 3, 1, 1)),
+    ("two groups of two waves", 4, (12, 28, 29, 224, 72, 3, 1, 1)),
+    ("128 x 64, three slots", 4, (48, 33, 32, 32, 40, 3, 1, 1)),
+    ("128 x 64, two slots", 4, (97, 33, 32, 32, 40, 3, 1, 1)),
+    ("64 x 128, three slots", 4, (24, 33, 32, 32, 72, 3, 1, 1)),
+    ("64 x 128, two slots", 4, (49, 33, 32, 64, 72, 1, 1, 0)),
+    ("128 x 128", 4, (49, 33, 32, 32, 72, 3, 1, 1)),
+    ("bytes, four groups", 8, (12, 20, 21, 176, 72, 3, 1, 1)),
+    ("bytes, two groups of four waves", 8, (12, 20, 21, 112, 70, 3, 1, 1)),
+    ("bytes, 32 x 32 a wave", 8, (24, 28, 29, 48, 72, 3, 1, 1)),
+    ("bytes, two groups of two waves", 8, (12, 28, 29, 112, 71, 3, 1, 1)),
+    ("bytes, 128 x 64", 8, (48, 33, 32, 48, 40, 3, 1, 1)),
+    ("bytes, 64 x 128", 8, (24, 33, 32, 48, 72, 3, 1, 1)),
+    ("bytes, 128 x 128, two slots", 8, (49, 33, 32, 48, 73, 3, 1, 1)),
+    ("bytes, 128 x 128, three slots", 8, (100, 33, 32, 32, 72, 3, 1, 1)),
+]
+
+
+@pytest.mark.parametrize("bits,dims", [v[1:] for v in VARIANTS], ids=[v[0] for v in VARIANTS])
+def test_tiled_variants(B, bits, dims):
+    import torch
+    nb, H, W, cin, cout, taps, stride, pad = dims
+    s = synth.ConvShape("v", nb, H, W, cin, cout, taps, taps, stride, pad)
+    geom = (nb, H, W, cin, cout, taps, taps, stride, pad)
+    rng = np.random.default_rng(s.K + s.M)
+    if bits == 4:
+        aw = O.pack_nibbles(synth.random_codes((nb, H, W, cin), 0, 15, 91).astype(np.uint8))
+        ww = O.pack_nibbles(synth.random_codes((cout, s.K), -7, 7, 92))   # of mean zero, so that sums of both signs come out
+        plain, acc_rows = B.qail_w4a4_gemm, O.w4a4_conv_acc_rows
+    else:
+        aw = O.pack_bytes(synth.random_codes((nb, H, W, cin), -127, 127, 93))
+        ww = O.pack_bytes(synth.random_codes((cout, s.K), -127, 127, 94))
+        plain, acc_rows = B.qail_w8a8_gemm, O.w8a8_conv_acc_rows
+    # the ends of the first and the last tiles, and pixels of all
+    rows = np.unique(np.concatenate([np.arange(130), np.arange(s.M - 130, s.M), rng.integers(0, s.M, 300)]))
+    ref = acc_rows(aw, ww, *geom, rows)
+    scale = (rng.random(cout) * 1e-2 + 1e-3).astype(np.float32)
+    bias = rng.standard_normal(cout).astype(np.float32)
+    acc = torch.full((s.M * cout,), 0x55555555, dtype=torch.int32, device="cuda")
+    y = torch.full((s.M * cout,), 7.0, device="cuda")
+    a, w, sc, bi = dev(aw), dev(ww), dev(scale), dev(bias)
+    plain(*geom, a, w, acc_out=acc, scale=sc, bias=bi, y_out=y)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(acc, np.int32).reshape(s.M, cout)[rows], ref)
+    assert np.array_equal(host(y, np.float32).reshape(s.M, cout)[rows], O.requant_f32(ref, scale, bias))
+    if bits == 8 or cout % 8:
+        return
+    # fused, with each kind of shortcut; the step at an ordinary size (both ways to a code) and beyond what is quick
+    codes = rng.integers(0, 16, size=(s.M, cout)).astype(np.uint8)
+    real = rng.standard_normal((s.M, cout)).astype(np.float32) * np.float32((ref * scale).max() / 4)
+    real.reshape(-1)[rng.integers(0, real.size, 2000)] = np.repeat(np.float32([np.inf, -np.inf, 3e38, 1e-45]), 500)
+    for power in (0, 110, -110):
+        k = np.float32(2.0) ** np.float32(power)
+        s_out, r_step = np.float32((ref * scale).max() / 18.0) * k, np.float32((ref * scale).max() / 30.0) * k
+        for res in (None, "codes", "floats"):
+            out = torch.full((s.M * cout // 8,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+            kw, okw = {}, {}
+            with np.errstate(invalid="ignore", over="ignore", under="ignore"):
+                if res == "codes":
+                    kw, okw = dict(res_u4=dev(O.pack_nibbles(codes)), res_scale=float(r_step)), dict(res_codes=codes[rows], res_scale=r_step)
+                elif res == "floats":
+                    kw, okw = dict(res_f32=dev(real * k)), dict(res_f32=(real * k)[rows])
+                B.qail_w4a4_conv_u4(*geom, a, w, dev(scale * k), dev(bias * k), float(s_out), out, **kw)
+                torch.cuda.synchronize()
+                want = O.fused_requant_u4(ref, scale * k, bias * k, s_out, **okw)
+            assert len(np.unique(want)) >= 10
+            assert np.array_equal(host(out, np.uint32).reshape(s.M, cout // 8)[rows], O.pack_nibbles(want)), (power, res)
