@@ -132,8 +132,29 @@ def lib() -> ctypes.CDLL:
         for name in EXPORTS:
             if name not in ("qail_status_string",):
                 getattr(L, name).restype = ctypes.c_int
+        _use_native(L)
         _lib = L
     return _lib
+
+
+# The marshalling of three calls in C++ (csrc/marshal.cpp): a function returns the library's status, or None for a call that is not
+# the plain case, which then goes the way below it.  Without the compiled module (another Python or torch than it was built for)
+# every call does.
+def _not_plain(*args):
+    return None
+
+
+_linear_native = _linear_batch_native = _conv_batch_native = _not_plain
+
+
+def _use_native(L: ctypes.CDLL) -> None:
+    global _linear_native, _linear_batch_native, _conv_batch_native
+    try:
+        from . import _marshal
+    except ImportError:
+        return
+    _marshal.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (L.qail_w4a16_linear, L.qail_w4a16_linear_batch, L.qail_w4a4_conv_batch)))
+    _linear_native, _linear_batch_native, _conv_batch_native = _marshal.w4a16_linear, _marshal.w4a16_linear_batch, _marshal.w4a4_conv_batch
 
 
 def status_string(status: int) -> str:
@@ -253,6 +274,11 @@ def qail_w4a16_linear(N: int, K: int, group_size: int, qweight: torch.Tensor, sc
                       workspace: Optional[torch.Tensor] = None) -> None:
     """x: bf16 [M, K]; y: bf16 [M, N]; both device tensors (torch.bfloat16 or a
     16-bit integer view of the same bits)."""
+    status = _linear_native(N, K, group_size, qweight, scales, zeros, x, y, M, workspace)
+    if status is not None:
+        if status:
+            raise QailError(status, "qail_w4a16_linear")
+        return
     G = K // group_size
     q, s = _arg(qweight, N * K // 2, "qweight"), _arg(scales, N * G * 2, "scales")
     z = _arg(zeros, N * ((G + 7) // 8) * 4, "zeros")
@@ -294,6 +320,10 @@ def qail_w4a16_batch_workspace(items, count: int, M: int) -> int:
 
 def qail_w4a16_linear_batch(items, count: int, M: int, workspace: Optional[torch.Tensor] = None,
                             stream: Optional[int] = None) -> None:
+    if stream is None and isinstance(items, ctypes.Array) and items._type_ is qail_w4a16_item:
+        status = _linear_batch_native(items, count, M, workspace)
+        if status is not None:
+            return _check(status, "qail_w4a16_linear_batch")
     wsb = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().qail_w4a16_linear_batch(items, count, M, _ptr(workspace), wsb,
                                          _stream() if stream is None else stream), "qail_w4a16_linear_batch")
@@ -377,6 +407,10 @@ def make_conv_items(entries: Sequence[dict]):
 
 
 def qail_w4a4_conv_batch(items, count: int, stream: Optional[int] = None) -> None:
+    if stream is None and isinstance(items, ctypes.Array) and items._type_ is qail_conv_item:
+        status = _conv_batch_native(items, count)
+        if status is not None:
+            return _check(status, "qail_w4a4_conv_batch")
     _check(lib().qail_w4a4_conv_batch(items, count, _stream() if stream is None else stream), "qail_w4a4_conv_batch")
 
 

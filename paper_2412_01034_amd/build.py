@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqail.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 SOURCES = ("api.hip", "quantize.hip", "w4a16_gemv.hip", "w4a16_decode4.hip", "w4a16_smallm.hip", "w4a16_midm.hip", "w4a16_gemm.hip", "w4a16_generic.hip", "w4a16_lora.hip", "w8.hip", "w8a16_gemv.hip", "train_ops.hip", "w4a4_conv.hip")
 
@@ -36,8 +37,25 @@ def _run(cmd):
     return out
 
 
+def build_marshal() -> str:
+    """Compile the binding's marshalling (csrc/marshal.cpp) against this Python and this torch."""
+    import sysconfig
+
+    import torch
+    top = os.path.dirname(torch.__file__)
+    tmp = MARSHAL + ".tmp"
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+          "-I", sysconfig.get_paths()["include"], "-I", os.path.join(top, "include"),
+          "-I", os.path.join(top, "include", "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
+          os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L", os.path.join(top, "lib"),
+          "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"])
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 def build_library(verbose: bool = False) -> str:
-    """Compile every HIP source and link libqail.so next to this file."""
+    """Compile every HIP source and link libqail.so next to this file, and the binding's marshalling beside it."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
@@ -50,8 +68,10 @@ def build_library(verbose: bool = False) -> str:
             print(out, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        marshal = ex.submit(build_marshal)
         objs = list(ex.map(compile_one, SOURCES))
+        marshal.result()
     tmp = LIB + ".tmp"
     _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, *objs])
     os.replace(tmp, LIB)
