@@ -419,10 +419,7 @@ int run_lora_batch(const qail_w4a16_item* items, const qail_lora* loras, int32_t
         return hip_status(launch_w4a16_gemv_lora(items, loras, t, kLoraStride, count, st));
     const int e = qail_w4a16_linear_batch(items, count, M, workspace, round256(base), stream);
     if (e != QAIL_OK) return e;
-    for (int i = 0; i < count; ++i)
-        if (launch_lora_up_add(items[i], loras[i], t + (size_t)i * M * kLoraStride, M, st) != hipSuccess)
-            return QAIL_ERR_HIP;
-    return QAIL_OK;
+    return hip_status(launch_lora_up_add(items, loras, t, kLoraStride, count, M, st));
 }
 
 // Scratch of the entry point that takes no workspace: device memory that exists from the

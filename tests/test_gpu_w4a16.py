@@ -544,6 +544,16 @@ def test_lora_beside_the_linear(B, M):
         assert w4a16_norm_err(y, ref, nx, nw) <= (TOL if K >= 512 else TOL_TINY_K), (N, K)
 
 
+# 7: the last block of lora_down_kernel<4> and of the up-projection is partly empty, and 20 linears take two launches.
+# 60 / 61: the last M with 64 columns that lora_down_kernel takes, the first of lora_down_tile_kernel (16 does not divide
+# 61 nor the rank 8, 512 not the 40, 1024 and 11008 columns).  513: 32 rows a block of the up-projection, and one left.
+@pytest.mark.parametrize("M,copies", [(7, 5), (60, 1), (61, 1), (513, 1)])
+def test_lora_rows_by_kernel(B, M, copies):
+    specs = copies * [(200, 4096, 128, 32, 2.0), (96, 1024, 128, 8, -0.5), (258, 11008, 128, 64, 1.0), (24, 40, 8, 16, 1.5)]
+    for (N, K, g, r, scaling), (y, ref, nx, nw) in zip(specs, _lora_run(B, specs, M, 900 + M)):
+        assert w4a16_norm_err(y, ref, nx, nw) <= (TOL if K >= 512 else TOL_TINY_K), (N, K)
+
+
 def test_lora_full_size_decode_layer_sampled(B):
     """The decode layer with rank-32 adapters as the benchmark launches it (four Llama-2-7B linears,
     M = 1, one batched call); the GPU quantises the full matrices, the oracle re-derives sampled rows."""
