@@ -12,22 +12,30 @@
 // receives column j of D.  Here product b is a stretch of k, the four rows of A are four
 // neighbouring weight rows and the four columns of B are the (up to) four rows of x:
 //
-//   lane 4b + i loads 16 bytes (32 codes) of weight row n0 + i at k = 512 c + 32 b ...,
-//   lane 4b + j reads from LDS the same 32 k of row j of x,
+//   lane 4b + i loads 32 bytes (64 codes) of weight row n0 + i at k = 1024 c + 64 b ...,
+//   lane 4b + j reads from LDS the same 64 k of row j of x,
 //
-// so that after eight chained instructions lane 4b + j holds, for i = 0..3, the dot product of
-// weight row n0 + i with row j of x over those 32 k.  A wave-wide load is four rows x 256
-// contiguous bytes.  Scale and zero-point belong to a weight row and are loaded by the lane that
+// so that after sixteen chained instructions lane 4b + j holds, for i = 0..3, the dot product of
+// weight row n0 + i with row j of x over those 64 k.  A chunk is four rows x 512 contiguous
+// bytes, in two wave-wide loads, with one load of scales and one of zero-points.  Scale and zero-point belong to a weight row and are loaded by the lane that
 // loads the row's codes; the lanes of a quad pass them to each other through DPP operands.
 // The sums over the 16 stretches b meet once per four rows (cross-lane adds), results stay in
 // registers until the wave has finished its rows.
 //
 // As in the M = 1 kernel: x is staged once per block in LDS as fp16 with a power of two per
-// 32-k stretch, together with the per-stretch sums the offsets need; a block works on rows of
+// 64-k stretch, together with the per-stretch sums the offsets need; a block works on rows of
 // one linear; one launch serves a list of linears, blocks divided by bytes; every wave keeps a
-// ring of wave-wide loads in flight with exact load waits (all loads unconditional, program
+// ring of chunks in flight with exact load waits (all loads unconditional, program
 // order = consumption order, nothing stored while loads fly); addresses are buffer descriptor
 // + scalar offset + a lane offset that never changes.
+// What bounds it: a layer's stream without any arithmetic takes 24.5 us in this form (the copy's rate: 20.6), the staging of
+// x 1.7 and the arithmetic about 3 on top when a chunk was 32 k of a lane and the ring 8 KB a wave.  64 k of a lane halve
+// the loads of scales and zero-points, the multiply-adds after the products and the scalar work per byte; two
+// chunks (4 KB) in flight a wave, 64 KB a CU, start sooner than more: a wave's first bytes queue behind all that
+// the CU has asked for.  Rows of x past M are not staged at all (their columns of D reach no output).
+// Decoder layer of a 7B model, new buffers from call to call, 32 k -> 64 k and ring of 8 -> 6 -> 4 KB, us:
+// M = 2 28.5 -> 24.5 -> 24.4 -> 23.8, M = 4 28.9 -> 25.8 -> 25.9 -> 25.7 (2 KB: 31.6); 4096 x 4096 alone,
+// M = 4 8.5 -> 7.4 -> 7.4 -> 6.6; 28672 x 4096 15.9 -> 14.0 -> 13.9 -> 12.6.
 #include <string.h>
 
 #include <atomic>
@@ -41,9 +49,11 @@ namespace {
 constexpr int kD4MaxItems = 16;
 constexpr int kD4Waves = 16;
 constexpr int kD4Threads = kD4Waves * kWave;
-constexpr int kD4Ring = 8;            // wave-wide loads (1 KB each) in flight per wave
-constexpr int kD4ChunkK = 512;        // k of a row per wave-wide load
-constexpr int kD4MaxChunks = 24;      // K <= 12288: x of four rows and its constants fit in LDS
+constexpr int kD4Sub = 2;             // wave-wide loads (1 KB each) of a chunk: 32 k of a lane each
+constexpr int kD4Ring = 2;            // chunks in flight per wave
+constexpr int kD4LaneK = 32 * kD4Sub;
+constexpr int kD4ChunkK = 16 * kD4LaneK;   // k of a row per chunk
+constexpr int kD4MaxChunks = 12;      // K <= 12288: x of four rows and its constants fit in LDS
 constexpr int kD4MaxBlocks = 4096;    // blocks of a launch that serves more than one item
 constexpr int kD4XRuns = kD4MaxChunks * (kD4ChunkK / 8) * 4 / kD4Threads;  // 8-k runs of x per thread
 
@@ -98,17 +108,16 @@ QAIL_QUAD_FMAC(3)
 __device__ __forceinline__ float sum_over_stretches(float v) {
     v += dpp_f<0x124>(v);  // row_ror:4
     v += dpp_f<0x128>(v);  // row_ror:8: the four stretches of this 16-lane row
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    v += __shfl_xor(v, 16); v += __shfl_xor(v, 32); return v;
 }
 
-// LDS map of a block (uint4 units), nc = ceil(K / 512) chunks per row:
-//   [0, nc*256)        staged activations: word e of lane L in chunk c at (c*4 + e)*64 + L
-//   then nc*64 float4  constants of lane L's stretch of chunk c at c*64 + L, with P = 2^e:
+// LDS map of a block (uint4 units), nc = ceil(K / 1024) chunks per row:
+//   [0, nc*512)        staged activations: word e of lane L in chunk c at (c*8 + e)*64 + L
+//   then nc*64 float4  constants of lane L's stretch of chunk c at c*64 + L, with P = 2^e / 2:
 //                      (P * 1024 * sum of the staged values, -P * sum of x * 2^-e, P, unused)
-// Lane L = 4b + j owns, in chunk c, the 32 k starting at 512 c + 32 b of row j of x (rows past
-// M are zero).  Its staged word e holds those k's 8e..8e+7 as fp16 in the order
+// Lane L = 4b + j owns, in chunk c, the 64 k starting at 1024 c + 64 b of row j of x (rows past
+// M are not written: whatever stands there reaches only the lanes of those rows, which store nothing).
+// Its staged word e holds those k's 8e..8e+7 as fp16 in the order
 // x0,x4 | x1/16,x5/16 | x2,x6 | x3/16,x7/16 (all times 2^-e), matching the four registers the
 // weight nibbles are expanded into.  Everything past K is zero.
 __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args args) {
@@ -126,10 +135,10 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
     const int G = K / g, zwords = (G + 7) / 8, kw = K / 8;
     const int nc = (K + kD4ChunkK - 1) / kD4ChunkK;
     uint4* const xl = d4_lds;
-    float4* const consts = reinterpret_cast<float4*>(d4_lds + nc * 4 * kWave);
+    float4* const consts = reinterpret_cast<float4*>(d4_lds + nc * (4 * kD4Sub) * kWave);
 
     // x first: it is needed first and loads return in order.  Run e = 8 consecutive k of one of
-    // four rows (rows past M are zeros); the 4 threads of a quad hold the 4 runs of one stretch.
+    // four rows; eight neighbouring threads hold the 8 runs of one stretch.
     // Run e of row j at position r is bytes 16 e .. 16 e + 15 of x ([M][K], rows back to back), so the
     // request needs neither j nor r, and runs past row M lie past the end of the buffer and read zeros
     // without a fetch: every load is issued, no condition and no division stands before it.
@@ -161,42 +170,44 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
     const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(it.zr), 0, N * zwords * 4, 0x00020000);
     const int gpc = g < kD4ChunkK ? kD4ChunkK / g : 1;   // groups per chunk
     const int cpg = g < kD4ChunkK ? 1 : g / kD4ChunkK;   // chunks per group
-    const int lgrp = g < kD4ChunkK ? (32 * lb) / g : 0;  // lane part of the group index
-    const bool tail_out = (nc - 1) * kD4ChunkK + 32 * lb >= K;
+    const int lgrp = g < kD4ChunkK ? (kD4LaneK * lb) / g : 0;  // lane part of the group index
+    const bool tail_out = (nc - 1) * kD4ChunkK + kD4LaneK * lb >= K;
     // (a wave without rows asks for offsets past the end of every tensor, all below 2 GB: the range
     // check answers with zeros and fetches nothing.  Its loads are issued all the same: with the
     // ring's first loads behind a condition the compiler can no longer count the loads in flight,
     // and the staging of x below would wait for the weights as well)
     const int past = (int)0x80000000u;
-    const int qlane = nqw == 0 ? past : li * kw * 4 + 16 * lb, qlane_last = (tail_out && nqw != 0) ? li * kw * 4 : qlane;
+    const int qlane = nqw == 0 ? past : li * kw * 4 + 16 * kD4Sub * lb, qlane_last = (tail_out && nqw != 0) ? li * kw * 4 : qlane;
     const int slane = nqw == 0 ? past : li * G * 2 + lgrp * 2, slane_last = (tail_out && nqw != 0) ? li * G * 2 : slane;
-    const int zlane = nqw == 0 ? past : li * zwords * 4;
-    // the zero-point word of group (chunk part + lane part) is the chunk part's word: the lane
-    // part stays below 8 and the chunk part is a multiple of gpc (8 or a divisor of 8)
-    // (both counts are powers of two: host check)
+    // the zero-point word of group (chunk part + lane part) is the chunk part's word plus the lane part's: the chunk part is a
+    // multiple of gpc, which is 16, 8 or a divisor of 8 (both counts are powers of two: host check)
+    const int zlane = nqw == 0 ? past : li * zwords * 4 + (lgrp >> 3) * 4, zlane_last = (tail_out && nqw != 0) ? li * zwords * 4 : zlane;
     const int cpg_shift = __builtin_ctz(cpg), gpc_shift = __builtin_ctz(gpc);
     auto chunk_group = [&](int c) { return (c >> cpg_shift) << gpc_shift; };
 
-    uint4 q[kD4Ring];
+    uint4 q[kD4Ring][kD4Sub];
     uint32_t sh[kD4Ring];  // fp16 bits as loaded (zero-extended): a conversion at the load would wait there
     uint32_t zw[kD4Ring];
     int iq = 0, ic = 0;  // quad (of this wave) and chunk of the next load to issue
     auto issue = [&](int p, int iq, int ic) {
-        const int n0 = (quad0 + wave + kD4Waves * iq) * 4;
+        const int n0 = (quad0 + wave + kD4Waves * min(iq, max(nqw - 1, 0))) * 4;
         const int cg = chunk_group(ic);
         const bool last = ic == nc - 1;
-        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rq, last ? qlane_last : qlane,
-                                                                n0 * (kw * 4) + ic * (kD4ChunkK / 2), 0);
-        q[p] = make_uint4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+        for (int h = 0; h < kD4Sub; ++h) {
+            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rq, (last ? qlane_last : qlane) + 16 * h,
+                                                                    n0 * (kw * 4) + ic * (kD4ChunkK / 2), 0);
+            q[p][h] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
         sh[p] = __builtin_amdgcn_raw_buffer_load_b16(rs, last ? slane_last : slane, n0 * (G * 2) + cg * 2, 0);
-        zw[p] = __builtin_amdgcn_raw_buffer_load_b32(rz, zlane, n0 * (zwords * 4) + (cg >> 3) * 4, 0);
+        zw[p] = __builtin_amdgcn_raw_buffer_load_b32(rz, last ? zlane_last : zlane, n0 * (zwords * 4) + (cg >> 3) * 4, 0);
     };
-    // next (quad, chunk) of the stream; past its end the last load is repeated (and not consumed)
+    // next (quad, chunk) of the stream; past its end the last quad is asked for again (and not consumed)
     auto advance = [&](int& qd, int& ch) {
-        const bool last = ch == nc - 1;
-        if (!(qd == nqw - 1 && last)) {
-            ch = last ? 0 : ch + 1;
-            qd += last ? 1 : 0;
+        ++ch;
+        if (ch == nc) {
+            ch = 0;
+            ++qd;
         }
     };
 #pragma unroll
@@ -210,9 +221,9 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
     {
 #pragma unroll
         for (int u = 0; u < kD4XRuns; ++u) {
-            if (u * kD4Threads >= 4 * row_runs) break;  // block-uniform
+            if (u * kD4Threads >= M * row_runs) break;  // block-uniform
             const int e = threadIdx.x + u * kD4Threads;
-            // e / row_runs, at most 4 here (the rows past the fourth are skipped below)
+            // e / row_runs, at most 4 here (the rows past M are skipped below)
             const int j = (e >= row_runs) + (e >= 2 * row_runs) + (e >= 3 * row_runs) + (e >= 4 * row_runs);
             const int r = e - __mul24(j, row_runs);
             const uint32_t w[4] = {xr[u].x, xr[u].y, xr[u].z, xr[u].w};
@@ -226,23 +237,25 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
             }
             amax = fmaxf(amax, dpp_f<0xB1>(amax));  // quad_perm [1,0,3,2]
             amax = fmaxf(amax, dpp_f<0x4E>(amax));  // quad_perm [2,3,0,1]
+            amax = fmaxf(amax, dpp_f<0x141>(amax)); // row_half_mirror: the other quad of the stretch's eight
             // 2^-e with amax * 2^-e in [2^14, 2^15): exponent arithmetic on the bit pattern
             const int ex = (int)((__builtin_bit_cast(uint32_t, amax) >> 23) & 0xFF);
             int down = (amax > 0.f) ? (ex - 141) : 0;  // 141 = 127 + 14
             down = max(-126, min(113, down));           // keeps both exponent fields valid
             const float pre = __builtin_bit_cast(float, (uint32_t)(127 - down) << 23);
             const float pre16 = pre * 0.0625f;
-            const bool live = j < M;
             _Float16 h[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) h[t] = live ? (_Float16)(f[t] * ((t & 1) ? pre16 : pre)) : (_Float16)0.f;
+            for (int t = 0; t < 8; ++t) h[t] = (_Float16)(f[t] * ((t & 1) ? pre16 : pre));
             float se = ((float)h[0] + (float)h[4]) + ((float)h[2] + (float)h[6]);
             float so = ((float)h[1] + (float)h[5]) + ((float)h[3] + (float)h[7]);
             se += dpp_f<0xB1>(se);
             se += dpp_f<0x4E>(se);
+            se += dpp_f<0x141>(se);
             so += dpp_f<0xB1>(so);
             so += dpp_f<0x4E>(so);
-            if (j < 4) {
+            so += dpp_f<0x141>(so);
+            if (j < M) {
                 auto pk = [](_Float16 lo, _Float16 hi) {
                     typedef __attribute__((ext_vector_type(2))) _Float16 h2;
                     const h2 v = {lo, hi};
@@ -250,22 +263,23 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
                 };
                 const uint4 o = make_uint4(pk(h[0], h[4]), pk(h[1], h[5]), pk(h[2], h[6]), pk(h[3], h[7]));
                 const int c = r / (kD4ChunkK / 8), rr = r % (kD4ChunkK / 8);
-                const int L = 4 * (rr >> 2) + j, t = rr & 3;
-                xl[(c * 4 + t) * kWave + L] = o;
-                if (t == 0)
-                {
-                    const float P = __builtin_bit_cast(float, (uint32_t)(127 + down) << 23);  // exact factors
+                const int L = 4 * (rr / (4 * kD4Sub)) + j, t = rr % (4 * kD4Sub);
+                xl[(c * (4 * kD4Sub) + t) * kWave + L] = o;
+                if (t == 0) {
+                    // exact factors; half of 2^e, made good at the end: P times sums over 64 k then overflows no
+                    // earlier than 2^e times sums over 32 k would
+                    const float P = 0.5f * __builtin_bit_cast(float, (uint32_t)(127 + down) << 23);
                     consts[c * kWave + L] = make_float4(P * (1024.f * (se + so)), -P * (se + 16.f * so), P, 0.f);
                 }
             }
         }
-        // the part of the last chunk past K, for all four rows
+        // the part of the last chunk past K
         const int pad = nc * (kD4ChunkK / 8) - row_runs;  // runs per row past K
-        for (int e = threadIdx.x; e < pad * 4; e += kD4Threads) {
+        for (int e = threadIdx.x; e < pad * M; e += kD4Threads) {
             const int j = e / pad, r = row_runs + e % pad;
             const int c = r / (kD4ChunkK / 8), rr = r % (kD4ChunkK / 8);
-            const int L = 4 * (rr >> 2) + j, t = rr & 3;
-            xl[(c * 4 + t) * kWave + L] = make_uint4(0, 0, 0, 0);
+            const int L = 4 * (rr / (4 * kD4Sub)) + j, t = rr % (4 * kD4Sub);
+            xl[(c * (4 * kD4Sub) + t) * kWave + L] = make_uint4(0, 0, 0, 0);
             if (t == 0) consts[c * kWave + L] = make_float4(0.f, 0.f, 1.f, 0.f);
         }
     }
@@ -285,14 +299,16 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
     auto consume = [&](int p, int cq, int cc) {
         int xo = lane;
         asm volatile("" : "+v"(xo));  // keeps the LDS reads inside the loop
-        uint4 xv[4];
+        uint4 xv[4 * kD4Sub];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) xv[e] = xl[(cc * 4 + e) * kWave + xo];
+        for (int e = 0; e < 4 * kD4Sub; ++e) xv[e] = xl[(cc * (4 * kD4Sub) + e) * kWave + xo];
         const float4 cst = consts[cc * kWave + xo];
-        const uint32_t w[4] = {q[p].x, q[p].y, q[p].z, q[p].w};
+        uint32_t w[4 * kD4Sub];
+#pragma unroll
+        for (int h = 0; h < kD4Sub; ++h) { w[4 * h] = q[p][h].x; w[4 * h + 1] = q[p][h].y; w[4 * h + 2] = q[p][h].z; w[4 * h + 3] = q[p][h].w; }
         f32x4_t d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < 4 * kD4Sub; ++e) {
             // codes 0,4 | 16*codes 1,5 | codes 2,6 | 16*codes 3,7, each plus 1024, as fp16
             const uint32_t w8 = w[e] >> 8;
             const uint2 a01 = make_uint2((w[e] & 0x000F000Fu) | magic, (w[e] & 0x00F000F0u) | magic);
@@ -358,7 +374,7 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
         uint16_t* dst = it.y + (size_t)li * N + n0;
         uint16_t h[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16_rne(keep[i]);
+        for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16_rne(2.f * keep[i]);
         // N is a multiple of 4 (host check), so the four values are one aligned 8-byte piece of row li of y
         *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
     }
@@ -371,7 +387,7 @@ size_t d4_item_bytes(const qail_wdesc& d) {
 
 size_t d4_lds_bytes(const qail_wdesc& d) {
     const size_t nc = ((size_t)d.K + kD4ChunkK - 1) / kD4ChunkK;
-    return nc * kWave * (4 * 16 + 16);  // staged activations and per-stretch constants
+    return nc * kWave * (4 * kD4Sub * 16 + 16);  // staged activations and per-stretch constants
 }
 
 hipError_t d4_launch_chunk(const qail_w4a16_item* items, int count, int M, hipStream_t st) {
@@ -381,7 +397,7 @@ hipError_t d4_launch_chunk(const qail_w4a16_item* items, int count, int M, hipSt
     if (!attr_done.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&w4a16_decode4_kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kD4MaxChunks * kWave * (4 * 16 + 16));
+                                                 kD4MaxChunks * kWave * (4 * kD4Sub * 16 + 16));
         if (e != hipSuccess) return e;
         attr_done.store(true, std::memory_order_release);
     }
@@ -450,8 +466,8 @@ hipError_t d4_launch_chunk(const qail_w4a16_item* items, int count, int M, hipSt
 
 bool decode4_supports(const qail_wdesc& d, int M) {
     const int g = d.group_size;
-    // a chunk of 512 k holds 1, 2, 4 or 8 whole groups, or a group a power-of-two number of chunks
-    const bool groups_ok = g == 64 || g == 128 || g == 256 || (g % kD4ChunkK == 0 && (g & (g - 1)) == 0);
+    // a chunk of 1024 k holds 1, 2, 4, 8 or 16 whole groups, or a group a power-of-two number of chunks; a lane's 64 k lie in one
+    const bool groups_ok = g == 64 || g == 128 || g == 256 || (g % 512 == 0 && (g & (g - 1)) == 0);
     return M >= 2 && M <= 4 && d.N % 4 == 0 && d.K % 32 == 0 && d.K <= kD4MaxChunks * kD4ChunkK && groups_ok &&
            (unsigned long long)d.N * d.K / 2 < 0x80000000ull;  // 32-bit byte offsets in the kernel
 }

@@ -179,18 +179,31 @@ def test_matrix_core_gemm_tiles_of_many_slots(B, N, K, M):
 
 @pytest.mark.parametrize("M", [2, 3, 4])
 @pytest.mark.parametrize("N,K,g", [(4, 512, 512),         # one quad, one chunk, one group
-                                   (260, 4096, 64),       # eight groups per 512-k chunk
-                                   (128, 2048, 256),      # two groups per chunk
-                                   (64, 2048, 512),       # a group is a chunk
-                                   (36, 4096, 1024),      # a group is two chunks
+                                   (260, 4096, 64),       # sixteen groups per 1024-k chunk
+                                   (128, 2048, 256),      # four groups per chunk
+                                   (64, 2048, 512),       # two groups per chunk
+                                   (36, 4096, 1024),      # a group is a chunk
                                    (20, 12288, 128),      # the longest K of the four-row stream
-                                   (8, 4160, 64),         # K = 8.125 chunks: 14 of the last chunk's 16 stretches are empty
-                                   (24, 960, 64),         # K just short of two chunks
+                                   (8, 4160, 64),         # K = 4 chunks and 64: 15 of the last chunk's 16 stretches are empty
+                                   (24, 960, 64),         # K just short of a chunk
                                    (5000, 1152, 128),     # five quads per block
                                    (263000, 64, 64)])     # more quads than 256 blocks x 16 waves x 16 hold: extra blocks
 def test_four_row_stream_shapes(B, M, N, K, g):
     check(B, N, K, g, M, 17 * M + N + K, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005),
           tol=TOL if K >= 512 else TOL_TINY_K)
+
+
+@pytest.mark.parametrize("N,K,g", [(36, 1024, 128), (20, 3136, 64), (12, 6144, 2048)])   # whole chunks, a tail, a group of two chunks
+def test_four_row_stream_value_ranges(B, N, K, g):
+    # 64 k of x of one sign: with (q + 1024) for q their sum is 5e38 in the first row, beyond fp32, over 32 k it is not
+    rng = np.random.default_rng(K)
+    w = synth.llm_weight(N, K, 41)
+    x = rng.uniform(0.5, 1.0, size=(3, K)).astype(np.float32) * np.float32([[1e34], [1.0], [2.0 ** -100]])
+    xb = synth.f32_to_bf16_bits(x)
+    qw, s, zw = oracle_pack(w, g)
+    y = gpu_linear(B, qw, s, zw, xb, g, N, K, 3)
+    nx, nw = O.w4a16_row_norms(xb, qw, s, zw, g)
+    assert w4a16_norm_err(y, O.w4a16_linear(xb, qw, s, zw, g), nx, nw) <= TOL
 
 
 @pytest.mark.parametrize("M", [3, 7, 15, 19, 31])
