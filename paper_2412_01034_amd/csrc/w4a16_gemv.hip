@@ -497,17 +497,28 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& args, const GemvLoraAr
     const int r0 = s0 + wave;
     const int r1 = max(0, (s1 - s0 - wave + kGemvWaves - 1) / kGemvWaves);  // number of rows
 
-    // about kUnits wave-wide loads (1 KB each) in flight per wave
+    // about kUnits wave-wide loads (1 KB each) in flight per wave; rows of one unit: half of that, and a quarter where a
+    // wave has three rows or more to itself.  A wave's first bytes queue behind all that its CU has asked for, and with
+    // one row in flight the refills (one per row consumed) keep the stream up: 8 -> 4 -> 2 KB a wave, new
+    // buffers from call to call, us: the layer of a 7B model 22.0 -> 21.7 -> 21.1, 28672 x 4096 13.1 -> 12.0 -> 11.5,
+    // 12288 x 4096 7.5 -> 7.4 -> 6.8; with two rows a wave or one, 8192 x 4096 6.0 -> 5.5 -> 5.9, 4096 x 4096
+    // 4.6 -> 4.4 -> 4.5; 16384 x 2048 (half a unit a row) 6.8 -> 6.6 -> 6.8.  Rows of two units are not
+    // faster with less (4096 x 5120 5.1 -> 5.7).
     if (wide) {
         switch (nu) {
-            case 1: stream_rows<1, kUnits / 2, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
+            case 1:
+                if (it.rows_base >= 3 * kGemvWaves && K > kWaveK)
+                    stream_rows<1, kUnits / 8, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
+                else
+                    stream_rows<1, kUnits / 4, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
+                break;
             case 2: stream_rows<2, kUnits / 4, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
             default: stream_rows<3, 1, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
         }
         return;
     }
     switch (nu) {
-        case 1: stream_rows<1, kUnits, 1, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
+        case 1: stream_rows<1, kUnits / 2, 1, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
         case 2: stream_rows<2, kUnits / 2, 1, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
         case 3: stream_rows<3, kUnits / 3, 1, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
         case 4: stream_rows<4, kUnits / 4, 1, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;

@@ -177,6 +177,12 @@ def test_matrix_core_gemm_tiles_of_many_slots(B, N, K, M):
     check(B, N, K, 128, M, 7000 + M, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005))
 
 
+@pytest.mark.parametrize("N,K", [(24 * 512, 4096), (24 * 512 - 1, 4096), (12810, 2112), (12300, 2048)])
+def test_gemv_rows_in_flight(B, N, K):
+    """Three rows a wave or just not (one row in flight, or two), a row that ends inside its unit, half a unit."""
+    check(B, N, K, 64, 1, N + K, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005))
+
+
 @pytest.mark.parametrize("M", [2, 3, 4])
 @pytest.mark.parametrize("N,K,g", [(4, 512, 512),         # one quad, one chunk, one group
                                    (260, 4096, 64),       # sixteen groups per 1024-k chunk
