@@ -38,6 +38,12 @@ constexpr int kChunkK = 32;                       // k per lane per load (16 byt
 constexpr int kWaveK = kWave * kChunkK;           // 2048 k per wave-wide load
 constexpr int kGemvMaxChunks = 6;                 // K <= 12288 (more chunks would spill registers)
 constexpr int kGemvMaxK = kGemvMaxChunks * kWaveK;
+// With 64 k per lane a row may have five units (six take 146 registers: one block per CU instead of two); the stream of
+// dependent linears keeps to kGemvMaxK.  Such rows went through the generic kernel: the layer of a 13B model
+// (down-projection 5120 x 13824) 567 us -> 35, 3584 x 18944 849 -> 10.7.  They are in a kernel
+// of their own, launched only for lists that hold such a row: in one kernel for all (118 registers instead of 111) the
+// 7B layer lost 1 %, with adapters 2 %.
+constexpr int kGemvMaxWideK = 5 * 2 * kWaveK;
 constexpr int kGemvMaxBlocks = 4096;              // blocks of a launch that serves more than one item
 
 // 64 bytes, so that a block fetches everything it needs to know with one scalar load.
@@ -465,7 +471,7 @@ __device__ __forceinline__ void stream_rows(const GemvItem& it, const GemvLora* 
     }
 }
 
-template <int kUnits, bool kLora>
+template <int kUnits, bool kLora, bool kLong>
 __device__ __forceinline__ void gemv_body(const GemvArgs& args, const GemvLoraArgs& lora) {
     extern __shared__ uint4 lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform: row
@@ -513,6 +519,12 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& args, const GemvLoraAr
                     stream_rows<1, kUnits / 4, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
                 break;
             case 2: stream_rows<2, kUnits / 4, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
+            case 4:
+                if constexpr (kLong) stream_rows<4, 1, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
+                break;
+            case 5:
+                if constexpr (kLong) stream_rows<5, 1, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
+                break;
             default: stream_rows<3, 1, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{}); break;
         }
         return;
@@ -527,15 +539,15 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& args, const GemvLoraAr
     }
 }
 
-template <int kUnits>
+template <int kUnits, bool kLong>
 __global__ __launch_bounds__(kGemvThreads) void w4a16_gemv_kernel(const GemvArgs args) {
-    gemv_body<kUnits, false>(args, GemvLoraArgs{});
+    gemv_body<kUnits, false, kLong>(args, GemvLoraArgs{});
 }
 
 // The same stream with the adapters' up-projection in the final store.
-template <int kUnits>
+template <int kUnits, bool kLong>
 __global__ __launch_bounds__(kGemvThreads) void w4a16_gemv_lora_kernel(const GemvArgs args, const GemvLoraArgs lora) {
-    gemv_body<kUnits, true>(args, lora);
+    gemv_body<kUnits, true, kLong>(args, lora);
 }
 
 // Linears that depend on each other, in ONE launch.  A decoder layer's linears cannot share a
@@ -681,6 +693,7 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
         return hipSuccess;
     }
     size_t lds = 0;
+    bool any_long = false;
     int bb = 0;
     for (int i = 0; i < count; ++i) {
         const qail_w4a16_item& s = items[i];
@@ -697,14 +710,20 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
         const int nu = wide ? (s.d.K + 2 * kWaveK - 1) / (2 * kWaveK) : (s.d.K + kWaveK - 1) / kWaveK;
         const size_t need_lds = (size_t)nu * kWave * (wide ? 9 : 5) * 16;
         if (need_lds > lds) lds = need_lds;
+        any_long = any_long || (wide && nu > 3);
     }
     for (int i = count; i < kGemvMaxItems; ++i) a.it[i] = a.it[count - 1];
     if (loras) {
         GemvLoraArgs la;
         for (int i = 0; i < kGemvMaxItems; ++i) la.l[i] = loras[i < count ? i : count - 1];
-        hipLaunchKernelGGL(w4a16_gemv_lora_kernel<8>, dim3(bb), dim3(kGemvThreads), lds + 256, st, a, la);
+        if (any_long)
+            hipLaunchKernelGGL((w4a16_gemv_lora_kernel<8, true>), dim3(bb), dim3(kGemvThreads), lds + 256, st, a, la);
+        else
+            hipLaunchKernelGGL((w4a16_gemv_lora_kernel<8, false>), dim3(bb), dim3(kGemvThreads), lds + 256, st, a, la);
+    } else if (any_long) {
+        hipLaunchKernelGGL((w4a16_gemv_kernel<8, true>), dim3(bb), dim3(kGemvThreads), lds, st, a);
     } else {
-        hipLaunchKernelGGL(w4a16_gemv_kernel<8>, dim3(bb), dim3(kGemvThreads), lds, st, a);
+        hipLaunchKernelGGL((w4a16_gemv_kernel<8, false>), dim3(bb), dim3(kGemvThreads), lds, st, a);
     }
     return hipGetLastError();
 }
@@ -713,7 +732,8 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
 
 bool gemv_supports(const qail_wdesc& d) {
     // the kernel addresses each tensor through a 32-bit byte offset (codes are the largest)
-    return d.K % kChunkK == 0 && d.group_size % kChunkK == 0 && d.K <= kGemvMaxK &&
+    const bool wide = d.group_size % (2 * kChunkK) == 0 && d.K % (2 * kChunkK) == 0;
+    return d.K % kChunkK == 0 && d.group_size % kChunkK == 0 && d.K <= (wide ? kGemvMaxWideK : kGemvMaxK) &&
            (unsigned long long)d.N * d.K / 2 < 0x80000000ull;
 }
 
@@ -747,7 +767,7 @@ static int chain_grid(size_t lds) {
 
 bool gemv_chain_supports(const qail_wdesc& d) {
     // every block takes a slab of every item, a wave keeps at most 64 rows' results
-    return gemv_supports(d) && (long long)d.N <= 64LL * kGemvWaves * device_cu_count();
+    return gemv_supports(d) && d.K <= kGemvMaxK && (long long)d.N <= 64LL * kGemvWaves * device_cu_count();
 }
 
 hipError_t launch_w4a16_chain(const qail_w4a16_item* items, int count, void* ws, hipStream_t st) {

@@ -183,6 +183,17 @@ def test_gemv_rows_in_flight(B, N, K):
     check(B, N, K, 64, 1, N + K, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005))
 
 
+@pytest.mark.parametrize("N,K,g", [(70, 12352, 64),      # the first K past three units of 4096
+                                   (5, 16384, 128),      # four whole units
+                                   (333, 16448, 64),     # one stretch of the fifth
+                                   (4100, 20480, 2048),  # the longest row, two rows a wave
+                                   (40, 12320, 32)])     # 32 k per lane: still the generic kernel
+def test_gemv_long_rows(B, N, K, g):
+    check(B, N, K, g, 1, N + K, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005))
+    for (n, k, *_), (y, ref, nx, nw) in zip([(N, K), (96, 1024)], _lora_run(B, [(N, K, g, 32, 2.0), (96, 1024, 128, 8, -0.5)], 1, K)):
+        assert w4a16_norm_err(y, ref, nx, nw) <= TOL, (n, k)
+
+
 @pytest.mark.parametrize("M", [2, 3, 4])
 @pytest.mark.parametrize("N,K,g", [(4, 512, 512),         # one quad, one chunk, one group
                                    (260, 4096, 64),       # sixteen groups per 1024-k chunk
