@@ -25,6 +25,8 @@
 // four GEMVs ramp up once and finish together.
 #include <string.h>
 
+#include <atomic>
+
 #include "qail_internal.h"
 
 namespace qail {
@@ -38,12 +40,20 @@ constexpr int kChunkK = 32;                       // k per lane per load (16 byt
 constexpr int kWaveK = kWave * kChunkK;           // 2048 k per wave-wide load
 constexpr int kGemvMaxChunks = 6;                 // K <= 12288 (more chunks would spill registers)
 constexpr int kGemvMaxK = kGemvMaxChunks * kWaveK;
-// With 64 k per lane a row may have five units (six take 146 registers: one block per CU instead of two); the stream of
-// dependent linears keeps to kGemvMaxK.  Such rows went through the generic kernel: the layer of a 13B model
-// (down-projection 5120 x 13824) 567 us -> 35, 3584 x 18944 849 -> 10.7.  They are in a kernel
-// of their own, launched only for lists that hold such a row: in one kernel for all (118 registers instead of 111) the
-// 7B layer lost 1 %, with adapters 2 %.
+// With 64 k per lane a row may have five units; the stream of dependent linears keeps to kGemvMaxK.  Rows of four and five units
+// are in a kernel of their own, launched only for lists that hold such a row (in one kernel for all the 7B layer lost 1 %, with
+// adapters 2 %), and their products are those of the generic kernel, which such rows took before: x times q - z in fp32, nothing
+// scaled, nothing offset (see consume_exact).  Relative error before the last rounding, K = 12352 .. 20480, normal x / with
+// outliers / of one sign: generic 0.4 - 0.8e-6, here 0.8 - 1.2e-7; with the matrix cores of the shorter rows 2e-5 - 4e-4.  New buffers
+// from call to call, generic / here / with the matrix cores, us: layer of a 13B model 575 / 35.7 / 35.0, 3584 x 18944 781 / 14.3 / 11.8,
+// 5120 x 13824 537 / 13.3 / 11.6.
 constexpr int kGemvMaxWideK = 5 * 2 * kWaveK;
+__host__ __device__ constexpr int units_of(int K, bool wide) { return (K + kWaveK * (wide ? 2 : 1) - 1) / (kWaveK * (wide ? 2 : 1)); }
+__host__ __device__ constexpr bool exact_products(int units, bool wide) { return wide && units > 3; }
+// What the staged activations of an item take, in pieces of 16 bytes (the LDS maps are below).
+__host__ __device__ constexpr int staged_pieces(int units, bool wide) {
+    return units * kWave * (exact_products(units, wide) ? 16 : wide ? 9 : 5);
+}
 constexpr int kGemvMaxBlocks = 4096;              // blocks of a launch that serves more than one item
 
 // 64 bytes, so that a block fetches everything it needs to know with one scalar load.
@@ -202,6 +212,27 @@ __device__ __forceinline__ void stage_x(const GemvItem& it, int nu, uint4* __res
     __syncthreads();
 }
 
+// Long rows: x as it is, in fp32.  Piece j (of 16) of lane L's stretch of unit c, its k's 4j .. 4j + 3, at (c*16 + j)*64 + L;
+// zeros past K.
+template <int kMaxRuns>
+__device__ __forceinline__ void stage_x_exact(int nu, float4* __restrict__ lds, const uint4 (&xr)[kMaxRuns]) {
+    const int runs = nu * kWave * 8;
+#pragma unroll
+    for (int u = 0; u < kMaxRuns; ++u) {
+        const int i = threadIdx.x + u * kGemvThreads;
+        if (i < runs) {
+            const int c = i / (kWave * 8), r = i % (kWave * 8), L = r / 8, j = 2 * (r % 8);
+            const uint32_t w[4] = {xr[u].x, xr[u].y, xr[u].z, xr[u].w};
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                lds[(c * 16 + j + h) * kWave + L] =
+                    make_float4(__builtin_bit_cast(float, w[2 * h] << 16), __builtin_bit_cast(float, w[2 * h] & 0xFFFF0000u),
+                                __builtin_bit_cast(float, w[2 * h + 1] << 16), __builtin_bit_cast(float, w[2 * h + 1] & 0xFFFF0000u));
+        }
+    }
+    __syncthreads();
+}
+
 // Rows [r0, r1) of one item, streamed by one wave.  The wave keeps NU * kSub * kPR wave-wide
 // loads (1 KB each) in flight: a register slot is refilled with the same unit of a later
 // row as soon as its codes have been consumed.  The first loads go out before the
@@ -326,7 +357,9 @@ __device__ __forceinline__ void stream_rows(const GemvItem& it, const GemvLora* 
             xr[u] = make_uint4(v[0], v[1], v[2], v[3]);
         }
     }
-    stage_x<kMaxRuns, kSub>(it, NU, xlds, xr);
+    constexpr bool kExact = exact_products(NU, kSub == 2);
+    if constexpr (kExact) stage_x_exact<kMaxRuns>(NU, reinterpret_cast<float4*>(xlds), xr);
+    else stage_x<kMaxRuns, kSub>(it, NU, xlds, xr);
 
     // Per unit, for the lane's own stretch (written by the staging):
     //   xoff = 1024 * (sum of the staged values): what the fp16 offsets add to the MFMA result
@@ -336,7 +369,7 @@ __device__ __forceinline__ void stream_rows(const GemvItem& it, const GemvLora* 
     constexpr bool kParked = NU > 4;
     const float4* parked = reinterpret_cast<const float4*>(xlds + NU * kSub * 4 * kWave);
     float xoff[NU], xsum[NU], post[NU];
-    if (!kParked) {
+    if (!kParked && !kExact) {
 #pragma unroll
         for (int c = 0; c < NU; ++c) {
             const float4 t = parked[c * kWave + lane];
@@ -346,6 +379,8 @@ __device__ __forceinline__ void stream_rows(const GemvItem& it, const GemvLora* 
     if (nrows <= 0) return;
     uint32_t magic = 0x64006400u;   // fp16 pair (1024, 1024); held in a vector register so that
     asm volatile("" : "+v"(magic)); // the AND-OR needs only one scalar operand
+    uint32_t magic64 = 0x54005400u; // (64, 64)
+    if (kExact) asm volatile("" : "+v"(magic64));
 
     // Results stay in registers (the wave's i-th row in lane i; the launcher gives a wave at most 64
     // rows) and are stored once at the end: a store between the loads would break the
@@ -423,17 +458,68 @@ __device__ __forceinline__ void stream_rows(const GemvItem& it, const GemvLora* 
         ykeep = (lane == i) ? v : ykeep;
     };
 
+    // The same for long rows, with the generic kernel's products.  Two codes become fp16 integers q - z with an AND-OR (as 1024 + q
+    // or 64 + q, by where they stand in the word) and a packed subtraction, exactly; a mixed multiply-add per code takes its half of the
+    // pair with x in fp32.  18 operations per 8 codes where the matrix cores take 5 (27 with a conversion per code: 5120 x 13824 15.9 us);
+    // sums of 8 k meet the scale, as in the generic kernel.
+    auto consume_exact = [&](int p, int i, int next) {
+        typedef __attribute__((ext_vector_type(2))) _Float16 h2;
+        float acc = 0.f;
+        const float4* const xf = reinterpret_cast<const float4*>(xlds);
+        int xo = lane;
+        asm volatile("" : "+v"(xo));
+#pragma unroll
+        for (int c = 0; c < NU; ++c) {
+            const float s = (float)__builtin_bit_cast(_Float16, sh[p][c]);
+            const uint32_t z = ((zw[p][c] >> (4 * (goff[c] & 7))) & 0xFu) * 0x00010001u;
+            const h2 z1024 = __builtin_bit_cast(h2, 0xE400E400u | z), z64 = __builtin_bit_cast(h2, 0xD400D400u | (z << 4));   // -1024 - z, -64 - z
+#pragma unroll
+            for (int h = 0; h < kSub; ++h) {
+                const uint32_t w[4] = {q[p][c][h].x, q[p][c][h].y, q[p][c][h].z, q[p][c][h].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t w8 = w[j] >> 8;
+                    const h2 d04 = __builtin_bit_cast(h2, (w[j] & 0x000F000Fu) | magic) + z1024;
+                    const h2 d15 = __builtin_bit_cast(h2, (w[j] & 0x00F000F0u) | magic64) + z64;
+                    const h2 d26 = __builtin_bit_cast(h2, (w8 & 0x000F000Fu) | magic) + z1024;
+                    const h2 d37 = __builtin_bit_cast(h2, (w8 & 0x00F000F0u) | magic64) + z64;
+                    const float4 x0 = xf[(c * 16 + h * 8 + j * 2) * kWave + xo], x1 = xf[(c * 16 + h * 8 + j * 2 + 1) * kWave + xo];
+                    float part = x0.x * (float)d04[0];
+                    part = fmaf(x0.y, (float)d15[0], part);
+                    part = fmaf(x0.z, (float)d26[0], part);
+                    part = fmaf(x0.w, (float)d37[0], part);
+                    part = fmaf(x1.x, (float)d04[1], part);
+                    part = fmaf(x1.y, (float)d15[1], part);
+                    part = fmaf(x1.z, (float)d26[1], part);
+                    part = fmaf(x1.w, (float)d37[1], part);
+                    acc = fmaf(part, s, acc);
+                }
+                asm volatile("" : "+v"(acc), "+v"(xo));   // keeps the next piece's reads of x behind this one's
+            }
+            if (next >= 0) {
+                issue(p, c, next);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const float v = wave_sum(acc);
+        ykeep = (lane == i) ? v : ykeep;
+    };
+    auto consume_row = [&](int p, int i, int next) {
+        if constexpr (kExact) consume_exact(p, i, next);
+        else consume(p, i, next);
+    };
+
     // main part: every consumed slot is refilled with the row kPR further on (clamped in
     // the last trip); then the last kPR rows are drained without further loads
     int r = 0;
     for (; r + kPR < nrows; r += kPR) {
 #pragma unroll
         for (int p = 0; p < kPR; ++p)
-            consume(p, r + p, min(rbase + min(r + p + kPR, ilast) * kGemvWaves, it.N - 1));
+            consume_row(p, r + p, min(rbase + min(r + p + kPR, ilast) * kGemvWaves, it.N - 1));
     }
 #pragma unroll
     for (int p = 0; p < kPR; ++p)
-        if (r + p < nrows) consume(p, r + p, -1);
+        if (r + p < nrows) consume_row(p, r + p, -1);
     if (lane < nrows) {
         const int row = rbase + lane * kGemvWaves;
         float v = ykeep;
@@ -487,10 +573,10 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& args, const GemvLoraAr
     const int K = it.K, N = it.N;
     // 64 k per lane and unit where the layout allows it, else 32
     const bool wide = it.g % (2 * kChunkK) == 0 && K % (2 * kChunkK) == 0;
-    const int nu = wide ? (K + 2 * kWaveK - 1) / (2 * kWaveK) : (K + kWaveK - 1) / kWaveK;
+    const int nu = units_of(K, wide);
     // the adapter's down-projection t (at most 64 floats) sits behind the staged activations; the
     // barrier inside the staging makes it visible
-    float4* lora_t = reinterpret_cast<float4*>(lds + nu * kWave * (wide ? 9 : 5));
+    float4* lora_t = reinterpret_cast<float4*>(lds + staged_pieces(nu, wide));
     if (kLora && (int)threadIdx.x < 64)
         reinterpret_cast<float*>(lora_t)[threadIdx.x] = (int)threadIdx.x < lo->r ? lo->t[threadIdx.x] : 0.f;
 
@@ -642,6 +728,20 @@ size_t item_bytes(const qail_wdesc& d) {
     return (size_t)d.N * (d.K / 2 + G * 2 + ((G + 7) / 8) * 4);
 }
 
+// The kernels of long rows ask for more LDS than a launch gets without a word (once per process).
+hipError_t allow_long_lds() {
+    static std::atomic<bool> done{false};
+    if (done.load(std::memory_order_acquire)) return hipSuccess;
+    const void* const kernels[] = {reinterpret_cast<const void*>(&w4a16_gemv_kernel<8, true>),
+                                   reinterpret_cast<const void*>(&w4a16_gemv_lora_kernel<8, true>)};
+    for (const void* k : kernels) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, staged_pieces(5, true) * 16 + 256);
+        if (e != hipSuccess) return e;
+    }
+    done.store(true, std::memory_order_release);
+    return hipSuccess;
+}
+
 hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int count, hipStream_t st) {
     GemvArgs a;
     memset(a.item_of_block, 0, sizeof(a.item_of_block));
@@ -654,14 +754,26 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
     int grid = device_cu_count();
     if (rows_total >= 2LL * grid * kGemvWaves * 3) grid *= 2;
     if (grid < count) grid = count;
-    // blocks per item in proportion to its bytes (largest remainder), at least one each
-    double total = 0;
-    for (int i = 0; i < count; ++i) total += (double)item_bytes(items[i].d);
+    // blocks per item in proportion to its bytes (largest remainder), at least one each.  A byte of a long row takes about
+    // 1.35 times as long (exact products), which counts as long as it leaves a CU at most one block of such rows; two that meet on
+    // a CU share its vector units.  Layer of a 13B model 41.7 us -> 35.8, 4096 x 16384 + 16384 x 4096 + 4096 x 4096 with more
+    // such blocks than CUs 17.7 -> 19.0.
+    double total = 0, total_long = 0;
+    bool is_long[kGemvMaxItems], any_long = false;
+    for (int i = 0; i < count; ++i) {
+        const qail_wdesc& d = items[i].d;
+        const bool wide = d.group_size % (2 * kChunkK) == 0 && d.K % (2 * kChunkK) == 0;
+        is_long[i] = exact_products(units_of(d.K, wide), wide);
+        any_long = any_long || is_long[i];
+        (is_long[i] ? total_long : total) += (double)item_bytes(d);
+    }
+    const double long_byte = 1.35 * total_long <= total ? 1.35 : 1.0;
+    total += long_byte * total_long;
     int nb[kGemvMaxItems];
     double frac[kGemvMaxItems];
     int used = 0;
     for (int i = 0; i < count; ++i) {
-        const double share = (double)item_bytes(items[i].d) / total * grid;
+        const double share = (is_long[i] ? long_byte : 1.0) * (double)item_bytes(items[i].d) / total * grid;
         nb[i] = (int)share;
         if (nb[i] < 1) nb[i] = 1;
         // a wave keeps its results in one register: at most 64 rows per wave
@@ -693,7 +805,6 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
         return hipSuccess;
     }
     size_t lds = 0;
-    bool any_long = false;
     int bb = 0;
     for (int i = 0; i < count; ++i) {
         const qail_w4a16_item& s = items[i];
@@ -707,12 +818,14 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
         bb += nb[i];
         // staged activations and per-unit constants, as laid out by the kernel
         const bool wide = s.d.group_size % (2 * kChunkK) == 0 && s.d.K % (2 * kChunkK) == 0;
-        const int nu = wide ? (s.d.K + 2 * kWaveK - 1) / (2 * kWaveK) : (s.d.K + kWaveK - 1) / kWaveK;
-        const size_t need_lds = (size_t)nu * kWave * (wide ? 9 : 5) * 16;
+        const size_t need_lds = (size_t)staged_pieces(units_of(s.d.K, wide), wide) * 16;
         if (need_lds > lds) lds = need_lds;
-        any_long = any_long || (wide && nu > 3);
     }
     for (int i = count; i < kGemvMaxItems; ++i) a.it[i] = a.it[count - 1];
+    if (any_long) {
+        const hipError_t e = allow_long_lds();
+        if (e != hipSuccess) return e;
+    }
     if (loras) {
         GemvLoraArgs la;
         for (int i = 0; i < kGemvMaxItems; ++i) la.l[i] = loras[i < count ? i : count - 1];
@@ -777,8 +890,7 @@ hipError_t launch_w4a16_chain(const qail_w4a16_item* items, int count, void* ws,
         for (int i = 0; i < c; ++i) {
             const qail_wdesc& d = items[i0 + i].d;
             const bool wide = d.group_size % (2 * kChunkK) == 0 && d.K % (2 * kChunkK) == 0;
-            const int nu = wide ? (d.K + 2 * kWaveK - 1) / (2 * kWaveK) : (d.K + kWaveK - 1) / kWaveK;
-            const size_t need_lds = (size_t)nu * kWave * (wide ? 9 : 5) * 16;
+            const size_t need_lds = (size_t)staged_pieces(units_of(d.K, wide), wide) * 16;
             if (need_lds > lds) lds = need_lds;
         }
         int P = chain_grid(lds);

@@ -71,8 +71,8 @@ def test_config0_tiny_gemv(B):
     (33, 8192, 64),          # two 4096-k units per row (64 k per lane and unit)
     (20, 11040, 32),         # K and g not multiples of 64: 32 k per lane, six chunks, constants re-read per row
     (18, 6176, 32),          # the same with four chunks, the last nearly empty
-    (16, 12288, 128),        # largest K of the streaming kernel
-    (3, 14336, 128),         # just beyond it
+    (16, 12288, 128),        # the longest row of three units
+    (3, 14336, 128),         # four units
     (5, 40, 8),              # shape only the generic kernel takes
     (24, 32768, 256),        # K beyond the streaming kernel
 ])
@@ -192,6 +192,34 @@ def test_gemv_long_rows(B, N, K, g):
     check(B, N, K, g, 1, N + K, w_kw=dict(outlier_frac=0.01), x_kw=dict(outlier_frac=0.005))
     for (n, k, *_), (y, ref, nx, nw) in zip([(N, K), (96, 1024)], _lora_run(B, [(N, K, g, 32, 2.0), (96, 1024, 128, 8, -0.5)], 1, K)):
         assert w4a16_norm_err(y, ref, nx, nw) <= TOL, (n, k)
+
+
+@pytest.mark.parametrize("N,K,g", [(70, 12352, 64), (33, 16448, 64), (12, 20480, 2048)])
+def test_gemv_long_rows_keep_every_bit_of_x(B, N, K, g):
+    """What fp32 products give and sums of scaled or offset ones do not: values 2^24 times the others that meet weights of zero
+    leave no trace (the error is measured against the others), and an infinity gives infinities, or NaN where it meets a zero."""
+    rng = np.random.default_rng(K)
+    w = synth.llm_weight(N, K, 43)
+    quiet = np.arange(K) % 64 == 17
+    w[:, quiet] = 0.0
+    for size in (1.0, 1e36, 2.0 ** -120):   # (sums of eight x (q - z) stay finite)
+        x = (rng.standard_normal((1, K)) * size).astype(np.float32)
+        small = x.copy()
+        small[:, quiet] = 0.0
+        if size == 1.0:
+            x[:, quiet] *= 2.0 ** 24
+        qw, s, zw = oracle_pack(w, g)
+        xb = synth.f32_to_bf16_bits(x)
+        y = gpu_linear(B, qw, s, zw, xb, g, N, K, 1)
+        nx, nw = O.w4a16_row_norms(synth.f32_to_bf16_bits(small), qw, s, zw, g)
+        assert w4a16_norm_err(y, O.w4a16_linear(xb, qw, s, zw, g), nx, nw) <= TOL, size
+    x[0, 64 * (K // 64 - 1) + 5] = np.inf
+    w[3, 64 * (K // 64 - 1) + 5] = 0.0
+    qw, s, zw = oracle_pack(w, g)
+    y = (gpu_linear(B, qw, s, zw, synth.f32_to_bf16_bits(x), g, N, K, 1).astype(np.uint32) << 16).view(np.float32)[0]
+    codes, zeros = O.unpack_nibbles_u4(qw, K)[:, 64 * (K // 64 - 1) + 5], O.unpack_nibbles_u4(zw, K // g)[:, -1]
+    want = np.where(codes == zeros, np.nan, np.where(codes > zeros, np.inf, -np.inf))
+    assert np.isnan(want[3]) and np.array_equal(y, want, equal_nan=True)
 
 
 @pytest.mark.parametrize("M", [2, 3, 4])
