@@ -15,15 +15,16 @@
 //   lane 4b + i loads 32 bytes (64 codes) of weight row n0 + i at k = 1024 c + 64 b ...,
 //   lane 4b + j reads from LDS the same 64 k of row j of x,
 //
-// so that after sixteen chained instructions lane 4b + j holds, for i = 0..3, the dot product of
-// weight row n0 + i with row j of x over those 64 k.  A chunk is four rows x 512 contiguous
-// bytes, in two wave-wide loads, with one load of scales and one of zero-points.  Scale and zero-point belong to a weight row and are loaded by the lane that
-// loads the row's codes; the lanes of a quad pass them to each other through DPP operands.
+// so that after two chains of eight instructions lane 4b + j holds, for i = 0..3, the dot products of
+// weight row n0 + i with row j of x over the two halves of those 64 k.  A chunk is four rows x 512 contiguous
+// bytes, in two wave-wide loads, with one load of scales and one of zero-points.  Scale and zero-point belong to a
+// weight row and are loaded by the lane that loads the row's codes; the lanes of a quad pass them to each other through DPP
+// operands.
 // The sums over the 16 stretches b meet once per four rows (cross-lane adds), results stay in
 // registers until the wave has finished its rows.
 //
 // As in the M = 1 kernel: x is staged once per block in LDS as fp16 with a power of two per
-// 64-k stretch, together with the per-stretch sums the offsets need; a block works on rows of
+// 32-k stretch, together with the per-stretch sums the offsets need; a block works on rows of
 // one linear; one launch serves a list of linears, blocks divided by bytes; every wave keeps a
 // ring of chunks in flight with exact load waits (all loads unconditional, program
 // order = consumption order, nothing stored while loads fly); addresses are buffer descriptor
@@ -33,6 +34,9 @@
 // the loads of scales and zero-points, the multiply-adds after the products and the scalar work per byte; two
 // chunks (4 KB) in flight a wave, 64 KB a CU, start sooner than more: a wave's first bytes queue behind all that
 // the CU has asked for.  Rows of x past M are not staged at all (their columns of D reach no output).
+// Power of two and offset stay those of 32 k: over 64 an element shares them with twice as many, and what
+// the offset's rounding costs beside a large one is lost to twice as many (relative error before the last rounding, K = 1024 ..
+// 11008, normal x / of one sign: 1.2 - 1.9e-5 / 4.6 - 6.6e-5; over 64 k 1.9 - 2.8e-5 / 0.9 - 1.4e-4).
 // Decoder layer of a 7B model, new buffers from call to call, 32 k -> 64 k and ring of 8 -> 6 -> 4 KB, us:
 // M = 2 28.5 -> 24.5 -> 24.4 -> 23.8, M = 4 28.9 -> 25.8 -> 25.9 -> 25.7 (2 KB: 31.6); 4096 x 4096 alone,
 // M = 4 8.5 -> 7.4 -> 7.4 -> 6.6; 28672 x 4096 15.9 -> 14.0 -> 13.9 -> 12.6.
@@ -113,8 +117,9 @@ __device__ __forceinline__ float sum_over_stretches(float v) {
 
 // LDS map of a block (uint4 units), nc = ceil(K / 1024) chunks per row:
 //   [0, nc*512)        staged activations: word e of lane L in chunk c at (c*8 + e)*64 + L
-//   then nc*64 float4  constants of lane L's stretch of chunk c at c*64 + L, with P = 2^e / 2:
-//                      (P * 1024 * sum of the staged values, -P * sum of x * 2^-e, P, unused)
+//   then nc*64 float4  constants of the two halves (32 k each) of lane L's stretch of chunk c at c*64 + L, with P = 2^e:
+//                      (P * 1024 * sum of the staged values, P) of each
+//   then nc*64 floats  - (sum over both halves of P * sum of x * 2^-e) at c*64 + L
 // Lane L = 4b + j owns, in chunk c, the 64 k starting at 1024 c + 64 b of row j of x (rows past
 // M are not written: whatever stands there reaches only the lanes of those rows, which store nothing).
 // Its staged word e holds those k's 8e..8e+7 as fp16 in the order
@@ -135,10 +140,11 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
     const int G = K / g, zwords = (G + 7) / 8, kw = K / 8;
     const int nc = (K + kD4ChunkK - 1) / kD4ChunkK;
     uint4* const xl = d4_lds;
-    float4* const consts = reinterpret_cast<float4*>(d4_lds + nc * (4 * kD4Sub) * kWave);
+    float2* const consts = reinterpret_cast<float2*>(d4_lds + nc * (4 * kD4Sub) * kWave);   // [nc * 64][2]
+    float* const xsums = reinterpret_cast<float*>(consts + nc * kWave * kD4Sub);
 
     // x first: it is needed first and loads return in order.  Run e = 8 consecutive k of one of
-    // four rows; eight neighbouring threads hold the 8 runs of one stretch.
+    // four rows; four neighbouring threads hold the 4 runs of half a stretch.
     // Run e of row j at position r is bytes 16 e .. 16 e + 15 of x ([M][K], rows back to back), so the
     // request needs neither j nor r, and runs past row M lie past the end of the buffer and read zeros
     // without a fetch: every load is issued, no condition and no division stands before it.
@@ -237,7 +243,6 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
             }
             amax = fmaxf(amax, dpp_f<0xB1>(amax));  // quad_perm [1,0,3,2]
             amax = fmaxf(amax, dpp_f<0x4E>(amax));  // quad_perm [2,3,0,1]
-            amax = fmaxf(amax, dpp_f<0x141>(amax)); // row_half_mirror: the other quad of the stretch's eight
             // 2^-e with amax * 2^-e in [2^14, 2^15): exponent arithmetic on the bit pattern
             const int ex = (int)((__builtin_bit_cast(uint32_t, amax) >> 23) & 0xFF);
             int down = (amax > 0.f) ? (ex - 141) : 0;  // 141 = 127 + 14
@@ -251,10 +256,11 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
             float so = ((float)h[1] + (float)h[5]) + ((float)h[3] + (float)h[7]);
             se += dpp_f<0xB1>(se);
             se += dpp_f<0x4E>(se);
-            se += dpp_f<0x141>(se);
             so += dpp_f<0xB1>(so);
             so += dpp_f<0x4E>(so);
-            so += dpp_f<0x141>(so);
+            const float P = __builtin_bit_cast(float, (uint32_t)(127 + down) << 23);  // exact factors
+            float xsum = -P * (se + 16.f * so);
+            xsum += dpp_f<0x141>(xsum);   // row_half_mirror: the other half of the stretch
             if (j < M) {
                 auto pk = [](_Float16 lo, _Float16 hi) {
                     typedef __attribute__((ext_vector_type(2))) _Float16 h2;
@@ -265,12 +271,8 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
                 const int c = r / (kD4ChunkK / 8), rr = r % (kD4ChunkK / 8);
                 const int L = 4 * (rr / (4 * kD4Sub)) + j, t = rr % (4 * kD4Sub);
                 xl[(c * (4 * kD4Sub) + t) * kWave + L] = o;
-                if (t == 0) {
-                    // exact factors; half of 2^e, made good at the end: P times sums over 64 k then overflows no
-                    // earlier than 2^e times sums over 32 k would
-                    const float P = 0.5f * __builtin_bit_cast(float, (uint32_t)(127 + down) << 23);
-                    consts[c * kWave + L] = make_float4(P * (1024.f * (se + so)), -P * (se + 16.f * so), P, 0.f);
-                }
+                if (t % 4 == 0) consts[(c * kWave + L) * kD4Sub + t / 4] = make_float2(P * (1024.f * (se + so)), P);
+                if (t == 0) xsums[c * kWave + L] = xsum;
             }
         }
         // the part of the last chunk past K
@@ -280,7 +282,8 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
             const int c = r / (kD4ChunkK / 8), rr = r % (kD4ChunkK / 8);
             const int L = 4 * (rr / (4 * kD4Sub)) + j, t = rr % (4 * kD4Sub);
             xl[(c * (4 * kD4Sub) + t) * kWave + L] = make_uint4(0, 0, 0, 0);
-            if (t == 0) consts[c * kWave + L] = make_float4(0.f, 0.f, 1.f, 0.f);
+            if (t % 4 == 0) consts[(c * kWave + L) * kD4Sub + t / 4] = make_float2(0.f, 1.f);
+            if (t == 0) xsums[c * kWave + L] = 0.f;
         }
     }
     __syncthreads();
@@ -302,13 +305,17 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
         uint4 xv[4 * kD4Sub];
 #pragma unroll
         for (int e = 0; e < 4 * kD4Sub; ++e) xv[e] = xl[(cc * (4 * kD4Sub) + e) * kWave + xo];
-        const float4 cst = consts[cc * kWave + xo];
+        const float4 cst = reinterpret_cast<const float4*>(consts)[cc * kWave + xo];
+        const float xsum = xsums[cc * kWave + xo];
         uint32_t w[4 * kD4Sub];
 #pragma unroll
         for (int h = 0; h < kD4Sub; ++h) { w[4 * h] = q[p][h].x; w[4 * h + 1] = q[p][h].y; w[4 * h + 2] = q[p][h].z; w[4 * h + 3] = q[p][h].w; }
-        f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+        f32x4_t dh[kD4Sub];
+#pragma unroll
+        for (int h = 0; h < kD4Sub; ++h) dh[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int e = 0; e < 4 * kD4Sub; ++e) {
+            f32x4_t& d = dh[e / 4];
             // codes 0,4 | 16*codes 1,5 | codes 2,6 | 16*codes 3,7, each plus 1024, as fp16
             const uint32_t w8 = w[e] >> 8;
             const uint2 a01 = make_uint2((w[e] & 0x000F000Fu) | magic, (w[e] & 0x00F000F0u) | magic);
@@ -324,12 +331,12 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
         const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sh[p]);
         const float z = (float)((zw[p] >> (4 * (grp & 7))) & 0xFu);
         // register i of d belongs to weight row n0 + i, whose scale and zero-point lane 4b + i holds:
-        //   s * P * sum_k x_k (q_k - z) = s * (P D - P xoff) + (s z) * (-P xsum)
+        //   s * P * sum_k x_k (q_k - z) = s * (P D - P xoff) + (s z) * (-P xsum), the halves added up before s
         const float sz = s * z;
-#define QAIL_D4_ROW(i)                                          \
-    {                                                           \
-        quad_fmac<i>(acc[i], s, fmaf(cst.z, d[i], -cst.x));     \
-        quad_fmac<i>(acc[i], sz, cst.y);                        \
+#define QAIL_D4_ROW(i)                                                                                   \
+    {                                                                                                    \
+        quad_fmac<i>(acc[i], s, fmaf(cst.y, dh[0][i], -cst.x) + fmaf(cst.w, dh[1][i], -cst.z));          \
+        quad_fmac<i>(acc[i], sz, xsum);                                                                  \
     }
         QAIL_D4_ROW(0) QAIL_D4_ROW(1) QAIL_D4_ROW(2) QAIL_D4_ROW(3)
 #undef QAIL_D4_ROW
@@ -374,7 +381,7 @@ __global__ __launch_bounds__(kD4Threads) void w4a16_decode4_kernel(const D4Args 
         uint16_t* dst = it.y + (size_t)li * N + n0;
         uint16_t h[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16_rne(2.f * keep[i]);
+        for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16_rne(keep[i]);
         // N is a multiple of 4 (host check), so the four values are one aligned 8-byte piece of row li of y
         *reinterpret_cast<uint2*>(dst) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
     }
@@ -387,7 +394,7 @@ size_t d4_item_bytes(const qail_wdesc& d) {
 
 size_t d4_lds_bytes(const qail_wdesc& d) {
     const size_t nc = ((size_t)d.K + kD4ChunkK - 1) / kD4ChunkK;
-    return nc * kWave * (4 * kD4Sub * 16 + 16);  // staged activations and per-stretch constants
+    return nc * kWave * (4 * kD4Sub * 16 + kD4Sub * 8 + 4);  // staged activations and per-stretch constants
 }
 
 hipError_t d4_launch_chunk(const qail_w4a16_item* items, int count, int M, hipStream_t st) {
@@ -397,7 +404,7 @@ hipError_t d4_launch_chunk(const qail_w4a16_item* items, int count, int M, hipSt
     if (!attr_done.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&w4a16_decode4_kernel),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kD4MaxChunks * kWave * (4 * kD4Sub * 16 + 16));
+                                                 kD4MaxChunks * kWave * (4 * kD4Sub * 16 + kD4Sub * 8 + 4));
         if (e != hipSuccess) return e;
         attr_done.store(true, std::memory_order_release);
     }

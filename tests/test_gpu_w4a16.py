@@ -240,15 +240,37 @@ def test_four_row_stream_shapes(B, M, N, K, g):
 
 @pytest.mark.parametrize("N,K,g", [(36, 1024, 128), (20, 3136, 64), (12, 6144, 2048)])   # whole chunks, a tail, a group of two chunks
 def test_four_row_stream_value_ranges(B, N, K, g):
-    # 64 k of x of one sign: with (q + 1024) for q their sum is 5e38 in the first row, beyond fp32, over 32 k it is not
+    # 64 k of x of one sign: with (q + 1024) for q their sum is 5e38 in the first row, beyond fp32, over 32 k it is not; in the
+    # last row the power of two that goes with a sum is as small as a normal number gets
     rng = np.random.default_rng(K)
     w = synth.llm_weight(N, K, 41)
-    x = rng.uniform(0.5, 1.0, size=(3, K)).astype(np.float32) * np.float32([[1e34], [1.0], [2.0 ** -100]])
+    x = rng.uniform(0.5, 1.0, size=(3, K)).astype(np.float32) * np.float32([[1e34], [1.0], [2.0 ** -111]])
     xb = synth.f32_to_bf16_bits(x)
     qw, s, zw = oracle_pack(w, g)
     y = gpu_linear(B, qw, s, zw, xb, g, N, K, 3)
     nx, nw = O.w4a16_row_norms(xb, qw, s, zw, g)
     assert w4a16_norm_err(y, O.w4a16_linear(xb, qw, s, zw, g), nx, nw) <= TOL
+
+
+@pytest.mark.parametrize("half", [0, 1])
+@pytest.mark.parametrize("N,K,g", [(36, 1024, 128), (20, 3136, 64), (12, 12288, 512)])
+def test_four_row_stream_halves_of_a_stretch_apart(B, N, K, g, half):
+    """A value 2^19 times the others in one half (32 k) of a lane's 64, where it meets a weight of zero, costs the other half
+    nothing: it shares neither the power of two nor the offset 1024 sum(x), whose rounding beside such a value is about 32 (the error is
+    measured against the other half alone)."""
+    rng = np.random.default_rng(K + half)
+    w = synth.llm_weight(N, K, 47)
+    large = np.arange(K) % 64 == 32 * half + 11
+    w[:, large] = 0.0
+    x = rng.standard_normal((4, K)).astype(np.float32)
+    x[:, np.arange(K) % 64 // 32 == half] = 0.0
+    qw, s, zw = oracle_pack(w, g)
+    nx, nw = O.w4a16_row_norms(synth.f32_to_bf16_bits(x), qw, s, zw, g)
+    x[:, large] = 2.0 ** 19
+    xb = synth.f32_to_bf16_bits(x)
+    for M in (2, 4):
+        y = gpu_linear(B, qw, s, zw, xb[:M], g, N, K, M)
+        assert w4a16_norm_err(y, O.w4a16_linear(xb[:M], qw, s, zw, g), nx[:M], nw) <= TOL
 
 
 @pytest.mark.parametrize("M", [3, 7, 15, 19, 31])
