@@ -48,7 +48,8 @@ constexpr int kGemvMaxK = kGemvMaxChunks * kWaveK;
 // from call to call, generic / here / with the matrix cores, us: layer of a 13B model 575 / 35.7 / 35.0, 3584 x 18944 781 / 14.3 / 11.8,
 // 5120 x 13824 537 / 13.3 / 11.6.
 constexpr int kGemvMaxWideK = 5 * 2 * kWaveK;
-__host__ __device__ constexpr int units_of(int K, bool wide) { return (K + kWaveK * (wide ? 2 : 1) - 1) / (kWaveK * (wide ? 2 : 1)); }
+// (two divisions by constants: one by a selected divisor costs every block 0.1 us)
+__host__ __device__ constexpr int units_of(int K, bool wide) { return wide ? (K + 2 * kWaveK - 1) / (2 * kWaveK) : (K + kWaveK - 1) / kWaveK; }
 __host__ __device__ constexpr bool exact_products(int units, bool wide) { return wide && units > 3; }
 // What the staged activations of an item take, in pieces of 16 bytes (the LDS maps are below).
 __host__ __device__ constexpr int staged_pieces(int units, bool wide) {
