@@ -66,9 +66,12 @@ struct GemvItem {
     uint16_t* y;
     int N, K, g;
     int block_begin;  // first block of the grid that works on this item
-    int rows_base;    // block b of the item owns rows_base rows, one more if b < rows_rem,
+    int rows_base;    // block b of the item owns rows_base rows (without kOneAhead), one more if b < rows_rem,
     int rows_rem;     // in the order of the blocks
 };
+// In rows_base: a wave asks for one row ahead (see gemv_body).  A word of its own would no longer lie in the 64 bytes, and
+// waiting for another load costs 0.1 - 0.2 us.
+constexpr int kOneAhead = 1 << 30;
 
 struct GemvArgs {
     GemvItem it[kGemvMaxItems];
@@ -583,24 +586,25 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& args, const GemvLoraAr
 
     // this block's slab of rows, then this wave's share of the slab
     const int b = (int)blockIdx.x - it.block_begin;
-    const int s0 = b * it.rows_base + min(b, it.rows_rem);
-    const int s1 = s0 + it.rows_base + (b < it.rows_rem ? 1 : 0);
+    const int rows_base = it.rows_base & ~kOneAhead;
+    const int s0 = b * rows_base + min(b, it.rows_rem);
+    const int s1 = s0 + rows_base + (b < it.rows_rem ? 1 : 0);
     // Rows are dealt to the waves of the block in turn, so that at any moment the block's
     // waves read adjacent rows: one contiguous stretch of memory per block.
     const int r0 = s0 + wave;
     const int r1 = max(0, (s1 - s0 - wave + kGemvWaves - 1) / kGemvWaves);  // number of rows
 
     // about kUnits wave-wide loads (1 KB each) in flight per wave; rows of one unit: half of that, and a quarter where a
-    // wave has three rows or more to itself.  A wave's first bytes queue behind all that its CU has asked for, and with
-    // one row in flight the refills (one per row consumed) keep the stream up: 8 -> 4 -> 2 KB a wave, new
+    // wave has three rows or more to itself and a CU two blocks.  A wave's first bytes queue behind all that its CU has asked for, and
+    // with one row in flight the refills (one per row consumed) keep the stream up: 8 -> 4 -> 2 KB a wave, new
     // buffers from call to call, us: the layer of a 7B model 22.0 -> 21.7 -> 21.1, 28672 x 4096 13.1 -> 12.0 -> 11.5,
-    // 12288 x 4096 7.5 -> 7.4 -> 6.8; with two rows a wave or one, 8192 x 4096 6.0 -> 5.5 -> 5.9, 4096 x 4096
-    // 4.6 -> 4.4 -> 4.5; 16384 x 2048 (half a unit a row) 6.8 -> 6.6 -> 6.8.  Rows of two units are not
-    // faster with less (4096 x 5120 5.1 -> 5.7).
+    // 12288 x 4096 7.5 -> 7.4 -> 6.8.  With one block per CU 2 KB a wave are too little: 11008 x 4096 7.6 -> 8.6 from 4 KB to 2, 8192 x 4096
+    // 6.0 -> 5.5 -> 5.9, 8192 x 3072 5.8 -> 6.3 from 4 to 2; 4096 x 4096 4.6 -> 4.4 -> 4.5; 16384 x 2048 (half a unit a row) 6.8 -> 6.6 -> 6.8.
+    // Rows of two units are not faster with less (4096 x 5120 5.1 -> 5.7).
     if (wide) {
         switch (nu) {
             case 1:
-                if (it.rows_base >= 3 * kGemvWaves && K > kWaveK)
+                if (it.rows_base & kOneAhead)
                     stream_rows<1, kUnits / 8, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
                 else
                     stream_rows<1, kUnits / 4, 2, false>(it, lo, lora_t, r0, r1, lane, lds, wave, ChainCtx{});
@@ -753,7 +757,8 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
     long long rows_total = 0;
     for (int i = 0; i < count; ++i) rows_total += items[i].d.N;
     int grid = device_cu_count();
-    if (rows_total >= 2LL * grid * kGemvWaves * 3) grid *= 2;
+    const bool two_blocks = rows_total >= 2LL * grid * kGemvWaves * 3;
+    if (two_blocks) grid *= 2;
     if (grid < count) grid = count;
     // blocks per item in proportion to its bytes (largest remainder), at least one each.  A byte of a long row takes about
     // 1.35 times as long (exact products), which counts as long as it leaves a CU at most one block of such rows; two that meet on
@@ -814,6 +819,7 @@ hipError_t launch_chunk(const qail_w4a16_item* items, const GemvLora* loras, int
         t.N = s.d.N; t.K = s.d.K; t.g = s.d.group_size;
         t.block_begin = bb;
         t.rows_base = s.d.N / nb[i];
+        if (two_blocks && t.rows_base >= 3 * kGemvWaves && s.d.K > kWaveK) t.rows_base |= kOneAhead;
         t.rows_rem = s.d.N % nb[i];
         for (int b = bb; b < bb + nb[i] && b < kGemvMaxBlocks; ++b) a.item_of_block[b / 8] |= (uint32_t)i << (4 * (b % 8));
         bb += nb[i];
