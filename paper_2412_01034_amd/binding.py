@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 from typing import Optional, Sequence, Tuple
 
 import torch
@@ -138,8 +139,8 @@ def lib() -> ctypes.CDLL:
 
 
 # The marshalling of three calls in C++ (csrc/marshal.cpp): a function returns the library's status, or None for a call that is not
-# the plain case, which then goes the way below it.  Without the compiled module (another Python or torch than it was built for)
-# every call does.
+# the plain case, which then goes the way below it.  Without the compiled module, or with one that was built for another Python,
+# torch or layout of the items, every call does.
 def _not_plain(*args):
     return None
 
@@ -147,11 +148,19 @@ def _not_plain(*args):
 _linear_native = _linear_batch_native = _conv_batch_native = _not_plain
 
 
+def _marshal_for() -> tuple:
+    """What a module has to be built for: its layouts are compiled in."""
+    return (sys.hexversion >> 16, "%s %s" % (torch.__version__, torch.version.git_version), ctypes.sizeof(qail_wdesc),
+            ctypes.sizeof(qail_w4a16_item), ctypes.sizeof(qail_conv_item))
+
+
 def _use_native(L: ctypes.CDLL) -> None:
     global _linear_native, _linear_batch_native, _conv_batch_native
     try:
         from . import _marshal
     except ImportError:
+        return
+    if getattr(_marshal, "built_for", None) != _marshal_for():
         return
     _marshal.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (L.qail_w4a16_linear, L.qail_w4a16_linear_batch, L.qail_w4a4_conv_batch)))
     _linear_native, _linear_batch_native, _conv_batch_native = _marshal.w4a16_linear, _marshal.w4a16_linear_batch, _marshal.w4a4_conv_batch

@@ -1,16 +1,18 @@
 """Builds libqail.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
 from __future__ import annotations
 
+import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqail.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))   # another Python does not look at it
 
 SOURCES = ("api.hip", "quantize.hip", "w4a16_gemv.hip", "w4a16_decode4.hip", "w4a16_smallm.hip", "w4a16_midm.hip", "w4a16_gemm.hip", "w4a16_generic.hip", "w4a16_lora.hip", "w8.hip", "w8a16_gemv.hip", "train_ops.hip", "w4a4_conv.hip")
 
@@ -38,14 +40,12 @@ def _run(cmd):
 
 
 def build_marshal() -> str:
-    """Compile the binding's marshalling (csrc/marshal.cpp) against this Python and this torch."""
-    import sysconfig
-
+    """Compile the binding's marshalling (csrc/marshal.cpp) against this Python and this torch, whose names it keeps."""
     import torch
     top = os.path.dirname(torch.__file__)
     tmp = MARSHAL + ".tmp"
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+          '-DQAIL_TORCH="%s %s"' % (torch.__version__, torch.version.git_version), "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(top, "include"),
           "-I", os.path.join(top, "include", "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
           os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L", os.path.join(top, "lib"),
@@ -68,6 +68,8 @@ def build_library(verbose: bool = False) -> str:
             print(out, file=sys.stderr)
         return obj
 
+    for old in glob.glob(os.path.join(os.path.dirname(MARSHAL), "_marshal*.so")):   # what is not built anew is not used
+        os.remove(old)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
         marshal = ex.submit(build_marshal)
         objs = list(ex.map(compile_one, SOURCES))

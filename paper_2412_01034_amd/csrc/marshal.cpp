@@ -5,6 +5,9 @@
 // A function returns the library's status, or None for everything that is not the plain case (another type than torch.Tensor, a
 // torch function mode, a tensor that is too small, on the host or not contiguous, numbers that do not fit): binding.py then goes its
 // own way, with its own errors.  Nothing is kept between calls but the addresses of the library's functions.
+//
+// Layouts of torch, Python and qail.h are compiled in, so the module says what it was built for (`built_for`) and binding.py uses it with
+// nothing else.
 #define PY_SSIZE_T_CLEAN
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
@@ -147,4 +150,15 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal() {
+    PyObject* m = PyModule_Create(&module);
+    PyObject* built_for = m ? Py_BuildValue("(lsnnn)", (long)(PY_VERSION_HEX >> 16), QAIL_TORCH, (Py_ssize_t)sizeof(qail_wdesc),
+                                            (Py_ssize_t)sizeof(qail_w4a16_item), (Py_ssize_t)sizeof(qail_conv_item))
+                            : nullptr;
+    if (!built_for || PyModule_AddObject(m, "built_for", built_for) < 0) {   // (takes the reference where it succeeds)
+        Py_XDECREF(built_for);
+        Py_XDECREF(m);
+        return nullptr;
+    }
+    return m;
+}

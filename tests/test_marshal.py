@@ -45,6 +45,22 @@ def test_calls_that_are_not_plain_are_left_to_python(B):
         B.qail_w4a16_linear(N, K, g, **{**t, "qweight": t["qweight"][:1]}, M=M)
 
 
+@pytest.mark.parametrize("built_for", [None, "python", "torch", "items"])
+def test_a_module_built_for_something_else_is_left_alone(B, monkeypatch, built_for):
+    from paper_2412_01034_amd import _marshal
+    same = _marshal.built_for
+    assert same == B._marshal_for()
+    for name in ("_linear_native", "_linear_batch_native", "_conv_batch_native"):
+        monkeypatch.setattr(B, name, B._not_plain)
+    if built_for is None:   # as one from before it said so
+        monkeypatch.delattr(_marshal, "built_for")
+    else:
+        other = {"python": (same[0] + 1, *same[1:]), "torch": (same[0], "2.0 0", *same[2:]), "items": (*same[:3], same[3] + 8, same[4])}
+        monkeypatch.setattr(_marshal, "built_for", other[built_for])
+    B._use_native(B.lib())
+    assert B._linear_native is B._linear_batch_native is B._conv_batch_native is B._not_plain
+
+
 @pytest.mark.gpu
 def test_status_of_the_library_comes_back(B):
     with pytest.raises(B.QailError):   # NULL pointers
