@@ -61,6 +61,31 @@ def test_a_module_built_for_something_else_is_left_alone(B, monkeypatch, built_f
     assert B._linear_native is B._linear_batch_native is B._conv_batch_native is B._not_plain
 
 
+@pytest.mark.parametrize("error", [RuntimeError("no Python.h"), FileNotFoundError("g++"), ImportError("torch"), None])
+def test_library_is_built_without_the_marshalling(monkeypatch, tmp_path, capsys, error):
+    from paper_2412_01034_amd import build
+
+    def run(cmd):
+        with open(cmd[cmd.index("-o") + 1], "w") as f:
+            f.write(cmd[0])
+        return ""
+
+    def marshal():
+        if error is not None:
+            raise error
+        open(build.MARSHAL, "w").close()
+
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libqail.so"))
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.here.so"))
+    monkeypatch.setattr(build, "_run", run)
+    monkeypatch.setattr(build, "build_marshal", marshal)
+    (tmp_path / "_marshal.so").touch()   # of an earlier build: not what is here now
+    assert build.build_library() == build.LIB and (tmp_path / "libqail.so").exists()
+    assert [p.name for p in tmp_path.glob("_marshal*")] == ([] if error else ["_marshal.here.so"])
+    assert (str(error) in capsys.readouterr().err) == (error is not None)
+
+
 @pytest.mark.gpu
 def test_status_of_the_library_comes_back(B):
     with pytest.raises(B.QailError):   # NULL pointers
