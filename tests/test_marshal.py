@@ -96,40 +96,73 @@ def test_status_of_the_library_comes_back(B):
         B.qail_w4a4_conv_batch((B.qail_w4a16_item * 1)(), 1)
 
 
-@pytest.mark.gpu
-def test_same_results_and_errors_as_the_way_through_python(B, monkeypatch):
+def plain_calls(B):
+    """The three calls on data that tells results apart: what their items point to, and of each the native function, the public
+    call and the output."""
     import torch
     t = tensors("cuda")
     rng = np.random.default_rng(5)
     t["qweight"].copy_(dev(rng.integers(0, 2**32, N * K // 8, dtype=np.uint32)))
     t["x"].copy_(torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)))
     items = B.make_w4a16_items([dict(N=N, K=K, group_size=g, **t)], M)
+    conv = dict(B=2, H=9, W=7, Cin=64, Cout=40, KH=3, KW=3, stride=1, pad=1, a_u4=dev(rng.integers(0, 2**32, 2 * 9 * 7 * 64 // 8, dtype=np.uint32)),
+                w_s4=dev(rng.integers(0, 2**32, 40 * 9 * 64 // 8, dtype=np.uint32)),
+                acc_out=torch.empty(2 * 9 * 7 * 40, dtype=torch.int32, device="cuda"))
+    conv_items = B.make_conv_items([conv])
+    return (t, conv), [(lambda: B._linear_native(N, K, g, *t.values(), M, None), lambda: B.qail_w4a16_linear(N, K, g, **t, M=M), t["y"]),
+                       (lambda: B._linear_batch_native(items, 1, M, None), lambda: B.qail_w4a16_linear_batch(items, 1, M), t["y"]),
+                       (lambda: B._conv_batch_native(conv_items, 1), lambda: B.qail_w4a4_conv_batch(conv_items, 1), conv["acc_out"])]
+
+
+@pytest.mark.gpu
+def test_plain_calls_are_taken_with_the_same_results_as_the_way_through_python(B, monkeypatch):
+    import torch
+    (t, conv), calls = plain_calls(B)
 
     class Mode(torch.overrides.TorchFunctionMode):
         def __torch_function__(self, func, types, args=(), kwargs=None):
             return func(*args, **(kwargs or {}))
 
-    def results():
-        out = []
-        for run in (lambda: B.qail_w4a16_linear(N, K, g, **t, M=M), lambda: B.qail_w4a16_linear_batch(items, 1, M)):
-            t["y"].fill_(7.0)
-            side = torch.cuda.Stream()
-            side.wait_stream(torch.cuda.current_stream())
-            with torch.cuda.stream(side):
-                run()
-                out.append(t["y"].clone())
-            side.synchronize()
-        return [host(y, np.uint16) for y in out]
+    def results(way):
+        found = []
+        for call in calls:
+            call[2].fill_(7)
+            assert call[way]() == (0 if way == 0 else None)   # the native function answers; the public one has nothing to say
+            found.append(host(call[2], np.uint32 if call[2].dtype == torch.int32 else np.uint16).copy())
+        return found
 
-    native = results()
+    native, public = results(0), results(1)
     with Mode():
-        assert B._linear_native(N, K, g, *t.values(), M, None) is None
-        moded = results()
-    monkeypatch.setattr(B, "_linear_native", B._not_plain)
-    monkeypatch.setattr(B, "_linear_batch_native", B._not_plain)
-    for a, b, c in zip(native, results(), moded):
-        assert np.array_equal(a, b) and np.array_equal(a, c) and len(np.unique(a)) > 10
+        assert all(call[0]() is None for call in calls)
+        moded = results(1)
+    for name in ("_linear_native", "_linear_batch_native", "_conv_batch_native"):
+        monkeypatch.setattr(B, name, B._not_plain)
+    for a, b, c, d in zip(native, public, moded, results(1)):
+        assert np.array_equal(a, b) and np.array_equal(a, c) and np.array_equal(a, d) and len(np.unique(a)) > 10
     monkeypatch.undo()
     for bad in (dict(x=t["x"].t().contiguous().t()), dict(y=t["y"][:1]), dict(scales=t["scales"].cpu())):
         with pytest.raises(ValueError):
             B.qail_w4a16_linear(N, K, g, **{**t, **bad}, M=M)
+
+
+@pytest.mark.gpu
+def test_plain_calls_go_to_the_current_stream(B):
+    """A stream under capture runs nothing: what is launched there is in the graph, what is launched elsewhere is not."""
+    import torch
+    held, calls = plain_calls(B)
+    for native, _, out in calls:
+        assert native() == 0   # (the first launch of a kernel loads it, which a capture does not allow)
+        want = out.clone()
+        torch.cuda.synchronize()
+        out.fill_(7)
+        torch.cuda.synchronize()
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=side):
+            status = native()
+        torch.cuda.synchronize()
+        assert status == 0 and (out == 7).all()
+        for _ in range(2):
+            out.fill_(7)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
