@@ -572,26 +572,31 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
     };
     // in flight at a step's wait: step s + 1 and, with three slots, step s + 2
     if constexpr (kBits == 4) {
-        const int halves = (kwords + kStepWords / 2 - 1) / (kStepWords / 2);   // half-steps of the whole problem
-        for (int s0 = 0; s0 < steps; s0 += ST) {
+        // One K step: slot `cur`, the next step's `nxt`, the one to refill `fill`.  Only the last step of the problem can have one half, so
+        // only a group's last step asks how many halves there are (a branch in the loop keeps a half's reads and widening from
+        // going between the other half's MFMAs).
+        auto step = [&](int cur, int nxt, int fill, int left) {
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(cur, 1, 1);
+            if (left > 0) multiply(0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ST == 3) refill(fill);
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm(ST == 3 ? kL : 0));
+            __syncthreads();
+            if (ST == 2) refill(fill);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(nxt, 0, 0);
+            if (left > 1) multiply(1);
+        };
+        for (int s0 = 0; s0 < steps - 1; s0 += ST) {
 #pragma unroll
             for (int u = 0; u < ST; ++u) {
-                if (s0 + u >= steps) break;
-                const int cur = u, nxt = (u + 1) % ST, fill = (u + 2) % ST;
-                const int left = halves - 2 * ((s0 + u) * KS + grp);
-                __builtin_amdgcn_sched_barrier(0);
-                fetch(cur, 1, 1);
-                if (KS == 1 || left > 0) multiply(0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (ST == 3) refill(fill);
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm(ST == 3 ? kL : 0));
-                __syncthreads();
-                if (ST == 2) refill(fill);
-                __builtin_amdgcn_sched_barrier(0);
-                fetch(nxt, 0, 0);
-                if (left > 1) multiply(1);
+                if (s0 + u >= steps - 1) break;
+                step(u, (u + 1) % ST, (u + 2) % ST, 2);
             }
         }
+        const int last = (steps - 1) % ST, halves = (kwords + kStepWords / 2 - 1) / (kStepWords / 2);   // half-steps of the whole problem
+        step(last, (last + 1) % ST, (last + 2) % ST, halves - 2 * ((steps - 1) * KS + grp));
     } else {
         // one MFMA step per K step: the operand registers alternate with the step's parity, so a ring of three is unrolled twice
         constexpr int kTurn = ST % 2 ? 2 * ST : ST;
