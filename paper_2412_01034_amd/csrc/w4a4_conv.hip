@@ -658,11 +658,14 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
 #pragma unroll
         for (int o = 0; o < kOwn; o += kE / 4) request(o);
     }
+    // Plain outputs of groups whose rings hold a whole tile each are added up on their way out instead (see there).
+    constexpr int kPitch = BN + 4;
+    constexpr bool kSumOut = KS > 1 && kGroupBytes >= BM * kPitch * 4;
     i32x4_t own[kOwn];
     if constexpr (KS == 1) {
 #pragma unroll
         for (int o = 0; o < kOwn; ++o) own[o] = quad(o);
-    } else {
+    } else if (fused || !kSumOut) {
         __syncthreads();   // the rings have been read
         unsigned char* const hand = ring + wave * ((KS - 1) * kQuads * 1024) + lane * 16;
 #pragma unroll
@@ -755,11 +758,36 @@ __device__ __forceinline__ void w4a4_conv_tile(const ConvGeom& gm, const uint32_
             }
             if (in && (kE == 8 || kh == 0)) out.out_u4[(uint32_t)m * (uint32_t)(gm.Cout / 8) + (uint32_t)n0 / 8u] = word;
         }
+    } else if constexpr (kSumOut) {
+        // Plain outputs of a tile whose K was split: every group stages its sums, the piece of a row that a thread stores is added up
+        // as it is read: two barriers, where handing over and staging take four.  us, handed over / this, W8A8 of
+        // 256 channels, 36 steps, 4 x 17 x 16 pixels 7.36 / 7.16, of 384, 54 steps, 9 x 14 x 16 9.75 / 9.48, W4A4 of 256, 18 steps 6.24 / 6.07.
+        int32_t* const stage = reinterpret_cast<int32_t*>(smem);
+        if (kBits == 4 && out.y) {
+            sc = *reinterpret_cast<const float4*>(&chan[0][nq]);
+            bi = *reinterpret_cast<const float4*>(&chan[1][nq]);
+        }
+        __syncthreads();   // the rings have been read
+#pragma unroll
+        for (int p = 0; p < kQuads; ++p) {
+            const int i = p / (4 * UN), j = p / 4 % UN, qd = p % 4 / 2 + 2 * (p % 2);
+            *reinterpret_cast<i32x4_t*>(&stage[((wm * UM + i) * 32 + r32) * kPitch + (wn * UN + j) * 32 + 8 * qd + 4 * kh]) = quad(p);
+        }
+        __syncthreads();
+        for (int row = t / (BN / 4); row < BM; row += kThreads / (BN / 4)) {
+            const int m = bm + row, n = bn + nq;
+            if (m >= gm.M || n >= gm.Cout) continue;
+            i32x4_t v = {0, 0, 0, 0};
+#pragma unroll
+            for (int g = 0; g < KS; ++g) v += *reinterpret_cast<const i32x4_t*>(ring + g * kGroupBytes + (row * kPitch + nq) * 4);
+            if (kBits == 4) v >>= 4;
+            store_plain(v, out, (size_t)m * gm.Cout + n, n, gm.Cout, sc, bi);
+        }
     } else {
         // Plain outputs leave as whole pieces of rows, through LDS (pitch BN + 4 words: the 16-byte writes of eight neighbouring
         // pixels fall on different banks), as many blocks of 32 rows at a time as the rings hold.  Stored from the registers, 32
         // bytes of each of 32 rows at a time, 12.8 MB took 30 us instead of 11.
-        constexpr int kPitch = BN + 4, kFit = KS * kGroupBytes / (32 * kPitch * 4), kBlocks = UM * WM;
+        constexpr int kFit = KS * kGroupBytes / (32 * kPitch * 4), kBlocks = UM * WM;
         constexpr int kAtOnce = kFit < kBlocks ? kFit : kBlocks;
         static_assert(kAtOnce >= 1 && kBlocks % kAtOnce == 0 && kThreads % (BN / 4) == 0, "whole turns; columns fixed per thread");
         int32_t* const stage = reinterpret_cast<int32_t*>(ring);
