@@ -1212,22 +1212,23 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     const bool one_tap = gm.KH * gm.KW == 1, fused = jobs[lead].out.out_u4 != nullptr;
     if (2 * all32 <= (one_tap && fused ? 5 : 7) * cus && work <= (one_tap && (fused || kBits == 8) ? 44 : 64) * cus)
         return launch_direct<kBits, 2, 2, 4, 1>(jobs, n, st);
-    // The tiled kernel's shapes, by the number t of 64 x 64 tiles per CU and the K steps (sweep of 96 convolutions with plain,
-    // 4-bit and, W8A8, plain outputs; us).  Up to one tile per CU K is split between groups of four waves with 32 x 32 each,
-    // four groups where it is long (36 steps 8.4, two groups 9.0; 18 steps 7.0 / 6.7; bytes 72 steps 8.0 / 8.5, 36 steps 6.4 /
-    // 6.2).  Up to three the same waves without a split as long as K is short (9 steps, t = 2.3, 7.9; split with 64 x 32 each 8.3),
-    // with one where it is long (18 steps, t = 1.5 / 2.7 8.7 / 11.1 against 9.3 / 11.7; at t = 2.3 12.3 against 10.9, which is the
-    // other way round up to 24 steps; 36 steps, t = 2.3 12.6 / 13.9).  Above that four waves with 64 x 32 or 32 x 64 each, whichever pads
+    // The tiled kernel's shapes, by the number t of 64 x 64 tiles per CU and the K steps (sweeps of some hundred drawn convolutions
+    // with operands that come from beyond L2, as a layer's do; us).  4-bit: up to one tile per CU K is split between groups of four
+    // waves with 32 x 32 each, four groups where it is long (36 steps 8.4, two groups 9.0; 18 steps 7.0 / 6.7).  Up to three the
+    // same waves without a split as long as K is short (9 steps, t = 2.3 7.6, split with 64 x 32 each 8.0; 13 steps, t = 1.1 / 2.6
+    // 7.4 / 9.4 against 7.1 / 9.9), with one where it is long (14 steps, t = 1.1 / 2.5 7.9 / 11.3 against 7.3 / 10.9; 18 steps, t =
+    // 1.1 / 2.3 / 2.8 9.1 / 11.8 / 12.7 against 8.2 / 11.1 / 11.7).  Above that four waves with 64 x 32 or 32 x 64 each, whichever pads
     // the channels less, a ring of three where all blocks fit a CU with it (t <= 6; t = 4.6, 5 steps 12.7 / 12.8, t = 3.8 9.0 / 9.4, t =
     // 6.1 11.7 / 10.7), and from t = 6 on 128 x 128 where that pads no more (t = 6.1, 9 steps 12.8, 128 x 64 15.0; 18 steps, t = 12.2 20.4 /
-    // 22.3), unless there are only a step or two (1x1, 128 -> 512 channels 12.9, 64 x 128 10.9).  Bytes, which have no widening and so
+    // 22.3), unless there are only a step or two (1x1, 128 -> 512 channels 12.9, 64 x 128 10.9).
+    // Bytes, which have no widening and so
     // load more per unit of time, keep two slots for 64 x 128 (t = 4.6, 36 steps 11.2, three 14.8) and for up to three blocks of 128 x 128 a CU (t = 6.1,
     // 18 steps 12.6 / 14.2; above, t = 12.2, 28.5 / 24.6), and three for 128 x 64 (t = 24.5 33.0 / 38.6).
     const bool fits128 = (gm.Cout + 127) / 128 * 2 == (gm.Cout + 63) / 64;   // tiles 128 wide pad no more than tiles 64 wide
     if constexpr (kBits == 4) {
         if (all64 <= cus) return ksteps >= 24 ? launch_tiled<4, 1, 1, 2, 2, 4, 3>(jobs, n, st) : launch_tiled<4, 1, 1, 2, 2, 2, 3>(jobs, n, st);
         if (all64 < 3 * cus) {
-            if (ksteps <= 14 || (all64 > 2 * cus && 2 * all64 <= 5 * cus && ksteps < 24)) return launch_tiled<4, 1, 1, 2, 2, 1, 2>(jobs, n, st);
+            if (ksteps <= 12) return launch_tiled<4, 1, 1, 2, 2, 1, 2>(jobs, n, st);
             return launch_tiled<4, 2, 1, 1, 2, 2, 2>(jobs, n, st);
         }
         if (fits128 && all64 >= 6 * cus && ksteps > 2) return launch_tiled<4, 2, 2, 2, 2, 1, 2>(jobs, n, st);
