@@ -1221,11 +1221,15 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
     // the channels less, a ring of three where all blocks fit a CU with it (t <= 6; t = 4.6, 5 steps 12.7 / 12.8, t = 3.8 9.0 / 9.4, t =
     // 6.1 11.7 / 10.7), and from t = 6 on 128 x 128 where that pads no more (t = 6.1, 9 steps 12.8, 128 x 64 15.0; 18 steps, t = 12.2 20.4 /
     // 22.3), unless there are only a step or two (1x1, 128 -> 512 channels 12.9, 64 x 128 10.9).
-    // Bytes, which have no widening and so
-    // load more per unit of time, keep two slots for 64 x 128 (t = 4.6, 36 steps 11.2, three 14.8) and for up to three blocks of 128 x 128 a CU (t = 6.1,
-    // 18 steps 12.6 / 14.2; above, t = 12.2, 28.5 / 24.6), and three for 128 x 64 (t = 24.5 33.0 / 38.6).
-    const bool fits128 = (gm.Cout + 127) / 128 * 2 == (gm.Cout + 63) / 64;   // tiles 128 wide pad no more than tiles 64 wide
+    // Bytes have nothing to widen and wait for their operands instead: three slots almost throughout.  Up to one tile per CU
+    // no split (up to 4 steps; 1 step 4.0, two groups 4.2), two groups or, from 24 steps on, four.  Up to three no split up to 16
+    // steps (9 steps, t = 1.3 / 2.1 6.3 / 6.3, with two slots 7.2 / 7.0), then two groups, of four waves up to t = 2 (25 steps, t = 1.5
+    // 9.0, two waves and two slots 9.7; 512 channels, t = 1.5, inside the body at batch 64 7 us less), of two waves above
+    // (72 steps, t = 2.3 20.1 / 23.1).  Above that 128 x 64 where tiles 128 wide would pad much (96 -> 280 channels, 14 steps 17.0, 128 x 128
+    // 19.2; but 400, 14 steps 19.2 / 15.6, and 1x1, 280 12.0, 64 x 128 10.7), else 64 x 128 up to t = 6 or 4 steps and 128 x 128 above, with two
+    // slots for one output (t = 6.1, 9 steps 9.9 / 10.6) and three for two (14.9 / 14.0) or many tiles (t = 12.2, 18 steps 28.5 / 24.6).
     if constexpr (kBits == 4) {
+        const bool fits128 = (gm.Cout + 127) / 128 * 2 == (gm.Cout + 63) / 64;   // tiles 128 wide pad no more than tiles 64 wide
         if (all64 <= cus) return ksteps >= 24 ? launch_tiled<4, 1, 1, 2, 2, 4, 3>(jobs, n, st) : launch_tiled<4, 1, 1, 2, 2, 2, 3>(jobs, n, st);
         if (all64 < 3 * cus) {
             if (ksteps <= 12) return launch_tiled<4, 1, 1, 2, 2, 1, 2>(jobs, n, st);
@@ -1235,14 +1239,20 @@ void launch_tiled_jobs(const ConvJob* jobs, int n, hipStream_t st) {
         if (all64 <= 6 * cus) return fits128 ? launch_tiled<4, 1, 2, 2, 2, 1, 3>(jobs, n, st) : launch_tiled<4, 2, 1, 2, 2, 1, 3>(jobs, n, st);
         return fits128 ? launch_tiled<4, 1, 2, 2, 2, 1, 2>(jobs, n, st) : launch_tiled<4, 2, 1, 2, 2, 1, 2>(jobs, n, st);
     } else {
-        if (all64 <= cus) return ksteps >= 24 ? launch_tiled<8, 1, 1, 2, 2, 4, 3>(jobs, n, st) : launch_tiled<8, 1, 1, 2, 2, 2, 3>(jobs, n, st);
-        if (all64 < 3 * cus) {
-            if (ksteps <= (4 * all64 <= 7 * cus ? 12 : 20)) return launch_tiled<8, 1, 1, 2, 2, 1, 2>(jobs, n, st);
-            if (4 * all64 <= 7 * cus) return launch_tiled<8, 2, 1, 1, 2, 2, 2>(jobs, n, st);
+        const bool two = jobs[lead].out.acc && jobs[lead].out.y;
+        const int n64 = (gm.Cout + 63) / 64, n128 = (gm.Cout + 127) / 128;
+        if (all64 <= cus) {
+            if (ksteps <= 4) return launch_tiled<8, 1, 1, 2, 2, 1, 3>(jobs, n, st);
+            return ksteps >= 24 ? launch_tiled<8, 1, 1, 2, 2, 4, 3>(jobs, n, st) : launch_tiled<8, 1, 1, 2, 2, 2, 3>(jobs, n, st);
         }
-        if (!fits128) return launch_tiled<8, 2, 1, 2, 2, 1, 3>(jobs, n, st);
-        if (all64 < 6 * cus || ksteps <= 2) return launch_tiled<8, 1, 2, 2, 2, 1, 2>(jobs, n, st);
-        return all64 <= 12 * cus ? launch_tiled<8, 2, 2, 2, 2, 1, 2>(jobs, n, st) : launch_tiled<8, 2, 2, 2, 2, 1, 3>(jobs, n, st);
+        const bool pads = ksteps <= 4 ? 10 * n128 > 6 * n64 : 14 * n128 > 8 * n64;   // tiles 128 wide by more than a fifth, a seventh
+        if (all64 < 3 * cus) {
+            if (ksteps <= 16) return launch_tiled<8, 1, 1, 2, 2, 1, 3>(jobs, n, st);
+            return all64 <= 2 * cus ? launch_tiled<8, 1, 1, 2, 2, 2, 3>(jobs, n, st) : launch_tiled<8, 2, 1, 1, 2, 2, 2>(jobs, n, st);
+        }
+        if (pads) return launch_tiled<8, 2, 1, 2, 2, 1, 3>(jobs, n, st);
+        if (all64 < 6 * cus || ksteps <= 4) return launch_tiled<8, 1, 2, 2, 2, 1, 3>(jobs, n, st);
+        return two || all64 > 12 * cus ? launch_tiled<8, 2, 2, 2, 2, 1, 3>(jobs, n, st) : launch_tiled<8, 2, 2, 2, 2, 1, 2>(jobs, n, st);
     }
 }
 

@@ -79,11 +79,14 @@ VARIANTS = [
     ("bytes, four groups", 8, (12, 20, 21, 176, 72, 3, 1, 1)),
     ("bytes, two groups of four waves", 8, (12, 20, 21, 112, 70, 3, 1, 1)),
     ("bytes, 32 x 32 a wave", 8, (24, 28, 29, 48, 72, 3, 1, 1)),
-    ("bytes, two groups of two waves", 8, (12, 28, 29, 112, 71, 3, 1, 1)),
+    ("bytes, two groups of four waves, more tiles", 8, (12, 28, 29, 112, 71, 3, 1, 1)),
+    ("bytes, two groups of two waves", 8, (24, 28, 29, 128, 71, 3, 1, 1)),
+    ("bytes, 32 x 32 a wave, ragged rows", 8, (24, 28, 29, 48, 141, 3, 1, 1)),
+    ("bytes, 64 x 128, few steps", 8, (49, 33, 32, 16, 260, 3, 1, 1)),
     ("bytes, 128 x 64", 8, (48, 33, 32, 48, 40, 3, 1, 1)),
     ("bytes, 64 x 128", 8, (24, 33, 32, 48, 72, 3, 1, 1)),
-    ("bytes, 128 x 128, two slots", 8, (49, 33, 32, 48, 73, 3, 1, 1)),
-    ("bytes, 128 x 128, three slots", 8, (100, 33, 32, 32, 72, 3, 1, 1)),
+    ("bytes, 128 x 128, three slots or, with one output, two", 8, (49, 33, 32, 48, 73, 3, 1, 1)),
+    ("bytes, 128 x 128, three slots", 8, (100, 33, 32, 48, 72, 3, 1, 1)),
 ]
 
 
@@ -114,6 +117,11 @@ def test_tiled_variants(B, bits, dims):
     torch.cuda.synchronize()
     assert np.array_equal(host(acc, np.int32).reshape(s.M, cout)[rows], ref)
     assert np.array_equal(host(y, np.float32).reshape(s.M, cout)[rows], O.requant_f32(ref, scale, bias))
+    # one output: bytes go by how many there are
+    acc.fill_(0x55555555)
+    plain(*geom, a, w, acc_out=acc)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(acc, np.int32).reshape(s.M, cout)[rows], ref)
     if bits == 8 or cout % 8:
         return
     # fused, with each kind of shortcut; the step at an ordinary size (both ways to a code) and beyond what is quick
