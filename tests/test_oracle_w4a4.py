@@ -391,3 +391,50 @@ def test_product_first_quotient_claim_used_by_the_fused_epilogue():
         sure = ~doubt & np.isfinite(u)
         assert sure.mean() > 0.3                      # the band is narrow: most pairs take the product
         assert np.array_equal(quick[sure], exact[sure])
+
+
+@pytest.mark.parametrize("shortcut", [None, "codes", "floats"])
+@pytest.mark.parametrize("spread", [1.0, 30.0, 3000.0])   # how large sums, biases and shortcuts are beside the step
+def test_step_unit_claim_used_by_the_tiled_fused_epilogue(shortcut, spread):
+    """The tiled kernel works out a code in units of the output step, u = (16 acc) c1 + c0 + shortcut with c1 = fl(scale fl(1 / s))
+    / 16 and c0 = fl(bias fl(1 / s)), two fused multiply-adds, where the definition takes three additions and a division, and keeps it
+    unless u (clamped to 0 .. 15) comes closer to a half-integer than 1.125 * 2^-21 (16 + |bias| / s + |shortcut| / s): the claim is that
+    both round to the same code then.  The kernel's operations are written out in float32 and compared with the oracle's, two
+    thirds of the cases within 30 roundings of a tie; with no such distance they do differ."""
+    rng = np.random.default_rng(int(spread) + len(shortcut or ""))
+    F, n = np.float32, 400_000
+    fma = lambda a, b, c: O.requant_f32(a[None, :], b, c)[0]
+    s = np.concatenate([rng.uniform(0.01, 2.0, n), np.exp2(rng.uniform(-95, 95, n // 2))]).astype(F)
+    n = s.size
+    acc = np.where(rng.random(n) < 0.5, rng.integers(-3000, 3000, n), rng.integers(-2**27, 2**27, n))
+    scale = (rng.uniform(-1, 1, n) * spread * s / np.maximum(np.abs(acc), 1)).astype(F)
+    codes = rng.integers(0, 16, n)
+    r_scale = (rng.uniform(0, 0.1, n) * spread * s).astype(F)
+    r = (rng.standard_normal(n) * 0.5 * spread * s).astype(F)
+    rest = acc.astype(np.float64) * scale + (codes * r_scale.astype(np.float64) if shortcut == "codes" else r.astype(np.float64) if shortcut else 0.0)
+    # a third anywhere, the others such that the result lies next to k + 1/2 steps
+    bias = (rng.uniform(-1, 16, n) * s - rest).astype(F)
+    tie = rng.random(n) < 2 / 3
+    near = ((rng.integers(0, 15, n) + 0.5) * s - rest) * (1 + rng.integers(-30, 31, n) * 2.0 ** -24)
+    bias = np.where(tie, near.astype(F), bias)
+
+    inv = (F(1) / s).astype(F)
+    c1, c0 = (scale * inv).astype(F) * F(0.0625), (bias * inv).astype(F)
+    u = fma((16 * acc).astype(F), c1, c0)
+    cr = (r_scale * inv).astype(F)
+    lim = F(0.5) - F(1.125 * 2.0 ** -21) * (F(16) + np.abs(c0) + (F(15) * np.abs(cr) if shortcut == "codes" else F(0)))
+    quick = lim > F(0.25)
+    if shortcut == "codes":
+        u = fma(codes.astype(F), cr, u)
+    elif shortcut:
+        u = fma(r, inv, u)
+        lim = lim - F(1.125 * 2.0 ** -21) * (np.abs(r) * inv)
+    u = np.clip(u, F(0), F(15))
+    q = np.rint(u)
+    assert u.dtype == lim.dtype == F
+    kw = dict(res_codes=codes[None, :], res_scale=r_scale) if shortcut == "codes" else dict(res_f32=r[None, :]) if shortcut else {}
+    want = O.fused_requant_u4(acc[None, :], scale, bias, s, **kw)[0]
+    kept = quick & (np.abs(u - q) <= lim)
+    assert np.array_equal(q[kept], want[kept])
+    assert kept[~tie].mean() > 0.99 and (~kept & tie & quick).mean() > 0.05   # hardly ever in doubt, and here often
+    assert (q[quick] != want[quick]).any()
